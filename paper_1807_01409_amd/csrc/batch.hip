@@ -1,11 +1,10 @@
-// batch.hip -- the small joins and the final sorts of many plans, each kind
-// in one launch per round of a batch (the lockstep rounds of
+// batch.hip -- the joins of many plans, in a few launches per round of a batch (the lockstep rounds of
 // tid_query_batch): one workgroup per job, the job table in device memory.
 // A plan's join whose sides both have at most kSmallRows rows does not launch
 // its own hash build, scans, probe and expansion; it is a job of the round's
-// one count launch, then of the next round's one expansion launch.  A plan's
-// final lexicographic sort of at most kSortRows rows is likewise a job of one
-// sort launch.  A job's hash table lives in the workgroup's LDS.
+// one count launch, then of the next round's one expansion launch.  A job's
+// hash table lives in the workgroup's LDS.  (The final sorts of a round are
+// batched too: rowsort.hip.)
 //
 // Join job (Sec. 4.2: an equi-join on the shared variable, done here with a
 // hash table in LDS): the R side's keys go into an open-addressing table
@@ -339,91 +338,6 @@ __global__ __launch_bounds__(kBatchBlock) void batch_join_split(const SplitJob *
 }
 
 // ---------------------------------------------------------------------------
-// batched sort: rows into LDS (column-major), a bitonic sort of row indices
-// with the lexicographic order over all columns, rows written out in that
-// order (DISTINCT: only rows differing from their predecessor)
-// ---------------------------------------------------------------------------
-
-namespace {
-__shared__ uint32_t s_vals[kSortWords];
-__shared__ uint16_t s_idx[kSortRows], s_pos[kSortRows];
-__shared__ uint32_t s_sw[kBatchSortBlock / dev::kWave];
-constexpr uint16_t kDropped = 0xFFFF;  // s_pos of a row DISTINCT leaves out
-
-__device__ __forceinline__ bool row_less(uint32_t a, uint32_t b, uint32_t n, int ncols) {
-    if (a >= n) return false;      // padding sorts last
-    if (b >= n) return true;
-    for (int c = 0; c < ncols; ++c) {
-        const uint32_t x = s_vals[c * n + a], y = s_vals[c * n + b];
-        if (x != y) return x < y;
-    }
-    return a < b;                  // equal rows keep their order: a total order
-}
-
-__device__ __forceinline__ bool row_equal(uint32_t a, uint32_t b, uint32_t n, int ncols) {
-    for (int c = 0; c < ncols; ++c)
-        if (s_vals[c * n + a] != s_vals[c * n + b]) return false;
-    return true;
-}
-}  // namespace
-
-// A workgroup of kBatchSortBlock threads per job.  Each step of the bitonic
-// network compares p/2 disjoint pairs (i, i + d), i with bit d clear; thread
-// q's pairs are numbered q, q + kBatchSortBlock, ... so that no thread idles.
-__global__ __launch_bounds__(kBatchSortBlock) void batch_sort(const SortJob *jobs) {
-    const SortJob &j = jobs[blockIdx.x];
-    const uint32_t n = j.n;
-    for (int c = 0; c < j.ncols; ++c)
-        for (uint32_t i = threadIdx.x; i < n; i += kBatchSortBlock)
-            s_vals[c * n + i] = gload(j.in[c] + i);
-    uint32_t p = 1;
-    while (p < n) p <<= 1;
-    for (uint32_t i = threadIdx.x; i < p; i += kBatchSortBlock) s_idx[i] = (uint16_t)i;
-    __syncthreads();
-    const uint32_t pairs = p >> 1;
-    for (uint32_t k = 2; k <= p; k <<= 1) {
-        for (uint32_t d = k >> 1; d > 0; d >>= 1) {
-            for (uint32_t q = threadIdx.x; q < pairs; q += kBatchSortBlock) {
-                const uint32_t i = ((q & ~(d - 1)) << 1) | (q & (d - 1));
-                const uint32_t x = i | d;
-                const uint32_t a = s_idx[i], b = s_idx[x];
-                const bool up = (i & k) == 0;
-                if (row_less(b, a, n, j.ncols) == up) {
-                    s_idx[i] = (uint16_t)b;
-                    s_idx[x] = (uint16_t)a;
-                }
-            }
-            __syncthreads();
-        }
-    }
-    // output positions: all rows, or (DISTINCT) the first of each run of equal
-    // rows; a thread counts a contiguous run of sorted rows, then the rows are
-    // written in sorted-position order across the threads
-    constexpr uint32_t kPer = kSortRows / kBatchSortBlock;  // 8
-    const uint32_t i0 = threadIdx.x * kPer;
-    bool kept[kPer];
-    uint32_t keep = 0;
-#pragma unroll
-    for (uint32_t u = 0; u < kPer; ++u) {
-        const uint32_t i = i0 + u;
-        kept[u] = i < n && (!j.distinct || i == 0 || !row_equal(s_idx[i], s_idx[i - 1], n, j.ncols));
-        keep += kept[u];
-    }
-    uint32_t all;
-    uint32_t o = block_exclusive<kBatchSortBlock>(keep, s_sw, &all);
-#pragma unroll
-    for (uint32_t u = 0; u < kPer; ++u) {
-        if (i0 + u >= n) break;
-        s_pos[i0 + u] = kept[u] ? (uint16_t)o++ : kDropped;
-    }
-    __syncthreads();
-    for (int c = 0; c < j.ncols; ++c)
-        for (uint32_t i = threadIdx.x; i < n; i += kBatchSortBlock)
-            if (s_pos[i] != kDropped) gstore(j.out[c] + s_pos[i], s_vals[c * n + s_idx[i]]);
-    if (threadIdx.x == 0) *j.count = all;
-}
-
-// ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
 
@@ -493,18 +407,9 @@ void flush_join_jobs(tid_ctx *ctx, BatchState &bs, bool expand) {
 }
 
 void flush_sort_jobs(tid_ctx *ctx, BatchState &bs) {
-    if (!bs.row_sorts.empty()) {
-        sort_rows_batched(ctx, bs.row_sorts, bs.keep, bs.host_keep);
-        bs.row_sorts.clear();
-    }
-    if (bs.sort_jobs.empty()) return;
-    const SortJob *d = upload(ctx, bs, bs.sort_jobs);
-    for (size_t j0 = 0; j0 < bs.sort_jobs.size(); j0 += 65535) {
-        const unsigned g = (unsigned)std::min<size_t>(65535, bs.sort_jobs.size() - j0);
-        hipLaunchKernelGGL(batch_sort, dim3(g), dim3(kBatchSortBlock), 0, ctx->stream, d + j0);
-        TID_HIP(hipGetLastError());
-    }
-    bs.sort_jobs.clear();
+    if (bs.row_sorts.empty()) return;
+    sort_rows_batched(ctx, bs.row_sorts, bs.keep, bs.host_keep);
+    bs.row_sorts.clear();
 }
 
 }  // namespace tid

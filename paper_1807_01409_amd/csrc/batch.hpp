@@ -12,10 +12,6 @@ constexpr uint32_t kSmallRows = 4096;       // rows per side of a batched join
 constexpr uint32_t kSmallSlots = 8192;      // LDS hash slots (>= 2 * kSmallRows)
 constexpr int kSmallCols = 8;               // columns per side of a batched join
 constexpr int kSmallEq = 4;                 // other shared variables of a batched join
-constexpr uint32_t kSortRows = 8192;        // rows of a batched sort
-constexpr int kBatchSortBlock = 1024;       // threads of a batched sort's workgroup
-constexpr uint32_t kSortWords = 24576;      // rows x columns of a batched sort
-constexpr int kSortCols = 16;
 constexpr uint32_t kEmptyKey = 0xFFFFFFFFu;  // empty LDS hash slot (the ID itself has its own slot)
 // A join job without other shared variables is expanded in tiles of
 // kSplitTile output rows, a workgroup each.
@@ -42,8 +38,8 @@ struct SplitJob {
     uint32_t tile0;
 };
 
-// A table to put in lexicographic row order with the round's other larger
-// sorts (sort_rows_batched, sort.hip): input, output (n rows allocated).
+// A table to put in lexicographic row order with the round's other sorts
+// (sort_rows_batched, sort.hip): input, output (n rows allocated).
 struct RowSortJob {
     const tid_table *in;
     tid_table *out;
@@ -52,19 +48,10 @@ struct RowSortJob {
 void sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &jobs,
                        std::vector<DevBuf> &keep, std::vector<std::vector<char>> &host_keep);
 
-struct SortJob {
-    const uint32_t *in[kSortCols];
-    uint32_t *out[kSortCols];
-    uint32_t n;
-    int32_t ncols, distinct;
-    uint64_t *count;
-};
-
 // Jobs of one round of a batch, launched together; the device job tables
 // and the host copies they came from are kept until the round's wait.
 struct BatchState {
     std::vector<JoinJob> count_jobs, expand_jobs;
-    std::vector<SortJob> sort_jobs;
     std::vector<RowSortJob> row_sorts;
     std::vector<DevBuf> keep;
     std::vector<std::vector<char>> host_keep;
@@ -75,7 +62,7 @@ struct BatchState {
 };
 // launch and clear the queued jobs of one kind
 void flush_join_jobs(tid_ctx *ctx, BatchState &bs, bool expand);
-void flush_sort_jobs(tid_ctx *ctx, BatchState &bs);  // small sorts, then the larger ones
+void flush_sort_jobs(tid_ctx *ctx, BatchState &bs);
 
 }  // namespace tid
 

@@ -469,32 +469,9 @@ static void advance(tid_ctx *ctx, PlanRun &r, Needs &needs, BatchState *bs) {
             }
             if (need_count(top.t.get(), needs)) return;
             const tid_table *T = top.t.get();
-            if (bs && ctx->opt.batch_small && T->ncols > 0 && T->ncols <= kSortCols &&
-                T->nrows > 1 && T->nrows <= kSortRows &&
-                T->nrows * (uint64_t)T->ncols <= kSortWords) {
-                // one job of the round's batched sort; the input stays alive
-                // in the batch state until the round's wait
-                auto out = make_table(ctx, T->ncols, T->vars, T->nrows);
-                out->maxv_known = T->maxv_known;
-                copy_bounds(out.get(), T, nullptr, T->ncols);
-                SortJob j{};
-                for (int c = 0; c < T->ncols; ++c) {
-                    j.in[c] = T->col[c];
-                    j.out[c] = out->col[c];
-                }
-                j.n = (uint32_t)T->nrows;
-                j.ncols = T->ncols;
-                j.distinct = 0;
-                j.count = out->d_count;
-                bs->sort_jobs.push_back(j);
-                bs->keep_tables.push_back(std::move(top.t));
-                r.result = std::move(out);
-                r.done = true;
-                return;
-            }
             if (bs && ctx->opt.batch_small && T->ncols > 0 && T->maxv_known &&
                 T->nrows > 1 && T->nrows < (1ull << 32)) {
-                // one job of the round's batched larger sorts; the input stays
+                // one job of the round's batched sorts; the input stays
                 // alive in the batch state until the round's wait
                 auto out = make_table(ctx, T->ncols, T->vars, T->nrows);
                 out->maxv_known = T->maxv_known;

@@ -1,0 +1,626 @@
+// rowsort.hip -- lexicographic row order of tables (Sec. 4.3: results merged
+// to distinct values; the canonical order of every result) by merge sort of
+// packed keys, for one table or for the tables of a whole batch round.
+//
+// A row's columns, at their known bit widths, are concatenated into W 64-bit
+// words (W <= 4); rows that compare equal are the same row, so the sort needs
+// neither stability nor a permutation, and the sorted rows are unpacked from
+// the keys: no gather.
+//   tile sort  a workgroup packs its tile of rows, each thread sorts kVT keys
+//              in registers, then runs are merged pairwise in LDS, every
+//              thread finding the kVT keys it produces by a binary search
+//              along its diagonal (the merge path of Green, McColl and Bader,
+//              "GPU merge path").  A table of one tile is written out here;
+//   merge      one launch per doubling of the run length: a workgroup
+//              produces kMergeTile rows, finds its two diagonals with a
+//              64-way search by a wave each, and merges out of LDS.  The last
+//              level writes the table's columns.
+//
+// Bound: a level reads and writes 8 W bytes a row from cache or HBM; below
+// about a million rows it is bound by the latency of the diagonal searches
+// and of the launch.  kVT is odd, so that the blocked accesses of a wave's
+// lanes fall on different LDS banks.  Why merge sort and not the LSD radix
+// sort of sort.hip (three launches per 8 key bits, and the rows gathered at
+// the end): see the sizes measured at rows_mergeable() below.
+#include "batch.hpp"
+#include "compact.hpp"
+
+#include <algorithm>
+
+namespace tid {
+
+namespace {
+
+constexpr int kVT = 7;                       // keys per thread
+constexpr int kMergeBlock = 256;
+constexpr uint32_t kMergeTile = kMergeBlock * kVT;
+constexpr int kMaxWords = 4;
+
+// threads of a tile sort: the tile's keys, 8 W bytes each, stay in LDS
+constexpr int tile_block(int words) { return words <= 2 ? 1024 : 512; }
+constexpr uint32_t tile_rows(int words) { return (uint32_t)tile_block(words) * kVT; }
+
+struct RowJob {
+    const uint32_t *in[TID_MAX_COLS];
+    uint32_t *out[TID_MAX_COLS];
+    uint64_t *key[2];              // W planes of n words each, double buffered
+    uint64_t *count;               // the table's device row count (null: not written here)
+    uint32_t n;
+    uint32_t tile0, mtile0;        // the job's first tile in the two kinds of launch
+    int32_t levels;                // merge launches the job takes part in
+    int16_t ncols;
+    int16_t distinct;              // one tile: keep the first of equal rows; several tiles
+                                   // (one-word keys only): leave the sorted keys
+    uint8_t word[TID_MAX_COLS];    // bit position of a column from the key's end:
+    uint8_t shift[TID_MAX_COLS];   // word (0 = least significant) and bit in it
+    uint8_t width[TID_MAX_COLS];   // bits (0: a column of zeros)
+};
+
+__device__ __forceinline__ uint32_t gload(const uint32_t *p) {
+    return *(const __attribute__((address_space(1))) uint32_t *)p;
+}
+__device__ __forceinline__ uint64_t gload(const uint64_t *p) {
+    return *(const __attribute__((address_space(1))) uint64_t *)p;
+}
+template <class T>
+__device__ __forceinline__ void gstore(T *p, T v) {
+    *(__attribute__((address_space(1))) T *)p = v;
+}
+
+template <int W>
+struct Key {
+    uint64_t w[W];  // most significant first
+};
+
+template <int W>
+__device__ __forceinline__ bool key_less(const Key<W> &a, const Key<W> &b) {
+#pragma unroll
+    for (int x = 0; x < W - 1; ++x)
+        if (a.w[x] != b.w[x]) return a.w[x] < b.w[x];
+    return a.w[W - 1] < b.w[W - 1];
+}
+
+template <int W>
+__device__ __forceinline__ Key<W> lds_key(const uint64_t *s, uint32_t stride, uint32_t i) {
+    Key<W> k;
+#pragma unroll
+    for (int x = 0; x < W; ++x) k.w[x] = s[x * stride + i];
+    return k;
+}
+
+template <int W>
+__device__ __forceinline__ void lds_put(uint64_t *s, uint32_t stride, uint32_t i,
+                                        const Key<W> &k) {
+#pragma unroll
+    for (int x = 0; x < W; ++x) s[x * stride + i] = k.w[x];
+}
+
+template <int W>
+__device__ __forceinline__ Key<W> pack_row(const RowJob &p, uint32_t i) {
+    Key<W> k;
+#pragma unroll
+    for (int x = 0; x < W; ++x) k.w[x] = 0;
+    for (int c = 0; c < p.ncols; ++c) {
+        if (p.width[c] == 0) continue;
+        const uint64_t v = gload(p.in[c] + i);
+        const int lw = p.word[c], sh = p.shift[c];
+        const bool over = sh + p.width[c] > 64;
+#pragma unroll
+        for (int x = 0; x < W; ++x) {  // static indices: the key stays in registers
+            if (W - 1 - x == lw) k.w[x] |= v << sh;
+            if (W - 1 - x == lw + 1 && over) k.w[x] |= v >> (64 - sh);
+        }
+    }
+    return k;
+}
+
+// column c of the key whose word x (most significant first) is word(x)
+template <int W, class Word>
+__device__ __forceinline__ uint32_t column_of(const RowJob &p, int c, const Word &word) {
+    const int b = p.width[c];
+    if (b == 0) return 0;
+    const int lw = p.word[c], sh = p.shift[c];
+    uint64_t v = word(W - 1 - lw) >> sh;
+    if (sh + b > 64) v |= word(W - 2 - lw) << (64 - sh);
+    return (uint32_t)(v & ((1ull << b) - 1));
+}
+
+// how many of the first d merged keys come from A (ties from A first): A is
+// the na keys at a, B the nb keys at b of LDS plane s
+template <int W>
+__device__ __forceinline__ uint32_t lds_diagonal(const uint64_t *s, uint32_t stride, uint32_t a,
+                                                 uint32_t na, uint32_t b, uint32_t nb,
+                                                 uint32_t d) {
+    uint32_t lo = d > nb ? d - nb : 0, hi = min(d, na);
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (!key_less(lds_key<W>(s, stride, b + d - 1 - mid), lds_key<W>(s, stride, a + mid)))
+            lo = mid + 1;
+        else
+            hi = mid;
+    }
+    return lo;
+}
+
+// the next kVT keys of the merge of s[a, a1) and s[b, b1)
+template <int W>
+__device__ __forceinline__ void serial_merge(const uint64_t *s, uint32_t stride, uint32_t a,
+                                             uint32_t a1, uint32_t b, uint32_t b1,
+                                             Key<W> (&out)[kVT]) {
+    Key<W> ka{}, kb{};
+    if (a < a1) ka = lds_key<W>(s, stride, a);
+    if (b < b1) kb = lds_key<W>(s, stride, b);
+#pragma unroll
+    for (int v = 0; v < kVT; ++v) {
+        const bool from_a = b >= b1 || (a < a1 && !key_less(kb, ka));
+        a += from_a ? 1u : 0u;
+        b += from_a ? 0u : 1u;
+        const uint32_t at = from_a ? a : b;
+        const bool more = at < (from_a ? a1 : b1);
+#pragma unroll
+        for (int x = 0; x < W; ++x) {  // word by word: the keys stay in registers
+            out[v].w[x] = from_a ? ka.w[x] : kb.w[x];
+            const uint64_t w = more ? s[x * stride + at] : 0ull;
+            ka.w[x] = from_a ? w : ka.w[x];
+            kb.w[x] = from_a ? kb.w[x] : w;
+        }
+    }
+}
+
+// rows [0, cnt) of LDS plane s to the job's columns, from row `at` on
+template <int W, int BLOCK>
+__device__ __forceinline__ void write_columns(const RowJob &p, const uint64_t *s, uint32_t stride,
+                                              uint32_t cnt, uint32_t at) {
+    for (int c = 0; c < p.ncols; ++c) {
+        uint32_t *out = p.out[c] + at;
+        for (uint32_t i = threadIdx.x; i < cnt; i += BLOCK)
+            gstore(out + i, column_of<W>(p, c, [&](int x) { return s[x * stride + i]; }));
+    }
+}
+
+template <int W, int BLOCK>
+__device__ __forceinline__ void write_keys(const RowJob &p, uint64_t *dst, const uint64_t *s,
+                                           uint32_t stride, uint32_t cnt, uint32_t at) {
+#pragma unroll
+    for (int x = 0; x < W; ++x)
+        for (uint32_t i = threadIdx.x; i < cnt; i += BLOCK)
+            gstore(dst + (uint64_t)x * p.n + at + i, s[x * stride + i]);
+}
+
+// the job of a tile: the last one whose first tile is <= tile
+template <bool MERGE>
+__device__ __forceinline__ int row_job_of(const RowJob *jobs, int J, uint32_t tile) {
+    int lo = 0, hi = J - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if ((MERGE ? jobs[mid].mtile0 : jobs[mid].tile0) <= tile) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+template <int W>
+__device__ __forceinline__ void tile_sort_body(const RowJob &p, uint32_t tile) {
+    constexpr int BLOCK = tile_block(W);
+    constexpr uint32_t TILE = tile_rows(W);
+    constexpr int NW = BLOCK / dev::kWave;
+    extern __shared__ __attribute__((aligned(16))) uint64_t s_tile[];
+    __shared__ uint32_t s_w[NW];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t t0 = tile * TILE;
+    const uint32_t cnt = min(TILE, p.n - t0);
+    // the tile's rows in order, kVT to a thread; past the end the largest key
+    // (a row holding that key is the same key, so either may be written)
+    Key<W> k[kVT];
+#pragma unroll
+    for (int v = 0; v < kVT; ++v) {
+        const uint32_t i = tid * kVT + v;
+        if (i < cnt) {
+            k[v] = pack_row<W>(p, t0 + i);
+        } else {
+#pragma unroll
+            for (int x = 0; x < W; ++x) k[v].w[x] = ~0ull;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kVT; ++r)  // odd-even transposition
+#pragma unroll
+        for (int v = r & 1; v + 1 < kVT; v += 2) {
+            const bool swap = key_less(k[v + 1], k[v]);
+#pragma unroll
+            for (int x = 0; x < W; ++x) {
+                const uint64_t lo = swap ? k[v + 1].w[x] : k[v].w[x];
+                k[v + 1].w[x] = swap ? k[v].w[x] : k[v + 1].w[x];
+                k[v].w[x] = lo;
+            }
+        }
+    // runs of `run` threads merge pairwise while one run is shorter than the tile
+    for (uint32_t run = 1; run * kVT < cnt; run *= 2) {
+#pragma unroll
+        for (int v = 0; v < kVT; ++v) lds_put(s_tile, TILE, tid * kVT + v, k[v]);
+        __syncthreads();
+        const uint32_t first = tid & ~(2 * run - 1);
+        const uint32_t a = first * kVT, len = run * kVT, b = a + len;
+        const uint32_t d = (tid - first) * kVT;
+        const uint32_t da = lds_diagonal<W>(s_tile, TILE, a, len, b, len, d);
+        serial_merge<W>(s_tile, TILE, a + da, a + len, b + d - da, b + len, k);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int v = 0; v < kVT; ++v) lds_put(s_tile, TILE, tid * kVT + v, k[v]);
+    __syncthreads();
+    if (p.levels > 0) {
+        write_keys<W, BLOCK>(p, p.key[0], s_tile, TILE, cnt, t0);
+        return;
+    }
+    if (!p.distinct) {
+        write_columns<W, BLOCK>(p, s_tile, TILE, cnt, 0);
+        if (tid == 0 && p.count) gstore(p.count, (uint64_t)cnt);
+        return;
+    }
+    // one tile, DISTINCT: the first of each run of equal rows
+    bool keep[kVT];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int v = 0; v < kVT; ++v) {
+        const uint32_t i = tid * kVT + v;
+        keep[v] = i < cnt;
+        if (i < cnt && i > 0) {
+            const Key<W> before = lds_key<W>(s_tile, TILE, i - 1);
+            bool same = true;
+#pragma unroll
+            for (int x = 0; x < W; ++x) same &= before.w[x] == k[v].w[x];
+            keep[v] = !same;
+        }
+        mine += keep[v];
+    }
+    const uint32_t incl = dev::wave_inclusive_sum(mine);
+    const int lane = tid % dev::kWave, wave = tid / dev::kWave;
+    if (lane == dev::kWave - 1) s_w[wave] = incl;
+    __syncthreads();
+    uint32_t at = incl - mine, all = 0;
+#pragma unroll
+    for (int x = 0; x < NW; ++x) {
+        if (x < wave) at += s_w[x];
+        all += s_w[x];
+    }
+#pragma unroll
+    for (int v = 0; v < kVT; ++v)
+        if (keep[v]) lds_put(s_tile, TILE, at++, k[v]);  // every key is in registers
+    __syncthreads();
+    write_columns<W, BLOCK>(p, s_tile, TILE, all, 0);
+    if (tid == 0 && p.count) gstore(p.count, (uint64_t)all);
+}
+
+template <int W>
+__global__ __launch_bounds__(tile_block(W)) void row_tile_sort(RowJob p) {
+    tile_sort_body<W>(p, blockIdx.x);
+}
+
+template <int W>
+__global__ __launch_bounds__(tile_block(W)) void row_tile_sort_many(const RowJob *jobs, int J,
+                                                                    uint32_t tile_base) {
+    const uint32_t tile = tile_base + blockIdx.x;
+    const RowJob &p = jobs[row_job_of<false>(jobs, J, tile)];
+    tile_sort_body<W>(p, tile - p.tile0);
+}
+
+// The same cut as lds_diagonal, for keys in global memory (planes of `stride`
+// words): the 64 lanes probe evenly spaced places of the interval and a
+// ballot keeps the part that holds the cut, so about log64(n) dependent reads.
+template <int W>
+__device__ __forceinline__ uint32_t wave_diagonal(const uint64_t *key, uint64_t stride,
+                                                  uint32_t a, uint32_t na, uint32_t b,
+                                                  uint32_t nb, uint32_t d) {
+    const uint32_t lane = (uint32_t)dev::lane_id();
+    uint32_t lo = d > nb ? d - nb : 0, hi = min(d, na);
+    while (lo < hi) {  // the same for every lane
+        const uint32_t step = (hi - lo + dev::kWave - 1) / dev::kWave;
+        const uint32_t m = lo + lane * step;
+        bool before = false;  // the cut is past A's key m
+        if (m < hi) {
+            Key<W> ka, kb;
+#pragma unroll
+            for (int x = 0; x < W; ++x) {
+                ka.w[x] = gload(key + (uint64_t)x * stride + a + m);
+                kb.w[x] = gload(key + (uint64_t)x * stride + b + d - 1 - m);
+            }
+            before = !key_less(kb, ka);
+        }
+        const uint32_t t = (uint32_t)__popcll(dev::ballot(before));  // a prefix of the lanes
+        const uint32_t next = t == 0 ? lo : lo + (t - 1) * step + 1;
+        hi = min(hi, lo + t * step);
+        lo = next;
+    }
+    return lo;
+}
+
+// Output rows [tile * kMergeTile, ...) of one merge level: runs of `run` rows
+// (a multiple of kMergeTile) pairwise into runs of 2 * run.
+template <int W>
+__device__ __forceinline__ void merge_body(const RowJob &p, uint32_t tile, int level) {
+    __shared__ uint64_t s_key[W * kMergeTile];
+    __shared__ uint32_t s_cut[2];
+    const uint32_t tid = threadIdx.x, wave = tid / dev::kWave;
+    const uint64_t run = (uint64_t)tile_rows(W) << level;
+    const uint64_t o0 = (uint64_t)tile * kMergeTile;
+    const uint32_t cnt = (uint32_t)min((uint64_t)kMergeTile, p.n - o0);
+    const uint64_t base = o0 / (2 * run) * (2 * run);
+    const uint32_t a = (uint32_t)base, na = (uint32_t)min(run, p.n - base);
+    const uint32_t b = a + na;
+    const uint32_t nb = (uint32_t)min(run, p.n - base - na);
+    const uint64_t *src = p.key[level & 1];
+    const uint32_t d0 = (uint32_t)(o0 - base), d1 = d0 + cnt;
+    if (wave < 2) {
+        const uint32_t cut = wave_diagonal<W>(src, p.n, a, na, b, nb, wave == 0 ? d0 : d1);
+        if (tid % dev::kWave == 0) s_cut[wave] = cut;
+    }
+    __syncthreads();
+    const uint32_t a0 = s_cut[0], a1 = s_cut[1];
+    const uint32_t b0 = d0 - a0, b1 = d1 - a1;
+    const uint32_t ca = a1 - a0, cb = b1 - b0;  // ca + cb = cnt
+#pragma unroll
+    for (int x = 0; x < W; ++x) {
+        const uint64_t *plane = src + (uint64_t)x * p.n;
+        uint64_t v[kVT];
+#pragma unroll
+        for (int u = 0; u < kVT; ++u) {
+            const uint32_t i = u * kMergeBlock + tid;
+            v[u] = 0;
+            if (i < cnt) v[u] = gload(plane + (i < ca ? a + a0 + i : b + b0 + (i - ca)));
+        }
+#pragma unroll
+        for (int u = 0; u < kVT; ++u) s_key[x * kMergeTile + u * kMergeBlock + tid] = v[u];
+    }
+    __syncthreads();
+    Key<W> k[kVT];
+    const uint32_t d = min(tid * kVT, cnt);
+    const uint32_t da = lds_diagonal<W>(s_key, kMergeTile, 0, ca, ca, cb, d);
+    serial_merge<W>(s_key, kMergeTile, da, ca, ca + d - da, cnt, k);
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < kVT; ++v) lds_put(s_key, kMergeTile, tid * kVT + v, k[v]);
+    __syncthreads();
+    if (level + 1 == p.levels && !p.distinct) {
+        write_columns<W, kMergeBlock>(p, s_key, kMergeTile, cnt, (uint32_t)o0);
+        if (o0 == 0 && tid == 0 && p.count) gstore(p.count, (uint64_t)p.n);
+    } else {
+        write_keys<W, kMergeBlock>(p, p.key[(level & 1) ^ 1], s_key, kMergeTile, cnt,
+                                   (uint32_t)o0);
+    }
+}
+
+template <int W>
+__global__ __launch_bounds__(kMergeBlock) void row_merge(RowJob p, int level) {
+    merge_body<W>(p, blockIdx.x, level);
+}
+
+template <int W>
+__global__ __launch_bounds__(kMergeBlock) void row_merge_many(const RowJob *jobs, int J,
+                                                              int level, uint32_t tile_base) {
+    const uint32_t tile = tile_base + blockIdx.x;
+    const RowJob &p = jobs[row_job_of<true>(jobs, J, tile)];
+    merge_body<W>(p, tile - p.mtile0, level);
+}
+
+// one-word keys of a sorted list that differ from the key before them
+struct UniqueKeySrc {
+    RowJob p;
+    const uint64_t *key;
+    uint64_t n;
+    struct Item {
+        uint64_t k;
+        bool first;
+    };
+    __device__ __forceinline__ Item load(uint64_t i) const {
+        Item t;
+        t.k = key[i];
+        t.first = i == 0 || key[i - 1] != t.k;
+        return t;
+    }
+    __device__ __forceinline__ bool match(int, const Item &t) const { return t.first; }
+    __device__ __forceinline__ uint32_t value(int, int c, const Item &t, uint64_t) const {
+        return column_of<1>(p, c, [&](int) { return t.k; });
+    }
+};
+
+int bits_of(uint32_t v) { return v ? 32 - __builtin_clz(v) : 0; }
+
+// words of a row's packed key, by the columns' bounds
+int key_words(const tid_table *t) {
+    int bits = 0;
+    for (int c = 0; c < t->ncols; ++c) bits += bits_of(t->maxv[c]);
+    return std::max(1, (bits + 63) / 64);
+}
+
+RowJob row_job(const tid_table *in, const tid_table *out, uint64_t n, int words, int distinct) {
+    RowJob p{};
+    p.ncols = (int16_t)in->ncols;
+    p.n = (uint32_t)n;
+    p.distinct = (int16_t)distinct;
+    int at = 0;  // bits below the column
+    for (int c = in->ncols - 1; c >= 0; --c) {
+        p.in[c] = in->col[c];
+        p.out[c] = out->col[c];
+        p.width[c] = (uint8_t)bits_of(in->maxv[c]);
+        p.word[c] = (uint8_t)(at / 64);
+        p.shift[c] = (uint8_t)(at % 64);
+        at += p.width[c];
+    }
+    for (uint64_t run = tile_rows(words); run < n; run *= 2) ++p.levels;
+    return p;
+}
+
+template <int W>
+void allow_lds(tid_ctx *ctx) {
+    // above 64 KB a kernel must be allowed its dynamic LDS first
+    constexpr size_t lds = (size_t)tile_rows(W) * 8 * W;
+    (void)ctx;
+    (void)resident_blocks((const void *)row_tile_sort<W>, tile_block(W), lds);
+    (void)resident_blocks((const void *)row_tile_sort_many<W>, tile_block(W), lds);
+}
+
+template <int W>
+void sort_one(tid_ctx *ctx, RowJob &p, tid_table *out) {
+    allow_lds<W>(ctx);
+    constexpr size_t lds = (size_t)tile_rows(W) * 8 * W;
+    DevBuf keys;
+    if (p.levels) {
+        const size_t half = (size_t)p.n * 8 * W;
+        keys = DevBuf(ctx, 2 * half);
+        p.key[0] = keys.get<uint64_t>();
+        p.key[1] = p.key[0] + (size_t)p.n * W;
+    }
+    const uint32_t tiles = (p.n + tile_rows(W) - 1) / tile_rows(W);
+    hipLaunchKernelGGL(row_tile_sort<W>, dim3(tiles), dim3(tile_block(W)), lds, ctx->stream, p);
+    TID_HIP(hipGetLastError());
+    const uint32_t mtiles = (p.n + kMergeTile - 1) / kMergeTile;
+    for (int l = 0; l < p.levels; ++l) {
+        hipLaunchKernelGGL(row_merge<W>, dim3(mtiles), dim3(kMergeBlock), 0, ctx->stream, p, l);
+        TID_HIP(hipGetLastError());
+    }
+    if (!p.distinct || !p.levels) return;
+    UniqueKeySrc src;
+    src.p = p;
+    src.key = p.key[p.levels & 1];
+    src.n = p.n;
+    CompactArgs<1, TID_MAX_COLS> a{};
+    for (int c = 0; c < p.ncols; ++c) a.out[0].col[c] = p.out[c];
+    a.out[0].cap = out->cap;
+    a.out[0].count = out->d_count;
+    a.out[0].ncols = p.ncols;
+    launch_compact<UniqueKeySrc, 256, 16, 1, TID_MAX_COLS>(ctx, src, a, 1, 8192);
+}
+
+template <int W>
+void sort_many(tid_ctx *ctx, std::vector<RowJob *> jobs, const RowJob *dev) {
+    allow_lds<W>(ctx);
+    constexpr size_t lds = (size_t)tile_rows(W) * 8 * W;
+    const int J = (int)jobs.size();
+    const RowJob &last = *jobs.back();
+    const uint32_t tiles = last.tile0 + (last.n + tile_rows(W) - 1) / tile_rows(W);
+    hipLaunchKernelGGL(row_tile_sort_many<W>, dim3(tiles), dim3(tile_block(W)), lds, ctx->stream,
+                       dev, J, 0u);
+    TID_HIP(hipGetLastError());
+    // jobs stand in order of falling size: a level's jobs are the first ones
+    int active = J;
+    for (int l = 0;; ++l) {
+        while (active && jobs[active - 1]->levels <= l) --active;
+        if (!active) break;
+        const RowJob &p = *jobs[active - 1];
+        const uint32_t mt = p.mtile0 + (p.n + kMergeTile - 1) / kMergeTile;
+        hipLaunchKernelGGL(row_merge_many<W>, dim3(mt), dim3(kMergeBlock), 0, ctx->stream, dev,
+                           active, l, 0u);
+        TID_HIP(hipGetLastError());
+    }
+}
+
+}  // namespace
+
+// Whether the merge sort takes a table's rows: column bounds on the host, at
+// most kMaxWords key words, and key buffers (16 B a row and word) no larger
+// than the radix sort's arrays (24 B a row) once a table is large.  Measured
+// on one MI355X, one table, merge sort against the LSD radix sort with its
+// gather (2 columns of 23 bits, one word / 7 columns of 25 bits, three words):
+//      7,168 rows    57 /  103 us against   110 /   309 us
+//     50,000 rows    99 /  164 us against   197 /   660 us
+//  1,000,000 rows   197 /  377 us against   281 /  1034 us
+//  4,000,000 rows   413 / 1099 us against   755 /  3038 us
+// 16,000,000 rows  1424 / 4653 us against  2586 / 11557 us
+// so it is the faster one wherever it is allowed.
+constexpr uint64_t kMergeRows1 = 1ull << 31;  // one key word
+constexpr uint64_t kMergeRows = 1ull << 26;   // more
+
+bool rows_mergeable(const tid_table *t, uint64_t n) {
+    if (!t->maxv_known || t->ncols <= 0) return false;
+    const int w = key_words(t);
+    return w == 1 ? n <= kMergeRows1 : w <= kMaxWords && n <= kMergeRows;
+}
+
+// Whether merge_sort_rows can also drop repeated rows; where it cannot, the
+// caller compacts the sorted table.
+bool merge_distinct_ok(const tid_table *t, uint64_t n) {
+    const int w = key_words(t);
+    return w == 1 || n <= tile_rows(w);
+}
+
+// The n >= 1 rows of `in` in lexicographic order into `out` (n rows
+// allocated), whose device count is written; distinct = 1: without repeats
+// (merge_distinct_ok).
+void merge_sort_rows(tid_ctx *ctx, const tid_table *in, uint64_t n, tid_table *out,
+                     int distinct) {
+    const int w = key_words(in);
+    RowJob p = row_job(in, out, n, w, distinct);
+    p.count = out->d_count;
+    if (w == 1) sort_one<1>(ctx, p, out);
+    else if (w == 2) sort_one<2>(ctx, p, out);
+    else if (w == 3) sort_one<3>(ctx, p, out);
+    else sort_one<4>(ctx, p, out);
+}
+
+// The same for many tables in shared launches (no DISTINCT, counts set by the
+// caller); every table must be rows_mergeable.
+void merge_sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &all,
+                             std::vector<DevBuf> &keep,
+                             std::vector<std::vector<char>> &host_keep) {
+    // chunks of jobs in order, each with at most kChunkBytes of keys (a larger job alone)
+    constexpr uint64_t kChunkBytes = 4ull << 30;
+    for (size_t j0 = 0; j0 < all.size();) {
+        std::vector<RowJob> by_words[kMaxWords + 1];
+        uint64_t bytes = 0;
+        size_t j1 = j0;
+        for (; j1 < all.size(); ++j1) {
+            const RowSortJob &r = all[j1];
+            const int w = key_words(r.in);
+            RowJob p = row_job(r.in, r.out, r.n, w, 0);
+            const uint64_t need = p.levels ? 2 * r.n * 8 * (uint64_t)w : 0;
+            if (j1 > j0 && bytes + need > kChunkBytes) break;
+            bytes += need;
+            by_words[w].push_back(p);
+        }
+        DevBuf arena(ctx, std::max<uint64_t>(bytes, 8));
+        uint64_t *at = arena.get<uint64_t>();
+        std::vector<RowJob> table;
+        size_t first[kMaxWords + 2] = {};
+        for (int w = 1; w <= kMaxWords; ++w) {
+            std::vector<RowJob> &v = by_words[w];
+            std::stable_sort(v.begin(), v.end(),
+                             [](const RowJob &x, const RowJob &y) { return x.n > y.n; });
+            uint32_t tiles = 0, mtiles = 0;
+            for (RowJob &p : v) {
+                if (p.levels) {
+                    p.key[0] = at;
+                    p.key[1] = at + (size_t)p.n * w;
+                    at += 2 * (size_t)p.n * w;
+                }
+                p.tile0 = tiles;
+                p.mtile0 = mtiles;
+                tiles += (p.n + tile_rows(w) - 1) / tile_rows(w);
+                mtiles += (p.n + kMergeTile - 1) / kMergeTile;
+            }
+            first[w] = table.size();
+            table.insert(table.end(), v.begin(), v.end());
+        }
+        first[kMaxWords + 1] = table.size();
+        const size_t tb = table.size() * sizeof(RowJob);
+        host_keep.emplace_back(reinterpret_cast<const char *>(table.data()),
+                               reinterpret_cast<const char *>(table.data()) + tb);
+        keep.emplace_back(ctx, tb);
+        const RowJob *dev = keep.back().get<const RowJob>();
+        TID_HIP(hipMemcpyAsync(keep.back().get(), host_keep.back().data(), tb,
+                               hipMemcpyHostToDevice, ctx->stream));
+        for (int w = 1; w <= kMaxWords; ++w) {
+            std::vector<RowJob *> v;
+            for (size_t x = first[w]; x < first[w + 1]; ++x) v.push_back(&table[x]);
+            if (v.empty()) continue;
+            if (w == 1) sort_many<1>(ctx, v, dev + first[w]);
+            else if (w == 2) sort_many<2>(ctx, v, dev + first[w]);
+            else if (w == 3) sort_many<3>(ctx, v, dev + first[w]);
+            else sort_many<4>(ctx, v, dev + first[w]);
+        }
+        keep.push_back(std::move(arena));
+        j0 = j1;
+    }
+}
+
+}  // namespace tid
