@@ -407,6 +407,24 @@ static bool use_slices(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats
     return 8 * rows < 12 * g->n;
 }
 
+bool scan_pages_ok(tid_ctx *ctx, const tid_graph *g, int k, tid_table *const *outs);
+void run_scan_pages(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, int k,
+                    tid_table *const *outs, const PatternSet *sets, const ScanFilter *filters);
+
+// Whether one pass of the block-ranged kernel holds the rows the tables'
+// sizes allow in its LDS staging (it reads the graph again where it does not).
+static bool staged_pass_ok(tid_ctx *ctx, const tid_graph *g, tid_table *const *outs, int k) {
+    if (k > 4) return false;
+    constexpr uint64_t kTile = 512 * 8;
+    const uint64_t ranges = std::max<uint64_t>(
+        1, std::min<uint64_t>((g->n + kTile - 1) / kTile, 2ull * (uint64_t)device_cus(ctx)));
+    uint64_t cols = 0;
+    for (int j = 0; j < k; ++j) cols += (uint64_t)outs[j]->ncols;
+    for (int j = 0; j < k; ++j)
+        if (outs[j]->ncols && outs[j]->cap / ranges > stage_words(ctx) / cols) return false;
+    return true;
+}
+
 static void run_scan_any(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, int k,
                          tid_table *const *outs, const PatternSet *sets,
                          const ScanFilter *filters) {
@@ -419,6 +437,12 @@ static void run_scan_any(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pa
         return;
     }
     const int shape = (int)ctx->opt.multi_shape;
+    if (ctx->opt.multi_kernel == 0 && shape == 0 && ctx->opt.compact_kernel == 0 &&
+        ctx->opt.capacity_override == 0 && !staged_pass_ok(ctx, g, outs, k) &&
+        scan_pages_ok(ctx, g, k, outs)) {
+        run_scan_pages(ctx, g, pats, k, outs, sets, filters);
+        return;
+    }
     if (ctx->opt.multi_kernel == 0) {
         const int passes = (k + 3) / 4;
         for (int p0 = 0, p = 0; p < passes; ++p) {
