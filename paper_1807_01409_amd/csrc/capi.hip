@@ -95,10 +95,9 @@ tid_status tid_ctx_create(int device, void *stream, tid_alloc_fn alloc, tid_free
         ctx->alloc_fn = alloc;
         ctx->free_fn = free_fn;
         ctx->user = user;
-        // words 0-1: error and overflow flags; word 2: the read probe's sink
-        ctx->d_flags = static_cast<uint32_t *>(ctx->alloc(4 * sizeof(uint32_t)));
-        TID_HIP(hipMemsetAsync(ctx->d_flags, 0, 4 * sizeof(uint32_t), ctx->stream));
-        TID_HIP(hipStreamSynchronize(ctx->stream));
+        TID_HIP(hipHostMalloc((void **)&ctx->d_flags, 4 * sizeof(uint32_t),
+                              hipHostMallocCoherent));
+        std::memset(ctx->d_flags, 0, 4 * sizeof(uint32_t));
         // once per device: the allocation-free scan's state array
         tid::noalloc_init(ctx);
     });
@@ -115,10 +114,8 @@ void tid_ctx_destroy(tid_ctx *ctx) {
     (void)hipSetDevice(ctx->device);
     if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
     if (ctx->ep_state) ctx->free(ctx->ep_state, ctx->ep_bytes);
-    if (ctx->d_flags) ctx->free(ctx->d_flags, 4 * sizeof(uint32_t));
-    if (ctx->rw_dev) ctx->free(ctx->rw_dev, ctx->rw_cap * 16);
-    if (ctx->rw_host_ptrs) (void)hipHostFree(ctx->rw_host_ptrs);
-    if (ctx->rw_host_vals) (void)hipHostFree(ctx->rw_host_vals);
+    if (ctx->rw_host) (void)hipHostFree(ctx->rw_host);
+    if (ctx->d_flags) (void)hipHostFree(ctx->d_flags);
     if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;

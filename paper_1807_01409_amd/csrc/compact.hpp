@@ -251,7 +251,7 @@ __global__ __launch_bounds__(BLOCK) void compact_kernel(Src src, CompactArgs<MAX
             uint32_t spins = 0;
             while ((w[u] >> kEpochShift) != a.epoch) {
                 if (++spins > kSpinLimit) {
-                    atomicOr(&flags[0], 1u);
+                    dev::raise(&flags[0]);
                     break;
                 }
                 __builtin_amdgcn_s_sleep(2);
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(BLOCK) void compact_kernel(Src src, CompactArgs<MAX
                 TID_FOR_COLS(MAXC, c, o.ncols)
                     dev::put(&o.col[c][dst], stage[o.stage_off + (uint32_t)c * o.stage_cap + r]);
             } else {
-                atomicOr(&flags[1], 1u);
+                dev::raise(&flags[1]);
             }
         }
     }
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(BLOCK) void compact_kernel(Src src, CompactArgs<MAX
                         TID_FOR_COLS(MAXC, c, o.ncols)
                             dev::put(&o.col[c][dst], src.value(j, c, item[it], i));
                     } else {
-                        atomicOr(&flags[1], 1u);
+                        dev::raise(&flags[1]);
                     }
                 }
             }
@@ -452,7 +452,7 @@ __global__ __launch_bounds__(BLOCK) void chunk_compact_kernel(Src src, CompactAr
                     uint32_t spins = 0;
                     while ((w[j][u] >> kEpochShift) != a.epoch) {
                         if (++spins > kSpinLimit) {
-                            atomicOr(&flags[0], 1u);
+                            dev::raise(&flags[0]);
                             break;
                         }
                         __builtin_amdgcn_s_sleep(2);
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(BLOCK) void chunk_compact_kernel(Src src, CompactAr
                     TID_FOR_COLS(MAXC, c, o.ncols)
                         dev::put(&o.col[c][dst], pb[o.stage_off + (uint32_t)c * o.stage_cap + r]);
                 } else {
-                    atomicOr(&flags[1], 1u);
+                    dev::raise(&flags[1]);
                 }
             }
         }
@@ -523,7 +523,7 @@ __global__ __launch_bounds__(BLOCK) void chunk_compact_kernel(Src src, CompactAr
                             TID_FOR_COLS(MAXC, c, o.ncols)
                                 dev::put(&o.col[c][dst], src.value(j, c, item[it], i));
                         } else {
-                            atomicOr(&flags[1], 1u);
+                            dev::raise(&flags[1]);
                         }
                     }
                 }

@@ -81,6 +81,12 @@ __device__ __forceinline__ T wave_sum(T v) {
     return v;
 }
 
+// Raise an error flag.  A context's flags are pinned host memory, so this is a
+// store and not an atomic; every raise stores the same value.
+__device__ __forceinline__ void raise(uint32_t *flag) {
+    __hip_atomic_store(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Words shared between workgroups of one kernel are written and read with
 // agent-scope atomics so that workgroups on different XCDs (each with its own
 // L2) see each other.

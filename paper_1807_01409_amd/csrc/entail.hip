@@ -176,7 +176,7 @@ std::unique_ptr<tid_table> entail(tid_ctx *ctx, const tid_graph *g, int rule,
             TID_HIP(hipMemcpyAsync(tri->col[1], tj->col[col_in(tj.get(), r.out_pv)], n * 4,
                                    hipMemcpyDeviceToDevice, ctx->stream));
     }
-    set_count(ctx, tri.get(), n);
+    set_count(tri.get(), n);
     tri->maxv_known = true;
     tri->maxv[0] = std::max({g->max_id[0], g->max_id[1], g->max_id[2]});
     tri->maxv[1] = tri->maxv[0];

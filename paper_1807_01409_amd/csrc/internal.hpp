@@ -52,6 +52,21 @@ class Pool {
     std::map<void *, size_t> live_;
 };
 
+// 64-bit words of pinned host memory that kernels write and the host reads once
+// the stream has passed them (row counts): no copy and no launch to fetch one.
+// Taken and given back in stream order, as the device blocks are: a kernel
+// still to write a word that was given back runs before any later owner's.
+class HostWords {
+  public:
+    ~HostWords();
+    uint64_t *take();
+    void give(uint64_t *w) { free_.push_back(w); }
+
+  private:
+    static constexpr size_t kSlab = 4096;  // words per allocation
+    std::vector<uint64_t *> slabs_, free_;
+};
+
 struct Options {
     int64_t capacity_override = 0;
     int64_t retry = 1;
@@ -94,11 +109,12 @@ struct tid_ctx {
     void *ep_state = nullptr;
     size_t ep_bytes = 0;
     uint32_t epoch = 0;
-    uint32_t *d_flags = nullptr;      // device error/overflow flags (2 words)
-    // staging for read_words: pinned pointer list and values, device copies
-    const uint64_t **rw_host_ptrs = nullptr;
-    uint64_t *rw_host_vals = nullptr;
-    void *rw_dev = nullptr;
+    // pinned host words that kernels write: 0-1 error and overflow flags, 2 the
+    // read probe's sink
+    uint32_t *d_flags = nullptr;
+    tid::HostWords words;
+    // pinned host memory that read_words' kernel writes
+    uint64_t *rw_host = nullptr;
     size_t rw_cap = 0;
 
     void *alloc(size_t bytes);
@@ -106,9 +122,8 @@ struct tid_ctx {
     // stamp for the next chunked launch; *state gets the slot area of `bytes`
     uint32_t next_epoch(size_t bytes, uint64_t **state);
     void sync();
-    // device row-count words whose values the host already knows, written
-    // together by tid::flush_counts (one launch per 128)
-    std::vector<std::pair<uint64_t *, uint64_t>> pending_counts;
+    // throws if a kernel that the stream has passed reported an inconsistency
+    void check_flags() const;
 };
 
 namespace tid {
@@ -151,6 +166,17 @@ class DevBuf {
     tid_ctx *ctx_ = nullptr;
     void *ptr_ = nullptr;
     size_t bytes_ = 0;
+};
+
+// A table's device memory, and the word its row count is written to.
+struct TableMem {
+    DevBuf buf;
+    tid_ctx *ctx = nullptr;
+    uint64_t *count = nullptr;
+    TableMem(tid_ctx *c, size_t bytes) : buf(c, bytes), ctx(c), count(c->words.take()) {}
+    TableMem(const TableMem &) = delete;
+    TableMem &operator=(const TableMem &) = delete;
+    ~TableMem() { ctx->words.give(count); }
 };
 
 constexpr size_t kAlign = 256;
@@ -207,11 +233,12 @@ struct tid_table {
     uint64_t cap = 0;                 // rows allocated per column
     uint64_t nrows = 0;               // valid when count_known
     bool count_known = false;
-    // columns (each align_up(cap*4)) + 8-byte device count; shared by the
-    // tables that alias one result (tables are never written after they are
-    // produced)
-    std::shared_ptr<tid::DevBuf> block;
+    // columns (each align_up(cap*4)) and the count word; shared by the tables
+    // that alias one result (tables are never written after they are produced)
+    std::shared_ptr<tid::TableMem> block;
     uint32_t *col[TID_MAX_COLS] = {};
+    // where a kernel writes the row count (pinned host memory); not written for
+    // tables whose count the host knows
     uint64_t *d_count = nullptr;
     // host-side upper bound of every column's values (valid when maxv_known);
     // lets sorts size their passes without reading the device
@@ -223,30 +250,18 @@ struct tid_table {
 
 namespace tid {
 
-// Allocate a table with `cap` rows per column and the given schema; the
-// device count word is not initialised.
+// Allocate a table with `cap` rows per column and the given schema; its count
+// is not known yet.
 std::unique_ptr<tid_table> make_table(tid_ctx *ctx, int32_t ncols, const int32_t *vars,
                                       uint64_t cap);
-// Read a batch of device counts into table->nrows with one synchronisation;
-// also checks the device error flag.
+// Bring the counts of the tables to the host with one synchronisation; also
+// checks the error flag.
 void resolve_counts(tid_ctx *ctx, tid_table *const *ts, int k);
-// Write a known row count to the table's device word and host copy.
-void set_count(tid_ctx *ctx, tid_table *t, uint64_t n);
-// The same, with the device word written by the next flush_counts (the host
-// copy at once); for the many tables of a batch round, whose device words no
-// kernel reads before the round's end.
-void set_count_later(tid_ctx *ctx, tid_table *t, uint64_t n);
-void flush_counts(tid_ctx *ctx);
-// Drops the counts still pending when a call fails (their tables may be
-// freed with the error); on success the call has flushed them itself.
-struct PendingCountsGuard {
-    tid_ctx *ctx;
-    int exc;
-    explicit PendingCountsGuard(tid_ctx *c) : ctx(c), exc(std::uncaught_exceptions()) {}
-    ~PendingCountsGuard() {
-        if (std::uncaught_exceptions() > exc) ctx->pending_counts.clear();
-    }
-};
+// A row count that the host knows (no kernel reads a table's count).
+inline void set_count(tid_table *t, uint64_t n) {
+    t->nrows = n;
+    t->count_known = true;
+}
 // Column value bounds: dst column c takes the bound of src column map[c].
 void copy_bounds(tid_table *dst, const tid_table *src, const int *map, int n, int dst_off = 0);
 
@@ -352,8 +367,8 @@ std::unique_ptr<PendingJoin> join_begin(tid_ctx *ctx, const tid_table *L, uint64
                                         const JoinPlan &jp, int kind = kJoinInner);
 std::unique_ptr<tid_table> join_finish(tid_ctx *ctx, PendingJoin &pj);
 
-// Read device words (counts, totals) to the host with one copy and one
-// synchronisation; also checks the device error flag.
+// Read device words (totals) to the host with one launch and one
+// synchronisation; also checks the error flag.
 void read_words(tid_ctx *ctx, const std::vector<const uint64_t *> &src, uint64_t *dst);
 
 // validate and return the schema of a pattern; throws on a malformed pattern

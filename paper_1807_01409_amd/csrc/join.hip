@@ -550,7 +550,7 @@ std::unique_ptr<tid_table> join_finish(tid_ctx *ctx, PendingJoin &pj) {
                            ctx->stream, ea);
         TID_HIP(hipGetLastError());
     }
-    set_count(ctx, out.get(), total);
+    set_count(out.get(), total);
     return out;
 }
 
@@ -593,7 +593,7 @@ static std::unique_ptr<tid_table> unmatched_right(tid_ctx *ctx, const tid_table 
     auto pj = join_begin(ctx, r, nr, rc, l, nl, lc, 1, none, kJoinLeft);
     auto out = make_table(ctx, (int)vars.size(), vars.data(), nr);
     if (nr == 0) {
-        set_count(ctx, out.get(), 0);
+        set_count(out.get(), 0);
         return out;
     }
     UnmatchedSrc src{};
@@ -687,7 +687,7 @@ std::unique_ptr<tid_table> join_tables_kind(tid_ctx *ctx, const tid_table *l, in
                     TID_HIP(hipMemcpyAsync(both->col[c] + raw->nrows, un->col[c], un->nrows * 4,
                                            hipMemcpyDeviceToDevice, ctx->stream));
             }
-            set_count(ctx, both.get(), raw->nrows + un->nrows);
+            set_count(both.get(), raw->nrows + un->nrows);
             raw = std::move(both);
         }
     }

@@ -134,7 +134,7 @@ void scan_slice(tid_ctx *ctx, const tid_graph *g, const tid_pattern &p, tid_tabl
     const uint64_t a = cdf[std::min<uint64_t>(p.p, last)];
     const uint64_t b = cdf[std::min<uint64_t>((uint64_t)p.p + 1, last)];
     if (b == a) {
-        set_count(ctx, out, 0);
+        set_count(out, 0);
         return;
     }
     SliceSrc src{};
@@ -391,9 +391,8 @@ void index_semijoin(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats,
         outs[j]->maxv_known = true;
         jobs[j].ncols = nc;
         jobs[j].obase = at[j];
-        set_count_later(ctx, outs[j].get(), rows);
+        set_count(outs[j].get(), rows);
     }
-    flush_counts(ctx);
     const uint64_t R = at[J];
     if (R) {
         DevBuf djobs2(ctx, sizeof(IdxJob) * J);

@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kProbeBlock) void read_probe_kernel(const uint32_t 
         }
     }
     // one word per launch; a value no read can produce keeps the loads live
-    if (acc == 0x9E3779B9u) atomicXor(sink, acc);
+    if (acc == 0x9E3779B9u) *sink = acc;
 }
 
 }  // namespace

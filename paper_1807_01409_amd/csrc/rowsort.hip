@@ -44,7 +44,7 @@ struct RowJob {
     const uint32_t *in[TID_MAX_COLS];
     uint32_t *out[TID_MAX_COLS];
     uint64_t *key[2];              // W planes of n words each, double buffered
-    uint64_t *count;               // the table's device row count (null: not written here)
+    uint64_t *count;               // DISTINCT of one tile: the row count (else null)
     uint32_t n;
     uint32_t tile0, mtile0;        // the job's first tile in the two kinds of launch
     int32_t levels;                // merge launches the job takes part in
@@ -255,7 +255,6 @@ __device__ __forceinline__ void tile_sort_body(const RowJob &p, uint32_t tile) {
     }
     if (!p.distinct) {
         write_columns<W, BLOCK>(p, s_tile, TILE, cnt, 0);
-        if (tid == 0 && p.count) gstore(p.count, (uint64_t)cnt);
         return;
     }
     // one tile, DISTINCT: the first of each run of equal rows
@@ -289,7 +288,7 @@ __device__ __forceinline__ void tile_sort_body(const RowJob &p, uint32_t tile) {
         if (keep[v]) lds_put(s_tile, TILE, at++, k[v]);  // every key is in registers
     __syncthreads();
     write_columns<W, BLOCK>(p, s_tile, TILE, all, 0);
-    if (tid == 0 && p.count) gstore(p.count, (uint64_t)all);
+    if (tid == 0) *p.count = all;
 }
 
 template <int W>
@@ -383,7 +382,6 @@ __device__ __forceinline__ void merge_body(const RowJob &p, uint32_t tile, int l
     __syncthreads();
     if (level + 1 == p.levels && !p.distinct) {
         write_columns<W, kMergeBlock>(p, s_key, kMergeTile, cnt, (uint32_t)o0);
-        if (o0 == 0 && tid == 0 && p.count) gstore(p.count, (uint64_t)p.n);
     } else {
         write_keys<W, kMergeBlock>(p, p.key[(level & 1) ^ 1], s_key, kMergeTile, cnt,
                                    (uint32_t)o0);
@@ -545,13 +543,13 @@ bool merge_distinct_ok(const tid_table *t, uint64_t n) {
 }
 
 // The n >= 1 rows of `in` in lexicographic order into `out` (n rows
-// allocated), whose device count is written; distinct = 1: without repeats
-// (merge_distinct_ok).
+// allocated); distinct = 1: without repeats (merge_distinct_ok), the count left
+// on the device.
 void merge_sort_rows(tid_ctx *ctx, const tid_table *in, uint64_t n, tid_table *out,
                      int distinct) {
     const int w = key_words(in);
     RowJob p = row_job(in, out, n, w, distinct);
-    p.count = out->d_count;
+    if (distinct) p.count = out->d_count;
     if (w == 1) sort_one<1>(ctx, p, out);
     else if (w == 2) sort_one<2>(ctx, p, out);
     else if (w == 3) sort_one<3>(ctx, p, out);

@@ -69,7 +69,21 @@ Pool::~Pool() {
 // tables
 // ---------------------------------------------------------------------------
 
-__global__ void set_u64(uint64_t *p, uint64_t v) { *p = v; }
+HostWords::~HostWords() {
+    for (uint64_t *s : slabs_) (void)hipHostFree(s);
+}
+
+uint64_t *HostWords::take() {
+    if (free_.empty()) {
+        uint64_t *s = nullptr;
+        TID_HIP(hipHostMalloc((void **)&s, kSlab * 8, hipHostMallocCoherent));
+        slabs_.push_back(s);
+        for (size_t i = kSlab; i-- > 0;) free_.push_back(s + i);
+    }
+    uint64_t *w = free_.back();
+    free_.pop_back();
+    return w;
+}
 
 std::unique_ptr<tid_table> make_table(tid_ctx *ctx, int32_t ncols, const int32_t *vars,
                                       uint64_t cap) {
@@ -80,11 +94,10 @@ std::unique_ptr<tid_table> make_table(tid_ctx *ctx, int32_t ncols, const int32_t
     for (int c = 0; c < ncols; ++c) t->vars[c] = vars[c];
     t->cap = cap;
     const size_t stride = align_up(std::max<uint64_t>(cap, 1) * sizeof(uint32_t));
-    const size_t bytes = stride * (size_t)ncols + kAlign;
-    t->block = std::make_shared<DevBuf>(ctx, bytes);
-    char *base = t->block->get<char>();
+    t->block = std::make_shared<TableMem>(ctx, stride * (size_t)ncols);
+    char *base = t->block->buf.get<char>();
     for (int c = 0; c < ncols; ++c) t->col[c] = reinterpret_cast<uint32_t *>(base + stride * c);
-    t->d_count = reinterpret_cast<uint64_t *>(base + stride * (size_t)ncols);
+    t->d_count = t->block->count;
     return t;
 }
 
@@ -96,96 +109,50 @@ void copy_bounds(tid_table *dst, const tid_table *src, const int *map, int n, in
     for (int c = 0; c < n; ++c) dst->maxv[dst_off + c] = src->maxv[map ? map[c] : c];
 }
 
-void set_count(tid_ctx *ctx, tid_table *t, uint64_t n) {
-    hipLaunchKernelGGL(set_u64, dim3(1), dim3(1), 0, ctx->stream, t->d_count, n);
-    TID_HIP(hipGetLastError());
-    t->nrows = n;
-    t->count_known = true;
-}
-
-constexpr int kCountSets = 128;
-struct CountSets {
-    uint64_t *p[kCountSets];
-    uint64_t v[kCountSets];
-    int n;
+// n device words to pinned host memory, which the host reads after its wait
+constexpr int kReadWords = 256;
+struct WordList {
+    const uint64_t *p[kReadWords];
 };
 
-__global__ void set_u64_many(CountSets s) {
-    if ((int)threadIdx.x < s.n) *s.p[threadIdx.x] = s.v[threadIdx.x];
-}
-
-void set_count_later(tid_ctx *ctx, tid_table *t, uint64_t n) {
-    ctx->pending_counts.emplace_back(t->d_count, n);
-    t->nrows = n;
-    t->count_known = true;
-}
-
-void flush_counts(tid_ctx *ctx) {
-    auto &pc = ctx->pending_counts;
-    for (size_t i = 0; i < pc.size(); i += kCountSets) {
-        CountSets s{};
-        s.n = (int)std::min<size_t>(kCountSets, pc.size() - i);
-        for (int j = 0; j < s.n; ++j) {
-            s.p[j] = pc[i + j].first;
-            s.v[j] = pc[i + j].second;
-        }
-        hipLaunchKernelGGL(set_u64_many, dim3(1), dim3(kCountSets), 0, ctx->stream, s);
-        TID_HIP(hipGetLastError());
-    }
-    pc.clear();
-}
-
-__global__ void gather_words(const uint64_t *const *src, uint64_t *dst, int n,
-                             const uint32_t *flags) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i <= n; i += gridDim.x * blockDim.x)
-        dst[i] = i < n ? *src[i] : (uint64_t)flags[0];
+__global__ __launch_bounds__(kReadWords) void gather_words(WordList src, uint64_t *dst, int n) {
+    if ((int)threadIdx.x < n) dst[threadIdx.x] = *src.p[threadIdx.x];
 }
 
 void read_words(tid_ctx *ctx, const std::vector<const uint64_t *> &src, uint64_t *dst) {
     const size_t n = src.size();
     if (n == 0) return;
-    if (ctx->rw_cap < n + 1) {
-        if (ctx->rw_host_ptrs) (void)hipHostFree(ctx->rw_host_ptrs);
-        if (ctx->rw_host_vals) (void)hipHostFree(ctx->rw_host_vals);
-        if (ctx->rw_dev) ctx->free(ctx->rw_dev, ctx->rw_cap * 16);
-        ctx->rw_host_ptrs = nullptr;
-        ctx->rw_host_vals = nullptr;
-        ctx->rw_dev = nullptr;
-        const size_t cap = std::max<size_t>(n + 1, 2 * ctx->rw_cap);
-        TID_HIP(hipHostMalloc((void **)&ctx->rw_host_ptrs, cap * 8, hipHostMallocDefault));
-        TID_HIP(hipHostMalloc((void **)&ctx->rw_host_vals, cap * 8, hipHostMallocDefault));
-        ctx->rw_dev = ctx->alloc(cap * 16);
+    if (ctx->rw_cap < n) {
+        if (ctx->rw_host) (void)hipHostFree(ctx->rw_host);
+        ctx->rw_host = nullptr;
+        const size_t cap = std::max<size_t>({n, 2 * ctx->rw_cap, 1024});
+        ctx->rw_cap = 0;
+        TID_HIP(hipHostMalloc((void **)&ctx->rw_host, cap * 8, hipHostMallocCoherent));
         ctx->rw_cap = cap;
     }
-    for (size_t i = 0; i < n; ++i) ctx->rw_host_ptrs[i] = src[i];
-    const uint64_t **dptrs = static_cast<const uint64_t **>(ctx->rw_dev);
-    uint64_t *dvals = reinterpret_cast<uint64_t *>(static_cast<char *>(ctx->rw_dev) + ctx->rw_cap * 8);
-    TID_HIP(hipMemcpyAsync(dptrs, ctx->rw_host_ptrs, n * 8, hipMemcpyHostToDevice, ctx->stream));
-    hipLaunchKernelGGL(gather_words, dim3((unsigned)std::min<size_t>((n + 256) / 256, 1024)),
-                       dim3(256), 0, ctx->stream, dptrs, dvals, (int)n, ctx->d_flags);
-    TID_HIP(hipGetLastError());
-    TID_HIP(hipMemcpyAsync(ctx->rw_host_vals, dvals, (n + 1) * 8, hipMemcpyDeviceToHost,
-                           ctx->stream));
-    TID_HIP(hipStreamSynchronize(ctx->stream));
-    TID_REQUIRE(ctx->rw_host_vals[n] == 0, TID_E_INTERNAL,
-                "a cross-workgroup wait exceeded its spin bound (device state inconsistent)");
-    for (size_t i = 0; i < n; ++i) dst[i] = ctx->rw_host_vals[i];
+    for (size_t i = 0; i < n; i += kReadWords) {
+        WordList w{};
+        const int m = (int)std::min<size_t>(kReadWords, n - i);
+        for (int j = 0; j < m; ++j) w.p[j] = src[i + j];
+        hipLaunchKernelGGL(gather_words, dim3(1), dim3(kReadWords), 0, ctx->stream, w,
+                           ctx->rw_host + i, m);
+        TID_HIP(hipGetLastError());
+    }
+    ctx->sync();
+    ctx->check_flags();
+    for (size_t i = 0; i < n; ++i) dst[i] = ctx->rw_host[i];
 }
 
 void resolve_counts(tid_ctx *ctx, tid_table *const *ts, int k) {
-    std::vector<const uint64_t *> src;
-    std::vector<tid_table *> who;
-    for (int j = 0; j < k; ++j)
-        if (!ts[j]->count_known) {
-            src.push_back(ts[j]->d_count);
-            who.push_back(ts[j]);
+    bool waited = false;
+    for (int j = 0; j < k; ++j) {
+        if (ts[j]->count_known) continue;
+        if (!waited) {  // the kernels that write the counts have then run
+            ctx->sync();
+            ctx->check_flags();
+            waited = true;
         }
-    if (src.empty()) return;
-    std::vector<uint64_t> v(src.size());
-    read_words(ctx, src, v.data());
-    for (size_t i = 0; i < who.size(); ++i) {
-        who[i]->nrows = v[i];
-        who[i]->count_known = true;
+        set_count(ts[j], *static_cast<const volatile uint64_t *>(ts[j]->d_count));
     }
 }
 
@@ -199,7 +166,7 @@ std::unique_ptr<tid_table> copy_columns(tid_ctx *ctx, const uint32_t *const *col
                                    on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
                                    ctx->stream));
     }
-    set_count(ctx, t.get(), nrows);
+    set_count(t.get(), nrows);
     return t;
 }
 
@@ -411,6 +378,11 @@ uint32_t tid_ctx::next_epoch(size_t bytes, uint64_t **state) {
 }
 
 void tid_ctx::sync() { TID_HIP(hipStreamSynchronize(stream)); }
+
+void tid_ctx::check_flags() const {
+    TID_REQUIRE(*static_cast<const volatile uint32_t *>(d_flags) == 0, TID_E_INTERNAL,
+                "a cross-workgroup wait exceeded its spin bound (device state inconsistent)");
+}
 
 namespace tid {
 

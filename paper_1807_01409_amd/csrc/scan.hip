@@ -167,7 +167,7 @@ __global__ __launch_bounds__(BLOCK) void scan_multi_kernel(const uint32_t *__res
             uint32_t spins = 0;
             while ((w[u] >> kEpochShift) != a.epoch) {
                 if (++spins > kSpinLimit) {
-                    atomicOr(&flags[0], 1u);
+                    dev::raise(&flags[0]);
                     break;
                 }
                 __builtin_amdgcn_s_sleep(2);
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(BLOCK) void scan_multi_kernel(const uint32_t *__res
                 TID_FOR_COLS(3, c, o.ncols)
                     o.col[c][dst] = stage[o.stage_off + (uint32_t)c * o.stage_cap + r];
             } else {
-                atomicOr(&flags[1], 1u);
+                dev::raise(&flags[1]);
             }
         }
     }
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(BLOCK) void scan_multi_kernel(const uint32_t *__res
                     if (dst < o.cap) {
                         TID_FOR_COLS(3, c, o.ncols) o.col[c][dst] = pick(t[it], q.src[c]);
                     } else {
-                        atomicOr(&flags[1], 1u);
+                        dev::raise(&flags[1]);
                     }
                 }
             }
@@ -505,7 +505,9 @@ static std::unique_ptr<tid_table> slice_table(tid_ctx *ctx, const tid_graph *g,
     const uint64_t last = cdf.size() - 1;
     const uint64_t a = cdf[std::min<uint64_t>(p.p, last)];
     const uint64_t b = cdf[std::min<uint64_t>((uint64_t)p.p + 1, last)];
-    auto t = make_table(ctx, nc, vars, 0);  // the count word only
+    auto t = make_table(ctx, 0, nullptr, 0);  // no memory of its own
+    t->ncols = nc;
+    for (int c = 0; c < nc; ++c) t->vars[c] = vars[c];
     for (int c = 0; c < nc; ++c) {
         t->col[c] = const_cast<uint32_t *>(
             (src[c] == 0 ? g->part_s : g->part_o).get<const uint32_t>() + a);
@@ -513,7 +515,7 @@ static std::unique_ptr<tid_table> slice_table(tid_ctx *ctx, const tid_graph *g,
     }
     t->maxv_known = true;
     t->cap = b - a;
-    set_count_later(ctx, t.get(), b - a);  // written when scan_many returns
+    set_count(t.get(), b - a);
     return t;
 }
 
@@ -528,7 +530,6 @@ static std::unique_ptr<tid_table> slice_table(tid_ctx *ctx, const tid_graph *g,
 void scan_many(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, int k,
                std::unique_ptr<tid_table> *outs, const PatternSet *sets,
                const ScanFilter *filters) {
-    PendingCountsGuard counts_guard(ctx);
     const int64_t wide_min = ctx->opt.wide_min > 0 ? ctx->opt.wide_min : 8;
     const bool parts = g->partitioned && ctx->opt.layout != 0 && g->n > 0 &&
                        ctx->opt.capacity_override <= 0 && !g->cdf[1].empty();
@@ -622,7 +623,6 @@ void scan_many(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, int k,
         scan_multi(ctx, g, rp.data(), m, rt, rs.data(), rf.data());
         for (int j = 0; j < m; ++j) outs[rest[r0 + j]] = std::move(rt[j]);
     }
-    flush_counts(ctx);  // the whole-slice tables' count words
 }
 
 void scan_multi(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, int k,
@@ -641,7 +641,7 @@ void scan_multi(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, int k
         outs[j]->maxv_known = true;
     }
     if (g->n == 0) {
-        for (int j = 0; j < k; ++j) set_count(ctx, outs[j].get(), 0);
+        for (int j = 0; j < k; ++j) set_count(outs[j].get(), 0);
         return;
     }
     std::vector<tid_table *> raw(k);
@@ -709,7 +709,7 @@ std::unique_ptr<tid_table> filter_range(tid_ctx *ctx, const tid_table *t, int co
     out->maxv_known = t->maxv_known;
     copy_bounds(out.get(), t, nullptr, t->ncols);
     if (in_rows == 0) {
-        set_count(ctx, out.get(), 0);
+        set_count(out.get(), 0);
         return out;
     }
     run_filter(ctx, t, in_rows, col, lo, hi, out.get());

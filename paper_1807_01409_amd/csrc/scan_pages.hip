@@ -133,7 +133,7 @@ __device__ __forceinline__ void place_tile(const PageArgs &a, PageLists &l, uint
                 if (page < a.max_pages) {
                     a.hdr[page] = (uint64_t)blockIdx.x << 40 | (uint64_t)lane << 32 | (have + x);
                 } else {
-                    atomicOr(&a.flags[0], 1u);
+                    dev::raise(&a.flags[0]);
                     page = 0;
                 }
                 s_page[lane][(have + x) & (kRing - 1)] = page;

@@ -516,7 +516,7 @@ std::unique_ptr<tid_table> unique_sorted(tid_ctx *ctx, const tid_table *t, uint6
     out->maxv_known = t->maxv_known;
     copy_bounds(out.get(), t, nullptr, t->ncols);
     if (n == 0) {
-        set_count(ctx, out.get(), 0);
+        set_count(out.get(), 0);
         return out;
     }
     UniqueSrc src{};
@@ -536,7 +536,7 @@ std::unique_ptr<tid_table> sort_rows(tid_ctx *ctx, const tid_table *t, uint64_t 
     if (t->ncols == 0) {
         // zero-width rows are all equal
         auto out = make_table(ctx, 0, t->vars, 0);
-        set_count(ctx, out.get(), distinct ? std::min<uint64_t>(n, 1) : n);
+        set_count(out.get(), distinct ? std::min<uint64_t>(n, 1) : n);
         return out;
     }
     tid_table bounded;  // a caller's own table: its column bounds are found here
@@ -554,7 +554,7 @@ std::unique_ptr<tid_table> sort_rows(tid_ctx *ctx, const tid_table *t, uint64_t 
         for (int c = 0; c < t->ncols && n; ++c)
             TID_HIP(hipMemcpyAsync(sorted->col[c], t->col[c], n * 4, hipMemcpyDeviceToDevice,
                                    ctx->stream));
-        set_count(ctx, sorted.get(), n);
+        set_count(sorted.get(), n);
         return sorted;
     }
     if (rows_mergeable(t, n)) {
@@ -566,7 +566,7 @@ std::unique_ptr<tid_table> sort_rows(tid_ctx *ctx, const tid_table *t, uint64_t 
     } else {
         DevBuf perm = sort_permutation(ctx, t, n);
         gather_table(ctx, t, perm.get<const uint32_t>(), n, sorted.get());
-        set_count(ctx, sorted.get(), n);
+        set_count(sorted.get(), n);
     }
     if (!distinct) return sorted;
     return unique_sorted(ctx, sorted.get(), n);
@@ -643,7 +643,7 @@ std::unique_ptr<tid_table> union_tables(tid_ctx *ctx, const tid_table *const *ts
         }
         at += n;
     }
-    set_count(ctx, out.get(), total);
+    set_count(out.get(), total);
     if (!dedupe) return out;
     return sort_rows(ctx, out.get(), total, 1);
 }

@@ -207,7 +207,7 @@ __device__ __forceinline__ void wide_walk(const WideArgs &a, const WidePat *s_pa
                             o.col[cc][pos] = t[it].v[src];
                         }
                     } else {
-                        atomicOr(&flags[1], 1u);
+                        dev::raise(&flags[1]);
                     }
                 }
                 if (lane == __builtin_ctzll(peers)) s_run[pid] = before + (uint32_t)__popcll(peers);
@@ -389,7 +389,7 @@ static void wide_pass(tid_ctx *ctx, WideSource src, const tid_pattern *pats, int
             TID_REQUIRE(wide_eligible(pats[j]) && seg_pred[pats[j].p], TID_E_INTERNAL,
                         "wide pass: pattern without segment");
         if (v == 0) {
-            for (int j = 0; j < k; ++j) set_count(ctx, outs[j], 0);
+            for (int j = 0; j < k; ++j) set_count(outs[j], 0);
             return;
         }
     }
@@ -607,7 +607,7 @@ void run_wide_parts(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, i
         uint64_t a, b;
         slice_of(pats[j].p, a, b);
         if (b == a) {  // no triple has the predicate
-            set_count(ctx, outs[j], 0);
+            set_count(outs[j], 0);
             continue;
         }
         used[pats[j].p] = 1;
