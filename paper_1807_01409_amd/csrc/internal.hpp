@@ -186,23 +186,58 @@ inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a
 
 }  // namespace tid
 
-// Per-position ID histograms kept on the host as cumulative counts:
-// cdf[x][id] = number of triples whose position x holds an ID < id.  Used to
-// bound scan output sizes without a device round trip.
+namespace tid {
+
+// How many triples hold each ID at one position, on the host: one byte an ID
+// (255: the count is in `big`), and per block of 64 IDs the triples and the
+// `big` entries of all IDs before it.  Nine bits an ID instead of the 64 of a
+// cumulative count, which is what loading a graph waits for: the copy to the
+// host and the first touch of its pages.
+struct IdCounts {
+    static constexpr uint32_t kBlock = 64;
+    static constexpr uint32_t kBig = 255;
+    struct Mem {
+        std::unique_ptr<uint8_t[]> bytes;   // of every position
+        std::unique_ptr<uint64_t[]> rows;   // per block: triples before it
+        std::unique_ptr<uint64_t[]> nbig;   // per block: `big` entries before it
+        std::unique_ptr<uint32_t[]> big;
+    };
+    std::shared_ptr<Mem> mem;               // shared by a graph's positions
+    uint64_t first = 0;                     // the position's first block in `mem`
+    uint64_t ids = 0;                       // IDs 0 .. ids - 1 (0: not counted)
+    uint64_t total = 0;                     // triples
+    bool empty() const { return ids == 0; }
+    // triples whose position holds an ID below `id`
+    uint64_t below(uint64_t id) const {
+        if (id >= ids) return total;
+        const uint64_t b = first + id / kBlock;
+        uint64_t s = mem->rows[b] - mem->rows[first];
+        const uint8_t *c = mem->bytes.get() + b * kBlock;
+        const uint32_t *big = mem->big.get() + mem->nbig[b];
+        for (uint64_t i = 0; i < id % kBlock; ++i) s += c[i] < kBig ? c[i] : *big++;
+        return s;
+    }
+};
+
+}  // namespace tid
+
 struct tid_graph {
     tid_ctx *ctx = nullptr;
     uint64_t n = 0;
     tid::DevBuf data;                 // n*12 bytes (+ padding), AoS s,p,o
-    std::vector<uint64_t> cdf[3];     // empty if the position's max ID is too large
+    // per-position ID counts, which bound scan outputs without a device round
+    // trip (empty if the position's largest ID is too large)
+    tid::IdCounts counts[3];
     uint32_t max_id[3] = {0, 0, 0};
     // Optional layout variant: the triples stably sorted by predicate, as two
     // columns (subject, object); predicate p's triples are rows
-    // [cdf[1][p], cdf[1][p + 1]) in ascending triple position.  Scans with a
+    // [counts[1].below(p), counts[1].below(p + 1)) in ascending triple position.
+    // Scans with a
     // constant predicate then read only that slice (8 B per triple of p).
     tid::DevBuf part_s, part_o;
     // The same rows ordered by (predicate, subject) and by (predicate,
     // object), ties in triple order, as (subject, object) columns: predicate
-    // p's rows are the same [cdf[1][p], cdf[1][p + 1]) in both.  A semi-join
+    // p's rows are the same range in both.  A semi-join
     // on a pattern's subject or object looks its keys up in these.
     tid::DevBuf ps_s, ps_o, po_s, po_o;
     bool partitioned = false;
@@ -373,7 +408,7 @@ void read_words(tid_ctx *ctx, const std::vector<const uint64_t *> &src, uint64_t
 
 // validate and return the schema of a pattern; throws on a malformed pattern
 int pattern_schema(const tid_pattern &p, int32_t *vars, int32_t *src);
-// per-position histograms (device) -> host cdf
+// per-position ID counts, from one pass over the graph, to the host
 void build_stats(tid_ctx *ctx, tid_graph *g);
 void check_no_zero(tid_ctx *ctx, const tid_graph *g);
 

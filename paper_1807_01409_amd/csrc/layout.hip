@@ -84,7 +84,7 @@ void partition_graph(tid_ctx *ctx, tid_graph *g, bool enable) {
         return;
     }
     if (g->partitioned) return;
-    TID_REQUIRE(!g->cdf[1].empty(), TID_E_UNSUPPORTED,
+    TID_REQUIRE(!g->counts[1].empty(), TID_E_UNSUPPORTED,
                 "partition: the graph has no predicate histogram");
     TID_REQUIRE(g->n < (1ull << 32), TID_E_UNSUPPORTED, "partition: 2^32 triples or more");
     const uint64_t n = g->n;
@@ -129,10 +129,9 @@ void partition_graph(tid_ctx *ctx, tid_graph *g, bool enable) {
 void scan_slice(tid_ctx *ctx, const tid_graph *g, const tid_pattern &p, tid_table *out,
                 const ScanFilter *filter) {
     TID_REQUIRE(g->partitioned && p.p != 0, TID_E_INTERNAL, "slice scan: no slice");
-    const auto &cdf = g->cdf[1];
-    const uint64_t last = cdf.size() - 1;
-    const uint64_t a = cdf[std::min<uint64_t>(p.p, last)];
-    const uint64_t b = cdf[std::min<uint64_t>((uint64_t)p.p + 1, last)];
+    const IdCounts &preds = g->counts[1];
+    const uint64_t a = preds.below(p.p);
+    const uint64_t b = preds.below((uint64_t)p.p + 1);
     if (b == a) {
         set_count(out, 0);
         return;
@@ -304,11 +303,10 @@ unsigned grid_for_rows(uint64_t n) {
 // with its values at filters[j].keys.  Synchronises once.
 void index_semijoin(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats,
                     const ScanFilter *filters, int J, std::unique_ptr<tid_table> *outs) {
-    TID_REQUIRE(g->partitioned && !g->cdf[1].empty(), TID_E_INTERNAL,
+    TID_REQUIRE(g->partitioned && !g->counts[1].empty(), TID_E_INTERNAL,
                 "index semi-join: no partitioned layout");
     if (J == 0) return;
-    const auto &cdf = g->cdf[1];
-    const uint64_t last = cdf.size() - 1;
+    const IdCounts &preds = g->counts[1];
     std::vector<DevBuf> keep;
     std::vector<std::vector<char>> host_keep;
     // 1. every job's values, sorted (tables of one column)
@@ -341,8 +339,8 @@ void index_semijoin(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats,
     uint64_t P = 0;
     for (int j = 0; j < J; ++j) {
         const ScanFilter &f = filters[j];
-        const uint64_t a = cdf[std::min<uint64_t>(pats[j].p, last)];
-        const uint64_t b = cdf[std::min<uint64_t>((uint64_t)pats[j].p + 1, last)];
+        const uint64_t a = preds.below(pats[j].p);
+        const uint64_t b = preds.below((uint64_t)pats[j].p + 1);
         const bool by_s = f.pos == 0;
         IdxJob &x = jobs[j];
         x = IdxJob{};

@@ -406,7 +406,7 @@ static std::unique_ptr<tid_table> alias_table(const tid_table *t, const tid_patt
 static bool index_semijoin_ok(tid_ctx *ctx, const tid_graph *g, const tid_pattern &p,
                               const PatternSet &set, int pos, uint64_t rows) {
     if (!g->partitioned || !ctx->opt.layout || !ctx->opt.index_semijoin ||
-        ctx->opt.capacity_override > 0 || g->cdf[1].empty())
+        ctx->opt.capacity_override > 0 || g->counts[1].empty())
         return false;
     if (p.p == 0 || p.s != 0 || p.o != 0 || p.range_pos >= 0 || (p.vs >= 0 && p.vs == p.vo) ||
         set.pos >= 0 || (pos != 0 && pos != 2) || rows >= (1ull << 32))

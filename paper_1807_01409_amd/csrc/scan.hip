@@ -501,10 +501,9 @@ static std::unique_ptr<tid_table> slice_table(tid_ctx *ctx, const tid_graph *g,
                                               const tid_pattern &p) {
     int32_t vars[3], src[3];
     const int nc = pattern_schema(p, vars, src);
-    const auto &cdf = g->cdf[1];
-    const uint64_t last = cdf.size() - 1;
-    const uint64_t a = cdf[std::min<uint64_t>(p.p, last)];
-    const uint64_t b = cdf[std::min<uint64_t>((uint64_t)p.p + 1, last)];
+    const IdCounts &preds = g->counts[1];
+    const uint64_t a = preds.below(p.p);
+    const uint64_t b = preds.below((uint64_t)p.p + 1);
     auto t = make_table(ctx, 0, nullptr, 0);  // no memory of its own
     t->ncols = nc;
     for (int c = 0; c < nc; ++c) t->vars[c] = vars[c];
@@ -532,7 +531,7 @@ void scan_many(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, int k,
                const ScanFilter *filters) {
     const int64_t wide_min = ctx->opt.wide_min > 0 ? ctx->opt.wide_min : 8;
     const bool parts = g->partitioned && ctx->opt.layout != 0 && g->n > 0 &&
-                       ctx->opt.capacity_override <= 0 && !g->cdf[1].empty();
+                       ctx->opt.capacity_override <= 0 && !g->counts[1].empty();
     // semi-joins by index: every such pattern of the call in one batch
     std::vector<int> idx;
     for (int j = 0; j < k && filters; ++j)

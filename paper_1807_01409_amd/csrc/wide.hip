@@ -532,7 +532,7 @@ void run_wide(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, int k,
                                   ? (uint64_t)ctx->opt.slice_rows
                                   : std::max<uint64_t>(uint64_t(1) << 16, g->n >> 12);
     std::vector<uint32_t> sliced;
-    if (ctx->opt.wide_slice && !g->cdf[1].empty())
+    if (ctx->opt.wide_slice && !g->counts[1].empty())
         for (uint32_t p = 1; p < kWidePreds; ++p)
             if (by_pred[p].size() >= 2 && g->count_in(1, p, p + 1) >= min_rows) sliced.push_back(p);
     if (sliced.empty()) {
@@ -590,13 +590,12 @@ void run_wide(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, int k,
 // pass would write it.
 void run_wide_parts(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, int k,
                     tid_table *const *outs, const ScanFilter *filters) {
-    TID_REQUIRE(g->partitioned && !g->cdf[1].empty(), TID_E_INTERNAL,
+    TID_REQUIRE(g->partitioned && !g->counts[1].empty(), TID_E_INTERNAL,
                 "segment pass: the graph has no partitioned layout");
-    const auto &cdf = g->cdf[1];
-    const uint64_t last = cdf.size() - 1;
+    const IdCounts &preds = g->counts[1];
     auto slice_of = [&](uint32_t p, uint64_t &a, uint64_t &b) {
-        a = cdf[std::min<uint64_t>(p, last)];
-        b = cdf[std::min<uint64_t>((uint64_t)p + 1, last)];
+        a = preds.below(p);
+        b = preds.below((uint64_t)p + 1);
     };
     std::vector<char> used(kWidePreds, 0);
     std::vector<tid_pattern> sp;
