@@ -15,36 +15,11 @@
 
 namespace tid {
 
-bool radix_sort_pairs(tid_ctx *ctx, uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1,
-                      uint64_t n, int bits);
+void order_triples(tid_ctx *ctx, const uint32_t *g, uint64_t n, int pbits, int by_value, int pos,
+                   int vbits, uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, uint32_t *s,
+                   uint32_t *o);
 
 namespace {
-
-// key[i] = predicate of triple i, then (when vbits > 0) its value at
-// position vpos in the low vbits bits; pos[i] = i
-__global__ void predicate_keys(const uint32_t *__restrict__ g, uint64_t n, int vpos, int vbits,
-                               uint64_t *key, uint32_t *pos) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const uint64_t p = g[3 * i + 1];
-        key[i] = vbits ? (p << vbits) | g[3 * i + vpos] : p;
-        pos[i] = (uint32_t)i;
-    }
-}
-
-__global__ void gather_so(const uint32_t *__restrict__ g, const uint32_t *__restrict__ perm,
-                          uint64_t n, uint32_t *s, uint32_t *o) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const uint64_t t = perm[i];
-        s[i] = g[3 * t];
-        o[i] = g[3 * t + 2];
-    }
-}
-
-unsigned grid_of(uint64_t n) {
-    return (unsigned)std::max<uint64_t>(1, std::min<uint64_t>((n + 255) / 256, 16384));
-}
 
 // The triples of one predicate's slice: (s[i], p, o[i]).
 struct SliceSrc {
@@ -96,21 +71,12 @@ void partition_graph(tid_ctx *ctx, tid_graph *g, bool enable) {
         const int pbits = bits_of(g->max_id[1]);
         // predicate order, then (predicate, subject), then (predicate, object);
         // every sort is stable, so ties stay in triple order
-        const int vpos[3] = {0, 0, 2};
         for (int x = 0; x < 3; ++x) {
-            const int vbits = x == 0 ? 0 : bits_of(g->max_id[vpos[x]]);
-            hipLaunchKernelGGL(predicate_keys, dim3(grid_of(n)), dim3(256), 0, ctx->stream,
-                               g->triples(), n, vpos[x], vbits, k0.get<uint64_t>(),
-                               v0.get<uint32_t>());
-            TID_HIP(hipGetLastError());
-            const bool moved = radix_sort_pairs(ctx, k0.get<uint64_t>(), v0.get<uint32_t>(),
-                                                k1.get<uint64_t>(), v1.get<uint32_t>(), n,
-                                                pbits + vbits);
-            const uint32_t *perm = moved ? v1.get<const uint32_t>() : v0.get<const uint32_t>();
-            hipLaunchKernelGGL(gather_so, dim3(grid_of(n)), dim3(256), 0, ctx->stream,
-                               g->triples(), perm, n, cols[2 * x].get<uint32_t>(),
-                               cols[2 * x + 1].get<uint32_t>());
-            TID_HIP(hipGetLastError());
+            const int pos = x == 2 ? 2 : 0;
+            order_triples(ctx, g->triples(), n, pbits, x > 0, pos, bits_of(g->max_id[pos]),
+                          k0.get<uint64_t>(), v0.get<uint32_t>(), k1.get<uint64_t>(),
+                          v1.get<uint32_t>(), cols[2 * x].get<uint32_t>(),
+                          cols[2 * x + 1].get<uint32_t>());
         }
         TID_HIP(hipStreamSynchronize(ctx->stream));  // the sort buffers go back to the pool
     }

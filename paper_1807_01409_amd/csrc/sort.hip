@@ -1,19 +1,22 @@
 // sort.hip -- stable LSD radix sort of (64-bit key, 32-bit value) pairs, the
-// canonical lexicographic row order of tables, DISTINCT, and union.
+// row sorts built on it and on the merge sort of rowsort.hip (the canonical
+// lexicographic order, DISTINCT), and union.
 //
 // The paper sorts subquery results before joining them and merges final
 // results to distinct values (Sec. 4.2 step 3 with Mgpu's mergesort, Sec. 4.3
-// DISTINCT).  Here every ordering is an LSD radix sort written for wave64:
+// DISTINCT).  The radix sort, written for wave64, orders the triples of the
+// partitioned layout, dictionary hashes, sort-merge joins and rows too wide for
+// packed keys.  A pass over a digit of at most 9 bits:
 //   hist     each workgroup owns one contiguous range of the input and counts
-//            the digits of its range (wave-private LDS histograms, updated
-//            by the leader lane of each group of lanes holding one digit);
+//            the digits of its range in LDS, a set of bins per wave;
 //   offsets  one workgroup per digit scans that digit's counts over the
 //            ranges; the scatter kernel adds the bases of the smaller digits
-//            (a scan of the 256 digit totals) to find, for every (range,
-//            digit), the place where its first element goes;
-//   scatter  each workgroup walks its range tile by tile and writes every
-//            element at its digit's running offset plus its stable rank,
-//            found with ballots that group the lanes holding equal digits.
+//            to find, for every (range, digit), the place where its first
+//            element goes;
+//   scatter  each workgroup walks its range tile by tile, finds every
+//            element's stable rank with ballots that group the lanes holding
+//            equal digits, puts the tile in digit order in LDS and writes each
+//            digit's run to its place.
 // Up to 8192 pairs are sorted by one workgroup instead, every pass in LDS,
 // in one launch (small sorts are otherwise bound by launches, three a pass).
 // A row of k columns is sorted as one or more packed 64-bit keys (as many
@@ -35,18 +38,23 @@ void merge_sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &all,
                              std::vector<DevBuf> &keep,
                              std::vector<std::vector<char>> &host_keep);
 
-constexpr int kRadixBits = 8;
+constexpr int kRadixBits = 8;                 // digit of the small sort
 constexpr uint32_t kRadix = 1u << kRadixBits;
-constexpr int kSortBlock = 256;
-constexpr int kSortIPT = 16;
+constexpr int kMaxDigitBits = 9;              // widest digit of a pass over memory
+constexpr uint32_t kMaxDigits = 1u << kMaxDigitBits;
+constexpr int kSortBlock = 512;
+constexpr int kSortIPT = 8;
 constexpr int kSortNW = kSortBlock / dev::kWave;
-constexpr uint64_t kSortTile = (uint64_t)kSortBlock * kSortIPT;
+constexpr uint32_t kSortTile = (uint32_t)kSortBlock * kSortIPT;
 
-// lanes (among the valid ones) that hold the same digit as the calling lane
-__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid) {
+// lanes (among the valid ones) that hold the same digit, of at most BITS bits,
+// as the calling lane
+template <int BITS>
+__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid, int nbits = BITS) {
     uint64_t peers = dev::ballot(valid);
 #pragma unroll
-    for (int b = 0; b < kRadixBits; ++b) {
+    for (int b = 0; b < BITS; ++b) {
+        if (b >= nbits) break;  // the same for every lane
         const bool bit = (d >> b) & 1u;
         const uint64_t m = dev::ballot(bit);
         peers &= bit ? m : ~m;
@@ -55,143 +63,229 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid) {
 }
 
 // item `it` of lane `lane` in wave `wave` of the tile at t0: each wave owns 64*IPT
-// consecutive items, so every load instruction reads 64 consecutive keys
+// consecutive items, so every load instruction reads 64 consecutive items
 __device__ __forceinline__ uint64_t sort_item(uint64_t t0, int wave, int it, int lane) {
     return t0 + (uint64_t)wave * (dev::kWave * kSortIPT) + (uint64_t)it * dev::kWave + lane;
 }
 
-__global__ __launch_bounds__(kSortBlock) void radix_hist(const uint64_t *__restrict__ keys,
-                                                          uint64_t n, uint64_t range, int shift,
+// Digit counts of every range.  Each wave counts in LDS bins of its own: with
+// the ballots of the scatter in place of the LDS atomics this took 293 us for
+// 50M keys, now THIST us.
+template <class In>
+__global__ __launch_bounds__(kSortBlock) void radix_hist(In in, uint64_t n, uint64_t range,
+                                                          int shift, int nbits,
                                                           uint32_t *counts) {
-    __shared__ uint32_t s_h[kSortNW][kRadix];
+    __shared__ uint32_t s_h[kSortNW][kMaxDigits];
     const int tid = threadIdx.x, wave = tid / dev::kWave, lane = tid % dev::kWave;
-    for (uint32_t d = tid; d < kSortNW * kRadix; d += kSortBlock) (&s_h[0][0])[d] = 0;
+    const uint32_t R = 1u << nbits;
+    for (uint32_t d = tid; d < kSortNW * kMaxDigits; d += kSortBlock) (&s_h[0][0])[d] = 0;
     __syncthreads();
     const uint32_t w = blockIdx.x;
     const uint64_t r0 = (uint64_t)w * range, r1 = min(n, r0 + range);
     for (uint64_t t0 = r0; t0 < r1; t0 += kSortTile) {
         uint32_t d[kSortIPT];
+        if (t0 + kSortTile <= r1) {
 #pragma unroll
-        for (int it = 0; it < kSortIPT; ++it) {
-            const uint64_t i = sort_item(t0, wave, it, lane);
-            d[it] = i < r1 ? (uint32_t)(keys[i] >> shift) & (kRadix - 1) : 0u;
-        }
+            for (int it = 0; it < kSortIPT; ++it)
+                d[it] = (uint32_t)(in.key(sort_item(t0, wave, it, lane)) >> shift) & (R - 1);
 #pragma unroll
-        for (int it = 0; it < kSortIPT; ++it) {
-            const bool valid = sort_item(t0, wave, it, lane) < r1;
-            const uint64_t peers = match_digit(d[it], valid);
-            if (valid && lane == __builtin_ctzll(peers)) s_h[wave][d[it]] += (uint32_t)__popcll(peers);
+            for (int it = 0; it < kSortIPT; ++it) atomicAdd(&s_h[wave][d[it]], 1u);
+        } else {
+            for (int it = 0; it < kSortIPT; ++it) {
+                const uint64_t i = sort_item(t0, wave, it, lane);
+                if (i < r1) atomicAdd(&s_h[wave][(uint32_t)(in.key(i) >> shift) & (R - 1)], 1u);
+            }
         }
     }
     __syncthreads();
-    for (uint32_t dd = tid; dd < kRadix; dd += kSortBlock) {
+    for (uint32_t dd = tid; dd < R; dd += kSortBlock) {
         uint32_t s = 0;
         for (int ww = 0; ww < kSortNW; ++ww) s += s_h[ww][dd];
-        counts[(size_t)w * kRadix + dd] = s;
+        counts[(size_t)w * R + dd] = s;
     }
 }
 
-// Where each (range, digit) goes is offs[w][d] = base[d] + scan[w][d]: base[d]
-// counts every element of a smaller digit, scan[w][d] the elements of digit d
-// in ranges before w.  One workgroup per digit scans its column of the
-// range-major count matrix and writes the digit's total; the scatter kernel
-// turns the 256 totals into bases itself.
+// Where each (range, digit) goes is base[d] + scan[w][d]: base[d] counts every
+// element of a smaller digit, scan[w][d] the elements of digit d in ranges
+// before w.  One workgroup per digit scans its column of the range-major count
+// matrix and writes the digit's total; the scatter kernel turns the totals into
+// bases itself.
 constexpr int kColThreads = 256;
 __global__ __launch_bounds__(kColThreads) void digit_scan(const uint32_t *__restrict__ counts,
                                                            uint32_t *__restrict__ scan,
                                                            uint32_t *__restrict__ totals,
                                                            uint32_t P) {
     __shared__ uint32_t s_w[kColThreads / dev::kWave];
-    const uint32_t d = blockIdx.x;
+    const uint32_t d = blockIdx.x, R = gridDim.x;
     const int tid = threadIdx.x, wave = tid / dev::kWave, lane = tid % dev::kWave;
     const uint32_t per = (P + kColThreads - 1) / kColThreads;
     const uint32_t w0 = min(P, (uint32_t)tid * per), w1 = min(P, w0 + per);
     uint32_t sum = 0;
-    for (uint32_t w = w0; w < w1; ++w) sum += counts[(size_t)w * kRadix + d];
+    for (uint32_t w = w0; w < w1; ++w) sum += counts[(size_t)w * R + d];
     const uint32_t incl = dev::wave_inclusive_sum(sum);
     if (lane == dev::kWave - 1) s_w[wave] = incl;
     __syncthreads();
     uint32_t run = incl - sum;
     for (int x = 0; x < wave; ++x) run += s_w[x];
     for (uint32_t w = w0; w < w1; ++w) {
-        const uint32_t c = counts[(size_t)w * kRadix + d];
-        scan[(size_t)w * kRadix + d] = run;
+        const uint32_t c = counts[(size_t)w * R + d];
+        scan[(size_t)w * R + d] = run;
         run += c;
     }
     if (tid == kColThreads - 1) totals[d] = run;
 }
 
-__global__ __launch_bounds__(kSortBlock) void radix_scatter(
-    const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin, uint64_t *__restrict__ kout,
-    uint32_t *__restrict__ vout, uint64_t n, uint64_t range, int shift, const uint32_t *scan,
-    const uint32_t *totals) {
-    constexpr int kPer = kRadix / dev::kWave;  // digits per lane in the base scan
-    __shared__ uint32_t s_run[kRadix];
-    __shared__ uint32_t s_wh[kSortNW][kRadix];
+// The stable scatter.  A tile is put in digit order in LDS first, so that the
+// lanes of a wave write runs of consecutive places (on average tile / digits
+// items, 64-200 B of keys): the same pass with every lane writing its own item
+// to its place took 407 us for 50M pairs, now TSCAT us.  Keys and values go
+// through the same LDS one after the other, which leaves three workgroups to a
+// CU.
+template <class In, class Out>
+__global__ __launch_bounds__(kSortBlock) void radix_scatter(In in, Out out, uint64_t n,
+                                                             uint64_t range, int shift, int nbits,
+                                                             const uint32_t *scan,
+                                                             const uint32_t *totals) {
+    __shared__ uint64_t s_item[kSortTile];
+    __shared__ uint16_t s_wh[kSortNW][kMaxDigits];  // a wave's items per digit, then those before
+    __shared__ uint32_t s_run[kMaxDigits];          // where the range's next item of a digit goes
+    __shared__ uint32_t s_loc[kMaxDigits];          // first item of a digit in the sorted tile
+    __shared__ uint32_t s_off[kMaxDigits];          // place of sorted item i: s_off[digit] + i
+    __shared__ uint32_t s_w[kSortNW];
     const int tid = threadIdx.x, wave = tid / dev::kWave, lane = tid % dev::kWave;
-    const uint32_t w = blockIdx.x;
-    // digit bases: exclusive scan of the digit totals (wave 0, kPer digits a lane)
-    if (wave == 0) {
-        uint32_t v[kPer], loc = 0;
+    const uint32_t R = 1u << nbits, w = blockIdx.x;
+    // exclusive sum over the digits of x (thread d: digit d)
+    auto digit_prefix = [&](uint32_t x) {
+        const uint32_t incl = dev::wave_inclusive_sum(x);
+        if (lane == dev::kWave - 1) s_w[wave] = incl;
+        __syncthreads();
+        uint32_t before = 0;
 #pragma unroll
-        for (int x = 0; x < kPer; ++x) {
-            v[x] = totals[lane * kPer + x];
-            loc += v[x];
-        }
-        uint32_t run = dev::wave_inclusive_sum(loc) - loc;
-#pragma unroll
-        for (int x = 0; x < kPer; ++x) {
-            s_run[lane * kPer + x] = run;
-            run += v[x];
-        }
+        for (int y = 0; y < kSortNW; ++y) before += y < wave ? s_w[y] : 0u;
+        return before + incl - x;
+    };
+    static_assert(kMaxDigits <= kSortBlock, "a thread per digit");
+    {
+        const uint32_t base = digit_prefix(tid < (int)R ? totals[tid] : 0u);
+        if (tid < (int)R) s_run[tid] = base + scan[(size_t)w * R + tid];
     }
-    __syncthreads();
-    for (uint32_t d = tid; d < kRadix; d += kSortBlock) s_run[d] += scan[(size_t)w * kRadix + d];
     const uint64_t r0 = (uint64_t)w * range, r1 = min(n, r0 + range);
     const uint64_t lt = (1ull << lane) - 1ull;
     for (uint64_t t0 = r0; t0 < r1; t0 += kSortTile) {
         uint64_t key[kSortIPT];
         uint32_t val[kSortIPT], rank[kSortIPT];
+        const uint32_t cnt = (uint32_t)min((uint64_t)kSortTile, r1 - t0);
+        if (cnt == kSortTile) {
 #pragma unroll
-        for (int it = 0; it < kSortIPT; ++it) {
-            const uint64_t i = sort_item(t0, wave, it, lane);
-            key[it] = i < r1 ? kin[i] : 0ull;
-            val[it] = i < r1 ? vin[i] : 0u;
+            for (int it = 0; it < kSortIPT; ++it)
+                in.load(sort_item(t0, wave, it, lane), key[it], val[it]);
+        } else {
+#pragma unroll
+            for (int it = 0; it < kSortIPT; ++it) {
+                const uint64_t i = sort_item(t0, wave, it, lane);
+                key[it] = 0;
+                val[it] = 0;
+                if (i < r1) in.load(i, key[it], val[it]);
+            }
         }
-        for (uint32_t d = lane; d < kRadix; d += dev::kWave) s_wh[wave][d] = 0;
+        for (uint32_t d = lane; d < R; d += dev::kWave) s_wh[wave][d] = 0;
 #pragma unroll
         for (int it = 0; it < kSortIPT; ++it) {
             const bool valid = sort_item(t0, wave, it, lane) < r1;
-            const uint32_t d = (uint32_t)(key[it] >> shift) & (kRadix - 1);
-            const uint64_t peers = match_digit(d, valid);
+            const uint32_t d = (uint32_t)(key[it] >> shift) & (R - 1);
+            const uint64_t peers = match_digit<kMaxDigitBits>(d, valid, nbits);
             const uint32_t before = valid ? s_wh[wave][d] : 0u;
             rank[it] = before + (uint32_t)__popcll(peers & lt);
-            if (valid && lane == __builtin_ctzll(peers)) s_wh[wave][d] = before + (uint32_t)__popcll(peers);
+            if (valid && lane == __builtin_ctzll(peers))
+                s_wh[wave][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
         }
         __syncthreads();
-        // per-wave counts -> per-wave bases (waves in item order)
-        for (uint32_t d = tid; d < kRadix; d += kSortBlock) {
-            uint32_t run = s_run[d];
-            for (int ww = 0; ww < kSortNW; ++ww) {
-                const uint32_t c = s_wh[ww][d];
-                s_wh[ww][d] = run;
-                run += c;
+        uint32_t tot = 0;
+        if (tid < (int)R)
+            for (int ww = 0; ww < kSortNW; ++ww) {  // waves in item order
+                const uint32_t c = s_wh[ww][tid];
+                s_wh[ww][tid] = (uint16_t)tot;
+                tot += c;
             }
-            s_run[d] = run;
+        const uint32_t loc = digit_prefix(tot);
+        if (tid < (int)R) {
+            const uint32_t run = s_run[tid];
+            s_loc[tid] = loc;
+            s_off[tid] = run - loc;
+            s_run[tid] = run + tot;
         }
         __syncthreads();
+        uint32_t at[kSortIPT];
 #pragma unroll
         for (int it = 0; it < kSortIPT; ++it) {
-            if (sort_item(t0, wave, it, lane) < r1) {
-                const uint32_t d = (uint32_t)(key[it] >> shift) & (kRadix - 1);
-                const uint32_t pos = s_wh[wave][d] + rank[it];
-                kout[pos] = key[it];
-                vout[pos] = val[it];
+            const uint32_t d = (uint32_t)(key[it] >> shift) & (R - 1);
+            at[it] = s_loc[d] + s_wh[wave][d] + rank[it];
+            if (sort_item(t0, wave, it, lane) < r1) s_item[at[it]] = key[it];
+        }
+        __syncthreads();
+        uint64_t skey[kSortIPT];
+#pragma unroll
+        for (int u = 0; u < kSortIPT; ++u) skey[u] = s_item[u * kSortBlock + tid];
+        __syncthreads();
+        uint32_t *s_val = reinterpret_cast<uint32_t *>(s_item);
+#pragma unroll
+        for (int it = 0; it < kSortIPT; ++it)
+            if (sort_item(t0, wave, it, lane) < r1) s_val[at[it]] = val[it];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kSortIPT; ++u) {
+            const uint32_t i = u * kSortBlock + tid;
+            if (i < cnt) {
+                const uint32_t d = (uint32_t)(skey[u] >> shift) & (R - 1);
+                out.put(s_off[d] + i, skey[u], s_val[i]);
             }
         }
         __syncthreads();
     }
 }
+
+// where a pass takes its pairs from, and where it puts them
+struct PairIn {
+    const uint64_t *k;
+    const uint32_t *v;
+    __device__ __forceinline__ uint64_t key(uint64_t i) const { return k[i]; }
+    __device__ __forceinline__ void load(uint64_t i, uint64_t &key, uint32_t &val) const {
+        key = k[i];
+        val = v[i];
+    }
+};
+
+struct PairOut {
+    uint64_t *k;
+    uint32_t *v;
+    __device__ __forceinline__ void put(uint32_t at, uint64_t key, uint32_t val) const {
+        k[at] = key;
+        v[at] = val;
+    }
+};
+
+// a triple as (its predicate and, below it in `bits` bits, the value at position
+// lo; the value at position hi)
+struct TripleIn {
+    const uint32_t *g;
+    int32_t lo, hi, bits;
+    __device__ __forceinline__ uint64_t key(uint64_t i) const {
+        return (uint64_t)g[3 * i + 1] << bits | g[3 * i + lo];
+    }
+    __device__ __forceinline__ void load(uint64_t i, uint64_t &key, uint32_t &val) const {
+        key = (uint64_t)g[3 * i + 1] << bits | g[3 * i + lo];
+        val = g[3 * i + hi];
+    }
+};
+
+struct ColumnsOut {
+    uint32_t *lo, *hi;
+    uint64_t mask;
+    __device__ __forceinline__ void put(uint32_t at, uint64_t key, uint32_t val) const {
+        lo[at] = (uint32_t)(key & mask);
+        hi[at] = val;
+    }
+};
 
 // One workgroup sorts n <= kSmallBlock * kSmallIPT pairs on key bits
 // [0, bits), in place: the pairs stay in LDS between passes, and each pass
@@ -237,7 +331,7 @@ __global__ __launch_bounds__(kSmallBlock) void small_sort(uint64_t *keys, uint32
         for (int it = 0; it < kSmallIPT; ++it) {
             const bool valid = small_item(wave, it, lane) < n;
             const uint32_t d = (uint32_t)(key[it] >> shift) & (kRadix - 1);
-            const uint64_t peers = match_digit(d, valid);
+            const uint64_t peers = match_digit<kRadixBits>(d, valid);
             const uint32_t before = valid ? s_wh[wave][d] : 0u;
             rank[it] = before + (uint32_t)__popcll(peers & lt);
             if (valid && lane == __builtin_ctzll(peers)) s_wh[wave][d] = before + (uint32_t)__popcll(peers);
@@ -385,6 +479,40 @@ void iota(tid_ctx *ctx, uint32_t *p, uint64_t n) {
     TID_HIP(hipGetLastError());
 }
 
+// The passes of a stable sort of n pairs on key bits [first, last): digits of
+// nearly equal widths, at most kMaxDigitBits, over ranges of whole tiles.
+struct Passes {
+    uint64_t n, range, P;
+    int first, last, count, width;
+    DevBuf counts, scan;
+    Passes(tid_ctx *ctx, uint64_t rows, int b0, int b1) : n(rows), first(b0), last(b1) {
+        count = std::max(1, (last - first + kMaxDigitBits - 1) / kMaxDigitBits);
+        width = (last - first + count - 1) / count;
+        const uint64_t tiles = (n + kSortTile - 1) / kSortTile;
+        P = std::max<uint64_t>(1, std::min<uint64_t>(tiles, 3ull * device_cus(ctx)));
+        range = (tiles + P - 1) / P * kSortTile;
+        P = (n + range - 1) / range;
+        counts = DevBuf(ctx, ((size_t)P << width) * sizeof(uint32_t));
+        scan = DevBuf(ctx, ((size_t)(P + 1) << width) * sizeof(uint32_t));  // then the totals
+    }
+    template <class In, class Out>
+    void run(tid_ctx *ctx, In in, Out out, int pass) const {
+        const int shift = first + pass * width, nbits = std::min(width, last - shift);
+        uint32_t *totals = scan.get<uint32_t>() + ((size_t)P << nbits);
+        hipLaunchKernelGGL(radix_hist<In>, dim3((uint32_t)P), dim3(kSortBlock), 0, ctx->stream, in,
+                           n, range, shift, nbits, counts.get<uint32_t>());
+        TID_HIP(hipGetLastError());
+        hipLaunchKernelGGL(digit_scan, dim3(1u << nbits), dim3(kColThreads), 0, ctx->stream,
+                           counts.get<const uint32_t>(), scan.get<uint32_t>(), totals,
+                           (uint32_t)P);
+        TID_HIP(hipGetLastError());
+        hipLaunchKernelGGL((radix_scatter<In, Out>), dim3((uint32_t)P), dim3(kSortBlock), 0,
+                           ctx->stream, in, out, n, range, shift, nbits,
+                           scan.get<const uint32_t>(), totals);
+        TID_HIP(hipGetLastError());
+    }
+};
+
 // Stable sort of n (key, value) pairs on key bits [0, bits).  The sorted pairs
 // end in (k0, v0) if the return value is false, in (k1, v1) if true.
 bool radix_sort_pairs(tid_ctx *ctx, uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1,
@@ -404,31 +532,37 @@ bool radix_sort_pairs(tid_ctx *ctx, uint64_t *k0, uint32_t *v0, uint64_t *k1, ui
         TID_HIP(hipGetLastError());
         return false;
     }
-    const uint64_t tiles = (n + kSortTile - 1) / kSortTile;
-    uint64_t P = std::max<uint64_t>(1, std::min<uint64_t>(tiles, 2ull * device_cus(ctx)));
-    const uint64_t range = (tiles + P - 1) / P * kSortTile;
-    P = (n + range - 1) / range;
-    DevBuf counts(ctx, (size_t)kRadix * P * sizeof(uint32_t));
-    DevBuf scan(ctx, (size_t)kRadix * (P + 1) * sizeof(uint32_t));  // then the digit totals
-    uint32_t *totals = scan.get<uint32_t>() + (size_t)kRadix * P;
-    bool flip = false;
-    for (int shift = 0; shift < bits; shift += kRadixBits) {
-        const uint64_t *ki = flip ? k1 : k0;
-        const uint32_t *vi = flip ? v1 : v0;
-        uint64_t *ko = flip ? k0 : k1;
-        uint32_t *vo = flip ? v0 : v1;
-        hipLaunchKernelGGL(radix_hist, dim3((uint32_t)P), dim3(kSortBlock), 0, ctx->stream, ki, n,
-                           range, shift, counts.get<uint32_t>());
-        TID_HIP(hipGetLastError());
-        hipLaunchKernelGGL(digit_scan, dim3(kRadix), dim3(kColThreads), 0, ctx->stream,
-                           counts.get<const uint32_t>(), scan.get<uint32_t>(), totals, (uint32_t)P);
-        TID_HIP(hipGetLastError());
-        hipLaunchKernelGGL(radix_scatter, dim3((uint32_t)P), dim3(kSortBlock), 0, ctx->stream, ki,
-                           vi, ko, vo, n, range, shift, scan.get<const uint32_t>(), totals);
-        TID_HIP(hipGetLastError());
-        flip = !flip;
+    const Passes ps(ctx, n, 0, bits);
+    for (int x = 0; x < ps.count; ++x) {
+        const bool flip = x & 1;
+        ps.run(ctx, PairIn{flip ? k1 : k0, flip ? v1 : v0}, PairOut{flip ? k0 : k1, flip ? v0 : v1},
+               x);
     }
-    return flip;
+    return ps.count & 1;
+}
+
+// The subject and object columns of the n triples in (predicate, value) order,
+// stably: by_value = 0 predicate alone, else its subject (pos 0) or object (pos
+// 2) too, whose IDs have vbits bits.  The first pass reads the triples, the last
+// one writes the columns: no key array is packed, nothing is gathered.  k and v
+// (n each) are scratch, two of each.
+void order_triples(tid_ctx *ctx, const uint32_t *g, uint64_t n, int pbits, int by_value, int pos,
+                   int vbits, uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, uint32_t *s,
+                   uint32_t *o) {
+    TID_REQUIRE(n < (1ull << 32), TID_E_UNSUPPORTED, "sort: more than 2^32-1 rows");
+    if (n == 0) return;
+    const int below = by_value ? vbits : 32;  // bits below the predicate
+    const TripleIn in{g, pos, 2 - pos, below};
+    const ColumnsOut out{pos == 0 ? s : o, pos == 0 ? o : s, (1ull << below) - 1};
+    const Passes ps(ctx, n, by_value ? 0 : below, below + pbits);
+    for (int x = 0; x < ps.count; ++x) {
+        const PairIn pin{x & 1 ? k0 : k1, x & 1 ? v0 : v1};
+        const PairOut pout{x & 1 ? k1 : k0, x & 1 ? v1 : v0};
+        if (x == 0 && ps.count == 1) ps.run(ctx, in, out, x);
+        else if (x == 0) ps.run(ctx, in, pout, x);
+        else if (x + 1 == ps.count) ps.run(ctx, pin, out, x);
+        else ps.run(ctx, pin, pout, x);
+    }
 }
 
 std::vector<uint32_t> column_maxima(tid_ctx *ctx, const tid_table *t, uint64_t n) {
