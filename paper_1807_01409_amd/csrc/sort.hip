@@ -62,15 +62,15 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid, int nbit
     return valid ? peers : 0ull;
 }
 
-// item `it` of lane `lane` in wave `wave` of the tile at t0: each wave owns 64*IPT
+// item `it` of lane `lane` in wave `wave` of a tile: each wave owns 64*IPT
 // consecutive items, so every load instruction reads 64 consecutive items
-__device__ __forceinline__ uint64_t sort_item(uint64_t t0, int wave, int it, int lane) {
-    return t0 + (uint64_t)wave * (dev::kWave * kSortIPT) + (uint64_t)it * dev::kWave + lane;
+__device__ __forceinline__ uint32_t sort_item(int wave, int it, int lane) {
+    return (uint32_t)(wave * (dev::kWave * kSortIPT) + it * dev::kWave + lane);
 }
 
 // Digit counts of every range.  Each wave counts in LDS bins of its own: with
 // the ballots of the scatter in place of the LDS atomics this took 293 us for
-// 50M keys, now THIST us.
+// 50M keys, now 120 us.
 template <class In>
 __global__ __launch_bounds__(kSortBlock) void radix_hist(In in, uint64_t n, uint64_t range,
                                                           int shift, int nbits,
@@ -83,17 +83,19 @@ __global__ __launch_bounds__(kSortBlock) void radix_hist(In in, uint64_t n, uint
     const uint32_t w = blockIdx.x;
     const uint64_t r0 = (uint64_t)w * range, r1 = min(n, r0 + range);
     for (uint64_t t0 = r0; t0 < r1; t0 += kSortTile) {
-        uint32_t d[kSortIPT];
-        if (t0 + kSortTile <= r1) {
+        const In at = in.from(t0);
+        const uint32_t cnt = (uint32_t)min((uint64_t)kSortTile, r1 - t0);
+        if (cnt == kSortTile) {
+            uint32_t d[kSortIPT];
 #pragma unroll
             for (int it = 0; it < kSortIPT; ++it)
-                d[it] = (uint32_t)(in.key(sort_item(t0, wave, it, lane)) >> shift) & (R - 1);
+                d[it] = (uint32_t)(at.key(sort_item(wave, it, lane)) >> shift) & (R - 1);
 #pragma unroll
             for (int it = 0; it < kSortIPT; ++it) atomicAdd(&s_h[wave][d[it]], 1u);
         } else {
             for (int it = 0; it < kSortIPT; ++it) {
-                const uint64_t i = sort_item(t0, wave, it, lane);
-                if (i < r1) atomicAdd(&s_h[wave][(uint32_t)(in.key(i) >> shift) & (R - 1)], 1u);
+                const uint32_t i = sort_item(wave, it, lane);
+                if (i < cnt) atomicAdd(&s_h[wave][(uint32_t)(at.key(i) >> shift) & (R - 1)], 1u);
             }
         }
     }
@@ -138,7 +140,9 @@ __global__ __launch_bounds__(kColThreads) void digit_scan(const uint32_t *__rest
 // The stable scatter.  A tile is put in digit order in LDS first, so that the
 // lanes of a wave write runs of consecutive places (on average tile / digits
 // items, 64-200 B of keys): the same pass with every lane writing its own item
-// to its place took 407 us for 50M pairs, now TSCAT us.  Keys and values go
+// to its place took 407 us for 50M pairs of 8-bit digits, now 392 us for 9-bit
+// ones (requesting the next tile early, or six waves to a SIMD, cost registers
+// and were slower).  Keys and values go
 // through the same LDS one after the other, which leaves three workgroups to a
 // CU.
 template <class In, class Out>
@@ -174,24 +178,25 @@ __global__ __launch_bounds__(kSortBlock) void radix_scatter(In in, Out out, uint
     for (uint64_t t0 = r0; t0 < r1; t0 += kSortTile) {
         uint64_t key[kSortIPT];
         uint32_t val[kSortIPT], rank[kSortIPT];
+        const In tile = in.from(t0);
         const uint32_t cnt = (uint32_t)min((uint64_t)kSortTile, r1 - t0);
         if (cnt == kSortTile) {
 #pragma unroll
             for (int it = 0; it < kSortIPT; ++it)
-                in.load(sort_item(t0, wave, it, lane), key[it], val[it]);
+                tile.load(sort_item(wave, it, lane), key[it], val[it]);
         } else {
 #pragma unroll
             for (int it = 0; it < kSortIPT; ++it) {
-                const uint64_t i = sort_item(t0, wave, it, lane);
+                const uint32_t i = sort_item(wave, it, lane);
                 key[it] = 0;
                 val[it] = 0;
-                if (i < r1) in.load(i, key[it], val[it]);
+                if (i < cnt) tile.load(i, key[it], val[it]);
             }
         }
         for (uint32_t d = lane; d < R; d += dev::kWave) s_wh[wave][d] = 0;
 #pragma unroll
         for (int it = 0; it < kSortIPT; ++it) {
-            const bool valid = sort_item(t0, wave, it, lane) < r1;
+            const bool valid = sort_item(wave, it, lane) < cnt;
             const uint32_t d = (uint32_t)(key[it] >> shift) & (R - 1);
             const uint64_t peers = match_digit<kMaxDigitBits>(d, valid, nbits);
             const uint32_t before = valid ? s_wh[wave][d] : 0u;
@@ -220,7 +225,7 @@ __global__ __launch_bounds__(kSortBlock) void radix_scatter(In in, Out out, uint
         for (int it = 0; it < kSortIPT; ++it) {
             const uint32_t d = (uint32_t)(key[it] >> shift) & (R - 1);
             at[it] = s_loc[d] + s_wh[wave][d] + rank[it];
-            if (sort_item(t0, wave, it, lane) < r1) s_item[at[it]] = key[it];
+            if (sort_item(wave, it, lane) < cnt) s_item[at[it]] = key[it];
         }
         __syncthreads();
         uint64_t skey[kSortIPT];
@@ -230,7 +235,7 @@ __global__ __launch_bounds__(kSortBlock) void radix_scatter(In in, Out out, uint
         uint32_t *s_val = reinterpret_cast<uint32_t *>(s_item);
 #pragma unroll
         for (int it = 0; it < kSortIPT; ++it)
-            if (sort_item(t0, wave, it, lane) < r1) s_val[at[it]] = val[it];
+            if (sort_item(wave, it, lane) < cnt) s_val[at[it]] = val[it];
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < kSortIPT; ++u) {
@@ -248,8 +253,9 @@ __global__ __launch_bounds__(kSortBlock) void radix_scatter(In in, Out out, uint
 struct PairIn {
     const uint64_t *k;
     const uint32_t *v;
-    __device__ __forceinline__ uint64_t key(uint64_t i) const { return k[i]; }
-    __device__ __forceinline__ void load(uint64_t i, uint64_t &key, uint32_t &val) const {
+    __device__ __forceinline__ PairIn from(uint64_t t0) const { return PairIn{k + t0, v + t0}; }
+    __device__ __forceinline__ uint64_t key(uint32_t i) const { return k[i]; }
+    __device__ __forceinline__ void load(uint32_t i, uint64_t &key, uint32_t &val) const {
         key = k[i];
         val = v[i];
     }
@@ -265,16 +271,22 @@ struct PairOut {
 };
 
 // a triple as (its predicate and, below it in `bits` bits, the value at position
-// lo; the value at position hi)
+// lo, 0 or 2; the value at the other one)
 struct TripleIn {
     const uint32_t *g;
-    int32_t lo, hi, bits;
-    __device__ __forceinline__ uint64_t key(uint64_t i) const {
-        return (uint64_t)g[3 * i + 1] << bits | g[3 * i + lo];
+    int32_t lo, bits;
+    __device__ __forceinline__ TripleIn from(uint64_t t0) const {
+        return TripleIn{g + 3 * t0, lo, bits};
     }
-    __device__ __forceinline__ void load(uint64_t i, uint64_t &key, uint32_t &val) const {
-        key = (uint64_t)g[3 * i + 1] << bits | g[3 * i + lo];
-        val = g[3 * i + hi];
+    __device__ __forceinline__ uint64_t key(uint32_t i) const {
+        const uint32_t *t = g + 3 * i;
+        return (uint64_t)t[1] << bits | (lo == 0 ? t[0] : t[2]);
+    }
+    __device__ __forceinline__ void load(uint32_t i, uint64_t &key, uint32_t &val) const {
+        const uint32_t *t = g + 3 * i;
+        const uint32_t s = t[0], p = t[1], o = t[2];  // one 12-byte load
+        key = (uint64_t)p << bits | (lo == 0 ? s : o);
+        val = lo == 0 ? o : s;
     }
 };
 
@@ -552,7 +564,7 @@ void order_triples(tid_ctx *ctx, const uint32_t *g, uint64_t n, int pbits, int b
     TID_REQUIRE(n < (1ull << 32), TID_E_UNSUPPORTED, "sort: more than 2^32-1 rows");
     if (n == 0) return;
     const int below = by_value ? vbits : 32;  // bits below the predicate
-    const TripleIn in{g, pos, 2 - pos, below};
+    const TripleIn in{g, pos, below};
     const ColumnsOut out{pos == 0 ? s : o, pos == 0 ? o : s, (1ull << below) - 1};
     const Passes ps(ctx, n, by_value ? 0 : below, below + pbits);
     for (int x = 0; x < ps.count; ++x) {
