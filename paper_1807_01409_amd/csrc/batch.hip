@@ -421,6 +421,9 @@ void flush_sort_jobs(tid_ctx *ctx, BatchState &bs) {
 namespace tid {
 
 void exclusive_scan_async(tid_ctx *ctx, const uint32_t *in, uint64_t n, uint64_t *out);
+void scan_words_async(tid_ctx *ctx, const uint64_t *in, uint64_t n, uint64_t *out);
+bool sort_keys32(tid_ctx *ctx, const uint32_t *col, uint64_t n, int bits, uint32_t *k0,
+                 uint32_t *v0, uint32_t *k1, uint32_t *v1);
 int device_cus(tid_ctx *ctx);
 
 namespace {
@@ -430,6 +433,7 @@ constexpr int kBigIPT = 4;
 constexpr uint64_t kBigTile = (uint64_t)kBigBlock * kBigIPT;
 constexpr int kBigLds = 2048;       // LDS rank table entries (> rows per tile)
 constexpr uint32_t kNoSlot32 = 0xFFFFFFFFu;
+constexpr int kProbeIPT = (int)kProbeTile / kBigBlock;
 
 // index j with base[j] <= x < base[j + 1] (base non-decreasing, base[0] = 0)
 __device__ __forceinline__ int job_of(const uint64_t *base, int J, uint64_t x) {
@@ -529,84 +533,191 @@ __device__ __forceinline__ bool big_agree(const uint32_t *const *el, const uint3
     return ok;
 }
 
-__global__ void big_probe(const BigCount *jobs, int J, const uint64_t *lbase, uint64_t nrows,
-                          const uint64_t *slots, const uint32_t *cnt, const uint64_t *start,
-                          const uint32_t *rows, uint32_t *lslot, uint32_t *lcount) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; g < nrows; g += stride) {
-        const int j = job_of(lbase, J, g);
-        const BigCount &b = jobs[j];
-        const uint64_t l = g - b.lbase;
-        const uint32_t key = b.lkey[l];
-        const uint64_t want = (uint64_t)key + 1ull;
-        uint32_t h = dev::hash32(key) & b.mask;
-        uint32_t slot = kNoSlot32, c = 0;
-        for (uint32_t probe = 0; probe <= b.mask; ++probe) {
-            const uint64_t cur = slots[b.sbase + h];
-            if (cur == want) {
-                slot = (uint32_t)(b.sbase + h);
-                break;
-            }
-            if (cur == 0ull) break;
-            h = (h + 1) & b.mask;
-        }
-        if (slot != kNoSlot32) {
-            if (b.neq == 0) {
-                c = cnt[slot];
-            } else {
-                const uint64_t a = start[slot];
-                for (uint32_t m = 0; m < cnt[slot]; ++m)
-                    c += big_agree(b.eq_l, b.eq_r, b.neq, l, rows[a + m]);
-            }
-        }
-        lslot[g] = slot;
-        lcount[g] = c;
+// Index of a sorted build side: for every present key, or group of keys that
+// share key >> shift, where its run starts and ends in the sorted rows.
+__global__ void index_runs(const uint32_t *__restrict__ key, uint32_t n, int shift, uint2 *index) {
+    const uint32_t stride = gridDim.x * blockDim.x;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+        const uint32_t h = key[i] >> shift;
+        if (i == 0 || key[i - 1] >> shift != h) index[h].x = i;
+        if (i + 1 == n || key[i + 1] >> shift != h) index[h].y = i + 1;
     }
 }
 
-__global__ void big_totals(const BigCount *jobs, int J, const uint64_t *loff, uint64_t *tot) {
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < J; j += gridDim.x * blockDim.x)
-        tot[j] = loff[jobs[j].lbase + jobs[j].nl] - loff[jobs[j].lbase];
+// The build rows of key k: `len` of them from `at` on in the job's rows.
+__device__ __forceinline__ void find_run(const BigCount &b, const uint64_t *slots,
+                                         const uint32_t *cnt, const uint64_t *start, uint32_t k,
+                                         uint32_t &at, uint32_t &len) {
+    at = len = 0;
+    if (b.index) {
+        if (k > b.max_key) return;
+        const uint2 run = b.index[k >> b.shift];
+        if (run.x >= run.y) return;  // absent (both words are ~0)
+        if (b.shift == 0) {
+            at = run.x;
+            len = run.y - run.x;
+            return;
+        }
+        uint32_t lo = run.x, hi = run.y;  // first row with key >= k
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (b.skey[mid] < k) lo = mid + 1;
+            else hi = mid;
+        }
+        at = lo;
+        hi = run.y;
+        while (lo < hi) {  // first row with key > k
+            const uint32_t mid = (lo + hi) >> 1;
+            if (b.skey[mid] <= k) lo = mid + 1;
+            else hi = mid;
+        }
+        len = lo - at;
+        return;
+    }
+    const uint64_t want = (uint64_t)k + 1ull;
+    uint32_t h = dev::hash32(k) & b.mask;
+    for (uint32_t probe = 0; probe <= b.mask; ++probe) {
+        const uint64_t cur = slots[b.sbase + h];
+        if (cur == want) {
+            len = cnt[b.sbase + h];
+            at = (uint32_t)start[b.sbase + h];
+            return;
+        }
+        if (cur == 0ull) return;
+        h = (h + 1) & b.mask;
+    }
 }
 
-// one output row per thread: its join, its L row (binary search over the
-// join's slice of the offsets), the k-th partner in the L row's slot
+// A tile of a job's probe rows: the rows that put out anything become entries
+// (row, first build row, output rows before it in the tile), packed at the
+// tile's start in `entries`; their number and the tile's output rows are left
+// for the expansion.  Only rows with output are written, and only the tiles'
+// sums are scanned afterwards: with an offset kept and scanned for every probe
+// row, joins of millions of rows and few matches spent as long on those.
+__global__ __launch_bounds__(kBigBlock) void big_probe(const BigCount *jobs, int J,
+                                                       const uint64_t *ltile,
+                                                       const uint64_t *slots, const uint32_t *cnt,
+                                                       const uint64_t *start, BigEntry *entries,
+                                                       uint32_t *tcount, uint64_t *ttotal) {
+    constexpr int NW = kBigBlock / dev::kWave;
+    __shared__ uint32_t s_m[NW];
+    __shared__ uint64_t s_s[NW];
+    const uint64_t tile = blockIdx.x;
+    const int j = job_of(ltile, J, tile);
+    const BigCount &b = jobs[j];
+    const uint64_t l0 = (tile - ltile[j]) * kProbeTile;
+    uint32_t key[kProbeIPT], at[kProbeIPT], len[kProbeIPT];
+#pragma unroll
+    for (int u = 0; u < kProbeIPT; ++u) {
+        const uint64_t l = l0 + (uint64_t)u * kBigBlock + threadIdx.x;
+        key[u] = l < b.nl ? b.lkey[l] : 0u;
+    }
+    uint32_t mine = 0;
+    uint64_t sum = 0;
+#pragma unroll
+    for (int u = 0; u < kProbeIPT; ++u) {
+        const uint64_t l = l0 + (uint64_t)u * kBigBlock + threadIdx.x;
+        at[u] = len[u] = 0;
+        if (l >= b.nl) continue;
+        find_run(b, slots, cnt, start, key[u], at[u], len[u]);
+        if (b.neq) {
+            uint32_t c = 0;
+            for (uint32_t m = 0; m < len[u]; ++m)
+                c += big_agree(b.eq_l, b.eq_r, b.neq, l, b.rows[at[u] + m]);
+            len[u] = c;
+        }
+        if (len[u]) {
+            if (!b.matched) len[u] = 0;
+        } else if (b.unmatched) {
+            at[u] = kNoSlot32;  // one output row, without a build row
+            len[u] = 1;
+        }
+        mine += len[u] != 0;
+        sum += len[u];
+    }
+    const int lane = dev::lane_id(), wave = threadIdx.x / dev::kWave;
+    const uint32_t mi = dev::wave_inclusive_sum(mine);
+    const uint64_t si = dev::wave_inclusive_sum(sum);
+    if (lane == dev::kWave - 1) {
+        s_m[wave] = mi;
+        s_s[wave] = si;
+    }
+    __syncthreads();
+    uint32_t m = mi - mine, all_m = 0;
+    uint64_t s = si - sum, all_s = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        if (w < wave) {
+            m += s_m[w];
+            s += s_s[w];
+        }
+        all_m += s_m[w];
+        all_s += s_s[w];
+    }
+    BigEntry *e = entries + tile * kProbeTile;
+#pragma unroll
+    for (int u = 0; u < kProbeIPT; ++u) {
+        if (!len[u]) continue;
+        e[m++] = BigEntry{(uint32_t)(l0 + (uint64_t)u * kBigBlock + threadIdx.x), at[u], s};
+        s += len[u];
+    }
+    if (threadIdx.x == 0) {
+        tcount[tile] = all_m;
+        ttotal[tile] = all_s;
+    }
+}
+
+__global__ void big_totals(const uint64_t *ltile, int J, const uint64_t *toff, uint64_t *tot) {
+    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < J; j += gridDim.x * blockDim.x)
+        tot[j] = toff[ltile[j + 1]] - toff[ltile[j]];
+}
+
+// one output row per thread: its join, its probe tile (a search of the tiles'
+// offsets), its entry in it, the k-th partner of that entry's row
 __global__ void big_expand(const BigExpand *jobs, int J, const uint64_t *obase, uint64_t ntotal,
-                           const uint64_t *loff, const uint32_t *lslot, const uint32_t *cnt,
-                           const uint64_t *start, const uint32_t *rows) {
+                           const uint64_t *toff, const uint32_t *tcount, const BigEntry *entries) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; g < ntotal; g += stride) {
         const int j = job_of(obase, J, g);
         const BigExpand &b = jobs[j];
         const uint64_t o = g - b.obase;
-        const uint64_t base = loff[b.lbase];
-        uint64_t lo = 0, hi = b.nl;  // last L row i with loff[i] - base <= o
+        const uint64_t x = toff[b.tile0] + o;
+        uint64_t lo = b.tile0, hi = b.tile1;  // last tile with toff <= x
         while (hi - lo > 1) {
             const uint64_t mid = (lo + hi) >> 1;
-            if (loff[b.lbase + mid] - base <= o) lo = mid;
+            if (toff[mid] <= x) lo = mid;
             else hi = mid;
         }
-        const uint64_t i = lo;
-        uint64_t k = o - (loff[b.lbase + i] - base);
-        const uint32_t slot = lslot[b.lbase + i];
-        const uint64_t a = start[slot];
-        uint32_t r;
-        if (b.neq == 0) {
-            r = rows[a + k];
-        } else {  // the k-th partner that also agrees on the other shared variables
-            uint32_t m = 0;
-            for (;; ++m) {
-                r = rows[a + m];
-                if (big_agree(b.eq_l, b.eq_r, b.neq, i, r)) {
+        const uint64_t in = x - toff[lo];
+        const BigEntry *e = entries + lo * kProbeTile;
+        uint32_t p = 0, q = tcount[lo];  // last entry with pre <= in
+        while (q - p > 1) {
+            const uint32_t mid = (p + q) >> 1;
+            if (e[mid].pre <= in) p = mid;
+            else q = mid;
+        }
+        const uint64_t l = e[p].row;
+        const uint32_t a = e[p].at;
+        uint64_t k = in - e[p].pre;
+        const bool paired = a != kNoSlot32;
+        uint32_t r = 0;
+        if (paired && b.neq == 0) {
+            r = b.rows[a + k];
+        } else if (paired) {  // the k-th partner that also agrees on the other shared variables
+            for (uint32_t m = 0;; ++m) {
+                r = b.rows[a + m];
+                if (big_agree(b.eq_l, b.eq_r, b.neq, l, r)) {
                     if (k == 0) break;
                     --k;
                 }
             }
         }
-        // the probe side is L or R; output columns are L's, then R's kept ones
-        const uint64_t li = b.probe_is_left ? i : r, ri = b.probe_is_left ? r : i;
-        for (int c = 0; c < b.nlc; ++c) b.out[c][o] = b.lcol[c][li];
-        for (int c = 0; c < b.nrc; ++c) b.out[b.nlc + c][o] = b.rcol[c][ri];
+        for (int c = 0; c < b.ncols; ++c) {
+            uint32_t v = 0;
+            if (b.side[c] == kFromProbe) v = b.col[c][l];
+            else if (b.side[c] == kFromBuild && paired) v = b.col[c][r];
+            b.out[c][o] = v;
+        }
     }
 }
 
@@ -616,30 +727,69 @@ unsigned grid_cap(uint64_t n, uint64_t cap = 16384) {
 
 }  // namespace
 
+// A large build side is sorted by key instead of hashed: its insertions are two
+// device atomics a row, which this chip does at about 15e9 a second (3M rows:
+// 392 us), against three or four radix passes and an index of plain stores
+// (3M rows: 130 us).  Below kSortBuildRows the passes' launches cost more.
+constexpr uint64_t kSortBuildRows = 1ull << 19;
+
+static void sort_build_side(tid_ctx *ctx, BigCount &b, BigArena &arena) {
+    // direct by key while that takes at most four index entries a row; else
+    // by the key's upper bits, about two entries a row
+    b.shift = 0;
+    if ((uint64_t)b.max_key + 1 > 4 * b.nr)
+        while (((uint64_t)b.max_key >> b.shift) + 1 > 2 * b.nr) ++b.shift;
+    const uint64_t n_index = ((uint64_t)b.max_key >> b.shift) + 1;
+    int bits = 1;
+    while (bits < 32 && b.max_key >> bits) ++bits;
+    DevBuf k0(ctx, b.nr * 4), k1(ctx, b.nr * 4), v0(ctx, b.nr * 4), v1(ctx, b.nr * 4);
+    const bool moved = sort_keys32(ctx, b.rkey, b.nr, bits, k0.get<uint32_t>(), v0.get<uint32_t>(),
+                                   k1.get<uint32_t>(), v1.get<uint32_t>());
+    DevBuf index(ctx, n_index * sizeof(uint2));
+    TID_HIP(hipMemsetAsync(index.get(), 0xFF, n_index * sizeof(uint2), ctx->stream));
+    DevBuf &key = moved ? k1 : k0, &row = moved ? v1 : v0;
+    hipLaunchKernelGGL(index_runs, dim3(grid_cap(b.nr)), dim3(256), 0, ctx->stream,
+                       key.get<const uint32_t>(), (uint32_t)b.nr, b.shift, index.get<uint2>());
+    TID_HIP(hipGetLastError());
+    b.index = index.get<const uint2>();
+    b.skey = key.get<const uint32_t>();
+    b.rows = row.get<const uint32_t>();
+    arena.builds.push_back(std::move(index));
+    arena.builds.push_back(std::move(key));
+    arena.builds.push_back(std::move(row));
+}
+
 void flush_big_count(tid_ctx *ctx, std::vector<BigJoinReq> &reqs,
                      std::shared_ptr<BigArena> *arena_out) {
     if (reqs.empty()) return;
     const int J = (int)reqs.size();
     std::vector<BigCount> jobs(J);
-    std::vector<uint64_t> tbase(J + 1, 0), rbase(J + 1, 0), lbase(J + 1, 0);
+    std::vector<uint64_t> tbase(J + 1, 0), rbase(J + 1, 0), ltile(J + 1, 0);
+    auto arena = std::make_shared<BigArena>();
     uint64_t S = 0;
     for (int j = 0; j < J; ++j) {
         BigCount &b = jobs[j];
         b = reqs[j].c;
+        ltile[j + 1] = ltile[j] + (b.nl + kProbeTile - 1) / kProbeTile;
+        rbase[j + 1] = rbase[j];
+        tbase[j + 1] = tbase[j];
+        if (b.nr >= kSortBuildRows) {
+            sort_build_side(ctx, b, *arena);
+            continue;
+        }
         uint64_t cap = 64;
         while (cap < 2 * b.nr) cap <<= 1;
         b.mask = (uint32_t)(cap - 1);
         b.sbase = S;
         S += cap;
         b.rbase = rbase[j];
-        b.lbase = lbase[j];
-        rbase[j + 1] = rbase[j] + b.nr;
-        lbase[j + 1] = lbase[j] + b.nl;
-        tbase[j + 1] = tbase[j] + (b.nr + kBigTile - 1) / kBigTile;
+        rbase[j + 1] += b.nr;
+        tbase[j + 1] += (b.nr + kBigTile - 1) / kBigTile;
     }
-    const uint64_t NR = rbase[J], NL = lbase[J], T = tbase[J];
+    const uint64_t NR = rbase[J], LT = ltile[J], T = tbase[J];
     TID_REQUIRE(S < (1ull << 32) && NR < (1ull << 32), TID_E_UNSUPPORTED,
                 "batched joins: too many build rows in one round");
+    TID_REQUIRE(LT < (1ull << 31), TID_E_UNSUPPORTED, "batched joins: too many probe rows");
     // one arena: job table and prefixes, then the per-slot and per-row arrays
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -648,63 +798,68 @@ void flush_big_count(tid_ctx *ctx, std::vector<BigJoinReq> &reqs,
         return at;
     };
     const size_t o_jobs = take(J * sizeof(BigCount)), o_tb = take((J + 1) * 8),
-                 o_rb = take((J + 1) * 8), o_lb = take((J + 1) * 8), o_work = take(8),
+                 o_rb = take((J + 1) * 8), o_lt = take((J + 1) * 8), o_work = take(8),
                  o_slots = take(S * 8), o_cnt = take(S * 4), o_start = take((S + 1) * 8),
                  o_slotof = take(NR * 4), o_rank = take(NR * 4), o_rows = take(NR * 4),
-                 o_lslot = take(NL * 4), o_lcnt = take(NL * 4), o_loff = take((NL + 1) * 8),
-                 o_tot = take(J * 8);
-    auto arena = std::make_shared<BigArena>();
+                 o_entries = take(LT * kProbeTile * sizeof(BigEntry)), o_tcount = take(LT * 4),
+                 o_ttotal = take(LT * 8), o_toff = take((LT + 1) * 8), o_tot = take(J * 8);
     arena->buf = DevBuf(ctx, off);
     char *base = arena->buf.get<char>();
-    arena->slots = reinterpret_cast<uint64_t *>(base + o_slots);
-    arena->cnt = reinterpret_cast<uint32_t *>(base + o_cnt);
-    arena->start = reinterpret_cast<uint64_t *>(base + o_start);
-    arena->rows = reinterpret_cast<uint32_t *>(base + o_rows);
-    arena->lslot = reinterpret_cast<uint32_t *>(base + o_lslot);
-    arena->loff = reinterpret_cast<uint64_t *>(base + o_loff);
-    arena->tot = reinterpret_cast<uint64_t *>(base + o_tot);
+    uint64_t *slots = reinterpret_cast<uint64_t *>(base + o_slots);
+    uint32_t *cnt = reinterpret_cast<uint32_t *>(base + o_cnt);
+    uint64_t *start = reinterpret_cast<uint64_t *>(base + o_start);
+    uint32_t *rows = reinterpret_cast<uint32_t *>(base + o_rows);
+    uint64_t *ttotal = reinterpret_cast<uint64_t *>(base + o_ttotal);
+    arena->entries = reinterpret_cast<BigEntry *>(base + o_entries);
+    arena->tcount = reinterpret_cast<uint32_t *>(base + o_tcount);
+    arena->toff = reinterpret_cast<uint64_t *>(base + o_toff);
+    uint64_t *tot = reinterpret_cast<uint64_t *>(base + o_tot);
+    for (BigCount &b : jobs)
+        if (!b.index) b.rows = rows;
     // host tables: one staging copy, then one upload
     std::vector<char> host(o_slots);
     std::memcpy(host.data() + o_jobs, jobs.data(), J * sizeof(BigCount));
     std::memcpy(host.data() + o_tb, tbase.data(), (J + 1) * 8);
     std::memcpy(host.data() + o_rb, rbase.data(), (J + 1) * 8);
-    std::memcpy(host.data() + o_lb, lbase.data(), (J + 1) * 8);
+    std::memcpy(host.data() + o_lt, ltile.data(), (J + 1) * 8);
     std::memset(host.data() + o_work, 0, 8);
     TID_HIP(hipMemcpyAsync(base, host.data(), o_slots, hipMemcpyHostToDevice, ctx->stream));
-    // slot words and counts start at zero (one clear of the contiguous run)
-    TID_HIP(hipMemsetAsync(base + o_slots, 0, o_start - o_slots, ctx->stream));
     const BigCount *dj = reinterpret_cast<const BigCount *>(base + o_jobs);
     const uint64_t *dtb = reinterpret_cast<const uint64_t *>(base + o_tb);
     const uint64_t *drb = reinterpret_cast<const uint64_t *>(base + o_rb);
-    const uint64_t *dlb = reinterpret_cast<const uint64_t *>(base + o_lb);
+    const uint64_t *dlt = reinterpret_cast<const uint64_t *>(base + o_lt);
     uint32_t *slot_of = reinterpret_cast<uint32_t *>(base + o_slotof);
     uint32_t *rank_of = reinterpret_cast<uint32_t *>(base + o_rank);
-    uint32_t *lcount = reinterpret_cast<uint32_t *>(base + o_lcnt);
-    const unsigned workers = (unsigned)std::max<uint64_t>(
-        1, std::min<uint64_t>(T, 4ull * (uint64_t)device_cus(ctx)));
-    if (T)
+    if (S)  // slot words and counts start at zero (one clear of the contiguous run)
+        TID_HIP(hipMemsetAsync(base + o_slots, 0, o_start - o_slots, ctx->stream));
+    if (NR) {
+        const unsigned workers = (unsigned)std::max<uint64_t>(
+            1, std::min<uint64_t>(T, 4ull * (uint64_t)device_cus(ctx)));
         hipLaunchKernelGGL(big_insert, dim3(workers), dim3(kBigBlock), 0, ctx->stream, dj, J,
-                           dtb, T, reinterpret_cast<uint32_t *>(base + o_work), arena->slots,
-                           arena->cnt, slot_of, rank_of);
-    TID_HIP(hipGetLastError());
-    exclusive_scan_async(ctx, arena->cnt, S, arena->start);
-    if (NR)
+                           dtb, T, reinterpret_cast<uint32_t *>(base + o_work), slots, cnt,
+                           slot_of, rank_of);
+        TID_HIP(hipGetLastError());
+        exclusive_scan_async(ctx, cnt, S, start);
         hipLaunchKernelGGL(big_fill, dim3(grid_cap(NR)), dim3(256), 0, ctx->stream, dj, J, drb,
-                           NR, slot_of, rank_of, arena->start, arena->rows);
-    TID_HIP(hipGetLastError());
-    if (NL)
-        hipLaunchKernelGGL(big_probe, dim3(grid_cap(NL)), dim3(256), 0, ctx->stream, dj, J, dlb,
-                           NL, arena->slots, arena->cnt, arena->start, arena->rows, arena->lslot,
-                           lcount);
-    TID_HIP(hipGetLastError());
-    exclusive_scan_async(ctx, lcount, NL, arena->loff);
-    hipLaunchKernelGGL(big_totals, dim3(grid_cap(J)), dim3(256), 0, ctx->stream, dj, J,
-                       arena->loff, arena->tot);
+                           NR, slot_of, rank_of, start, rows);
+        TID_HIP(hipGetLastError());
+    }
+    if (LT) {
+        hipLaunchKernelGGL(big_probe, dim3((unsigned)LT), dim3(kBigBlock), 0, ctx->stream, dj, J,
+                           dlt, slots, cnt, start, arena->entries, arena->tcount, ttotal);
+        TID_HIP(hipGetLastError());
+    }
+    scan_words_async(ctx, ttotal, LT, arena->toff);
+    hipLaunchKernelGGL(big_totals, dim3(grid_cap(J)), dim3(256), 0, ctx->stream, dlt, J,
+                       arena->toff, tot);
     TID_HIP(hipGetLastError());
     for (int j = 0; j < J; ++j) {
-        reqs[j].pj->total_ptr = arena->tot + j;
-        reqs[j].pj->big_lbase = lbase[j];
-        reqs[j].pj->big_arena = arena;
+        PendingJoin *pj = reqs[j].pj;
+        pj->total_ptr = tot + j;
+        pj->big_tile0 = ltile[j];
+        pj->big_tile1 = ltile[j + 1];
+        pj->big_rows = jobs[j].rows;
+        pj->big_arena = arena;
     }
     reqs.clear();
     *arena_out = arena;
@@ -732,8 +887,8 @@ void flush_big_expand(tid_ctx *ctx, const BigArena &arena, std::vector<BigExpand
     if (total)
         hipLaunchKernelGGL(big_expand, dim3(grid_cap(total)), dim3(256), 0, ctx->stream,
                            reinterpret_cast<const BigExpand *>(d), J,
-                           reinterpret_cast<const uint64_t *>(d + bytes_jobs), total, arena.loff,
-                           arena.lslot, arena.cnt, arena.start, arena.rows);
+                           reinterpret_cast<const uint64_t *>(d + bytes_jobs), total, arena.toff,
+                           arena.tcount, arena.entries);
     TID_HIP(hipGetLastError());
     jobs.clear();
     bs.big_out_total = 0;

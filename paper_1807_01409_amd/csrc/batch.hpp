@@ -69,48 +69,65 @@ void flush_sort_jobs(tid_ctx *ctx, BatchState &bs);
 namespace tid {
 
 // Larger hash joins of a batch (sides above kSmallRows rows): every join of
-// a round in the same few launches, each a persistent kernel over the
-// concatenation of all the joins' rows.  Count phase: build (insert with
-// per-workgroup rank reservation in LDS, slot scan, fill), probe, offsets,
-// per-join totals; expansion phase (next round): one output-row-parallel
-// launch for all joins.
+// a round in the same few launches over the concatenation of all the joins'
+// rows.  Count phase: build (insert with per-workgroup rank reservation in LDS,
+// slot scan, fill; large build sides are sorted instead), probe into entries
+// per tile, scan of the tiles' output rows, per-join totals; expansion phase
+// (next round): one output-row-parallel launch for all joins.
 constexpr int kBigCols = TID_MAX_COLS;
 // largest build side of a batched larger join (as the automatic choice of
 // tid_join: 2^23 rows, 2^24 slots)
 constexpr uint64_t kBigBuildMax = 1ull << 23;
 
+constexpr uint64_t kProbeTile = 2048;   // probe rows of a workgroup
+
 // "l" is the probe side and "r" the build side here (the build is the
 // smaller table, which may be the join's L or R); eq_l / eq_r are columns of
 // the probe / build side that must agree (the join's other shared variables).
+// matched, unmatched: whether probe rows with, without a partner put out rows
+// (inner join 1 0, left outer 1 1, the rest of a full outer join 0 1).
 struct BigCount {
     const uint32_t *lkey, *rkey;
     uint64_t nl, nr;
-    uint64_t lbase, rbase;     // offsets in the concatenated probe and build rows
+    uint64_t rbase;            // offset in the concatenated hashed build rows
     uint64_t sbase;            // first slot in the concatenated slot arrays
     uint32_t mask;             // slots - 1 (a power of two minus one)
+    uint32_t max_key;          // bound of the build keys
     int32_t neq;
+    int32_t matched, unmatched;
     const uint32_t *eq_l[kSmallEq], *eq_r[kSmallEq];
+    // a sorted build side: run of each key >> shift (null: hashed), sorted keys
+    const uint2 *index;
+    const uint32_t *skey;
+    int32_t shift;
+    const uint32_t *rows;      // build rows grouped by key
 };
 
+// A probe row with output: its first build row (~0u: none), and the output
+// rows of its tile before it.
+struct BigEntry {
+    uint32_t row, at;
+    uint64_t pre;
+};
+
+constexpr uint8_t kFromProbe = 0, kFromBuild = 1, kFromNone = 2;
 struct BigExpand {
-    uint64_t lbase, nl, obase;   // probe rows (as in BigCount), first output row
-    int32_t neq, nlc, nrc;       // nlc / nrc: output columns from the join's L / R
-    int32_t probe_is_left;
+    uint64_t tile0, tile1, obase;   // probe tiles, first output row
+    const uint32_t *rows;           // build rows grouped by key
+    int32_t neq, ncols;
     const uint32_t *eq_l[kSmallEq], *eq_r[kSmallEq];
-    const uint32_t *lcol[kBigCols], *rcol[kBigCols];
+    const uint32_t *col[kBigCols];  // output column c: this column of the side, or zeros
     uint32_t *out[kBigCols];
+    uint8_t side[kBigCols];
 };
 
 // The device state of one round's larger joins, kept until their expansion.
 struct BigArena {
     DevBuf buf;
-    uint64_t *slots = nullptr;     // key + 1 per slot, 0 = empty
-    uint32_t *cnt = nullptr;       // rows per slot
-    uint64_t *start = nullptr;     // first row of each slot in `rows`
-    uint32_t *rows = nullptr;      // R rows grouped by slot (local row numbers)
-    uint32_t *lslot = nullptr;     // per L row: its key's slot, or ~0u
-    uint64_t *loff = nullptr;      // per L row: exclusive output offset (global)
-    uint64_t *tot = nullptr;       // per join: its output rows
+    BigEntry *entries = nullptr;   // kProbeTile per probe tile
+    uint32_t *tcount = nullptr;    // entries of each tile
+    uint64_t *toff = nullptr;      // per tile: output rows of all tiles before it
+    std::vector<DevBuf> builds;    // sorted build sides
 };
 
 struct BigJoinReq {
@@ -122,8 +139,8 @@ struct BigJoinReq {
 // PendingJoin's total at its word in the new arena.
 void flush_big_count(tid_ctx *ctx, std::vector<BigJoinReq> &reqs,
                      std::shared_ptr<BigArena> *arena_out);
-// Expansion of larger joins whose totals are known (each job's lbase refers
-// to `arena`).
+// Expansion of larger joins whose totals are known (each job's tiles refer to
+// `arena`).
 void flush_big_expand(tid_ctx *ctx, const BigArena &arena, std::vector<BigExpand> &jobs,
                       BatchState &bs);
 

@@ -179,7 +179,7 @@ std::unique_ptr<tid_table> entail(tid_ctx *ctx, const tid_graph *g, int rule,
     set_count(tri.get(), n);
     tri->maxv_known = true;
     tri->maxv[0] = std::max({g->max_id[0], g->max_id[1], g->max_id[2]});
-    tri->maxv[1] = tri->maxv[0];
+    tri->maxv[1] = std::max(tri->maxv[0], r.out_p);  // a vocabulary ID the graph may lack
     tri->maxv[2] = tri->maxv[0];
     return sort_rows(ctx, tri.get(), n, 1);
 }

@@ -365,7 +365,6 @@ struct PendingJoin {
     JoinPlan jp;
     std::vector<int32_t> vars;
     DevBuf start, count, off, keys[4], vals[4];
-    DevBuf slots, slot_of, rank, slot_start, rows;  // slots: slot words, then counts
     const uint32_t *qrow = nullptr, *brow = nullptr;
     int probe_is_left = 1;
     // left outer join (probe side = L): each probe row with no partner still
@@ -388,7 +387,9 @@ struct PendingJoin {
     bool big = false;
     std::shared_ptr<void> big_arena;
     const uint64_t *total_ptr = nullptr;
-    uint64_t big_lbase = 0;
+    uint64_t big_tile0 = 0, big_tile1 = 0;
+    const uint32_t *big_rows = nullptr;
+    bool hashed = false;  // a join of its own, counted as a round of one larger join
     const uint64_t *d_total() const {
         if (total_ptr) return total_ptr;
         return small ? sj_total.get<const uint64_t>() : off.get<const uint64_t>() + nq;

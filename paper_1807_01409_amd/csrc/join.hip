@@ -7,11 +7,11 @@
 // output row finds its (left, right) pair by binary search over the offsets:
 //   sort-merge  radix-sort both sides on the key; each left key finds its
 //               run in the sorted right keys by binary search;
-//   hash        build an open-addressing table of distinct keys on the
-//               smaller side, with each key's rows laid out contiguously
-//               (count, scan, fill), and probe it with the other side.
+//   hash        the larger joins of batch.hip, with one join: a hash table or a
+//               sorted index over the smaller side, probed with the other.
 // Output rows are then put in lexicographic order by the caller.
-#include "compact.hpp"
+#include "batch.hpp"
+#include "device_common.hpp"
 
 #include <algorithm>
 
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(kScanBlock) void range_sums(const uint32_t *__restr
     }
 }
 
-// exclusive scan of P <= 4096 uint64 in one workgroup; base[P] = total
+// exclusive scan of P uint64 in one workgroup; base[P] = total
 __global__ __launch_bounds__(1024) void small_exclusive_scan(const uint64_t *in, uint64_t *base,
                                                               uint32_t P) {
     __shared__ uint64_t s_w[16];
@@ -154,6 +154,13 @@ __global__ __launch_bounds__(kOneBlock) void one_block_scan(const uint32_t *__re
     if (tid == 0) out[n] = carry;
 }
 
+// The same for 64-bit words, in one workgroup (some thousands of tile sums).
+void scan_words_async(tid_ctx *ctx, const uint64_t *in, uint64_t n, uint64_t *out) {
+    hipLaunchKernelGGL(small_exclusive_scan, dim3(1), dim3(1024), 0, ctx->stream, in, out,
+                       (uint32_t)n);
+    TID_HIP(hipGetLastError());
+}
+
 // out[0..n] = exclusive prefix sums of in[0..n); out[n] = total, left on the device.
 void exclusive_scan_async(tid_ctx *ctx, const uint32_t *in, uint64_t n, uint64_t *out) {
     if (n == 0) {
@@ -218,114 +225,8 @@ __global__ void merge_counts(const uint64_t *qk, uint64_t nq, const uint64_t *bk
     }
 }
 
-// ---------------------------------------------------------------------------
-// hash build and probe
-// ---------------------------------------------------------------------------
-
-
-// Build: every build row finds (or claims) its key's slot -- slot words hold
-// key + 1, 0 = empty -- and takes a rank among the rows of that slot.  The
-// ranks are reserved per workgroup round, not per row: the round's rows are
-// grouped by slot in an LDS table, and one global atomic per slot present
-// reserves that group's ranks, so a key held by many rows (a hub) costs one
-// global atomic per round instead of one per row.
-constexpr int kHashBlock = 256;
-constexpr int kHashIPT = 4;
-constexpr int kHashLds = 2048;  // entries; a round holds at most 1024 distinct slots
-constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
-// largest build side the automatic choice sends to the hash join (2^23 rows:
-// 2^24 slots of 12 B = 192 MB)
+// largest build side the automatic choice sends to the hash join
 constexpr uint64_t kHashAutoMaxRows = 1ull << 23;
-
-__global__ __launch_bounds__(kHashBlock) void hash_insert(const uint32_t *keys, uint64_t n,
-                                                          unsigned long long *slots, uint32_t mask,
-                                                          uint32_t *slot_of, uint32_t *rank_of,
-                                                          uint32_t *slot_count) {
-    __shared__ uint32_t s_slot[kHashLds], s_cnt[kHashLds], s_base[kHashLds];
-    for (int x = threadIdx.x; x < kHashLds; x += kHashBlock) {
-        s_slot[x] = kNoSlot;
-        s_cnt[x] = 0;
-    }
-    __syncthreads();
-    const uint64_t per_round = (uint64_t)kHashBlock * kHashIPT;
-    // the trip count is the same for every thread of the workgroup
-    for (uint64_t i0 = (uint64_t)blockIdx.x * per_round; i0 < n;
-         i0 += (uint64_t)gridDim.x * per_round) {
-        uint32_t h[kHashIPT], e[kHashIPT], local[kHashIPT];
-#pragma unroll
-        for (int u = 0; u < kHashIPT; ++u) {
-            const uint64_t i = i0 + (uint64_t)u * kHashBlock + threadIdx.x;
-            if (i >= n) continue;
-            const uint32_t key = keys[i];
-            const unsigned long long want = (unsigned long long)key + 1ull;
-            uint32_t hh = dev::hash32(key) & mask;
-            for (uint32_t probe = 0; probe <= mask; ++probe) {
-                unsigned long long cur = slots[hh];
-                if (cur == 0ull) cur = atomicCAS(&slots[hh], 0ull, want);
-                if (cur == 0ull || cur == want) break;
-                hh = (hh + 1) & mask;
-            }
-            uint32_t ee = hh & (kHashLds - 1);
-            for (;;) {  // ends: fewer distinct slots per round than entries
-                const uint32_t prev = atomicCAS(&s_slot[ee], kNoSlot, hh);
-                if (prev == kNoSlot || prev == hh) break;
-                ee = (ee + 1) & (kHashLds - 1);
-            }
-            h[u] = hh;
-            e[u] = ee;
-            local[u] = atomicAdd(&s_cnt[ee], 1u);
-        }
-        __syncthreads();
-        // reserve each group's ranks and clear the entry for the next round
-        for (int x = threadIdx.x; x < kHashLds; x += kHashBlock) {
-            const uint32_t sl = s_slot[x];
-            if (sl != kNoSlot) {
-                s_base[x] = atomicAdd(&slot_count[sl], s_cnt[x]);
-                s_slot[x] = kNoSlot;
-                s_cnt[x] = 0;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < kHashIPT; ++u) {
-            const uint64_t i = i0 + (uint64_t)u * kHashBlock + threadIdx.x;
-            if (i >= n) continue;
-            slot_of[i] = h[u];
-            rank_of[i] = s_base[e[u]] + local[u];
-        }
-        // s_base is next written after the next round's first barrier
-    }
-}
-
-__global__ void hash_fill(const uint32_t *slot_of, const uint32_t *rank_of, uint64_t n,
-                          const uint64_t *slot_start, uint32_t *rows) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-        rows[slot_start[slot_of[i]] + rank_of[i]] = (uint32_t)i;
-}
-
-__global__ void hash_probe(const uint32_t *keys, uint64_t n, const unsigned long long *slots,
-                           uint32_t mask, const uint32_t *slot_count, const uint64_t *slot_start,
-                           uint32_t *start, uint32_t *count) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const unsigned long long want = (unsigned long long)keys[i] + 1ull;
-        uint32_t h = dev::hash32(keys[i]) & mask;
-        uint32_t c = 0, s = 0;
-        for (uint32_t probe = 0; probe <= mask; ++probe) {
-            const unsigned long long cur = slots[h];
-            if (cur == want) {
-                c = slot_count[h];
-                s = (uint32_t)slot_start[h];
-                break;
-            }
-            if (cur == 0ull) break;
-            h = (h + 1) & mask;
-        }
-        start[i] = s;
-        count[i] = c;
-    }
-}
 
 // ---------------------------------------------------------------------------
 // expansion: output row o -> (probe position a, build position j)
@@ -418,11 +319,9 @@ std::unique_ptr<PendingJoin> join_begin(tid_ctx *ctx, const tid_table *L, uint64
     if (nr == 0) algo = 1;  // left join of L with nothing: every L row, padded
     TID_REQUIRE(nl < (1ull << 32) && nr < (1ull << 32), TID_E_UNSUPPORTED,
                 "join: inputs of 2^32 rows or more");
-    // automatic choice by size: a hash table over the smaller side while its
-    // slot words and counts (12 B per slot, at least two slots per build row)
-    // fit the 256 MB last-level cache, so probes mostly stay on chip;
-    // sort-merge above that, where the sorts stream both sides through HBM
-    // instead of probing it at random
+    // automatic choice by size: probes of an index over the smaller side while
+    // it fits the 256 MB last-level cache; sort-merge above that, where the
+    // sorts stream both sides through HBM instead of probing it at random
     if (algo == 0) algo = std::min(nl, nr) <= kHashAutoMaxRows ? 1 : 2;
     if (algo == 2) {
         // sort both sides on the key, then find each left key's run on the right
@@ -466,43 +365,23 @@ std::unique_ptr<PendingJoin> join_begin(tid_ctx *ctx, const tid_table *L, uint64
         const bool build_right = kind == kJoinLeft || nr <= nl;
         const tid_table *B = build_right ? R : L;
         const tid_table *Q = build_right ? L : R;
-        const uint64_t nb = build_right ? nr : nl;
-        const uint64_t nq = build_right ? nl : nr;
-        const uint32_t *bkey = B->col[build_right ? rc : lc];
-        const uint32_t *qkey = Q->col[build_right ? lc : rc];
-        uint64_t cap = 1024;
-        while (cap < 2 * nb) cap <<= 1;
-        TID_REQUIRE(cap <= (1ull << 31), TID_E_UNSUPPORTED, "join: hash table too large");
-        const uint32_t mask = (uint32_t)(cap - 1);
-        // slot words (cap x 8 B) then slot counts (cap x 4 B): one clear
-        pj->slots = DevBuf(ctx, cap * 12);
-        unsigned long long *slots = pj->slots.get<unsigned long long>();
-        uint32_t *slot_count = reinterpret_cast<uint32_t *>(slots + cap);
-        pj->rank = DevBuf(ctx, nb * 4);
-        pj->slot_of = DevBuf(ctx, nb * 4);
-        pj->slot_start = DevBuf(ctx, (cap + 1) * 8);
-        pj->rows = DevBuf(ctx, nb * 4);
-        TID_HIP(hipMemsetAsync(slots, 0, cap * 12, ctx->stream));
-        hipLaunchKernelGGL(hash_insert, dim3(grid_of(nb, kHashBlock * kHashIPT)),
-                           dim3(kHashBlock), 0, ctx->stream, bkey, nb, slots, mask,
-                           pj->slot_of.get<uint32_t>(), pj->rank.get<uint32_t>(), slot_count);
-        TID_HIP(hipGetLastError());
-        exclusive_scan_async(ctx, slot_count, cap, pj->slot_start.get<uint64_t>());
-        hipLaunchKernelGGL(hash_fill, dim3(grid_of(nb)), dim3(256), 0, ctx->stream,
-                           pj->slot_of.get<const uint32_t>(), pj->rank.get<const uint32_t>(), nb,
-                           pj->slot_start.get<const uint64_t>(), pj->rows.get<uint32_t>());
-        TID_HIP(hipGetLastError());
-        pj->nq = nq;
-        pj->start = DevBuf(ctx, nq * 4);
-        pj->count = DevBuf(ctx, nq * 4);
-        hipLaunchKernelGGL(hash_probe, dim3(grid_of(nq)), dim3(256), 0, ctx->stream, qkey, nq,
-                           pj->slots.get<const unsigned long long>(), mask, slot_count,
-                           pj->slot_start.get<const uint64_t>(), pj->start.get<uint32_t>(),
-                           pj->count.get<uint32_t>());
-        TID_HIP(hipGetLastError());
-        pj->qrow = nullptr;
-        pj->brow = pj->rows.get<uint32_t>();
+        const int bc = build_right ? rc : lc;
+        std::vector<BigJoinReq> reqs(1);
+        BigCount &c = reqs[0].c;
+        c = BigCount{};
+        c.lkey = Q->col[build_right ? lc : rc];
+        c.rkey = B->col[bc];
+        c.nl = build_right ? nl : nr;
+        c.nr = build_right ? nr : nl;
+        c.max_key = B->maxv_known ? B->maxv[bc] : 0xFFFFFFFFu;
+        c.matched = 1;
+        c.unmatched = kind == kJoinLeft;
+        reqs[0].pj = pj.get();
+        std::shared_ptr<BigArena> arena;
+        flush_big_count(ctx, reqs, &arena);
+        pj->hashed = true;
         pj->probe_is_left = build_right ? 1 : 0;
+        return pj;
     }
     if (kind == kJoinLeft) {
         // a probe row with no partner still takes one output row
@@ -518,6 +397,16 @@ std::unique_ptr<PendingJoin> join_begin(tid_ctx *ctx, const tid_table *L, uint64
     return pj;
 }
 
+// the expansion of a join counted as a round of one larger join, its columns
+// still to be filled in
+static BigExpand big_expand_of(const PendingJoin &pj) {
+    BigExpand x{};
+    x.tile0 = pj.big_tile0;
+    x.tile1 = pj.big_tile1;
+    x.rows = pj.big_rows;
+    return x;
+}
+
 // Materialise a counted join once its output size is on the host.
 std::unique_ptr<tid_table> join_finish(tid_ctx *ctx, PendingJoin &pj) {
     TID_REQUIRE(pj.total_known, TID_E_INTERNAL, "join: output size not read yet");
@@ -530,8 +419,22 @@ std::unique_ptr<tid_table> join_finish(tid_ctx *ctx, PendingJoin &pj) {
         copy_bounds(out.get(), R, pj.jp.rkeep.data(), (int)pj.jp.rkeep.size(),
                     (int)pj.jp.lkeep.size());
     }
-    if (total) {
-        TID_REQUIRE(total < (1ull << 40), TID_E_UNSUPPORTED, "join: output too large");
+    if (total) TID_REQUIRE(total < (1ull << 40), TID_E_UNSUPPORTED, "join: output too large");
+    if (total && pj.hashed) {
+        std::vector<BigExpand> jobs(1);
+        BigExpand &x = jobs[0];
+        x = big_expand_of(pj);
+        auto put = [&](const uint32_t *col, bool left) {
+            x.col[x.ncols] = col;
+            x.out[x.ncols] = out->col[x.ncols];
+            x.side[x.ncols++] = left == (pj.probe_is_left != 0) ? kFromProbe : kFromBuild;
+        };
+        for (int c : pj.jp.lkeep) put(L->col[c], true);
+        for (int c : pj.jp.rkeep) put(R->col[c], false);
+        BatchState bs;
+        bs.big_out_total = total;
+        flush_big_expand(ctx, *std::static_pointer_cast<BigArena>(pj.big_arena), jobs, bs);
+    } else if (total) {
         ExpandArgs ea{};
         ea.off = pj.off.get<const uint64_t>();
         ea.start = pj.start.get<const uint32_t>();
@@ -569,48 +472,44 @@ std::unique_ptr<tid_table> join_unsorted(tid_ctx *ctx, const tid_table *L, uint6
 
 // R rows whose key has no partner in L, as rows of the join's schema (L's
 // columns, then R's without rc): L's cells 0 except lc, which takes the R
-// row's key.  `matches` holds, per R row, its partner count.
-struct UnmatchedSrc {
-    const uint32_t *matches;
-    const uint32_t *rkey;
-    const uint32_t *rcol[TID_MAX_COLS];
-    uint64_t n;
-    int nl, lc;
-    using Item = uint32_t;
-    __device__ __forceinline__ Item load(uint64_t i) const { return matches[i]; }
-    __device__ __forceinline__ bool match(int, Item m) const { return m == 0; }
-    __device__ __forceinline__ uint32_t value(int, int c, Item, uint64_t i) const {
-        return c < nl ? (c == lc ? rkey[i] : 0u) : rcol[c - nl][i];
-    }
-};
-
+// row's key.
 static std::unique_ptr<tid_table> unmatched_right(tid_ctx *ctx, const tid_table *l, uint64_t nl,
                                                   int lc, const tid_table *r, uint64_t nr,
                                                   int rc, const std::vector<int32_t> &vars) {
-    // partner counts of R's rows: a left join of R against L probes R in
-    // row order (hash join, built on L)
-    JoinPlan none;
-    auto pj = join_begin(ctx, r, nr, rc, l, nl, lc, 1, none, kJoinLeft);
-    auto out = make_table(ctx, (int)vars.size(), vars.data(), nr);
-    if (nr == 0) {
-        set_count(out.get(), 0);
-        return out;
-    }
-    UnmatchedSrc src{};
-    src.matches = pj->matches.get<const uint32_t>();
-    src.rkey = r->col[rc];
-    int k = 0;
+    TID_REQUIRE(nl < (1ull << 32) && nr < (1ull << 32), TID_E_UNSUPPORTED,
+                "join: inputs of 2^32 rows or more");
+    PendingJoin pj;
+    std::vector<BigJoinReq> reqs(1);
+    BigCount &q = reqs[0].c;
+    q = BigCount{};
+    q.lkey = r->col[rc];
+    q.rkey = l->col[lc];
+    q.nl = nr;
+    q.nr = nl;
+    q.max_key = l->maxv_known ? l->maxv[lc] : 0xFFFFFFFFu;
+    q.unmatched = 1;
+    reqs[0].pj = &pj;
+    std::shared_ptr<BigArena> arena;
+    flush_big_count(ctx, reqs, &arena);
+    uint64_t total = 0;
+    read_words(ctx, {pj.d_total()}, &total);
+    auto out = make_table(ctx, (int)vars.size(), vars.data(), total);
+    set_count(out.get(), total);
+    if (total == 0) return out;
+    std::vector<BigExpand> jobs(1);
+    BigExpand &x = jobs[0];
+    x = big_expand_of(pj);
+    auto put = [&](const uint32_t *col) {
+        x.col[x.ncols] = col;
+        x.out[x.ncols] = out->col[x.ncols];
+        x.side[x.ncols++] = col ? kFromProbe : kFromNone;
+    };
+    for (int c = 0; c < l->ncols; ++c) put(c == lc ? r->col[rc] : nullptr);
     for (int c = 0; c < r->ncols; ++c)
-        if (c != rc) src.rcol[k++] = r->col[c];
-    src.n = nr;
-    src.nl = l->ncols;
-    src.lc = lc;
-    CompactArgs<1, TID_MAX_COLS> a{};
-    for (int c = 0; c < out->ncols; ++c) a.out[0].col[c] = out->col[c];
-    a.out[0].cap = out->cap;
-    a.out[0].count = out->d_count;
-    a.out[0].ncols = out->ncols;
-    launch_compact<UnmatchedSrc, 256, 16, 1, TID_MAX_COLS>(ctx, src, a, 1, 16384u);
+        if (c != rc) put(r->col[c]);
+    BatchState bs;
+    bs.big_out_total = total;
+    flush_big_expand(ctx, *arena, jobs, bs);
     return out;
 }
 
@@ -670,15 +569,15 @@ std::unique_ptr<tid_table> join_tables_kind(tid_ctx *ctx, const tid_table *l, in
                             kind == kJoinInner ? kJoinInner : kJoinLeft);
         if (kind == kJoinFull) {
             auto un = unmatched_right(ctx, l, l->nrows, lcol, r, r->nrows, rcol, vars);
-            if (raw->maxv_known) copy_bounds(un.get(), raw.get(), nullptr, raw->ncols);
-            un->maxv_known = raw->maxv_known;
             // rows of both parts, one schema (which may name a variable twice,
             // so this is a plain concatenation, not a union over variables)
-            tid_table *parts[2] = {raw.get(), un.get()};
-            resolve_counts(ctx, parts, 2);
+            tid_table *part = raw.get();
+            resolve_counts(ctx, &part, 1);
             auto both = make_table(ctx, raw->ncols, raw->vars, raw->nrows + un->nrows);
             both->maxv_known = raw->maxv_known;
             copy_bounds(both.get(), raw.get(), nullptr, raw->ncols);
+            if (both->maxv_known)  // L's key column also holds keys of R
+                both->maxv[lcol] = std::max(both->maxv[lcol], r->maxv[rcol]);
             for (int c = 0; c < raw->ncols; ++c) {
                 if (raw->nrows)
                     TID_HIP(hipMemcpyAsync(both->col[c], raw->col[c], raw->nrows * 4,

@@ -583,27 +583,28 @@ static void advance(tid_ctx *ctx, PlanRun &r, Needs &needs, BatchState *bs) {
                 c.rkey = probe_left ? R->col[rc] : L->col[lc];
                 c.nl = probe_left ? L->nrows : R->nrows;
                 c.nr = probe_left ? R->nrows : L->nrows;
+                c.max_key = probe_left ? (R->maxv_known ? R->maxv[rc] : 0xFFFFFFFFu)
+                                       : (L->maxv_known ? L->maxv[lc] : 0xFFFFFFFFu);
+                c.matched = 1;
                 c.neq = (int)r.pj_eq.size();
                 BigExpand &x = r.bx;
                 x = BigExpand{};
-                x.nl = c.nl;
                 x.neq = c.neq;
-                x.probe_is_left = probe_left ? 1 : 0;
                 for (int e = 0; e < c.neq; ++e) {
                     const uint32_t *lcol_e = L->col[r.pj_eq[e].first];
                     const uint32_t *rcol_e = R->col[jp.rkeep[r.pj_eq[e].second - L->ncols]];
                     c.eq_l[e] = x.eq_l[e] = probe_left ? lcol_e : rcol_e;
                     c.eq_r[e] = x.eq_r[e] = probe_left ? rcol_e : lcol_e;
                 }
-                x.nlc = L->ncols;
                 for (int cc = 0; cc < L->ncols; ++cc) {
-                    x.lcol[cc] = L->col[cc];
+                    x.col[x.ncols] = L->col[cc];
+                    x.side[x.ncols++] = probe_left ? kFromProbe : kFromBuild;
                     pj->vars.push_back(L->vars[cc]);
                 }
-                x.nrc = 0;
                 for (size_t k = L->ncols; k < r.pj_keep.size(); ++k) {
                     const int rcx = jp.rkeep[r.pj_keep[k] - L->ncols];
-                    x.rcol[x.nrc++] = R->col[rcx];
+                    x.col[x.ncols] = R->col[rcx];
+                    x.side[x.ncols++] = probe_left ? kFromBuild : kFromProbe;
                     pj->vars.push_back(R->vars[rcx]);
                 }
                 q.pj = pj.get();
@@ -839,15 +840,17 @@ std::vector<std::unique_ptr<tid_table>> run_plans(
             const tid_table *L = r.pj->own_l.get(), *R = r.pj->own_r.get();
             t->maxv_known = L->maxv_known && R->maxv_known;
             if (t->maxv_known) {
-                for (int c = 0; c < r.bx.nlc; ++c) t->maxv[c] = L->maxv[c];
-                for (int c = 0; c < r.bx.nrc; ++c)
-                    for (int x = 0; x < R->ncols; ++x)
-                        if (R->col[x] == r.bx.rcol[c]) t->maxv[r.bx.nlc + c] = R->maxv[x];
+                for (int c = 0; c < t->ncols; ++c)
+                    for (const tid_table *T : {L, R})
+                        for (int x = 0; x < T->ncols; ++x)
+                            if (T->col[x] == r.bx.col[c]) t->maxv[c] = T->maxv[x];
             }
             if (r.pj->total) {
                 TID_REQUIRE(r.pj->total < (1ull << 40), TID_E_UNSUPPORTED, "join: output too large");
                 BigExpand x = r.bx;
-                x.lbase = r.pj->big_lbase;
+                x.tile0 = r.pj->big_tile0;
+                x.tile1 = r.pj->big_tile1;
+                x.rows = r.pj->big_rows;
                 x.obase = bs.big_out_total;
                 for (int c = 0; c < t->ncols; ++c) x.out[c] = t->col[c];
                 bs.big_out_total += r.pj->total;

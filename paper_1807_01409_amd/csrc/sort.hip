@@ -270,6 +270,28 @@ struct PairOut {
     }
 };
 
+// 32-bit keys (v null: the item's number)
+struct KeyIn {
+    const uint32_t *k, *v;
+    uint32_t first;
+    __device__ __forceinline__ KeyIn from(uint64_t t0) const {
+        return KeyIn{k + t0, v ? v + t0 : nullptr, first + (uint32_t)t0};
+    }
+    __device__ __forceinline__ uint64_t key(uint32_t i) const { return k[i]; }
+    __device__ __forceinline__ void load(uint32_t i, uint64_t &key, uint32_t &val) const {
+        key = k[i];
+        val = v ? v[i] : first + i;
+    }
+};
+
+struct KeyOut {
+    uint32_t *k, *v;
+    __device__ __forceinline__ void put(uint32_t at, uint64_t key, uint32_t val) const {
+        k[at] = (uint32_t)key;
+        v[at] = val;
+    }
+};
+
 // a triple as (its predicate and, below it in `bits` bits, the value at position
 // lo, 0 or 2; the value at the other one)
 struct TripleIn {
@@ -551,6 +573,21 @@ bool radix_sort_pairs(tid_ctx *ctx, uint64_t *k0, uint32_t *v0, uint64_t *k1, ui
                x);
     }
     return ps.count & 1;
+}
+
+// A column's values in ascending order and their rows (stable), on key bits
+// [0, bits): in (k0, v0) if the return value is false, in (k1, v1) if true.
+bool sort_keys32(tid_ctx *ctx, const uint32_t *col, uint64_t n, int bits, uint32_t *k0,
+                 uint32_t *v0, uint32_t *k1, uint32_t *v1) {
+    TID_REQUIRE(n >= 1 && n < (1ull << 32) && bits >= 1, TID_E_UNSUPPORTED,
+                "sort: more than 2^32-1 rows");
+    const Passes ps(ctx, n, 0, bits);
+    for (int x = 0; x < ps.count; ++x) {
+        const KeyOut out{x & 1 ? k1 : k0, x & 1 ? v1 : v0};
+        if (x == 0) ps.run(ctx, KeyIn{col, nullptr, 0}, out, x);
+        else ps.run(ctx, KeyIn{x & 1 ? k0 : k1, x & 1 ? v0 : v1, 0}, out, x);
+    }
+    return (ps.count & 1) == 0;
 }
 
 // The subject and object columns of the n triples in (predicate, value) order,
