@@ -235,11 +235,10 @@ class CircularServer:
         self.ctx.close()
 
     def _submit(self, plan) -> int:
-        from .tid import _plan
-        keep: list = []
-        cp = _plan(plan, keep)
+        from .tid import _Plans
+        block = _Plans([plan])
         t = self._ct.c_uint64()
-        self._check(self.ctx.ptr, self.ctx._lib.tid_serve_submit(self._s, self._ct.byref(cp),
+        self._check(self.ctx.ptr, self.ctx._lib.tid_serve_submit(self._s, block.first(),
                                                                  self._ct.byref(t)))
         return int(t.value)
 
