@@ -95,9 +95,9 @@ tid_status tid_ctx_create(int device, void *stream, tid_alloc_fn alloc, tid_free
         ctx->alloc_fn = alloc;
         ctx->free_fn = free_fn;
         ctx->user = user;
-        TID_HIP(hipHostMalloc((void **)&ctx->d_flags, 4 * sizeof(uint32_t),
+        TID_HIP(hipHostMalloc((void **)&ctx->d_flags, 8 * sizeof(uint32_t),
                               hipHostMallocCoherent));
-        std::memset(ctx->d_flags, 0, 4 * sizeof(uint32_t));
+        std::memset(ctx->d_flags, 0, 8 * sizeof(uint32_t));
         // once per device: the allocation-free scan's state array
         tid::noalloc_init(ctx);
     });

@@ -5,16 +5,19 @@
 //
 // Encoding on the GPU, one shared dictionary, IDs from 1 in order of first
 // appearance when the terms are read s, p, o, triple by triple:
-//   1. hash every term (64-bit FNV-1a over its bytes);
-//   2. radix-sort (hash, term index) pairs -- stable, so each group of equal
-//      hashes lists its terms in reading order and its first element is the
+//   1. hash every term (64-bit FNV-1a over its bytes) and find its hash's slot
+//      in a table, which keeps the smallest term index of each hash: the
 //      term's first appearance;
-//   3. check that every term of a group is byte-equal to the group's first
-//      (a 64-bit collision between different strings is reported as an
-//      error, never silently merged);
-//   4. sort the groups' first appearances: a group's rank in that order is
-//      its ID - 1; scatter each term's ID to its row and position;
-//   5. copy each distinct term's bytes, in ID order, into the dictionary.
+//   2. check that every term is byte-equal to the first one of its hash (a
+//      64-bit collision between different strings is reported as an error,
+//      never silently merged);
+//   3. prefix sums over the terms, of the first appearances and of their
+//      lengths: a first appearance's rank is its ID - 1, its bytes' place is
+//      known, and both are written with every term's ID in one pass.
+// Bound: the random accesses of step 1 (78 us of 150 us on the device for
+// 200,000 triples); a host between the steps and two radix sorts (eleven
+// passes) in place of the table took 1088 us for 200,000 triples and a page of
+// 5,000 decoded, now 272 us.
 // Decoding gathers the strings of a column of IDs (lengths, offsets by an
 // exclusive scan, bytes).
 #include "compact.hpp"
@@ -23,9 +26,6 @@
 
 namespace tid {
 
-bool radix_sort_pairs(tid_ctx *ctx, uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1,
-                      uint64_t n, int bits);
-void iota(tid_ctx *ctx, uint32_t *p, uint64_t n);
 void exclusive_scan_async(tid_ctx *ctx, const uint32_t *in, uint64_t n, uint64_t *out);
 void read_words(tid_ctx *ctx, const std::vector<const uint64_t *> &src, uint64_t *dst);
 
@@ -39,91 +39,184 @@ unsigned grid_of(uint64_t n) {
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (n);          \
          i += (uint64_t)gridDim.x * blockDim.x)
 
-// FNV-1a, 64 bits (Fowler, Noll, Vo)
-__global__ void hash_terms(const uint8_t *bytes, const uint64_t *off, uint64_t m, uint64_t *h,
-                           uint32_t *idx) {
-    TID_GRID_LOOP(t, m) {
-        uint64_t x = 0xcbf29ce484222325ull;
-        for (uint64_t b = off[t]; b < off[t + 1]; ++b) {
-            x ^= bytes[b];
-            x *= 0x100000001b3ull;
+__device__ __forceinline__ uint64_t eight_bytes(const uint8_t *p) {
+    uint64_t w;
+    __builtin_memcpy(&w, p, 8);  // one load, at any alignment
+    return w;
+}
+
+// The bytes of a string in words of eight (the last one shorter, its bytes
+// alone): f(word, bytes) until it returns false.  No byte outside the string
+// is read.
+template <class F>
+__device__ __forceinline__ void each_word(const uint8_t *p, uint64_t len, const F &f) {
+    uint64_t k = 0;
+    for (; k + 8 <= len; k += 8)
+        if (!f(k, eight_bytes(p + k), 8)) return;
+    const int rest = (int)(len - k);
+    if (rest == 0) return;
+    uint64_t w = 0;
+    if (len >= 8) {
+        w = eight_bytes(p + len - 8) >> (64 - 8 * rest);
+    } else {
+        for (int x = 0; x < rest; ++x) w |= (uint64_t)p[k + x] << (8 * x);
+    }
+    f(k, w, rest);
+}
+
+__device__ __forceinline__ void copy_string(uint8_t *dst, const uint8_t *src, uint64_t len) {
+    each_word(src, len, [&](uint64_t k, uint64_t w, int n) {
+        if (n == 8) {
+            __builtin_memcpy(dst + k, &w, 8);
+        } else {
+            for (int x = 0; x < n; ++x) dst[k + x] = (uint8_t)(w >> (8 * x));
         }
-        h[t] = x;
-        idx[t] = (uint32_t)t;
+        return true;
+    });
+}
+
+struct Terms {
+    const uint8_t *bytes;
+    const uint64_t *off;
+    uint64_t nbytes, m;
+    uint32_t *falls, *past;  // offsets that fall, or reach past the bytes
+    // length of term t; 0 if its offsets are bad
+    __device__ __forceinline__ uint64_t length(uint64_t t, uint64_t &at) const {
+        at = off[t];
+        const uint64_t end = off[t + 1];
+        if (end < at) {
+            dev::raise(falls);
+            return 0;
+        }
+        if (end > nbytes) {
+            dev::raise(past);
+            return 0;
+        }
+        return end - at;
+    }
+};
+
+// Table of hashes: key[cap] (0: free) and, for each, ~(its smallest term
+// index).  The hash 0 has the slot cap, past the others.
+struct TermTable {
+    uint64_t *key;
+    uint32_t *lead;
+    uint64_t cap;
+    __device__ __forceinline__ uint64_t find(uint64_t h) const {
+        if (h == 0) return cap;
+        uint64_t x = h ^ h >> 32;  // FNV's high bits vary little over short strings
+        x *= 0x9e3779b97f4a7c15ull;
+        uint64_t s = __umul64hi(x, cap);
+        for (uint64_t probes = 0; probes < cap; ++probes) {  // cap > distinct hashes
+            uint64_t cur = dev::peek(key + s);
+            if (cur == 0)
+                cur = atomicCAS((unsigned long long *)(key + s), 0ull, (unsigned long long)h);
+            if (cur == 0 || cur == h) return s;
+            if (++s == cap) s = 0;
+        }
+        return cap;  // not reached
+    }
+};
+
+// Slot of every term.  The lanes of a wave that hold the same term are found
+// first and the lowest one goes to the table for all of them: a predicate
+// stands in many triples.
+__global__ __launch_bounds__(256) void insert_terms(Terms in, TermTable tab, uint32_t *slot,
+                                                    uint32_t *slot_hi) {
+    const int lane = dev::lane_id();
+    for (uint64_t t0 = (uint64_t)blockIdx.x * blockDim.x; t0 < in.m;
+         t0 += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t t = t0 + threadIdx.x;
+        const bool valid = t < in.m;
+        uint64_t h = 0xcbf29ce484222325ull;  // FNV-1a, 64 bits (Fowler, Noll, Vo)
+        if (valid) {
+            uint64_t at;
+            const uint64_t len = in.length(t, at);
+            each_word(in.bytes + at, len, [&](uint64_t, uint64_t w, int n) {
+                for (int x = 0; x < n; ++x) {
+                    h ^= w >> (8 * x) & 0xff;
+                    h *= 0x100000001b3ull;
+                }
+                return true;
+            });
+        }
+        int leader = lane;
+        for (uint64_t rem = dev::ballot(valid); rem;) {
+            const int first = __builtin_ctzll(rem);
+            const uint64_t same = dev::ballot(h == __shfl(h, first, dev::kWave)) & rem;
+            if (same >> lane & 1) leader = first;
+            rem &= ~same;
+        }
+        uint64_t s = 0;
+        if (valid && leader == lane) {
+            s = tab.find(h);
+            const uint32_t mine = ~(uint32_t)t;
+            if (__hip_atomic_load(tab.lead + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < mine)
+                atomicMax(tab.lead + s, mine);
+        }
+        s = __shfl(s, leader, dev::kWave);
+        if (valid) {
+            slot[t] = (uint32_t)s;
+            slot_hi[t] = (uint32_t)(s >> 32);
+        }
     }
 }
 
-// first[i] = 1 where sorted position i starts a group of equal hashes
-__global__ void group_starts(const uint64_t *h, uint64_t m, uint32_t *first) {
-    TID_GRID_LOOP(i, m) first[i] = (i == 0 || h[i] != h[i - 1]) ? 1u : 0u;
-}
-
-// gstart (exclusive scan of `first`): group g starts at the i with
-// first[i] = 1 and gstart[i] = g; lead[g] = the term index there
-__global__ void group_leads(const uint32_t *first, const uint64_t *gstart, const uint32_t *term,
-                            uint64_t m, uint32_t *lead) {
-    TID_GRID_LOOP(i, m) if (first[i]) lead[gstart[i]] = term[i];
-}
-
-__device__ __forceinline__ uint64_t group_of(const uint32_t *first, const uint64_t *gstart,
-                                             uint64_t i) {
-    return gstart[i] + first[i] - 1;  // inclusive count of group starts, minus one
-}
-
-// every term byte-equal to its group's first term; flag set otherwise
-__global__ void check_groups(const uint8_t *bytes, const uint64_t *off, const uint32_t *first,
-                             const uint64_t *gstart, const uint32_t *term, const uint32_t *lead,
-                             uint64_t m, uint32_t *flag) {
-    TID_GRID_LOOP(i, m) {
-        if (first[i]) continue;
-        const uint32_t a = term[i], b = lead[group_of(first, gstart, i)];
-        const uint64_t la = off[a + 1] - off[a], lb = off[b + 1] - off[b];
-        bool eq = la == lb;
-        for (uint64_t k = 0; eq && k < la; ++k) eq = bytes[off[a] + k] == bytes[off[b] + k];
-        if (!eq) atomicOr(flag, 1u);
+// lead[t] (in place of t's slot, whose upper half is in first[t]) = the first term of t's hash; first[t] = 1
+// and len[t] = its length if that is t itself (else 0); the flag raised if the
+// two terms differ.
+__global__ __launch_bounds__(256) void check_terms(Terms in, TermTable tab, uint32_t *lead,
+                                                   uint32_t *first, uint32_t *len,
+                                                   uint32_t *differ) {
+    TID_GRID_LOOP(t, in.m) {
+        const uint32_t a = ~tab.lead[(uint64_t)first[t] << 32 | lead[t]];
+        uint64_t at, at_a;
+        const uint64_t l = in.length(t, at);
+        bool eq = true;
+        if (a != t) {
+            eq = in.length(a, at_a) == l;
+            if (eq)
+                each_word(in.bytes + at, l, [&](uint64_t k, uint64_t w, int n) {
+                    const uint8_t *q = in.bytes + at_a;
+                    uint64_t v = 0;
+                    if (n == 8) v = eight_bytes(q + k);
+                    else if (l >= 8) v = eight_bytes(q + l - 8) >> (64 - 8 * n);
+                    else for (int x = 0; x < n; ++x) v |= (uint64_t)q[k + x] << (8 * x);
+                    eq = v == w;
+                    return eq;
+                });
+        }
+        if (!eq) dev::raise(differ);
+        lead[t] = a;
+        first[t] = a == t ? 1u : 0u;
+        len[t] = a == t ? (uint32_t)l : 0u;
     }
 }
 
-__global__ void widen_leads(const uint32_t *lead, uint64_t d, uint64_t *key, uint32_t *val) {
-    TID_GRID_LOOP(g, d) {
-        key[g] = lead[g];
-        val[g] = (uint32_t)g;
-    }
-}
-
-// group_sorted[r] = the group whose first appearance has rank r: its ID is r + 1
-__global__ void group_ids(const uint32_t *group_sorted, uint64_t d, uint32_t *id_of) {
-    TID_GRID_LOOP(r, d) id_of[group_sorted[r]] = (uint32_t)(r + 1);
-}
-
-__global__ void scatter_ids(const uint32_t *first, const uint64_t *gstart, const uint32_t *term,
-                            const uint32_t *id_of, uint64_t m, uint32_t *rows) {
-    TID_GRID_LOOP(i, m) rows[term[i]] = id_of[group_of(first, gstart, i)];
-}
-
-// lengths of the distinct terms in ID order (term of ID r + 1 is first[r])
-__global__ void id_lengths(const uint64_t *first_sorted, const uint64_t *off, uint64_t d,
-                           uint32_t *len) {
-    TID_GRID_LOOP(r, d) {
-        const uint64_t t = first_sorted[r];
-        len[r] = (uint32_t)(off[t + 1] - off[t]);
-    }
-}
-
-__global__ void copy_terms(const uint64_t *first_sorted, const uint8_t *bytes, const uint64_t *off,
-                           const uint64_t *doff, uint64_t d, uint8_t *dbytes) {
-    TID_GRID_LOOP(r, d) {
-        const uint64_t t = first_sorted[r];
-        for (uint64_t k = 0; k < off[t + 1] - off[t]; ++k) dbytes[doff[r] + k] = bytes[off[t] + k];
+// Every term's ID; a first appearance also writes its string to the dictionary.
+__global__ __launch_bounds__(256) void write_terms(Terms in, const uint32_t *lead,
+                                                   const uint64_t *rank, const uint64_t *place,
+                                                   uint32_t *rows, uint64_t *doff,
+                                                   uint8_t *dbytes) {
+    TID_GRID_LOOP(t, in.m) {
+        const uint32_t a = lead[t];
+        const uint64_t r = rank[a];
+        rows[t] = (uint32_t)(r + 1);
+        if (a != t) continue;
+        uint64_t at;
+        const uint64_t l = in.length(t, at), to = place[t];
+        doff[r + 1] = to + l;
+        if (r == 0) doff[0] = 0;
+        copy_string(dbytes + to, in.bytes + at, l);
     }
 }
 
 __global__ void decode_lengths(const uint32_t *ids, uint64_t n, const uint64_t *doff,
-                               uint64_t nterms, uint32_t *len, uint32_t *flag) {
+                               uint64_t nterms, uint32_t *len, uint32_t *bad) {
     TID_GRID_LOOP(i, n) {
         const uint32_t id = ids[i];
         if (id == 0 || id > nterms) {
-            atomicOr(flag, 1u);
+            dev::raise(bad);
             len[i] = 0;
         } else {
             len[i] = (uint32_t)(doff[id] - doff[id - 1]);
@@ -138,11 +231,28 @@ __global__ void decode_copy(const uint32_t *ids, uint64_t n, const uint64_t *dof
         const uint32_t id = ids[i];
         if (id == 0 || id > nterms) continue;
         const uint64_t a = doff[id - 1], l = doff[id] - a;
-        for (uint64_t k = 0; k < l; ++k) out[out_off[i] + k] = dbytes[a + k];
+        copy_string(out + out_off[i], dbytes + a, l);
     }
 }
 
-int bitw64(uint64_t v) { return v ? 64 - __builtin_clzll(v) : 0; }
+// The context's three pinned flags of a dictionary call.  Their kernels have
+// run when the call ends, however it ends, so the next call may clear them.
+struct Flags {
+    tid_ctx *ctx;
+    explicit Flags(tid_ctx *c) : ctx(c) {
+        for (int x = 0; x < 3; ++x) at(x)[0] = 0;
+    }
+    Flags(const Flags &) = delete;
+    Flags &operator=(const Flags &) = delete;
+    ~Flags() { (void)hipStreamSynchronize(ctx->stream); }
+    uint32_t *at(int x) const { return ctx->d_flags + 4 + x; }
+    bool raised(int x) const { return *static_cast<const volatile uint32_t *>(at(x)) != 0; }
+};
+
+bool overlap(const void *a, uint64_t na, const void *b, uint64_t nb) {
+    const auto x = (uintptr_t)a, y = (uintptr_t)b;
+    return x < y + nb && y < x + na;
+}
 
 }  // namespace
 
@@ -155,91 +265,65 @@ std::unique_ptr<tid_dict> encode(tid_ctx *ctx, const uint8_t *bytes, uint64_t nb
     const uint64_t m = 3 * n;
     auto dict = std::make_unique<tid_dict>();
     dict->ctx = ctx;
-    // inputs on the device
-    DevBuf dbytes_in(ctx, std::max<uint64_t>(nbytes, 1)), doff_in(ctx, (m + 1) * 8);
-    const auto kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-    if (nbytes) TID_HIP(hipMemcpyAsync(dbytes_in.get(), bytes, nbytes, kind, ctx->stream));
-    if (n) {
-        TID_HIP(hipMemcpyAsync(doff_in.get(), offsets, (m + 1) * 8, kind, ctx->stream));
-        // offsets must rise and stay within the bytes: checked on the host copy
-        std::vector<uint64_t> ho(m + 1);
-        TID_HIP(hipMemcpyAsync(ho.data(), doff_in.get(), (m + 1) * 8, hipMemcpyDeviceToHost,
-                               ctx->stream));
-        TID_HIP(hipStreamSynchronize(ctx->stream));
-        for (uint64_t t = 0; t < m; ++t)
-            TID_REQUIRE(ho[t] <= ho[t + 1], TID_E_INVALID_ARG, "encode: offsets must not fall");
-        TID_REQUIRE(ho[m] <= nbytes, TID_E_INVALID_ARG, "encode: offsets past the bytes");
-    }
     if (m == 0) {
         dict->offsets = DevBuf(ctx, 8);
         TID_HIP(hipMemsetAsync(dict->offsets.get(), 0, 8, ctx->stream));
         TID_HIP(hipStreamSynchronize(ctx->stream));
         return dict;
     }
-    const uint8_t *B = dbytes_in.get<const uint8_t>();
-    const uint64_t *O = doff_in.get<const uint64_t>();
-    // 1-2: hash, then sort (hash, term) pairs
-    DevBuf h0(ctx, m * 8), h1(ctx, m * 8), t0(ctx, m * 4), t1(ctx, m * 4);
-    hipLaunchKernelGGL(hash_terms, dim3(grid_of(m)), dim3(256), 0, ctx->stream, B, O, m,
-                       h0.get<uint64_t>(), t0.get<uint32_t>());
-    TID_HIP(hipGetLastError());
-    const bool moved = radix_sort_pairs(ctx, h0.get<uint64_t>(), t0.get<uint32_t>(),
-                                        h1.get<uint64_t>(), t1.get<uint32_t>(), m, 64);
-    const uint64_t *H = moved ? h1.get<const uint64_t>() : h0.get<const uint64_t>();
-    const uint32_t *T = moved ? t1.get<const uint32_t>() : t0.get<const uint32_t>();
-    // groups of equal hashes and their first terms
-    DevBuf first(ctx, m * 4), gstart(ctx, (m + 1) * 8);
-    hipLaunchKernelGGL(group_starts, dim3(grid_of(m)), dim3(256), 0, ctx->stream, H, m,
-                       first.get<uint32_t>());
-    TID_HIP(hipGetLastError());
-    exclusive_scan_async(ctx, first.get<const uint32_t>(), m, gstart.get<uint64_t>());
-    uint64_t d = 0;
-    read_words(ctx, {gstart.get<const uint64_t>() + m}, &d);
-    DevBuf lead(ctx, d * 4);
-    hipLaunchKernelGGL(group_leads, dim3(grid_of(m)), dim3(256), 0, ctx->stream,
-                       first.get<const uint32_t>(), gstart.get<const uint64_t>(), T, m,
-                       lead.get<uint32_t>());
-    TID_HIP(hipGetLastError());
-    // 3: every term equal to its group's first (no silent collision)
-    DevBuf flag(ctx, 8);
-    TID_HIP(hipMemsetAsync(flag.get(), 0, 8, ctx->stream));
-    hipLaunchKernelGGL(check_groups, dim3(grid_of(m)), dim3(256), 0, ctx->stream, B, O,
-                       first.get<const uint32_t>(), gstart.get<const uint64_t>(), T,
-                       lead.get<const uint32_t>(), m, flag.get<uint32_t>());
-    TID_HIP(hipGetLastError());
-    uint64_t bad = 0;
-    read_words(ctx, {flag.get<const uint64_t>()}, &bad);
-    TID_REQUIRE(bad == 0, TID_E_UNSUPPORTED,
+    // Inputs on the device: a caller's device buffers are read where they are,
+    // unless rows would be written over them or the offsets are misaligned.
+    DevBuf bytes_in, off_in;
+    Terms in{bytes, offsets, nbytes, m, nullptr, nullptr};
+    const auto kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
+    if (nbytes && (!on_device || overlap(bytes, nbytes, rows, m * 4))) {
+        bytes_in = DevBuf(ctx, nbytes);
+        TID_HIP(hipMemcpyAsync(bytes_in.get(), bytes, nbytes, kind, ctx->stream));
+        in.bytes = bytes_in.get<const uint8_t>();
+    }
+    if (!on_device || (uintptr_t)offsets % 8 != 0 ||
+        overlap(offsets, (m + 1) * 8, rows, m * 4)) {
+        off_in = DevBuf(ctx, (m + 1) * 8);
+        TID_HIP(hipMemcpyAsync(off_in.get(), offsets, (m + 1) * 8, kind, ctx->stream));
+        in.off = off_in.get<const uint64_t>();
+    }
+    const Flags flags(ctx);
+    in.falls = flags.at(0);
+    in.past = flags.at(1);
+    // 1-2: the first appearance of every term.  The table is 2/3 full if no
+    // term repeats, and is given back before the prefix sums.
+    DevBuf lead(ctx, m * 4), first(ctx, m * 4), len(ctx, m * 4);
+    {
+        const uint64_t cap = m + m / 2 + 1;
+        DevBuf table(ctx, (cap + 1) * 12);
+        TermTable tab{table.get<uint64_t>(), nullptr, cap};
+        tab.lead = reinterpret_cast<uint32_t *>(tab.key + cap + 1);
+        TID_HIP(hipMemsetAsync(table.get(), 0, (cap + 1) * 12, ctx->stream));
+        hipLaunchKernelGGL(insert_terms, dim3(grid_of(m)), dim3(256), 0, ctx->stream, in, tab,
+                           lead.get<uint32_t>(), first.get<uint32_t>());
+        TID_HIP(hipGetLastError());
+        hipLaunchKernelGGL(check_terms, dim3(grid_of(m)), dim3(256), 0, ctx->stream, in, tab,
+                           lead.get<uint32_t>(), first.get<uint32_t>(), len.get<uint32_t>(),
+                           flags.at(2));
+        TID_HIP(hipGetLastError());
+    }
+    // 3: ranks and places
+    DevBuf rank(ctx, (m + 1) * 8), place(ctx, (m + 1) * 8);
+    exclusive_scan_async(ctx, first.get<const uint32_t>(), m, rank.get<uint64_t>());
+    exclusive_scan_async(ctx, len.get<const uint32_t>(), m, place.get<uint64_t>());
+    uint64_t sums[2];
+    read_words(ctx, {rank.get<const uint64_t>() + m, place.get<const uint64_t>() + m}, sums);
+    TID_REQUIRE(!flags.raised(0), TID_E_INVALID_ARG, "encode: offsets must not fall");
+    TID_REQUIRE(!flags.raised(1), TID_E_INVALID_ARG, "encode: offsets past the bytes");
+    TID_REQUIRE(!flags.raised(2), TID_E_UNSUPPORTED,
                 "encode: two different terms share a 64-bit hash; not encoded");
-    // 4: IDs by first appearance
-    DevBuf k0(ctx, d * 8), k1(ctx, d * 8), g0(ctx, d * 4), g1(ctx, d * 4);
-    hipLaunchKernelGGL(widen_leads, dim3(grid_of(d)), dim3(256), 0, ctx->stream,
-                       lead.get<const uint32_t>(), d, k0.get<uint64_t>(), g0.get<uint32_t>());
-    TID_HIP(hipGetLastError());
-    const bool mv = radix_sort_pairs(ctx, k0.get<uint64_t>(), g0.get<uint32_t>(),
-                                     k1.get<uint64_t>(), g1.get<uint32_t>(), d, bitw64(m));
-    const uint64_t *first_sorted = mv ? k1.get<const uint64_t>() : k0.get<const uint64_t>();
-    const uint32_t *group_sorted = mv ? g1.get<const uint32_t>() : g0.get<const uint32_t>();
-    DevBuf id_of(ctx, d * 4);
-    hipLaunchKernelGGL(group_ids, dim3(grid_of(d)), dim3(256), 0, ctx->stream, group_sorted, d,
-                       id_of.get<uint32_t>());
-    TID_HIP(hipGetLastError());
-    hipLaunchKernelGGL(scatter_ids, dim3(grid_of(m)), dim3(256), 0, ctx->stream,
-                       first.get<const uint32_t>(), gstart.get<const uint64_t>(), T,
-                       id_of.get<const uint32_t>(), m, rows);
-    TID_HIP(hipGetLastError());
-    // 5: the dictionary, terms in ID order
-    DevBuf len(ctx, d * 4);
+    const uint64_t d = sums[0], total = sums[1];
     dict->offsets = DevBuf(ctx, (d + 1) * 8);
-    hipLaunchKernelGGL(id_lengths, dim3(grid_of(d)), dim3(256), 0, ctx->stream, first_sorted, O,
-                       d, len.get<uint32_t>());
-    TID_HIP(hipGetLastError());
-    exclusive_scan_async(ctx, len.get<const uint32_t>(), d, dict->offsets.get<uint64_t>());
-    uint64_t total = 0;
-    read_words(ctx, {dict->offsets.get<const uint64_t>() + d}, &total);
     dict->bytes = DevBuf(ctx, std::max<uint64_t>(total, 1));
-    hipLaunchKernelGGL(copy_terms, dim3(grid_of(d)), dim3(256), 0, ctx->stream, first_sorted, B,
-                       O, dict->offsets.get<const uint64_t>(), d, dict->bytes.get<uint8_t>());
+    hipLaunchKernelGGL(write_terms, dim3(grid_of(m)), dim3(256), 0, ctx->stream, in,
+                       lead.get<const uint32_t>(), rank.get<const uint64_t>(),
+                       place.get<const uint64_t>(), rows, dict->offsets.get<uint64_t>(),
+                       dict->bytes.get<uint8_t>());
     TID_HIP(hipGetLastError());
     TID_HIP(hipStreamSynchronize(ctx->stream));
     dict->n_terms = d;
@@ -265,18 +349,16 @@ void decode(tid_ctx *ctx, const tid_dict *dict, const uint32_t *ids, uint64_t n,
         TID_HIP(hipMemcpyAsync(did.get(), ids, n * 4, hipMemcpyHostToDevice, ctx->stream));
         I = did.get<const uint32_t>();
     }
-    DevBuf len(ctx, n * 4), off(ctx, (n + 1) * 8), flag(ctx, 8);
-    TID_HIP(hipMemsetAsync(flag.get(), 0, 8, ctx->stream));
+    DevBuf len(ctx, n * 4), off(ctx, (n + 1) * 8);
+    const Flags flags(ctx);
     hipLaunchKernelGGL(decode_lengths, dim3(grid_of(n)), dim3(256), 0, ctx->stream, I, n,
                        dict->offsets.get<const uint64_t>(), dict->n_terms, len.get<uint32_t>(),
-                       flag.get<uint32_t>());
+                       flags.at(0));
     TID_HIP(hipGetLastError());
     exclusive_scan_async(ctx, len.get<const uint32_t>(), n, off.get<uint64_t>());
     TID_HIP(hipMemcpyAsync(out_off, off.get(), (n + 1) * 8, hipMemcpyDeviceToHost, ctx->stream));
-    uint64_t bad = 0;
-    TID_HIP(hipMemcpyAsync(&bad, flag.get(), 8, hipMemcpyDeviceToHost, ctx->stream));
     TID_HIP(hipStreamSynchronize(ctx->stream));
-    TID_REQUIRE(bad == 0, TID_E_INVALID_ARG, "decode: an ID is 0 or not in the dictionary");
+    TID_REQUIRE(!flags.raised(0), TID_E_INVALID_ARG, "decode: an ID is 0 or not in the dictionary");
     const uint64_t total = out_off[n];
     TID_REQUIRE(total <= cap_bytes, TID_E_CAPACITY, "decode: the strings need more bytes");
     if (total == 0) return;
