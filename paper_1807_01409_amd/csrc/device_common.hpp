@@ -62,6 +62,21 @@ __device__ __forceinline__ void bloom_add(uint32_t *bits, uint32_t mask, uint32_
 // that the graph's next tiles would use.
 __device__ __forceinline__ void put(uint32_t *p, uint32_t v) { __builtin_nontemporal_store(v, p); }
 
+// lanes (among the valid ones) that hold the same digit, of at most BITS bits,
+// as the calling lane
+template <int BITS>
+__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid, int nbits = BITS) {
+    uint64_t peers = ballot(valid);
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+        if (b >= nbits) break;  // the same for every lane
+        const bool bit = (d >> b) & 1u;
+        const uint64_t m = ballot(bit);
+        peers &= bit ? m : ~m;
+    }
+    return valid ? peers : 0ull;
+}
+
 // inclusive prefix sum across the wave
 template <class T>
 __device__ __forceinline__ T wave_inclusive_sum(T v) {

@@ -1,0 +1,326 @@
+// idcount.hip -- how many triples have each ID at each position, for graphs of
+// some million triples (the load statistics of runtime.hip).
+//
+// Adding every triple to a bin per ID in global memory is bound by the chip's
+// rate of scattered atomics.  Here the IDs are split by their upper bits into
+// buckets of kBucketIds consecutive IDs, and a bucket's bins fit in LDS:
+//   buckets  a workgroup counts, over one contiguous range of the triples, the
+//            IDs of each bucket; a position with few IDs (the predicates) is
+//            counted in LDS bins directly;
+//   (scan)   digit_scan of sort.hip finds where each range's IDs of a bucket go;
+//   split    a workgroup puts the IDs of a tile in bucket order in LDS and
+//            writes their lower bits, 16 a time, to the buckets' runs;
+//   count    a workgroup counts equal shares of the split IDs, bucket by
+//            bucket, in LDS bins, and adds the bins to the global ones.
+// Bound: the split, which reads 12 bytes a triple and writes 2 a position.
+// 50M triples, 5M subject and object IDs: buckets 173 us, split 489, count 231;
+// with global atomics, an LDS table for the hubs before them, 3653 us.
+#include "compact.hpp"
+
+#include <algorithm>
+
+namespace tid {
+
+int device_cus(tid_ctx *ctx);
+int resident_blocks(const void *kernel, int block, size_t lds);
+void scan_digits(tid_ctx *ctx, const uint32_t *counts, uint32_t *scan, uint32_t *totals,
+                 uint32_t ranges, uint32_t digits);
+
+namespace {
+
+constexpr int kLowBits = 15;
+constexpr uint32_t kBucketIds = 1u << kLowBits;  // 128 KB of bins
+constexpr int kBucketBits = 9;
+constexpr uint32_t kMaxBuckets = 1u << kBucketBits;
+constexpr uint32_t kDirectIds = 8192;            // counted without a split
+constexpr int kBlock = 512;
+constexpr int kIPT = 8;
+constexpr uint32_t kTile = (uint32_t)kBlock * kIPT;
+constexpr int kNW = kBlock / dev::kWave;
+constexpr uint32_t kCopies = 4;                  // bucket counters of the waves
+constexpr int kCountBlock = 1024;
+constexpr uint32_t kShares = 256;
+
+enum Mode : int32_t { kNone = 0, kDirect, kSplit };
+
+struct IdArgs {
+    const uint32_t *g;
+    uint64_t n, range;
+    Mode mode[3];
+    uint32_t ids[3];       // IDs are below this
+    uint32_t buckets[3];
+    uint32_t lds[3];       // first word of the position's counters in LDS
+    uint32_t lds_words;
+    uint32_t *hist[3];
+    uint32_t *counts[3], *scan[3], *totals[3];
+    uint16_t *low[3];      // the split IDs' lower bits
+};
+
+__global__ __launch_bounds__(kBlock) void count_buckets(IdArgs a) {
+    extern __shared__ uint32_t s_cnt[];
+    const uint32_t tid = threadIdx.x, copy = tid / dev::kWave % kCopies;
+    for (uint32_t i = tid; i < a.lds_words; i += kBlock) s_cnt[i] = 0;
+    __syncthreads();
+    const uint64_t r0 = (uint64_t)blockIdx.x * a.range, r1 = min(a.n, r0 + a.range);
+    auto add = [&](const uint32_t (&v)[3]) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            if (a.mode[x] == kDirect) atomicAdd(&s_cnt[a.lds[x] + v[x]], 1u);
+            else if (a.mode[x] == kSplit)
+                atomicAdd(&s_cnt[a.lds[x] + copy * a.buckets[x] + (v[x] >> kLowBits)], 1u);
+        }
+    };
+    for (uint64_t t0 = r0; t0 < r1; t0 += kTile) {
+        if (r1 - t0 >= kTile) {
+            uint32_t v[kIPT][3];
+#pragma unroll
+            for (int u = 0; u < kIPT; ++u)
+#pragma unroll
+                for (int x = 0; x < 3; ++x) v[u][x] = a.g[3 * (t0 + u * kBlock + tid) + x];
+#pragma unroll
+            for (int u = 0; u < kIPT; ++u) add(v[u]);
+        } else {
+            for (uint64_t i = t0 + tid; i < r1; i += kBlock) {
+                const uint32_t v[3] = {a.g[3 * i], a.g[3 * i + 1], a.g[3 * i + 2]};
+                add(v);
+            }
+        }
+    }
+    __syncthreads();
+    for (int x = 0; x < 3; ++x) {
+        const uint32_t *s = s_cnt + a.lds[x];
+        if (a.mode[x] == kDirect) {
+            for (uint32_t i = tid; i < a.ids[x]; i += kBlock)
+                if (s[i]) atomicAdd(&a.hist[x][i], s[i]);
+        } else if (a.mode[x] == kSplit) {
+            const uint32_t B = a.buckets[x];
+            for (uint32_t b = tid; b < B; b += kBlock) {
+                uint32_t sum = 0;
+#pragma unroll
+                for (uint32_t c = 0; c < kCopies; ++c) sum += s[c * B + b];
+                a.counts[x][(size_t)blockIdx.x * B + b] = sum;
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void split_ids(IdArgs a) {
+    __shared__ uint32_t s_id[kTile];
+    __shared__ uint16_t s_wh[kNW][kMaxBuckets];  // a wave's IDs of a bucket, then those before
+    __shared__ uint32_t s_run[3][kMaxBuckets];   // where the range's next ID of a bucket goes
+    __shared__ uint32_t s_loc[kMaxBuckets];      // a bucket's first ID in the ordered tile
+    __shared__ uint32_t s_off[kMaxBuckets];      // place of ordered ID i: s_off[bucket] + i
+    __shared__ uint32_t s_w[kNW];
+    const uint32_t tid = threadIdx.x, w = blockIdx.x;
+    const int wave = tid / dev::kWave, lane = tid % dev::kWave;
+    static_assert(kMaxBuckets <= kBlock, "a thread per bucket");
+    auto prefix = [&](uint32_t v) {  // exclusive sum over the threads
+        const uint32_t incl = dev::wave_inclusive_sum(v);
+        __syncthreads();
+        if (lane == dev::kWave - 1) s_w[wave] = incl;
+        __syncthreads();
+        uint32_t before = 0;
+#pragma unroll
+        for (int y = 0; y < kNW; ++y) before += y < wave ? s_w[y] : 0u;
+        return before + incl - v;
+    };
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+        if (a.mode[x] != kSplit) continue;
+        const bool in = tid < a.buckets[x];
+        const uint32_t base = prefix(in ? a.totals[x][tid] : 0u);
+        if (in) s_run[x][tid] = base + a.scan[x][(size_t)w * a.buckets[x] + tid];
+    }
+    const uint64_t r0 = (uint64_t)w * a.range, r1 = min(a.n, r0 + a.range);
+    const uint64_t lt = (1ull << lane) - 1ull;
+    for (uint64_t t0 = r0; t0 < r1; t0 += kTile) {
+        const uint32_t cnt = (uint32_t)min((uint64_t)kTile, r1 - t0);
+        uint32_t v[kIPT][3];
+#pragma unroll
+        for (int u = 0; u < kIPT; ++u) {
+            const uint32_t i = u * kBlock + tid;
+#pragma unroll
+            for (int x = 0; x < 3; ++x) v[u][x] = i < cnt ? a.g[3 * (t0 + i) + x] : 0u;
+        }
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            if (a.mode[x] != kSplit) continue;
+            const uint32_t B = a.buckets[x];
+            const int nbits = B > 1 ? 32 - __builtin_clz(B - 1) : 0;
+            for (uint32_t b = lane; b < B; b += dev::kWave) s_wh[wave][b] = 0;
+            uint32_t rank[kIPT];
+#pragma unroll
+            for (int u = 0; u < kIPT; ++u) {
+                const bool valid = u * kBlock + tid < cnt;
+                const uint32_t b = v[u][x] >> kLowBits;
+                const uint64_t peers = dev::match_digit<kBucketBits>(b, valid, nbits);
+                const uint32_t before = valid ? s_wh[wave][b] : 0u;
+                rank[u] = before + (uint32_t)__popcll(peers & lt);
+                if (valid && lane == __builtin_ctzll(peers))
+                    s_wh[wave][b] = (uint16_t)(before + (uint32_t)__popcll(peers));
+            }
+            __syncthreads();
+            uint32_t tot = 0;
+            if (tid < B)
+                for (int y = 0; y < kNW; ++y) {
+                    const uint32_t c = s_wh[y][tid];
+                    s_wh[y][tid] = (uint16_t)tot;
+                    tot += c;
+                }
+            const uint32_t loc = prefix(tot);
+            if (tid < B) {
+                const uint32_t run = s_run[x][tid];
+                s_loc[tid] = loc;
+                s_off[tid] = run - loc;
+                s_run[x][tid] = run + tot;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kIPT; ++u) {
+                const uint32_t b = v[u][x] >> kLowBits;
+                if (u * kBlock + tid < cnt) s_id[s_loc[b] + s_wh[wave][b] + rank[u]] = v[u][x];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kIPT; ++u) {
+                const uint32_t i = u * kBlock + tid;
+                if (i >= cnt) continue;
+                const uint32_t id = s_id[i];
+                a.low[x][s_off[id >> kLowBits] + i] = (uint16_t)(id & (kBucketIds - 1));
+            }
+            __syncthreads();
+        }
+    }
+}
+
+__global__ __launch_bounds__(kCountBlock) void count_split(IdArgs a) {
+    extern __shared__ uint32_t s_cnt[];           // kBucketIds bins
+    __shared__ uint32_t s_first[kMaxBuckets + 1];  // a bucket's first place
+    const int x = blockIdx.y;
+    if (a.mode[x] != kSplit) return;
+    const uint32_t tid = threadIdx.x, B = a.buckets[x];
+    if (tid < dev::kWave) {  // one wave: bucket totals to first places
+        uint32_t run = 0;
+        for (uint32_t b0 = 0; b0 < B; b0 += dev::kWave) {
+            const uint32_t b = b0 + tid, c = b < B ? a.totals[x][b] : 0u;
+            const uint32_t incl = dev::wave_inclusive_sum(c);
+            if (b < B) s_first[b] = run + incl - c;
+            run += __shfl(incl, dev::kWave - 1, dev::kWave);
+        }
+        if (tid == 0) s_first[B] = run;
+    }
+    __syncthreads();
+    const uint64_t share = (a.n + kShares - 1) / kShares;
+    uint64_t at = blockIdx.x * share;
+    const uint64_t end = min(a.n, at + share);
+    uint32_t b = 0;  // the bucket that holds place `at`
+    for (uint32_t hi = B; b + 1 < hi;) {
+        const uint32_t mid = (b + hi) / 2;
+        if (s_first[mid] <= at) b = mid;
+        else hi = mid;
+    }
+    const uint4 *low = reinterpret_cast<const uint4 *>(a.low[x]);  // eight IDs
+    for (; at < end && b < B; ++b) {
+        const uint64_t stop = min(end, (uint64_t)s_first[b + 1]);
+        if (stop <= at) continue;
+        const uint32_t id0 = b << kLowBits, ids = min(kBucketIds, a.ids[x] - id0);
+        for (uint32_t i = tid; i < ids; i += kCountBlock) s_cnt[i] = 0;
+        __syncthreads();
+        for (uint64_t c = at / 8 + tid; 8 * c < stop; c += kCountBlock) {
+            const uint4 q = low[c];
+            const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint64_t i = 8 * c + u;
+                if (i >= at && i < stop) atomicAdd(&s_cnt[w[u / 2] >> (16 * (u & 1)) & 0xffff], 1u);
+            }
+        }
+        __syncthreads();
+        for (uint32_t i = tid; i < ids; i += kCountBlock)
+            if (s_cnt[i]) atomicAdd(&a.hist[x][id0 + i], s_cnt[i]);
+        __syncthreads();
+        at = stop;
+    }
+}
+
+}  // namespace
+
+// Counts into hist[x][0 .. nbins[x]) (zeroed; null: not counted); false, and
+// nothing done, where the atomics of runtime.hip are the better way (a whole
+// load with them / with the split: 100,000 triples 171 / 198 us, 200,000 226 /
+// 228, 300,000 275 / 250, 4M 591 / 394; IDs up to 16M at 1M triples 2621 /
+// 2578), a position has more buckets than a tile can keep apart, or there is no
+// memory for the split.
+constexpr uint64_t kSplitRows = 1ull << 18;
+bool count_ids(tid_ctx *ctx, const uint32_t *g, uint64_t n, uint32_t *const *hist,
+               const uint32_t *nbins) {
+    if (n < kSplitRows || n >= (1ull << 32)) return false;
+    IdArgs a{};
+    a.g = g;
+    a.n = n;
+    int splits = 0;
+    for (int x = 0; x < 3; ++x) {
+        a.hist[x] = hist[x];
+        a.ids[x] = nbins[x];
+        if (!hist[x]) continue;
+        a.lds[x] = a.lds_words;
+        if (nbins[x] <= kDirectIds) {
+            a.mode[x] = kDirect;
+            a.lds_words += nbins[x];
+            continue;
+        }
+        a.mode[x] = kSplit;
+        a.buckets[x] = (nbins[x] + kBucketIds - 1) >> kLowBits;
+        if (a.buckets[x] > kMaxBuckets) return false;
+        a.lds_words += kCopies * a.buckets[x];
+        ++splits;
+    }
+    const uint64_t tiles = (n + kTile - 1) / kTile;
+    uint64_t P = std::max<uint64_t>(1, std::min<uint64_t>(tiles, 3ull * device_cus(ctx)));
+    a.range = (tiles + P - 1) / P * kTile;
+    P = (n + a.range - 1) / a.range;
+    DevBuf mem;
+    if (splits) {
+        size_t bytes = 0;
+        for (int pass = 0; pass < 2; ++pass) {
+            char *at = mem.get<char>();
+            bytes = 0;
+            auto take = [&](size_t len) {
+                char *p = at + bytes;
+                bytes += align_up(len);
+                return p;
+            };
+            for (int x = 0; x < 3; ++x) {
+                if (a.mode[x] != kSplit) continue;
+                const size_t cells = (size_t)P * a.buckets[x] * 4;
+                a.counts[x] = reinterpret_cast<uint32_t *>(take(cells));
+                a.scan[x] = reinterpret_cast<uint32_t *>(take(cells));
+                a.totals[x] = reinterpret_cast<uint32_t *>(take((size_t)a.buckets[x] * 4));
+                a.low[x] = reinterpret_cast<uint16_t *>(take((n + 8) * 2));
+            }
+            if (pass) break;
+            try {
+                mem = DevBuf(ctx, bytes);
+            } catch (const Error &) {
+                return false;
+            }
+        }
+    }
+    const size_t lds = (size_t)a.lds_words * 4, bins = (size_t)kBucketIds * 4;
+    // above 64 KB a kernel must be allowed its dynamic LDS first
+    if (lds > (64u << 10)) (void)resident_blocks((const void *)count_buckets, kBlock, lds);
+    hipLaunchKernelGGL(count_buckets, dim3((uint32_t)P), dim3(kBlock), lds, ctx->stream, a);
+    TID_HIP(hipGetLastError());
+    if (!splits) return true;
+    for (int x = 0; x < 3; ++x)
+        if (a.mode[x] == kSplit)
+            scan_digits(ctx, a.counts[x], a.scan[x], a.totals[x], (uint32_t)P, a.buckets[x]);
+    hipLaunchKernelGGL(split_ids, dim3((uint32_t)P), dim3(kBlock), 0, ctx->stream, a);
+    TID_HIP(hipGetLastError());
+    (void)resident_blocks((const void *)count_split, kCountBlock, bins);
+    hipLaunchKernelGGL(count_split, dim3(kShares, 3), dim3(kCountBlock), bins, ctx->stream, a);
+    TID_HIP(hipGetLastError());
+    return true;
+}
+
+}  // namespace tid

@@ -228,7 +228,8 @@ __global__ void init_minmax(uint32_t *mm) {
     else if (threadIdx.x < 6) mm[threadIdx.x] = 0u;
 }
 
-// Per-position ID histograms in one pass over the graph.  Each workgroup
+// Per-position ID histograms in one pass over the graph, where count_ids does
+// not take them (small graphs, IDs of 2^24 and more).  Each workgroup
 // counts in LDS first and adds its counts to the global bins at the end:
 //  - a position whose IDs fit kDirectBins bins (the predicates) is counted
 //    in LDS bins directly;
@@ -239,6 +240,8 @@ __global__ void init_minmax(uint32_t *mm) {
 //    kHashProbes steps is added to its global bin directly.
 // IDs are >= 1 here (checked before), so key 0 marks an empty entry.
 int device_cus(tid_ctx *ctx);
+bool count_ids(tid_ctx *ctx, const uint32_t *g, uint64_t n, uint32_t *const *hist,
+               const uint32_t *nbins);
 
 constexpr uint32_t kDirectBins = 8192;
 constexpr uint32_t kHashEntries = 2048;
@@ -407,11 +410,13 @@ void build_stats(tid_ctx *ctx, tid_graph *g) {
     TID_HIP(hipMemsetAsync(hist.get(), 0, total, ctx->stream));
     for (int x = 0; x < 3; ++x)
         if (a.nbins[x]) a.hist[x] = reinterpret_cast<uint32_t *>(hist.get<char>() + off[x]);
-    const int hb = (int)std::min<uint64_t>((g->n + kHistBlock - 1) / kHistBlock,
-                                           2ull * (uint64_t)device_cus(ctx));
-    hipLaunchKernelGGL(hist3_kernel, dim3(hb), dim3(kHistBlock), 0, ctx->stream,
-                       g->data.get<const uint32_t>(), g->n, a);
-    TID_HIP(hipGetLastError());
+    if (!count_ids(ctx, g->data.get<const uint32_t>(), g->n, a.hist, a.nbins)) {
+        const int hb = (int)std::min<uint64_t>((g->n + kHistBlock - 1) / kHistBlock,
+                                               2ull * (uint64_t)device_cus(ctx));
+        hipLaunchKernelGGL(hist3_kernel, dim3(hb), dim3(kHistBlock), 0, ctx->stream,
+                           g->data.get<const uint32_t>(), g->n, a);
+        TID_HIP(hipGetLastError());
+    }
     // every position starts on a whole block (align_up: 64 bins)
     static_assert(kAlign == IdCounts::kBlock * sizeof(uint32_t), "positions start on blocks");
     const auto mem = counts_to_host(ctx, hist.get<const uint32_t>(),

@@ -47,21 +47,6 @@ constexpr int kSortIPT = 8;
 constexpr int kSortNW = kSortBlock / dev::kWave;
 constexpr uint32_t kSortTile = (uint32_t)kSortBlock * kSortIPT;
 
-// lanes (among the valid ones) that hold the same digit, of at most BITS bits,
-// as the calling lane
-template <int BITS>
-__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid, int nbits = BITS) {
-    uint64_t peers = dev::ballot(valid);
-#pragma unroll
-    for (int b = 0; b < BITS; ++b) {
-        if (b >= nbits) break;  // the same for every lane
-        const bool bit = (d >> b) & 1u;
-        const uint64_t m = dev::ballot(bit);
-        peers &= bit ? m : ~m;
-    }
-    return valid ? peers : 0ull;
-}
-
 // item `it` of lane `lane` in wave `wave` of a tile: each wave owns 64*IPT
 // consecutive items, so every load instruction reads 64 consecutive items
 __device__ __forceinline__ uint32_t sort_item(int wave, int it, int lane) {
@@ -198,7 +183,7 @@ __global__ __launch_bounds__(kSortBlock) void radix_scatter(In in, Out out, uint
         for (int it = 0; it < kSortIPT; ++it) {
             const bool valid = sort_item(wave, it, lane) < cnt;
             const uint32_t d = (uint32_t)(key[it] >> shift) & (R - 1);
-            const uint64_t peers = match_digit<kMaxDigitBits>(d, valid, nbits);
+            const uint64_t peers = dev::match_digit<kMaxDigitBits>(d, valid, nbits);
             const uint32_t before = valid ? s_wh[wave][d] : 0u;
             rank[it] = before + (uint32_t)__popcll(peers & lt);
             if (valid && lane == __builtin_ctzll(peers))
@@ -365,7 +350,7 @@ __global__ __launch_bounds__(kSmallBlock) void small_sort(uint64_t *keys, uint32
         for (int it = 0; it < kSmallIPT; ++it) {
             const bool valid = small_item(wave, it, lane) < n;
             const uint32_t d = (uint32_t)(key[it] >> shift) & (kRadix - 1);
-            const uint64_t peers = match_digit<kRadixBits>(d, valid);
+            const uint64_t peers = dev::match_digit<kRadixBits>(d, valid);
             const uint32_t before = valid ? s_wh[wave][d] : 0u;
             rank[it] = before + (uint32_t)__popcll(peers & lt);
             if (valid && lane == __builtin_ctzll(peers)) s_wh[wave][d] = before + (uint32_t)__popcll(peers);
@@ -513,6 +498,14 @@ void iota(tid_ctx *ctx, uint32_t *p, uint64_t n) {
     TID_HIP(hipGetLastError());
 }
 
+// digit_scan of a matrix of `ranges` rows of `digits` counts
+void scan_digits(tid_ctx *ctx, const uint32_t *counts, uint32_t *scan, uint32_t *totals,
+                 uint32_t ranges, uint32_t digits) {
+    hipLaunchKernelGGL(digit_scan, dim3(digits), dim3(kColThreads), 0, ctx->stream, counts, scan,
+                       totals, ranges);
+    TID_HIP(hipGetLastError());
+}
+
 // The passes of a stable sort of n pairs on key bits [first, last): digits of
 // nearly equal widths, at most kMaxDigitBits, over ranges of whole tiles.
 struct Passes {
@@ -536,10 +529,8 @@ struct Passes {
         hipLaunchKernelGGL(radix_hist<In>, dim3((uint32_t)P), dim3(kSortBlock), 0, ctx->stream, in,
                            n, range, shift, nbits, counts.get<uint32_t>());
         TID_HIP(hipGetLastError());
-        hipLaunchKernelGGL(digit_scan, dim3(1u << nbits), dim3(kColThreads), 0, ctx->stream,
-                           counts.get<const uint32_t>(), scan.get<uint32_t>(), totals,
-                           (uint32_t)P);
-        TID_HIP(hipGetLastError());
+        scan_digits(ctx, counts.get<const uint32_t>(), scan.get<uint32_t>(), totals, (uint32_t)P,
+                    1u << nbits);
         hipLaunchKernelGGL((radix_scatter<In, Out>), dim3((uint32_t)P), dim3(kSortBlock), 0,
                            ctx->stream, in, out, n, range, shift, nbits,
                            scan.get<const uint32_t>(), totals);

@@ -32,3 +32,38 @@ def test_counts(ctx, ids, hubs):
             want = cum[min(hi, ids + 1)] - cum[min(lo, ids + 1)] if hi > lo else 0
             assert G.count(pos, lo, hi) == want, (pos, lo, hi)
         G.free()
+
+
+@pytest.mark.parametrize("n,ids", [
+    ((1 << 18) - 1, (40, 8192, 8191)),                 # the last size counted with atomics
+    (1 << 18, (8190, 8191, 8192)),                     # IDs counted in LDS at every position
+    (1 << 18, (8192, 100, 32766)),                     # one bucket, nearly full
+    (1 << 18, (32767, 32768, 65535)),                  # one bucket full, two buckets
+    (300_001, (1_000_003, 90_000, 5)),                 # three kinds at once
+    (4096 * 77 + 1, (70_000, 12, (1 << 24) - 1)),      # as many buckets as there may be
+    (270_000, (1 << 24, 3, 50)),                       # one more
+    (3_000_000, (200_000, 50, 600_000)),
+])
+@pytest.mark.parametrize("hub", [0.0, 0.7])
+def test_counts_split(ctx, n, ids, hub):
+    import torch
+    rng = np.random.default_rng(n)
+    g = np.empty((n, 3), dtype=np.uint32)
+    for x in range(3):
+        g[:, x] = rng.integers(1, ids[x] + 1, n)
+        if hub:     # most triples have one ID, the last of a bucket if there is one
+            g[rng.random(n) < hub, x] = min(ids[x], 32767)
+        g[0, x], g[-1, x] = ids[x], 1
+    t = torch.from_numpy(g.view(np.int32)).cuda()
+    torch.cuda.synchronize()
+    G = ctx.load(t)
+    for x in range(3):
+        cum = np.concatenate([[0], np.cumsum(np.bincount(g[:, x], minlength=ids[x] + 1))])
+        near = [v for b in range(0, ids[x] + 1, 32768) for v in (b - 1, b, b + 1)]
+        pick = np.concatenate([[1, ids[x]], near, rng.integers(1, ids[x] + 1, 300)])
+        for v in pick[(pick >= 1) & (pick <= ids[x])]:
+            assert G.count(x, int(v), int(v) + 1) == cum[v + 1] - cum[v], (x, v)
+        for lo, hi in rng.integers(1, ids[x] + 2, (100, 2)):
+            want = cum[hi] - cum[lo] if hi > lo else 0
+            assert G.count(x, int(lo), int(hi)) == want, (x, lo, hi)
+    G.free()
