@@ -11,7 +11,9 @@
 //              thread finding the kVT keys it produces by a binary search
 //              along its diagonal (the merge path of Green, McColl and Bader,
 //              "GPU merge path").  A table of one tile is written out here;
-//   merge      one launch per doubling of the run length: a workgroup
+//   rank merge tables of up to 114,688 rows: a launch puts eight runs together
+//              (row_rank_merge);
+//   merge      larger ones: one launch per doubling of the run length: a workgroup
 //              produces kMergeTile rows, finds its two diagonals with a
 //              64-way search by a wave each, and merges out of LDS.  The last
 //              level writes the table's columns.
@@ -39,6 +41,12 @@ constexpr int kMaxWords = 4;
 // threads of a tile sort: the tile's keys, 8 W bytes each, stay in LDS
 constexpr int tile_block(int words) { return words <= 2 ? 1024 : 512; }
 constexpr uint32_t tile_rows(int words) { return (uint32_t)tile_block(words) * kVT; }
+
+constexpr int kRankBlock = 256;
+constexpr uint32_t kWays = 8;                // runs that row_rank_merge puts together
+constexpr uint32_t kRankPart = 2560;         // rows of other runs in LDS (about 7 * kRankBlock)
+constexpr int kSmallTile = 256;              // threads of a tile sort before it
+static_assert(kSmallTile * kVT % kRankBlock == 0 && kRankBlock == 2 * kWays * 16, "");
 
 struct RowJob {
     const uint32_t *in[TID_MAX_COLS];
@@ -199,10 +207,9 @@ __device__ __forceinline__ int row_job_of(const RowJob *jobs, int J, uint32_t ti
     return lo;
 }
 
-template <int W>
+template <int W, int BLOCK>
 __device__ __forceinline__ void tile_sort_body(const RowJob &p, uint32_t tile) {
-    constexpr int BLOCK = tile_block(W);
-    constexpr uint32_t TILE = tile_rows(W);
+    constexpr uint32_t TILE = (uint32_t)BLOCK * kVT;
     constexpr int NW = BLOCK / dev::kWave;
     extern __shared__ __attribute__((aligned(16))) uint64_t s_tile[];
     __shared__ uint32_t s_w[NW];
@@ -291,9 +298,9 @@ __device__ __forceinline__ void tile_sort_body(const RowJob &p, uint32_t tile) {
     if (tid == 0) *p.count = all;
 }
 
-template <int W>
-__global__ __launch_bounds__(tile_block(W)) void row_tile_sort(RowJob p) {
-    tile_sort_body<W>(p, blockIdx.x);
+template <int W, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void row_tile_sort(RowJob p) {
+    tile_sort_body<W, BLOCK>(p, blockIdx.x);
 }
 
 template <int W>
@@ -301,7 +308,113 @@ __global__ __launch_bounds__(tile_block(W)) void row_tile_sort_many(const RowJob
                                                                     uint32_t tile_base) {
     const uint32_t tile = tile_base + blockIdx.x;
     const RowJob &p = jobs[row_job_of<false>(jobs, J, tile)];
-    tile_sort_body<W>(p, tile - p.tile0);
+    tile_sort_body<W, tile_block(W)>(p, tile - p.tile0);
+}
+
+// One launch for three merge levels, for tables that leave the chip idle: a
+// workgroup finds the places of kRankBlock consecutive rows of one run among
+// the kWays runs that are put together (rows that compare equal in the order
+// of their runs).  In each of the other runs the rows' places lie between
+// those of the workgroup's first and last row, which 16 lanes each find with a
+// 16-way search; that part of the run is then searched in LDS (in memory, if
+// the parts together do not fit).  Reads src's keys; the last launch writes
+// the table's columns.
+template <int W>
+__global__ __launch_bounds__(kRankBlock) void row_rank_merge(RowJob p, uint32_t run, int src,
+                                                             int last) {
+    extern __shared__ __attribute__((aligned(16))) uint64_t s_part[];  // W planes of kRankPart
+    __shared__ uint32_t s_cut[2][kWays];
+    const uint32_t tid = threadIdx.x, lane = tid % dev::kWave;
+    const uint32_t e0 = blockIdx.x * kRankBlock, e1 = min(p.n, e0 + kRankBlock);
+    const uint64_t *key = p.key[src];
+    auto load = [&](uint32_t i) {
+        Key<W> k;
+#pragma unroll
+        for (int x = 0; x < W; ++x) k.w[x] = gload(key + (uint64_t)x * p.n + i);
+        return k;
+    };
+    // a run is a multiple of kRankBlock rows: the workgroup's rows are of one run
+    const uint32_t group = e0 / (kWays * run) * (kWays * run), own = (e0 - group) / run;
+    auto rows_of = [&](uint32_t j) {
+        const uint64_t first = (uint64_t)group + j * run;
+        return j == own || first >= p.n ? 0u : (uint32_t)min((uint64_t)run, p.n - first);
+    };
+    auto precedes = [&](uint32_t j, const Key<W> &q, const Key<W> &k) {  // q of run j, k of own
+        return j < own ? !key_less(k, q) : key_less(q, k);
+    };
+    const uint32_t i = min(e0 + tid, e1 - 1);
+    const Key<W> k = load(i);
+    {
+        const uint32_t q = tid / 16, j = q / 2, l16 = tid % 16;
+        const Key<W> edge = load(q % 2 ? e1 - 1 : e0);
+        const uint32_t first = group + j * run;
+        uint32_t lo = 0, hi = rows_of(j);
+        while (dev::ballot(lo < hi)) {
+            const uint32_t step = (hi - lo + 15) / 16, m = lo + l16 * step;
+            const bool before = m < hi && precedes(j, load(first + m), edge);
+            const uint32_t t = __popc((uint32_t)(dev::ballot(before) >> (lane & 48)) & 0xffffu);
+            const uint32_t next = t == 0 ? lo : lo + (t - 1) * step + 1;
+            hi = min(hi, lo + t * step);
+            lo = next;
+        }
+        if (l16 == 0) s_cut[q % 2][j] = lo;
+    }
+    __syncthreads();
+    uint32_t before[kWays], len[kWays], off[kWays], all = 0, most = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kWays; ++j) {
+        before[j] = s_cut[0][j];
+        len[j] = s_cut[1][j] - before[j];
+        off[j] = all;
+        all += len[j];
+        most = max(most, len[j]);
+    }
+    uint32_t at = i - own * run;  // rows of the same run
+#pragma unroll
+    for (uint32_t j = 0; j < kWays; ++j) at += before[j];
+    const bool fits = all <= kRankPart;
+    if (fits) {
+        Key<W> v[kWays];
+#pragma unroll
+        for (uint32_t j = 0; j < kWays; ++j) {
+            v[j] = k;
+            if (tid < len[j]) v[j] = load(group + j * run + before[j] + tid);
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < kWays; ++j) {
+            if (tid < len[j]) lds_put(s_part, kRankPart, off[j] + tid, v[j]);
+            for (uint32_t y = tid + kRankBlock; y < len[j]; y += kRankBlock)
+                lds_put(s_part, kRankPart, off[j] + y, load(group + j * run + before[j] + y));
+        }
+        __syncthreads();
+    }
+    uint32_t c[kWays] = {};
+    for (uint32_t step = most ? 1u << (31 - __builtin_clz(most)) : 0u; step; step >>= 1) {
+#pragma unroll
+        for (uint32_t j = 0; j < kWays; ++j) {
+            const uint32_t to = c[j] + step;
+            if (to > len[j]) continue;
+            const Key<W> q = fits ? lds_key<W>(s_part, kRankPart, off[j] + to - 1)
+                                  : load(group + j * run + before[j] + to - 1);
+            c[j] = precedes(j, q, k) ? to : c[j];
+        }
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kWays; ++j) at += c[j];
+    if (e0 + tid >= e1) return;
+    if (last && !p.distinct) {
+        for (int col = 0; col < p.ncols; ++col)
+            gstore(p.out[col] + at, column_of<W>(p, col, [&](int x) {
+                       uint64_t w = 0;
+#pragma unroll
+                       for (int y = 0; y < W; ++y) w = x == y ? k.w[y] : w;
+                       return w;
+                   }));
+        return;
+    }
+    uint64_t *to = p.key[src ^ 1];
+#pragma unroll
+    for (int x = 0; x < W; ++x) gstore(to + (uint64_t)x * p.n + at, k.w[x]);
 }
 
 // The same cut as lds_diagonal, for keys in global memory (planes of `stride`
@@ -454,14 +567,31 @@ void allow_lds(tid_ctx *ctx) {
     // above 64 KB a kernel must be allowed its dynamic LDS first
     constexpr size_t lds = (size_t)tile_rows(W) * 8 * W;
     (void)ctx;
-    (void)resident_blocks((const void *)row_tile_sort<W>, tile_block(W), lds);
+    (void)resident_blocks((const void *)row_rank_merge<W>, kRankBlock, (size_t)kRankPart * 8 * W);
+    (void)resident_blocks((const void *)row_tile_sort<W, tile_block(W)>, tile_block(W), lds);
     (void)resident_blocks((const void *)row_tile_sort_many<W>, tile_block(W), lds);
 }
+
+// Up to two levels of row_rank_merge: beyond, its reads (eight of every row, a
+// level) cost more than the launches it spares.  A sort of one table, small
+// tiles with row_rank_merge against large tiles with row_merge, one key word /
+// two, with the call's own 40 us:
+//    14,000 rows   55 /  70 us against  63 /  97 us
+//   100,000 rows   77 / 104 us against 101 / 151 us
+//   250,000 rows  114 / 175 us against 120 / 183 us
+//   500,000 rows  157 / 246 us against 143 / 216 us
+constexpr uint32_t kRankRows = kSmallTile * kVT * kWays * kWays;  // 114,688
 
 template <int W>
 void sort_one(tid_ctx *ctx, RowJob &p, tid_table *out) {
     allow_lds<W>(ctx);
     constexpr size_t lds = (size_t)tile_rows(W) * 8 * W;
+    // DISTINCT of rows that fit one large tile is done there
+    const bool ranked = p.n <= kRankRows && !(p.distinct && p.n <= tile_rows(W));
+    if (ranked) {
+        p.levels = 0;
+        for (uint64_t run = (uint64_t)kSmallTile * kVT; run < p.n; run *= kWays) ++p.levels;
+    }
     DevBuf keys;
     if (p.levels) {
         const size_t half = (size_t)p.n * 8 * W;
@@ -469,13 +599,30 @@ void sort_one(tid_ctx *ctx, RowJob &p, tid_table *out) {
         p.key[0] = keys.get<uint64_t>();
         p.key[1] = p.key[0] + (size_t)p.n * W;
     }
-    const uint32_t tiles = (p.n + tile_rows(W) - 1) / tile_rows(W);
-    hipLaunchKernelGGL(row_tile_sort<W>, dim3(tiles), dim3(tile_block(W)), lds, ctx->stream, p);
-    TID_HIP(hipGetLastError());
-    const uint32_t mtiles = (p.n + kMergeTile - 1) / kMergeTile;
-    for (int l = 0; l < p.levels; ++l) {
-        hipLaunchKernelGGL(row_merge<W>, dim3(mtiles), dim3(kMergeBlock), 0, ctx->stream, p, l);
+    if (ranked) {
+        constexpr uint32_t rows = (uint32_t)kSmallTile * kVT;
+        hipLaunchKernelGGL((row_tile_sort<W, kSmallTile>), dim3((p.n + rows - 1) / rows),
+                           dim3(kSmallTile), (size_t)rows * 8 * W, ctx->stream, p);
         TID_HIP(hipGetLastError());
+        constexpr size_t part = (size_t)kRankPart * 8 * W;
+        uint32_t run = rows;
+        for (int l = 0; l < p.levels; ++l, run *= kWays) {
+            hipLaunchKernelGGL(row_rank_merge<W>, dim3((p.n + kRankBlock - 1) / kRankBlock),
+                               dim3(kRankBlock), part, ctx->stream, p, run, l & 1,
+                               (int)(l + 1 == p.levels));
+            TID_HIP(hipGetLastError());
+        }
+    } else {
+        const uint32_t tiles = (p.n + tile_rows(W) - 1) / tile_rows(W);
+        hipLaunchKernelGGL((row_tile_sort<W, tile_block(W)>), dim3(tiles), dim3(tile_block(W)),
+                           lds, ctx->stream, p);
+        TID_HIP(hipGetLastError());
+        const uint32_t mtiles = (p.n + kMergeTile - 1) / kMergeTile;
+        for (int l = 0; l < p.levels; ++l) {
+            hipLaunchKernelGGL(row_merge<W>, dim3(mtiles), dim3(kMergeBlock), 0, ctx->stream, p,
+                               l);
+            TID_HIP(hipGetLastError());
+        }
     }
     if (!p.distinct || !p.levels) return;
     UniqueKeySrc src;

@@ -41,3 +41,30 @@ def test_row_sort(ctx, schema, n):
     assert got.nrows == n
     assert np.array_equal(got.to_numpy(), oracle.sort_rows(ot).rows)
     assert np.array_equal(ctx.sort(t, True).to_numpy(), oracle.distinct(ot).rows)
+
+
+@pytest.mark.parametrize("n", [14335, 14336, 14337, 14592, 114688, 114689])
+@pytest.mark.parametrize("schema", ["1 word, one column", "1 word, all 64 bits",
+                                    "2 words, a column across them", "3 words", "4 words"])
+@pytest.mark.parametrize("kind", ["random", "sorted", "reversed", "apart", "one"])
+def test_rank_merge(ctx, schema, n, kind):
+    """Runs that interleave, follow one another (their parts of another run are
+    empty or, out of order, all of it, more than fits LDS) or are all equal."""
+    hi = np.array(SCHEMAS[schema], dtype=np.int64)
+    rng = np.random.default_rng(n)
+    u = rng.random(n)
+    if kind == "sorted":
+        u = np.sort(u)
+    elif kind == "reversed":
+        u = np.sort(u)[::-1]
+    elif kind == "apart":   # a run of large rows among runs of small ones
+        u = np.where((np.arange(n) // 1792) % 8 == 3, 0.9 + u / 20, u / 1000)
+        u[::256] = 1.0
+    elif kind == "one":
+        u[:] = 0.5
+    rows = np.minimum((u[:, None] * (hi + 1)).astype(np.int64), hi)
+    rows[0] = hi
+    rows = rows.astype(np.uint32)
+    t, ot = ctx.table(rows, list(range(len(hi)))), OTable(rows, list(range(len(hi))))
+    assert np.array_equal(ctx.sort(t, False).to_numpy(), oracle.sort_rows(ot).rows)
+    assert np.array_equal(ctx.sort(t, True).to_numpy(), oracle.distinct(ot).rows)
