@@ -15,8 +15,9 @@
 
 namespace tid {
 
-void order_triples(tid_ctx *ctx, const uint32_t *g, uint64_t n, int pbits, int by_value, int pos,
-                   int vbits, uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, uint32_t *s,
+bool triples_pack(const int (&bits)[3]);
+void order_triples(tid_ctx *ctx, const uint32_t *g, uint64_t n, const int (&bits)[3], int by_value,
+                   int pos, uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, uint32_t *s,
                    uint32_t *o);
 
 namespace {
@@ -67,16 +68,16 @@ void partition_graph(tid_ctx *ctx, tid_graph *g, bool enable) {
     DevBuf cols[6] = {DevBuf(ctx, col), DevBuf(ctx, col), DevBuf(ctx, col),
                       DevBuf(ctx, col), DevBuf(ctx, col), DevBuf(ctx, col)};
     if (n) {
-        DevBuf k0(ctx, n * 8), k1(ctx, n * 8), v0(ctx, n * 4), v1(ctx, n * 4);
-        const int pbits = bits_of(g->max_id[1]);
+        const int bits[3] = {bits_of(g->max_id[0]), bits_of(g->max_id[1]), bits_of(g->max_id[2])};
+        const size_t val = triples_pack(bits) ? 0 : n * 4;
+        DevBuf k0(ctx, n * 8), k1(ctx, n * 8), v0(ctx, val), v1(ctx, val);
         // predicate order, then (predicate, subject), then (predicate, object);
         // every sort is stable, so ties stay in triple order
         for (int x = 0; x < 3; ++x) {
             const int pos = x == 2 ? 2 : 0;
-            order_triples(ctx, g->triples(), n, pbits, x > 0, pos, bits_of(g->max_id[pos]),
-                          k0.get<uint64_t>(), v0.get<uint32_t>(), k1.get<uint64_t>(),
-                          v1.get<uint32_t>(), cols[2 * x].get<uint32_t>(),
-                          cols[2 * x + 1].get<uint32_t>());
+            order_triples(ctx, g->triples(), n, bits, x > 0, pos, k0.get<uint64_t>(),
+                          v0.get<uint32_t>(), k1.get<uint64_t>(), v1.get<uint32_t>(),
+                          cols[2 * x].get<uint32_t>(), cols[2 * x + 1].get<uint32_t>());
         }
         TID_HIP(hipStreamSynchronize(ctx->stream));  // the sort buffers go back to the pool
     }

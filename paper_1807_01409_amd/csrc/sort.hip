@@ -1,12 +1,13 @@
-// sort.hip -- stable LSD radix sort of (64-bit key, 32-bit value) pairs, the
-// row sorts built on it and on the merge sort of rowsort.hip (the canonical
+// sort.hip -- stable LSD radix sort of 64-bit keys, alone or with 32-bit
+// values, the row sorts built on it and on the merge sort of rowsort.hip (the canonical
 // lexicographic order, DISTINCT), and union.
 //
 // The paper sorts subquery results before joining them and merges final
 // results to distinct values (Sec. 4.2 step 3 with Mgpu's mergesort, Sec. 4.3
 // DISTINCT).  The radix sort, written for wave64, orders the triples of the
-// partitioned layout, dictionary hashes, sort-merge joins and rows too wide for
-// packed keys.  A pass over a digit of at most 9 bits:
+// partitioned layout, the build sides of large joins, sort-merge joins and rows
+// too wide for packed keys.  A pass over a digit of at most 9 bits (10 where
+// that spares a pass):
 //   hist     each workgroup owns one contiguous range of the input and counts
 //            the digits of its range in LDS, a set of bins per wave;
 //   offsets  one workgroup per digit scans that digit's counts over the
@@ -40,8 +41,8 @@ void merge_sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &all,
 
 constexpr int kRadixBits = 8;                 // digit of the small sort
 constexpr uint32_t kRadix = 1u << kRadixBits;
-constexpr int kMaxDigitBits = 9;              // widest digit of a pass over memory
-constexpr uint32_t kMaxDigits = 1u << kMaxDigitBits;
+constexpr int kDigitBits = 9;                 // widest digit of a pass over memory,
+constexpr int kWideBits = 10;                 // and where that spares a pass
 constexpr int kSortBlock = 512;
 constexpr int kSortIPT = 8;
 constexpr int kSortNW = kSortBlock / dev::kWave;
@@ -56,10 +57,11 @@ __device__ __forceinline__ uint32_t sort_item(int wave, int it, int lane) {
 // Digit counts of every range.  Each wave counts in LDS bins of its own: with
 // the ballots of the scatter in place of the LDS atomics this took 293 us for
 // 50M keys, now 120 us.
-template <class In>
+template <class In, int BITS>
 __global__ __launch_bounds__(kSortBlock) void radix_hist(In in, uint64_t n, uint64_t range,
                                                           int shift, int nbits,
                                                           uint32_t *counts) {
+    constexpr uint32_t kMaxDigits = 1u << BITS;
     __shared__ uint32_t s_h[kSortNW][kMaxDigits];
     const int tid = threadIdx.x, wave = tid / dev::kWave, lane = tid % dev::kWave;
     const uint32_t R = 1u << nbits;
@@ -126,37 +128,55 @@ __global__ __launch_bounds__(kColThreads) void digit_scan(const uint32_t *__rest
 // lanes of a wave write runs of consecutive places (on average tile / digits
 // items, 64-200 B of keys): the same pass with every lane writing its own item
 // to its place took 407 us for 50M pairs of 8-bit digits, now 392 us for 9-bit
-// ones (requesting the next tile early, or six waves to a SIMD, cost registers
-// and were slower).  Keys and values go
-// through the same LDS one after the other, which leaves three workgroups to a
-// CU.
-template <class In, class Out>
+// ones, and keys alone 287 us.  Keys and values go through the same LDS one
+// after the other, which leaves three workgroups to a CU; what hides the
+// latencies is those workgroups: tiles twice as large (347 us for keys alone),
+// six waves to a SIMD and, with pairs, requesting the next tile early were
+// slower.
+template <class In, class Out, int BITS>
 __global__ __launch_bounds__(kSortBlock) void radix_scatter(In in, Out out, uint64_t n,
                                                              uint64_t range, int shift, int nbits,
                                                              const uint32_t *scan,
                                                              const uint32_t *totals) {
+    constexpr uint32_t kMaxDigits = 1u << BITS;
+    constexpr int kPer = kMaxDigits > kSortBlock ? kMaxDigits / kSortBlock : 1;
     __shared__ uint64_t s_item[kSortTile];
     __shared__ uint16_t s_wh[kSortNW][kMaxDigits];  // a wave's items per digit, then those before
     __shared__ uint32_t s_run[kMaxDigits];          // where the range's next item of a digit goes
     __shared__ uint32_t s_loc[kMaxDigits];          // first item of a digit in the sorted tile
     __shared__ uint32_t s_off[kMaxDigits];          // place of sorted item i: s_off[digit] + i
     __shared__ uint32_t s_w[kSortNW];
-    const int tid = threadIdx.x, wave = tid / dev::kWave, lane = tid % dev::kWave;
+    const uint32_t tid = threadIdx.x;
+    const int wave = tid / dev::kWave, lane = tid % dev::kWave;
     const uint32_t R = 1u << nbits, w = blockIdx.x;
-    // exclusive sum over the digits of x (thread d: digit d)
-    auto digit_prefix = [&](uint32_t x) {
-        const uint32_t incl = dev::wave_inclusive_sum(x);
+    // exclusive sums over the digits (a thread's kPer digits at x), in place
+    auto digit_prefix = [&](uint32_t (&x)[kPer]) {
+        uint32_t sum = 0;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) sum += x[q];
+        const uint32_t incl = dev::wave_inclusive_sum(sum);
         if (lane == dev::kWave - 1) s_w[wave] = incl;
         __syncthreads();
-        uint32_t before = 0;
+        uint32_t run = incl - sum;
 #pragma unroll
-        for (int y = 0; y < kSortNW; ++y) before += y < wave ? s_w[y] : 0u;
-        return before + incl - x;
+        for (int y = 0; y < kSortNW; ++y) run += y < wave ? s_w[y] : 0u;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const uint32_t c = x[q];
+            x[q] = run;
+            run += c;
+        }
     };
-    static_assert(kMaxDigits <= kSortBlock, "a thread per digit");
     {
-        const uint32_t base = digit_prefix(tid < (int)R ? totals[tid] : 0u);
-        if (tid < (int)R) s_run[tid] = base + scan[(size_t)w * R + tid];
+        uint32_t base[kPer];
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) base[q] = tid * kPer + q < R ? totals[tid * kPer + q] : 0u;
+        digit_prefix(base);
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const uint32_t d = tid * kPer + q;
+            if (d < R) s_run[d] = base[q] + scan[(size_t)w * R + d];
+        }
     }
     const uint64_t r0 = (uint64_t)w * range, r1 = min(n, r0 + range);
     const uint64_t lt = (1ull << lane) - 1ull;
@@ -183,26 +203,36 @@ __global__ __launch_bounds__(kSortBlock) void radix_scatter(In in, Out out, uint
         for (int it = 0; it < kSortIPT; ++it) {
             const bool valid = sort_item(wave, it, lane) < cnt;
             const uint32_t d = (uint32_t)(key[it] >> shift) & (R - 1);
-            const uint64_t peers = dev::match_digit<kMaxDigitBits>(d, valid, nbits);
+            const uint64_t peers = dev::match_digit<BITS>(d, valid, nbits);
             const uint32_t before = valid ? s_wh[wave][d] : 0u;
             rank[it] = before + (uint32_t)__popcll(peers & lt);
             if (valid && lane == __builtin_ctzll(peers))
                 s_wh[wave][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
         }
         __syncthreads();
-        uint32_t tot = 0;
-        if (tid < (int)R)
-            for (int ww = 0; ww < kSortNW; ++ww) {  // waves in item order
-                const uint32_t c = s_wh[ww][tid];
-                s_wh[ww][tid] = (uint16_t)tot;
-                tot += c;
+        uint32_t tot[kPer], loc[kPer];
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const uint32_t d = tid * kPer + q;
+            tot[q] = 0;
+            if (d < R)
+                for (int ww = 0; ww < kSortNW; ++ww) {  // waves in item order
+                    const uint32_t c = s_wh[ww][d];
+                    s_wh[ww][d] = (uint16_t)tot[q];
+                    tot[q] += c;
+                }
+            loc[q] = tot[q];
+        }
+        digit_prefix(loc);
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const uint32_t d = tid * kPer + q;
+            if (d < R) {
+                const uint32_t run = s_run[d];
+                s_loc[d] = loc[q];
+                s_off[d] = run - loc[q];
+                s_run[d] = run + tot[q];
             }
-        const uint32_t loc = digit_prefix(tot);
-        if (tid < (int)R) {
-            const uint32_t run = s_run[tid];
-            s_loc[tid] = loc;
-            s_off[tid] = run - loc;
-            s_run[tid] = run + tot;
         }
         __syncthreads();
         uint32_t at[kSortIPT];
@@ -213,6 +243,18 @@ __global__ __launch_bounds__(kSortBlock) void radix_scatter(In in, Out out, uint
             if (sort_item(wave, it, lane) < cnt) s_item[at[it]] = key[it];
         }
         __syncthreads();
+        if constexpr (!In::kPairs) {
+#pragma unroll
+            for (int u = 0; u < kSortIPT; ++u) {
+                const uint32_t i = u * kSortBlock + tid;
+                if (i < cnt) {
+                    const uint64_t k = s_item[i];
+                    out.put(s_off[(uint32_t)(k >> shift) & (R - 1)] + i, k, 0);
+                }
+            }
+            __syncthreads();
+            continue;
+        }
         uint64_t skey[kSortIPT];
 #pragma unroll
         for (int u = 0; u < kSortIPT; ++u) skey[u] = s_item[u * kSortBlock + tid];
@@ -234,8 +276,9 @@ __global__ __launch_bounds__(kSortBlock) void radix_scatter(In in, Out out, uint
     }
 }
 
-// where a pass takes its pairs from, and where it puts them
+// where a pass takes its pairs (or its keys alone) from, and where it puts them
 struct PairIn {
+    static constexpr bool kPairs = true;
     const uint64_t *k;
     const uint32_t *v;
     __device__ __forceinline__ PairIn from(uint64_t t0) const { return PairIn{k + t0, v + t0}; }
@@ -257,6 +300,7 @@ struct PairOut {
 
 // 32-bit keys (v null: the item's number)
 struct KeyIn {
+    static constexpr bool kPairs = true;
     const uint32_t *k, *v;
     uint32_t first;
     __device__ __forceinline__ KeyIn from(uint64_t t0) const {
@@ -280,6 +324,7 @@ struct KeyOut {
 // a triple as (its predicate and, below it in `bits` bits, the value at position
 // lo, 0 or 2; the value at the other one)
 struct TripleIn {
+    static constexpr bool kPairs = true;
     const uint32_t *g;
     int32_t lo, bits;
     __device__ __forceinline__ TripleIn from(uint64_t t0) const {
@@ -294,6 +339,48 @@ struct TripleIn {
         const uint32_t s = t[0], p = t[1], o = t[2];  // one 12-byte load
         key = (uint64_t)p << bits | (lo == 0 ? s : o);
         val = lo == 0 ? o : s;
+    }
+};
+
+// a whole triple in a key: the predicate, below it the value at position lo (0
+// or 2), below that, in `bits` bits, the other one
+struct PackIn {
+    static constexpr bool kPairs = false;
+    const uint32_t *g;
+    int32_t lo, lo_bits, bits;
+    __device__ __forceinline__ PackIn from(uint64_t t0) const {
+        return PackIn{g + 3 * t0, lo, lo_bits, bits};
+    }
+    __device__ __forceinline__ uint64_t key(uint32_t i) const {
+        const uint32_t *t = g + 3 * i;
+        const uint32_t s = t[0], p = t[1], o = t[2];  // one 12-byte load
+        const uint64_t a = lo == 0 ? s : o, b = lo == 0 ? o : s;
+        return ((uint64_t)p << lo_bits | a) << bits | b;
+    }
+    __device__ __forceinline__ void load(uint32_t i, uint64_t &k, uint32_t &) const { k = key(i); }
+};
+
+struct WordIn {
+    static constexpr bool kPairs = false;
+    const uint64_t *k;
+    __device__ __forceinline__ WordIn from(uint64_t t0) const { return WordIn{k + t0}; }
+    __device__ __forceinline__ uint64_t key(uint32_t i) const { return k[i]; }
+    __device__ __forceinline__ void load(uint32_t i, uint64_t &key, uint32_t &) const { key = k[i]; }
+};
+
+struct WordOut {
+    uint64_t *k;
+    __device__ __forceinline__ void put(uint32_t at, uint64_t key, uint32_t) const { k[at] = key; }
+};
+
+// PackIn's keys back to two columns
+struct UnpackOut {
+    uint32_t *lo, *hi;
+    int32_t bits;
+    uint32_t lo_mask, mask;
+    __device__ __forceinline__ void put(uint32_t at, uint64_t key, uint32_t) const {
+        lo[at] = (uint32_t)(key >> bits) & lo_mask;
+        hi[at] = (uint32_t)key & mask;
     }
 };
 
@@ -507,13 +594,14 @@ void scan_digits(tid_ctx *ctx, const uint32_t *counts, uint32_t *scan, uint32_t 
 }
 
 // The passes of a stable sort of n pairs on key bits [first, last): digits of
-// nearly equal widths, at most kMaxDigitBits, over ranges of whole tiles.
+// nearly equal widths, at most kWideBits, over ranges of whole tiles.
 struct Passes {
     uint64_t n, range, P;
     int first, last, count, width;
     DevBuf counts, scan;
     Passes(tid_ctx *ctx, uint64_t rows, int b0, int b1) : n(rows), first(b0), last(b1) {
-        count = std::max(1, (last - first + kMaxDigitBits - 1) / kMaxDigitBits);
+        auto passes = [&](int bits) { return std::max(1, (last - first + bits - 1) / bits); };
+        count = std::min(passes(kDigitBits), passes(kWideBits));
         width = (last - first + count - 1) / count;
         const uint64_t tiles = (n + kSortTile - 1) / kSortTile;
         P = std::max<uint64_t>(1, std::min<uint64_t>(tiles, 3ull * device_cus(ctx)));
@@ -524,14 +612,19 @@ struct Passes {
     }
     template <class In, class Out>
     void run(tid_ctx *ctx, In in, Out out, int pass) const {
+        if (width <= kDigitBits) run_bits<kDigitBits>(ctx, in, out, pass);
+        else run_bits<kWideBits>(ctx, in, out, pass);
+    }
+    template <int BITS, class In, class Out>
+    void run_bits(tid_ctx *ctx, In in, Out out, int pass) const {
         const int shift = first + pass * width, nbits = std::min(width, last - shift);
         uint32_t *totals = scan.get<uint32_t>() + ((size_t)P << nbits);
-        hipLaunchKernelGGL(radix_hist<In>, dim3((uint32_t)P), dim3(kSortBlock), 0, ctx->stream, in,
-                           n, range, shift, nbits, counts.get<uint32_t>());
+        hipLaunchKernelGGL((radix_hist<In, BITS>), dim3((uint32_t)P), dim3(kSortBlock), 0,
+                           ctx->stream, in, n, range, shift, nbits, counts.get<uint32_t>());
         TID_HIP(hipGetLastError());
         scan_digits(ctx, counts.get<const uint32_t>(), scan.get<uint32_t>(), totals, (uint32_t)P,
                     1u << nbits);
-        hipLaunchKernelGGL((radix_scatter<In, Out>), dim3((uint32_t)P), dim3(kSortBlock), 0,
+        hipLaunchKernelGGL((radix_scatter<In, Out, BITS>), dim3((uint32_t)P), dim3(kSortBlock), 0,
                            ctx->stream, in, out, n, range, shift, nbits,
                            scan.get<const uint32_t>(), totals);
         TID_HIP(hipGetLastError());
@@ -583,26 +676,43 @@ bool sort_keys32(tid_ctx *ctx, const uint32_t *col, uint64_t n, int bits, uint32
 
 // The subject and object columns of the n triples in (predicate, value) order,
 // stably: by_value = 0 predicate alone, else its subject (pos 0) or object (pos
-// 2) too, whose IDs have vbits bits.  The first pass reads the triples, the last
-// one writes the columns: no key array is packed, nothing is gathered.  k and v
-// (n each) are scratch, two of each.
-void order_triples(tid_ctx *ctx, const uint32_t *g, uint64_t n, int pbits, int by_value, int pos,
-                   int vbits, uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, uint32_t *s,
+// 2) too.  bits: width of the IDs of each position.  The first pass reads the
+// triples, the last one writes the columns; between them a triple is one 64-bit
+// key if its IDs fit (scratch k0, k1 of n words), else a pair of predicate and
+// value and the other position (also v0, v1).  50M triples, all three orders,
+// 1000 predicates: 5.07 ms with pairs and digits of at most 9 bits, now 3.97.
+bool triples_pack(const int (&bits)[3]) { return bits[0] + bits[1] + bits[2] <= 64; }
+
+void order_triples(tid_ctx *ctx, const uint32_t *g, uint64_t n, const int (&bits)[3], int by_value,
+                   int pos, uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, uint32_t *s,
                    uint32_t *o) {
     TID_REQUIRE(n < (1ull << 32), TID_E_UNSUPPORTED, "sort: more than 2^32-1 rows");
     if (n == 0) return;
-    const int below = by_value ? vbits : 32;  // bits below the predicate
-    const TripleIn in{g, pos, below};
-    const ColumnsOut out{pos == 0 ? s : o, pos == 0 ? o : s, (1ull << below) - 1};
-    const Passes ps(ctx, n, by_value ? 0 : below, below + pbits);
-    for (int x = 0; x < ps.count; ++x) {
-        const PairIn pin{x & 1 ? k0 : k1, x & 1 ? v0 : v1};
-        const PairOut pout{x & 1 ? k1 : k0, x & 1 ? v1 : v0};
-        if (x == 0 && ps.count == 1) ps.run(ctx, in, out, x);
-        else if (x == 0) ps.run(ctx, in, pout, x);
-        else if (x + 1 == ps.count) ps.run(ctx, pin, out, x);
-        else ps.run(ctx, pin, pout, x);
+    uint32_t *lo = pos == 0 ? s : o, *hi = pos == 0 ? o : s;
+    auto sort = [&](const Passes &ps, auto in, auto mid_in, auto mid_out, auto out) {
+        for (int x = 0; x < ps.count; ++x) {
+            if (x == 0 && ps.count == 1) ps.run(ctx, in, out, x);
+            else if (x == 0) ps.run(ctx, in, mid_out(x), x);
+            else if (x + 1 == ps.count) ps.run(ctx, mid_in(x), out, x);
+            else ps.run(ctx, mid_in(x), mid_out(x), x);
+        }
+    };
+    auto from = [&](int x) { return x & 1 ? k0 : k1; };
+    auto to = [&](int x) { return x & 1 ? k1 : k0; };
+    if (triples_pack(bits)) {
+        const int nlo = bits[pos], nhi = bits[2 - pos];
+        const Passes ps(ctx, n, nhi + (by_value ? 0 : nlo), nhi + nlo + bits[1]);
+        sort(ps, PackIn{g, pos, nlo, nhi}, [&](int x) { return WordIn{from(x)}; },
+             [&](int x) { return WordOut{to(x)}; },
+             UnpackOut{lo, hi, nhi, (uint32_t)((1ull << nlo) - 1), (uint32_t)((1ull << nhi) - 1)});
+        return;
     }
+    const int below = by_value ? bits[pos] : 32;  // bits below the predicate
+    const Passes ps(ctx, n, by_value ? 0 : below, below + bits[1]);
+    sort(ps, TripleIn{g, pos, below},
+         [&](int x) { return PairIn{from(x), x & 1 ? v0 : v1}; },
+         [&](int x) { return PairOut{to(x), x & 1 ? v1 : v0}; },
+         ColumnsOut{lo, hi, (1ull << below) - 1});
 }
 
 std::vector<uint32_t> column_maxima(tid_ctx *ctx, const tid_table *t, uint64_t n) {

@@ -60,3 +60,32 @@ def test_sort_merge_join(ctx, n, bits):
     got = ctx.join(ctx.table(L, [0, 1]), 0, ctx.table(R, [2, 0]), 1, 2).to_numpy()
     want = oracle.join(OTable(L, [0, 1]), 0, OTable(R, [2, 0]), 1, "sortmerge").rows
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("n", [4095, 12289])
+@pytest.mark.parametrize("preds", [15, 16])   # with 30-bit IDs: a triple is 64 bits, or 65
+@pytest.mark.parametrize("side", [0, 2])
+def test_orders_widest_key(ctx, n, preds, side):
+    rng = np.random.default_rng(n + preds)
+    top = 2**30 - 1
+    g = np.stack([rng.integers(top - 999, top + 1, n), 1 + np.arange(n) % preds,
+                  rng.integers(top - 999, top + 1, n)], axis=1).astype(np.uint32)
+    g[:, 2 - side] = rng.permutation(n) + 1        # one position has few IDs, one the largest
+    g[0] = [top, preds, top]
+    G = ctx.load(g)
+    G.partition(True)
+    old = ctx.get_option("semijoin_min")
+    try:
+        ctx.set_option("semijoin_min", 1)
+        for q in (1, preds):
+            t = pat(f"?s {q} ?o")
+            assert np.array_equal(ctx.scan(G, t).to_numpy(), oracle.scan(g, t).rows)
+        x = int(g[g[:, 1] == preds][0, 2 - side])
+        names = {}
+        first, second = ((f"?x {preds} {x}", "?x 1 ?y") if side == 0 else
+                         (f"{x} {preds} ?x", "?y 1 ?x"))
+        plan = Plan().scan(pat(first, names)).scan(pat(second, names)).join(names["?x"])
+        assert np.array_equal(ctx.query(G, plan).to_numpy(), oracle.query(g, plan).rows)
+    finally:
+        ctx.set_option("semijoin_min", old)
+        G.free()
