@@ -31,6 +31,8 @@
 
 namespace tid {
 
+void exclusive_scan_async(tid_ctx *ctx, const uint32_t *in, uint64_t n, uint64_t *out);
+
 namespace {
 
 constexpr int kVT = 7;                       // keys per thread
@@ -52,13 +54,15 @@ struct RowJob {
     const uint32_t *in[TID_MAX_COLS];
     uint32_t *out[TID_MAX_COLS];
     uint64_t *key[2];              // W planes of n words each, double buffered
-    uint64_t *count;               // DISTINCT of one tile: the row count (else null)
+    uint64_t *count;               // DISTINCT: the row count (else null)
+    uint32_t *kept;                // DISTINCT, last merge level: a tile's first-of-equals
     uint32_t n;
     uint32_t tile0, mtile0;        // the job's first tile in the two kinds of launch
     int32_t levels;                // merge launches the job takes part in
     int16_t ncols;
-    int16_t distinct;              // one tile: keep the first of equal rows; several tiles
-                                   // (one-word keys only): leave the sorted keys
+    int16_t distinct;              // one tile: keep the first of equal rows; several: the
+                                   // last row_merge keeps them, tile by tile; the last
+                                   // row_rank_merge leaves the sorted keys
     uint8_t word[TID_MAX_COLS];    // bit position of a column from the key's end:
     uint8_t shift[TID_MAX_COLS];   // word (0 = least significant) and bit in it
     uint8_t width[TID_MAX_COLS];   // bits (0: a column of zeros)
@@ -447,6 +451,41 @@ __device__ __forceinline__ uint32_t wave_diagonal(const uint64_t *key, uint64_t 
     return lo;
 }
 
+// The first of each run of equal keys in a sorted tile (in s_key, a thread's
+// kVT keys also in k; before: the key before the tile, if `leads`) to the front
+// of s_key; their number.
+template <int W>
+__device__ __forceinline__ uint32_t keep_firsts(uint64_t *s_key, const Key<W> (&k)[kVT],
+                                                Key<W> before, bool leads, uint32_t cnt) {
+    __shared__ uint32_t s_w[kMergeBlock / dev::kWave];
+    const uint32_t tid = threadIdx.x, wave = tid / dev::kWave;
+    bool keep[kVT];
+    uint32_t mine = 0;
+    if (tid > 0) before = lds_key<W>(s_key, kMergeTile, tid * kVT - 1);
+#pragma unroll
+    for (int v = 0; v < kVT; ++v) {
+        bool same = v > 0 || tid > 0 || leads;
+#pragma unroll
+        for (int x = 0; x < W; ++x) same &= k[v].w[x] == (v ? k[v - 1].w[x] : before.w[x]);
+        keep[v] = !same && tid * kVT + v < cnt;
+        mine += keep[v];
+    }
+    const uint32_t incl = dev::wave_inclusive_sum(mine);
+    if (tid % dev::kWave == dev::kWave - 1) s_w[wave] = incl;
+    __syncthreads();  // also: every thread has read its keys
+    uint32_t at = incl - mine, all = 0;
+#pragma unroll
+    for (uint32_t x = 0; x < kMergeBlock / dev::kWave; ++x) {
+        at += x < wave ? s_w[x] : 0u;
+        all += s_w[x];
+    }
+#pragma unroll
+    for (int v = 0; v < kVT; ++v)
+        if (keep[v]) lds_put(s_key, kMergeTile, at++, k[v]);
+    __syncthreads();
+    return all;
+}
+
 // Output rows [tile * kMergeTile, ...) of one merge level: runs of `run` rows
 // (a multiple of kMergeTile) pairwise into runs of 2 * run.
 template <int W>
@@ -493,12 +532,112 @@ __device__ __forceinline__ void merge_body(const RowJob &p, uint32_t tile, int l
 #pragma unroll
     for (int v = 0; v < kVT; ++v) lds_put(s_key, kMergeTile, tid * kVT + v, k[v]);
     __syncthreads();
-    if (level + 1 == p.levels && !p.distinct) {
-        write_columns<W, kMergeBlock>(p, s_key, kMergeTile, cnt, (uint32_t)o0);
-    } else {
-        write_keys<W, kMergeBlock>(p, p.key[(level & 1) ^ 1], s_key, kMergeTile, cnt,
-                                   (uint32_t)o0);
+    uint64_t *const dst = p.key[(level & 1) ^ 1];
+    if (level + 1 < p.levels || !p.distinct) {
+        if (level + 1 == p.levels)
+            write_columns<W, kMergeBlock>(p, s_key, kMergeTile, cnt, (uint32_t)o0);
+        else
+            write_keys<W, kMergeBlock>(p, dst, s_key, kMergeTile, cnt, (uint32_t)o0);
+        return;
     }
+    // DISTINCT, last level: the first of each run of equal keys; the key before
+    // the tile is the larger of the last ones cut off from the two runs
+    Key<W> before{};
+    const bool leads = tid == 0 && o0 > 0;
+    if (leads) {
+#pragma unroll
+        for (int x = 0; x < W; ++x) {
+            const uint64_t *plane = src + (uint64_t)x * p.n;
+            before.w[x] = gload(plane + (a0 > 0 ? a + a0 - 1 : b + b0 - 1));
+        }
+        if (a0 > 0 && b0 > 0) {
+            Key<W> q;
+#pragma unroll
+            for (int x = 0; x < W; ++x) q.w[x] = gload(src + (uint64_t)x * p.n + b + b0 - 1);
+            const bool less = key_less(before, q);
+#pragma unroll
+            for (int x = 0; x < W; ++x) before.w[x] = less ? q.w[x] : before.w[x];
+        }
+    }
+    const uint32_t all = keep_firsts<W>(s_key, k, before, leads, cnt);
+    write_keys<W, kMergeBlock>(p, dst, s_key, kMergeTile, all, (uint32_t)o0);
+    if (tid == 0) p.kept[tile] = all;
+}
+
+// The same for sorted keys in memory (key[from]).  p.kept null, for a few
+// tiles: straight to the columns, every workgroup counting the first-of-equals
+// before its tile itself; else into the other buffer.
+template <int W>
+__global__ __launch_bounds__(kMergeBlock) void row_keep_firsts(RowJob p, int from) {
+    __shared__ uint64_t s_key[W * kMergeTile];
+    __shared__ uint32_t s_sum[kMergeBlock / dev::kWave];
+    const uint32_t tid = threadIdx.x, tile = blockIdx.x;
+    const uint32_t o0 = tile * kMergeTile, cnt = min(kMergeTile, p.n - o0);
+    const uint64_t *src = p.key[from];
+#pragma unroll
+    for (int x = 0; x < W; ++x)
+        for (uint32_t i = tid; i < cnt; i += kMergeBlock)
+            s_key[x * kMergeTile + i] = gload(src + (uint64_t)x * p.n + o0 + i);
+    Key<W> before{};
+    const bool leads = tid == 0 && o0 > 0;
+    if (leads) {
+#pragma unroll
+        for (int x = 0; x < W; ++x) before.w[x] = gload(src + (uint64_t)x * p.n + o0 - 1);
+    }
+    uint32_t earlier = 0;
+    if (!p.kept) {
+#pragma unroll 4
+        for (uint32_t i = tid; i < o0; i += kMergeBlock) {
+            bool same = i > 0;
+#pragma unroll
+            for (int x = 0; x < W; ++x) {
+                const uint64_t *w = src + (uint64_t)x * p.n + i;
+                same &= i > 0 && gload(w) == gload(w - 1);
+            }
+            earlier += !same;
+        }
+        earlier = dev::wave_sum(earlier);
+        if (tid % dev::kWave == 0) s_sum[tid / dev::kWave] = earlier;
+    }
+    __syncthreads();
+    Key<W> k[kVT];
+#pragma unroll
+    for (int v = 0; v < kVT; ++v) k[v] = lds_key<W>(s_key, kMergeTile, tid * kVT + v);
+    const uint32_t all = keep_firsts<W>(s_key, k, before, leads, cnt);
+    if (p.kept) {
+        write_keys<W, kMergeBlock>(p, p.key[from ^ 1], s_key, kMergeTile, all, o0);
+        if (tid == 0) p.kept[tile] = all;
+        return;
+    }
+    earlier = 0;
+#pragma unroll
+    for (int x = 0; x < kMergeBlock / dev::kWave; ++x) earlier += s_sum[x];
+    write_columns<W, kMergeBlock>(p, s_key, kMergeTile, all, earlier);
+    if (tile + 1 == gridDim.x && tid == 0) *p.count = earlier + all;
+}
+
+// The kept keys of every tile (first: exclusive sums of their numbers) to the
+// table's columns.
+template <int W>
+__global__ __launch_bounds__(kMergeBlock) void kept_to_columns(RowJob p, int from,
+                                                              const uint64_t *first) {
+    const uint32_t tile = blockIdx.x;
+    const uint64_t *key = p.key[from] + (uint64_t)tile * kMergeTile;
+    const uint64_t at = first[tile];
+    const uint32_t cnt = (uint32_t)(first[tile + 1] - at);
+    for (uint32_t i = threadIdx.x; i < cnt; i += kMergeBlock) {
+        Key<W> k;
+#pragma unroll
+        for (int x = 0; x < W; ++x) k.w[x] = gload(key + (uint64_t)x * p.n + i);
+        for (int c = 0; c < p.ncols; ++c)
+            gstore(p.out[c] + at + i, column_of<W>(p, c, [&](int x) {
+                       uint64_t w = 0;
+#pragma unroll
+                       for (int y = 0; y < W; ++y) w = x == y ? k.w[y] : w;
+                       return w;
+                   }));
+    }
+    if (tile + 1 == gridDim.x && threadIdx.x == 0) *p.count = at + cnt;
 }
 
 template <int W>
@@ -513,27 +652,6 @@ __global__ __launch_bounds__(kMergeBlock) void row_merge_many(const RowJob *jobs
     const RowJob &p = jobs[row_job_of<true>(jobs, J, tile)];
     merge_body<W>(p, tile - p.mtile0, level);
 }
-
-// one-word keys of a sorted list that differ from the key before them
-struct UniqueKeySrc {
-    RowJob p;
-    const uint64_t *key;
-    uint64_t n;
-    struct Item {
-        uint64_t k;
-        bool first;
-    };
-    __device__ __forceinline__ Item load(uint64_t i) const {
-        Item t;
-        t.k = key[i];
-        t.first = i == 0 || key[i - 1] != t.k;
-        return t;
-    }
-    __device__ __forceinline__ bool match(int, const Item &t) const { return t.first; }
-    __device__ __forceinline__ uint32_t value(int, int c, const Item &t, uint64_t) const {
-        return column_of<1>(p, c, [&](int) { return t.k; });
-    }
-};
 
 int bits_of(uint32_t v) { return v ? 32 - __builtin_clz(v) : 0; }
 
@@ -580,10 +698,13 @@ void allow_lds(tid_ctx *ctx) {
 //   100,000 rows   77 / 104 us against 101 / 151 us
 //   250,000 rows  114 / 175 us against 120 / 183 us
 //   500,000 rows  157 / 246 us against 143 / 216 us
+// DISTINCT after it in one launch (row_keep_firsts) for so many merge tiles,
+// else in three: 14,000 rows of one word 69 us against 83, 28,000 rows 102 against 95.
+constexpr uint32_t kFewTiles = 8;
 constexpr uint32_t kRankRows = kSmallTile * kVT * kWays * kWays;  // 114,688
 
 template <int W>
-void sort_one(tid_ctx *ctx, RowJob &p, tid_table *out) {
+void sort_one(tid_ctx *ctx, RowJob &p) {
     allow_lds<W>(ctx);
     constexpr size_t lds = (size_t)tile_rows(W) * 8 * W;
     // DISTINCT of rows that fit one large tile is done there
@@ -599,6 +720,14 @@ void sort_one(tid_ctx *ctx, RowJob &p, tid_table *out) {
         p.key[0] = keys.get<uint64_t>();
         p.key[1] = p.key[0] + (size_t)p.n * W;
     }
+    const uint32_t mtiles = (p.n + kMergeTile - 1) / kMergeTile;
+    DevBuf kept, first;
+    if (p.distinct && p.levels && !(ranked && mtiles <= kFewTiles)) {
+        kept = DevBuf(ctx, (size_t)mtiles * 4);
+        first = DevBuf(ctx, ((size_t)mtiles + 1) * 8);
+        p.kept = kept.get<uint32_t>();
+    }
+    int from = p.levels & 1;  // the buffer of the sorted keys
     if (ranked) {
         constexpr uint32_t rows = (uint32_t)kSmallTile * kVT;
         hipLaunchKernelGGL((row_tile_sort<W, kSmallTile>), dim3((p.n + rows - 1) / rows),
@@ -612,29 +741,28 @@ void sort_one(tid_ctx *ctx, RowJob &p, tid_table *out) {
                                (int)(l + 1 == p.levels));
             TID_HIP(hipGetLastError());
         }
+        if (p.distinct) {
+            hipLaunchKernelGGL(row_keep_firsts<W>, dim3(mtiles), dim3(kMergeBlock), 0,
+                               ctx->stream, p, from);
+            TID_HIP(hipGetLastError());
+            from ^= 1;
+        }
     } else {
         const uint32_t tiles = (p.n + tile_rows(W) - 1) / tile_rows(W);
         hipLaunchKernelGGL((row_tile_sort<W, tile_block(W)>), dim3(tiles), dim3(tile_block(W)),
                            lds, ctx->stream, p);
         TID_HIP(hipGetLastError());
-        const uint32_t mtiles = (p.n + kMergeTile - 1) / kMergeTile;
         for (int l = 0; l < p.levels; ++l) {
             hipLaunchKernelGGL(row_merge<W>, dim3(mtiles), dim3(kMergeBlock), 0, ctx->stream, p,
                                l);
             TID_HIP(hipGetLastError());
         }
     }
-    if (!p.distinct || !p.levels) return;
-    UniqueKeySrc src;
-    src.p = p;
-    src.key = p.key[p.levels & 1];
-    src.n = p.n;
-    CompactArgs<1, TID_MAX_COLS> a{};
-    for (int c = 0; c < p.ncols; ++c) a.out[0].col[c] = p.out[c];
-    a.out[0].cap = out->cap;
-    a.out[0].count = out->d_count;
-    a.out[0].ncols = p.ncols;
-    launch_compact<UniqueKeySrc, 256, 16, 1, TID_MAX_COLS>(ctx, src, a, 1, 8192);
+    if (!p.kept) return;
+    exclusive_scan_async(ctx, p.kept, mtiles, first.get<uint64_t>());
+    hipLaunchKernelGGL(kept_to_columns<W>, dim3(mtiles), dim3(kMergeBlock), 0, ctx->stream, p,
+                       from, first.get<const uint64_t>());
+    TID_HIP(hipGetLastError());
 }
 
 template <int W>
@@ -682,25 +810,17 @@ bool rows_mergeable(const tid_table *t, uint64_t n) {
     return w == 1 ? n <= kMergeRows1 : w <= kMaxWords && n <= kMergeRows;
 }
 
-// Whether merge_sort_rows can also drop repeated rows; where it cannot, the
-// caller compacts the sorted table.
-bool merge_distinct_ok(const tid_table *t, uint64_t n) {
-    const int w = key_words(t);
-    return w == 1 || n <= tile_rows(w);
-}
-
 // The n >= 1 rows of `in` in lexicographic order into `out` (n rows
-// allocated); distinct = 1: without repeats (merge_distinct_ok), the count left
-// on the device.
+// allocated); distinct = 1: without repeats, the count left to the kernels.
 void merge_sort_rows(tid_ctx *ctx, const tid_table *in, uint64_t n, tid_table *out,
                      int distinct) {
     const int w = key_words(in);
     RowJob p = row_job(in, out, n, w, distinct);
     if (distinct) p.count = out->d_count;
-    if (w == 1) sort_one<1>(ctx, p, out);
-    else if (w == 2) sort_one<2>(ctx, p, out);
-    else if (w == 3) sort_one<3>(ctx, p, out);
-    else sort_one<4>(ctx, p, out);
+    if (w == 1) sort_one<1>(ctx, p);
+    else if (w == 2) sort_one<2>(ctx, p);
+    else if (w == 3) sort_one<3>(ctx, p);
+    else sort_one<4>(ctx, p);
 }
 
 // The same for many tables in shared launches (no DISTINCT, counts set by the

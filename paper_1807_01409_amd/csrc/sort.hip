@@ -33,7 +33,6 @@
 namespace tid {
 
 bool rows_mergeable(const tid_table *t, uint64_t n);
-bool merge_distinct_ok(const tid_table *t, uint64_t n);
 void merge_sort_rows(tid_ctx *ctx, const tid_table *in, uint64_t n, tid_table *out, int distinct);
 void merge_sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &all,
                              std::vector<DevBuf> &keep,
@@ -842,9 +841,8 @@ std::unique_ptr<tid_table> sort_rows(tid_ctx *ctx, const tid_table *t, uint64_t 
         return sorted;
     }
     if (rows_mergeable(t, n)) {
-        const bool drop = distinct && merge_distinct_ok(t, n);
-        merge_sort_rows(ctx, t, n, sorted.get(), drop);
-        if (drop) return sorted;  // its count is on the device
+        merge_sort_rows(ctx, t, n, sorted.get(), distinct);
+        if (distinct) return sorted;  // its count is still to come
         sorted->nrows = n;
         sorted->count_known = true;
     } else {
@@ -887,6 +885,23 @@ std::unique_ptr<tid_table> sort_table(tid_ctx *ctx, const tid_table *t, int dist
     return sort_rows(ctx, t, n, distinct);
 }
 
+// Columns of several tables put one after the other, in one launch (a copy
+// each took 48 us for 16 columns of 400,000 rows).
+constexpr int kPieces = 64;
+struct Pieces {
+    const uint32_t *src[kPieces];  // null: zeros
+    uint32_t *dst[kPieces];
+    uint64_t n[kPieces];
+};
+
+__global__ __launch_bounds__(256) void copy_pieces(Pieces p) {
+    const uint32_t *src = p.src[blockIdx.y];
+    uint32_t *dst = p.dst[blockIdx.y];
+    const uint64_t n = p.n[blockIdx.y], step = (uint64_t)gridDim.x * 256;
+    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += step)
+        dst[i] = src ? src[i] : 0u;
+}
+
 // Outer union: schema = ordered union of the inputs' variables; unbound cells 0.
 std::unique_ptr<tid_table> union_tables(tid_ctx *ctx, const tid_table *const *ts, int k,
                                         int dedupe) {
@@ -911,22 +926,33 @@ std::unique_ptr<tid_table> union_tables(tid_ctx *ctx, const tid_table *const *ts
         out->maxv[c] = m;
     }
     for (int j = 0; j < k; ++j) out->maxv_known &= ts[j]->maxv_known;
-    uint64_t at = 0;
+    Pieces p{};
+    int np = 0;
+    uint64_t at = 0, most = 0;
+    auto flush = [&] {
+        if (!np) return;
+        const unsigned gx = (unsigned)std::min<uint64_t>((most + 1023) / 1024, 1024);
+        hipLaunchKernelGGL(copy_pieces, dim3(gx, np), dim3(256), 0, ctx->stream, p);
+        TID_HIP(hipGetLastError());
+        np = 0;
+        most = 0;
+    };
     for (int j = 0; j < k; ++j) {
         const uint64_t n = ts[j]->nrows;
         if (!n) continue;
         for (size_t c = 0; c < vars.size(); ++c) {
-            int src = -1;
+            const uint32_t *src = nullptr;
             for (int x = 0; x < ts[j]->ncols; ++x)
-                if (ts[j]->vars[x] == vars[c]) src = x;
-            if (src >= 0)
-                TID_HIP(hipMemcpyAsync(out->col[c] + at, ts[j]->col[src], n * 4,
-                                       hipMemcpyDeviceToDevice, ctx->stream));
-            else
-                fill(ctx, out->col[c] + at, n, 0u);
+                if (ts[j]->vars[x] == vars[c]) src = ts[j]->col[x];
+            p.src[np] = src;
+            p.dst[np] = out->col[c] + at;
+            p.n[np] = n;
+            most = std::max(most, n);
+            if (++np == kPieces) flush();
         }
         at += n;
     }
+    flush();
     set_count(out.get(), total);
     if (!dedupe) return out;
     return sort_rows(ctx, out.get(), total, 1);

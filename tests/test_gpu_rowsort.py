@@ -68,3 +68,35 @@ def test_rank_merge(ctx, schema, n, kind):
     t, ot = ctx.table(rows, list(range(len(hi)))), OTable(rows, list(range(len(hi))))
     assert np.array_equal(ctx.sort(t, False).to_numpy(), oracle.sort_rows(ot).rows)
     assert np.array_equal(ctx.sort(t, True).to_numpy(), oracle.distinct(ot).rows)
+
+
+@pytest.mark.parametrize("n", [114689, 116480, 116481, 229377, 300007])
+@pytest.mark.parametrize("schema", ["1 word, all 64 bits", "2 words, a column across them",
+                                    "3 words", "4 words"])
+@pytest.mark.parametrize("rows_each", [1.0, 2.5, 3000])
+def test_distinct_of_merged(ctx, schema, n, rows_each):
+    """DISTINCT in the last merge level: equal rows within a tile, over tile
+    edges and over several tiles."""
+    hi = np.array(SCHEMAS[schema], dtype=np.int64)
+    rng = np.random.default_rng(n)
+    pool = rng.integers(0, hi + 1, (max(1, int(n / rows_each)), hi.size), dtype=np.int64)
+    rows = pool[rng.integers(0, len(pool), n)] if rows_each > 1 else pool
+    rows[0] = hi
+    rows = rows.astype(np.uint32)
+    t, ot = ctx.table(rows, list(range(len(hi)))), OTable(rows, list(range(len(hi))))
+    assert np.array_equal(ctx.sort(t, True).to_numpy(), oracle.distinct(ot).rows)
+
+
+@pytest.mark.parametrize("dedupe", [False, True])
+def test_union_of_many(ctx, dedupe):
+    """More columns than one launch copies; empty tables; variables that only some have."""
+    rng = np.random.default_rng(5)
+    ts, ots = [], []
+    for j in range(90):
+        vs = [[0, 1], [1, 2], [2], [0, 1, 2]][j % 4]
+        rows = rng.integers(1, 50, (int(rng.integers(0, 3)) * j * 7 % 1100, len(vs)),
+                            dtype=np.int64).astype(np.uint32)
+        ts.append(ctx.table(rows, vs))
+        ots.append(OTable(rows, vs))
+    got, want = ctx.union(ts, dedupe), oracle.union(ots, dedupe)
+    assert np.array_equal(got.to_numpy(), want.rows)
