@@ -11,9 +11,11 @@
 //   split    a workgroup puts the IDs of a tile in bucket order in LDS and
 //            writes their lower bits, 16 a time, to the buckets' runs;
 //   count    a workgroup counts equal shares of the split IDs, bucket by
-//            bucket, in LDS bins, and adds the bins to the global ones.
+//            bucket, in LDS bins, and adds the bins to the global ones (a
+//            workgroup a bucket, its bins stored, took 488 us for 234: the
+//            LDS atomics bound it, and equal shares balance them).
 // Bound: the split, which reads 12 bytes a triple and writes 2 a position.
-// 50M triples, 5M subject and object IDs: buckets 173 us, split 489, count 231;
+// 50M triples, 5M subject and object IDs: buckets 173 us, split 328, count 234;
 // with global atomics, an LDS table for the hubs before them, 3653 us.
 #include "compact.hpp"
 
@@ -30,8 +32,7 @@ namespace {
 
 constexpr int kLowBits = 15;
 constexpr uint32_t kBucketIds = 1u << kLowBits;  // 128 KB of bins
-constexpr int kBucketBits = 9;
-constexpr uint32_t kMaxBuckets = 1u << kBucketBits;
+constexpr uint32_t kMaxBuckets = 512;
 constexpr uint32_t kDirectIds = 8192;            // counted without a split
 constexpr int kBlock = 512;
 constexpr int kIPT = 8;
@@ -104,12 +105,15 @@ __global__ __launch_bounds__(kBlock) void count_buckets(IdArgs a) {
     }
 }
 
+// The order of a bucket's IDs does not matter, so an ID's place is what an LDS
+// counter held before it (ballots that keep the triples' order took 489 us for
+// 50M triples).
 __global__ __launch_bounds__(kBlock) void split_ids(IdArgs a) {
     __shared__ uint32_t s_id[kTile];
-    __shared__ uint16_t s_wh[kNW][kMaxBuckets];  // a wave's IDs of a bucket, then those before
-    __shared__ uint32_t s_run[3][kMaxBuckets];   // where the range's next ID of a bucket goes
-    __shared__ uint32_t s_loc[kMaxBuckets];      // a bucket's first ID in the ordered tile
-    __shared__ uint32_t s_off[kMaxBuckets];      // place of ordered ID i: s_off[bucket] + i
+    __shared__ uint32_t s_cnt[kMaxBuckets];     // the tile's IDs of a bucket
+    __shared__ uint32_t s_run[3][kMaxBuckets];  // where the range's next ID of a bucket goes
+    __shared__ uint32_t s_loc[kMaxBuckets];     // a bucket's first ID in the ordered tile
+    __shared__ uint32_t s_off[kMaxBuckets];     // place of ordered ID i: s_off[bucket] + i
     __shared__ uint32_t s_w[kNW];
     const uint32_t tid = threadIdx.x, w = blockIdx.x;
     const int wave = tid / dev::kWave, lane = tid % dev::kWave;
@@ -124,6 +128,7 @@ __global__ __launch_bounds__(kBlock) void split_ids(IdArgs a) {
         for (int y = 0; y < kNW; ++y) before += y < wave ? s_w[y] : 0u;
         return before + incl - v;
     };
+    if (tid < kMaxBuckets) s_cnt[tid] = 0;
 #pragma unroll
     for (int x = 0; x < 3; ++x) {
         if (a.mode[x] != kSplit) continue;
@@ -131,8 +136,8 @@ __global__ __launch_bounds__(kBlock) void split_ids(IdArgs a) {
         const uint32_t base = prefix(in ? a.totals[x][tid] : 0u);
         if (in) s_run[x][tid] = base + a.scan[x][(size_t)w * a.buckets[x] + tid];
     }
+    __syncthreads();
     const uint64_t r0 = (uint64_t)w * a.range, r1 = min(a.n, r0 + a.range);
-    const uint64_t lt = (1ull << lane) - 1ull;
     for (uint64_t t0 = r0; t0 < r1; t0 += kTile) {
         const uint32_t cnt = (uint32_t)min((uint64_t)kTile, r1 - t0);
         uint32_t v[kIPT][3];
@@ -145,41 +150,24 @@ __global__ __launch_bounds__(kBlock) void split_ids(IdArgs a) {
 #pragma unroll
         for (int x = 0; x < 3; ++x) {
             if (a.mode[x] != kSplit) continue;
-            const uint32_t B = a.buckets[x];
-            const int nbits = B > 1 ? 32 - __builtin_clz(B - 1) : 0;
-            for (uint32_t b = lane; b < B; b += dev::kWave) s_wh[wave][b] = 0;
             uint32_t rank[kIPT];
 #pragma unroll
-            for (int u = 0; u < kIPT; ++u) {
-                const bool valid = u * kBlock + tid < cnt;
-                const uint32_t b = v[u][x] >> kLowBits;
-                const uint64_t peers = dev::match_digit<kBucketBits>(b, valid, nbits);
-                const uint32_t before = valid ? s_wh[wave][b] : 0u;
-                rank[u] = before + (uint32_t)__popcll(peers & lt);
-                if (valid && lane == __builtin_ctzll(peers))
-                    s_wh[wave][b] = (uint16_t)(before + (uint32_t)__popcll(peers));
-            }
+            for (int u = 0; u < kIPT; ++u)
+                if (u * kBlock + tid < cnt) rank[u] = atomicAdd(&s_cnt[v[u][x] >> kLowBits], 1u);
             __syncthreads();
-            uint32_t tot = 0;
-            if (tid < B)
-                for (int y = 0; y < kNW; ++y) {
-                    const uint32_t c = s_wh[y][tid];
-                    s_wh[y][tid] = (uint16_t)tot;
-                    tot += c;
-                }
+            const uint32_t tot = tid < a.buckets[x] ? s_cnt[tid] : 0u;
             const uint32_t loc = prefix(tot);
-            if (tid < B) {
+            if (tid < a.buckets[x]) {
                 const uint32_t run = s_run[x][tid];
                 s_loc[tid] = loc;
                 s_off[tid] = run - loc;
                 s_run[x][tid] = run + tot;
+                s_cnt[tid] = 0;
             }
             __syncthreads();
 #pragma unroll
-            for (int u = 0; u < kIPT; ++u) {
-                const uint32_t b = v[u][x] >> kLowBits;
-                if (u * kBlock + tid < cnt) s_id[s_loc[b] + s_wh[wave][b] + rank[u]] = v[u][x];
-            }
+            for (int u = 0; u < kIPT; ++u)
+                if (u * kBlock + tid < cnt) s_id[s_loc[v[u][x] >> kLowBits] + rank[u]] = v[u][x];
             __syncthreads();
 #pragma unroll
             for (int u = 0; u < kIPT; ++u) {
