@@ -429,11 +429,9 @@ int device_cus(tid_ctx *ctx);
 namespace {
 
 constexpr int kBigBlock = 256;
-constexpr int kBigIPT = 4;
-constexpr uint64_t kBigTile = (uint64_t)kBigBlock * kBigIPT;
-constexpr int kBigLds = 2048;       // LDS rank table entries (> rows per tile)
+constexpr int kBigIPT = 4, kProbeIPT = 8;  // build and probe rows of a thread,
+constexpr int kFewIPT = 1, kFewProbeIPT = 2;  // and where that leaves the chip idle
 constexpr uint32_t kNoSlot32 = 0xFFFFFFFFu;
-constexpr int kProbeIPT = (int)kProbeTile / kBigBlock;
 
 // index j with base[j] <= x < base[j + 1] (base non-decreasing, base[0] = 0)
 __device__ __forceinline__ int job_of(const uint64_t *base, int J, uint64_t x) {
@@ -449,12 +447,17 @@ __device__ __forceinline__ int job_of(const uint64_t *base, int J, uint64_t x) {
 // Build: R rows, tile by tile from a work counter (tiles of all joins
 // concatenated; tbase = tile prefix per join).  Each row finds or claims its
 // key's slot; ranks within a slot are reserved per tile through an LDS table
-// (one global atomic per slot present in the tile, not per row).
+// (one global atomic per slot present in the tile, not per row).  IPT rows a
+// thread: one where that leaves workgroups for the whole chip, since a thread
+// claims its rows' slots one after the other (1,800 rows 18 us with four).
+template <int IPT>
 __global__ __launch_bounds__(kBigBlock) void big_insert(const BigCount *jobs, int J,
                                                         const uint64_t *tbase, uint64_t ntiles,
                                                         uint32_t *work, uint64_t *slots,
                                                         uint32_t *cnt, uint32_t *slot_of,
                                                         uint32_t *rank_of) {
+    constexpr uint64_t kTile = (uint64_t)kBigBlock * IPT;
+    constexpr int kBigLds = 2 * (int)kTile;  // rank table entries (> rows of a tile)
     __shared__ uint32_t s_slot[kBigLds], s_cnt[kBigLds], s_base[kBigLds];
     __shared__ uint64_t s_tile;
     for (int x = threadIdx.x; x < kBigLds; x += kBigBlock) {
@@ -469,10 +472,10 @@ __global__ __launch_bounds__(kBigBlock) void big_insert(const BigCount *jobs, in
         if (t >= ntiles) break;
         const int j = job_of(tbase, J, t);
         const BigCount &b = jobs[j];
-        const uint64_t r0 = (t - tbase[j]) * kBigTile;
-        uint32_t h[kBigIPT], e[kBigIPT], local[kBigIPT];
+        const uint64_t r0 = (t - tbase[j]) * kTile;
+        uint32_t h[IPT], e[IPT], local[IPT];
 #pragma unroll
-        for (int u = 0; u < kBigIPT; ++u) {
+        for (int u = 0; u < IPT; ++u) {
             const uint64_t r = r0 + (uint64_t)u * kBigBlock + threadIdx.x;
             if (r >= b.nr) continue;
             const uint32_t key = b.rkey[r];
@@ -507,7 +510,7 @@ __global__ __launch_bounds__(kBigBlock) void big_insert(const BigCount *jobs, in
         }
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < kBigIPT; ++u) {
+        for (int u = 0; u < IPT; ++u) {
             const uint64_t r = r0 + (uint64_t)u * kBigBlock + threadIdx.x;
             if (r >= b.nr) continue;
             slot_of[b.rbase + r] = h[u];
@@ -593,29 +596,32 @@ __device__ __forceinline__ void find_run(const BigCount &b, const uint64_t *slot
 // tile's start in `entries`; their number and the tile's output rows are left
 // for the expansion.  Only rows with output are written, and only the tiles'
 // sums are scanned afterwards: with an offset kept and scanned for every probe
-// row, joins of millions of rows and few matches spent as long on those.
+// row, joins of millions of rows and few matches spent as long on those.  IPT
+// rows a thread, as for big_insert.
+template <int IPT>
 __global__ __launch_bounds__(kBigBlock) void big_probe(const BigCount *jobs, int J,
                                                        const uint64_t *ltile,
                                                        const uint64_t *slots, const uint32_t *cnt,
                                                        const uint64_t *start, BigEntry *entries,
                                                        uint32_t *tcount, uint64_t *ttotal) {
     constexpr int NW = kBigBlock / dev::kWave;
+    constexpr uint64_t kTile = (uint64_t)kBigBlock * IPT;
     __shared__ uint32_t s_m[NW];
     __shared__ uint64_t s_s[NW];
     const uint64_t tile = blockIdx.x;
     const int j = job_of(ltile, J, tile);
     const BigCount &b = jobs[j];
-    const uint64_t l0 = (tile - ltile[j]) * kProbeTile;
-    uint32_t key[kProbeIPT], at[kProbeIPT], len[kProbeIPT];
+    const uint64_t l0 = (tile - ltile[j]) * kTile;
+    uint32_t key[IPT], at[IPT], len[IPT];
 #pragma unroll
-    for (int u = 0; u < kProbeIPT; ++u) {
+    for (int u = 0; u < IPT; ++u) {
         const uint64_t l = l0 + (uint64_t)u * kBigBlock + threadIdx.x;
         key[u] = l < b.nl ? b.lkey[l] : 0u;
     }
     uint32_t mine = 0;
     uint64_t sum = 0;
 #pragma unroll
-    for (int u = 0; u < kProbeIPT; ++u) {
+    for (int u = 0; u < IPT; ++u) {
         const uint64_t l = l0 + (uint64_t)u * kBigBlock + threadIdx.x;
         at[u] = len[u] = 0;
         if (l >= b.nl) continue;
@@ -654,9 +660,9 @@ __global__ __launch_bounds__(kBigBlock) void big_probe(const BigCount *jobs, int
         all_m += s_m[w];
         all_s += s_s[w];
     }
-    BigEntry *e = entries + tile * kProbeTile;
+    BigEntry *e = entries + tile * kTile;
 #pragma unroll
-    for (int u = 0; u < kProbeIPT; ++u) {
+    for (int u = 0; u < IPT; ++u) {
         if (!len[u]) continue;
         e[m++] = BigEntry{(uint32_t)(l0 + (uint64_t)u * kBigBlock + threadIdx.x), at[u], s};
         s += len[u];
@@ -675,7 +681,8 @@ __global__ void big_totals(const uint64_t *ltile, int J, const uint64_t *toff, u
 // one output row per thread: its join, its probe tile (a search of the tiles'
 // offsets), its entry in it, the k-th partner of that entry's row
 __global__ void big_expand(const BigExpand *jobs, int J, const uint64_t *obase, uint64_t ntotal,
-                           const uint64_t *toff, const uint32_t *tcount, const BigEntry *entries) {
+                           const uint64_t *toff, const uint32_t *tcount, const BigEntry *entries,
+                           uint32_t tile) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; g < ntotal; g += stride) {
         const int j = job_of(obase, J, g);
@@ -689,7 +696,7 @@ __global__ void big_expand(const BigExpand *jobs, int J, const uint64_t *obase, 
             else hi = mid;
         }
         const uint64_t in = x - toff[lo];
-        const BigEntry *e = entries + lo * kProbeTile;
+        const BigEntry *e = entries + lo * tile;
         uint32_t p = 0, q = tcount[lo];  // last entry with pre <= in
         while (q - p > 1) {
             const uint32_t mid = (p + q) >> 1;
@@ -766,11 +773,20 @@ void flush_big_count(tid_ctx *ctx, std::vector<BigJoinReq> &reqs,
     std::vector<BigCount> jobs(J);
     std::vector<uint64_t> tbase(J + 1, 0), rbase(J + 1, 0), ltile(J + 1, 0);
     auto arena = std::make_shared<BigArena>();
-    uint64_t S = 0;
+    uint64_t S = 0, build = 0, probe = 0;
+    for (const BigJoinReq &r : reqs) {
+        if (r.c.nr < kSortBuildRows) build += r.c.nr;
+        probe += r.c.nl;
+    }
+    const uint64_t chip = 4ull * (uint64_t)device_cus(ctx) * kBigBlock;  // threads at a time
+    const bool few_build = build <= chip * kFewIPT, few_probe = probe <= chip * kFewProbeIPT;
+    const uint64_t btile = (uint64_t)kBigBlock * (few_build ? kFewIPT : kBigIPT);
+    const uint64_t ptile = (uint64_t)kBigBlock * (few_probe ? kFewProbeIPT : kProbeIPT);
+    arena->tile = (uint32_t)ptile;
     for (int j = 0; j < J; ++j) {
         BigCount &b = jobs[j];
         b = reqs[j].c;
-        ltile[j + 1] = ltile[j] + (b.nl + kProbeTile - 1) / kProbeTile;
+        ltile[j + 1] = ltile[j] + (b.nl + ptile - 1) / ptile;
         rbase[j + 1] = rbase[j];
         tbase[j + 1] = tbase[j];
         if (b.nr >= kSortBuildRows) {
@@ -784,7 +800,7 @@ void flush_big_count(tid_ctx *ctx, std::vector<BigJoinReq> &reqs,
         S += cap;
         b.rbase = rbase[j];
         rbase[j + 1] += b.nr;
-        tbase[j + 1] += (b.nr + kBigTile - 1) / kBigTile;
+        tbase[j + 1] += (b.nr + btile - 1) / btile;
     }
     const uint64_t NR = rbase[J], LT = ltile[J], T = tbase[J];
     TID_REQUIRE(S < (1ull << 32) && NR < (1ull << 32), TID_E_UNSUPPORTED,
@@ -801,7 +817,7 @@ void flush_big_count(tid_ctx *ctx, std::vector<BigJoinReq> &reqs,
                  o_rb = take((J + 1) * 8), o_lt = take((J + 1) * 8), o_work = take(8),
                  o_slots = take(S * 8), o_cnt = take(S * 4), o_start = take((S + 1) * 8),
                  o_slotof = take(NR * 4), o_rank = take(NR * 4), o_rows = take(NR * 4),
-                 o_entries = take(LT * kProbeTile * sizeof(BigEntry)), o_tcount = take(LT * 4),
+                 o_entries = take(LT * ptile * sizeof(BigEntry)), o_tcount = take(LT * 4),
                  o_ttotal = take(LT * 8), o_toff = take((LT + 1) * 8), o_tot = take(J * 8);
     arena->buf = DevBuf(ctx, off);
     char *base = arena->buf.get<char>();
@@ -835,9 +851,10 @@ void flush_big_count(tid_ctx *ctx, std::vector<BigJoinReq> &reqs,
     if (NR) {
         const unsigned workers = (unsigned)std::max<uint64_t>(
             1, std::min<uint64_t>(T, 4ull * (uint64_t)device_cus(ctx)));
-        hipLaunchKernelGGL(big_insert, dim3(workers), dim3(kBigBlock), 0, ctx->stream, dj, J,
-                           dtb, T, reinterpret_cast<uint32_t *>(base + o_work), slots, cnt,
-                           slot_of, rank_of);
+        hipLaunchKernelGGL(few_build ? big_insert<kFewIPT> : big_insert<kBigIPT>, dim3(workers),
+                           dim3(kBigBlock), 0, ctx->stream, dj, J, dtb, T,
+                           reinterpret_cast<uint32_t *>(base + o_work), slots, cnt, slot_of,
+                           rank_of);
         TID_HIP(hipGetLastError());
         exclusive_scan_async(ctx, cnt, S, start);
         hipLaunchKernelGGL(big_fill, dim3(grid_cap(NR)), dim3(256), 0, ctx->stream, dj, J, drb,
@@ -845,8 +862,9 @@ void flush_big_count(tid_ctx *ctx, std::vector<BigJoinReq> &reqs,
         TID_HIP(hipGetLastError());
     }
     if (LT) {
-        hipLaunchKernelGGL(big_probe, dim3((unsigned)LT), dim3(kBigBlock), 0, ctx->stream, dj, J,
-                           dlt, slots, cnt, start, arena->entries, arena->tcount, ttotal);
+        hipLaunchKernelGGL(few_probe ? big_probe<kFewProbeIPT> : big_probe<kProbeIPT>,
+                           dim3((unsigned)LT), dim3(kBigBlock), 0, ctx->stream, dj, J, dlt, slots,
+                           cnt, start, arena->entries, arena->tcount, ttotal);
         TID_HIP(hipGetLastError());
     }
     scan_words_async(ctx, ttotal, LT, arena->toff);
@@ -888,7 +906,7 @@ void flush_big_expand(tid_ctx *ctx, const BigArena &arena, std::vector<BigExpand
         hipLaunchKernelGGL(big_expand, dim3(grid_cap(total)), dim3(256), 0, ctx->stream,
                            reinterpret_cast<const BigExpand *>(d), J,
                            reinterpret_cast<const uint64_t *>(d + bytes_jobs), total, arena.toff,
-                           arena.tcount, arena.entries);
+                           arena.tcount, arena.entries, arena.tile);
     TID_HIP(hipGetLastError());
     jobs.clear();
     bs.big_out_total = 0;

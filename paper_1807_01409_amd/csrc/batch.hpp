@@ -79,8 +79,6 @@ constexpr int kBigCols = TID_MAX_COLS;
 // tid_join: 2^23 rows, 2^24 slots)
 constexpr uint64_t kBigBuildMax = 1ull << 23;
 
-constexpr uint64_t kProbeTile = 2048;   // probe rows of a workgroup
-
 // "l" is the probe side and "r" the build side here (the build is the
 // smaller table, which may be the join's L or R); eq_l / eq_r are columns of
 // the probe / build side that must agree (the join's other shared variables).
@@ -124,7 +122,8 @@ struct BigExpand {
 // The device state of one round's larger joins, kept until their expansion.
 struct BigArena {
     DevBuf buf;
-    BigEntry *entries = nullptr;   // kProbeTile per probe tile
+    BigEntry *entries = nullptr;   // `tile` per probe tile
+    uint32_t tile = 0;             // probe rows of a workgroup
     uint32_t *tcount = nullptr;    // entries of each tile
     uint64_t *toff = nullptr;      // per tile: output rows of all tiles before it
     std::vector<DevBuf> builds;    // sorted build sides

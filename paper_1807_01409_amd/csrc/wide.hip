@@ -59,6 +59,7 @@ struct WideOut {
 struct WideSeg {
     uint64_t vbase, pbase;
     uint32_t len, p;
+    uint32_t bucket;  // its patterns, as a word of WideArgs::bucket
 };
 
 struct WideArgs {
@@ -68,7 +69,7 @@ struct WideArgs {
     uint32_t nseg;
     uint64_t n;                 // triples (graph pass) or virtual positions (segment pass)
     const WidePat *pats;      // k
-    const uint32_t *bucket;   // kWidePreds words: start << 12 | len
+    const uint32_t *bucket;   // graph pass: kWidePreds words, start << 12 | len
     const uint16_t *ids;      // k pattern ids grouped by predicate
     const WideOut *outs;      // k
     uint64_t **counts_out;    // k device row-count words
@@ -118,7 +119,8 @@ __device__ __forceinline__ void wide_setup(const WideArgs &a, WidePat *s_pat, ui
         s_pat[i] = a.pats[i];
         s_ids[i] = a.ids[i];
     }
-    for (uint32_t p = threadIdx.x; p < kWidePreds; p += blockDim.x) s_bucket[p] = a.bucket[p];
+    if (a.bucket)
+        for (uint32_t p = threadIdx.x; p < kWidePreds; p += blockDim.x) s_bucket[p] = a.bucket[p];
 }
 
 // Walk the calling wave's sub-range in triple order.  For every match the
@@ -149,10 +151,12 @@ __device__ __forceinline__ void wide_walk(const WideArgs &a, const WidePat *s_pa
     uint32_t sg = SLICE && r0 < r1 ? wide_seg_of(a, r0) : 0u;
     for (uint64_t t0 = r0; t0 < r1; t0 += kWideUnit) {
         WTri t[kWideIPT];
+        uint32_t bucket = 0;
         if (SLICE) {
             while (sg + 1 < a.nseg && a.segs[sg + 1].vbase <= t0) ++sg;
             const WideSeg sgm = a.segs[sg];
             const uint64_t off = t0 - sgm.vbase;
+            bucket = sgm.bucket;
 #pragma unroll
             for (int it = 0; it < kWideIPT; ++it) {
                 const uint64_t l = off + (uint64_t)it * dev::kWave + lane;
@@ -181,7 +185,8 @@ __device__ __forceinline__ void wide_walk(const WideArgs &a, const WidePat *s_pa
 #pragma unroll
         for (int it = 0; it < kWideIPT; ++it) {
             const uint32_t p = t[it].v[1];
-            const uint32_t b = (p > 0 && p < kWidePreds) ? s_bucket[p] : 0u;
+            const uint32_t b = SLICE ? (p ? bucket : 0u)
+                                     : (p > 0 && p < kWidePreds) ? s_bucket[p] : 0u;
             const uint32_t start = b >> 12, len = b & 0xFFFu;
             for (uint32_t c = 0; dev::ballot(c < len); ++c) {
                 const bool has = c < len;
@@ -216,7 +221,7 @@ __device__ __forceinline__ void wide_walk(const WideArgs &a, const WidePat *s_pa
     }
 }
 
-// LDS layout: patterns (k), predicate buckets, pattern ids (k, padded to
+// LDS layout: patterns (k), predicate buckets (graph pass), pattern ids (k, padded to
 // words), then one running counter per (wave, pattern)
 struct WideLds {
     WidePat *pat;
@@ -225,11 +230,11 @@ struct WideLds {
     uint32_t *run;
 };
 
-__device__ __forceinline__ WideLds wide_lds(uint32_t *lds, int k) {
+__device__ __forceinline__ WideLds wide_lds(uint32_t *lds, int k, bool slice) {
     WideLds l;
     l.pat = reinterpret_cast<WidePat *>(lds);
     l.bucket = reinterpret_cast<uint32_t *>(l.pat + k);
-    l.ids = reinterpret_cast<uint16_t *>(l.bucket + kWidePreds);
+    l.ids = reinterpret_cast<uint16_t *>(l.bucket + (slice ? 0 : kWidePreds));
     l.run = reinterpret_cast<uint32_t *>(l.ids + ((k + 1) & ~1));
     return l;
 }
@@ -237,7 +242,7 @@ __device__ __forceinline__ WideLds wide_lds(uint32_t *lds, int k) {
 template <bool SLICE>
 __global__ __launch_bounds__(kWideBlock) void wide_count(WideArgs a, uint32_t *flags) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-    const WideLds l = wide_lds(lds, a.k);
+    const WideLds l = wide_lds(lds, a.k, SLICE);
     WidePat *s_pat = l.pat;
     uint32_t *s_bucket = l.bucket;
     uint16_t *s_ids = l.ids;
@@ -290,7 +295,7 @@ __global__ __launch_bounds__(kColBlock) void wide_offsets(WideArgs a) {
 template <bool SLICE>
 __global__ __launch_bounds__(kWideBlock) void wide_write(WideArgs a, uint32_t *flags) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-    const WideLds l = wide_lds(lds, a.k);
+    const WideLds l = wide_lds(lds, a.k, SLICE);
     WidePat *s_pat = l.pat;
     uint32_t *s_bucket = l.bucket;
     uint16_t *s_ids = l.ids;
@@ -340,8 +345,8 @@ static WidePat compile_wide(const tid_pattern &p) {
     return w;
 }
 
-static size_t wide_lds_bytes(int k) {
-    return sizeof(WidePat) * (size_t)k + 4 * kWidePreds + 2 * (size_t)((k + 1) & ~1) +
+static size_t wide_lds_bytes(int k, bool slice) {
+    return sizeof(WidePat) * (size_t)k + (slice ? 0 : 4 * kWidePreds) + 2 * (size_t)((k + 1) & ~1) +
            4 * (size_t)kWideNW * (size_t)k;
 }
 
@@ -396,7 +401,6 @@ static void wide_pass(tid_ctx *ctx, WideSource src, const tid_pattern *pats, int
     std::vector<WidePat> wp(k);
     std::vector<WideOut> wo(k);
     std::vector<uint64_t *> wc(k);
-    std::vector<std::vector<uint16_t>> by_pred(kWidePreds);
     for (int j = 0; j < k; ++j) {
         TID_REQUIRE(wide_eligible(pats[j]), TID_E_INTERNAL, "wide pass: pattern not eligible");
         wp[j] = compile_wide(pats[j]);
@@ -409,17 +413,22 @@ static void wide_pass(tid_ctx *ctx, WideSource src, const tid_pattern *pats, int
         for (int c = 0; c < 3; ++c) wo[j].col[c] = c < outs[j]->ncols ? outs[j]->col[c] : nullptr;
         wo[j].cap = outs[j]->cap;
         wc[j] = outs[j]->d_count;
-        by_pred[pats[j].p].push_back((uint16_t)j);
     }
+    // pattern ids grouped by predicate, in order; a segment pass keeps a
+    // predicate's group with its segment, a graph pass in a table
+    std::vector<uint16_t> ids(k);
+    for (int j = 0; j < k; ++j) ids[j] = (uint16_t)j;
+    std::stable_sort(ids.begin(), ids.end(),
+                     [&](uint16_t x, uint16_t y) { return pats[x].p < pats[y].p; });
     std::vector<uint32_t> bucket(kWidePreds, 0);
-    std::vector<uint16_t> ids;
-    for (uint32_t p = 0; p < kWidePreds; ++p) {
-        if (by_pred[p].empty()) continue;
-        bucket[p] = ((uint32_t)ids.size() << 12) | (uint32_t)by_pred[p].size();
-        ids.insert(ids.end(), by_pred[p].begin(), by_pred[p].end());
+    for (int i = 0, e; i < k; i = e) {
+        const uint32_t p = pats[ids[i]].p;
+        for (e = i; e < k && pats[ids[e]].p == p; ++e) {}
+        bucket[p] = ((uint32_t)i << 12) | (uint32_t)(e - i);
     }
+    for (WideSeg &sg : src.segs) sg.bucket = bucket[sg.p];
     // the grid: one sub-range per resident wave
-    const size_t lds = wide_lds_bytes(k);
+    const size_t lds = wide_lds_bytes(k, slice);
     const void *count_fn = slice ? (const void *)wide_count<true> : (const void *)wide_count<false>;
     const void *write_fn = slice ? (const void *)wide_write<true> : (const void *)wide_write<false>;
     if (slice) set_wide_lds_limit<true>();
@@ -439,7 +448,7 @@ static void wide_pass(tid_ctx *ctx, WideSource src, const tid_pattern *pats, int
         double total = 0;
         std::vector<double> unit_cost(src.segs.size());
         for (size_t x = 0; x < src.segs.size(); ++x) {
-            unit_cost[x] = (double)unit * (1.0 + (double)by_pred[src.segs[x].p].size());
+            unit_cost[x] = (double)unit * (1.0 + (double)(src.segs[x].bucket & 0xFFFu));
             total += unit_cost[x] * (double)((src.segs[x].len + unit - 1) / unit);
         }
         wb.assign(W + 1, src.n);
@@ -464,7 +473,7 @@ static void wide_pass(tid_ctx *ctx, WideSource src, const tid_pattern *pats, int
 
     // tables of constants, in one device block
     const size_t nseg = src.segs.size();
-    const size_t b_pats = align_up(sizeof(WidePat) * k), b_bucket = align_up(4 * kWidePreds),
+    const size_t b_pats = align_up(sizeof(WidePat) * k), b_bucket = slice ? 0 : align_up(4 * kWidePreds),
                  b_ids = align_up(2 * (size_t)k), b_outs = align_up(sizeof(WideOut) * k),
                  b_cnts = align_up(8 * (size_t)k), b_tot = align_up(8 * (size_t)k),
                  b_segs = align_up(sizeof(WideSeg) * std::max<size_t>(nseg, 1)),
@@ -473,7 +482,7 @@ static void wide_pass(tid_ctx *ctx, WideSource src, const tid_pattern *pats, int
     std::vector<char> host(consts, 0);
     char *h = host.data();
     std::memcpy(h, wp.data(), sizeof(WidePat) * k);
-    std::memcpy(h + b_pats, bucket.data(), 4 * kWidePreds);
+    if (!slice) std::memcpy(h + b_pats, bucket.data(), 4 * kWidePreds);
     std::memcpy(h + b_pats + b_bucket, ids.data(), 2 * (size_t)k);
     std::memcpy(h + b_pats + b_bucket + b_ids, wo.data(), sizeof(WideOut) * k);
     std::memcpy(h + b_pats + b_bucket + b_ids + b_outs, wc.data(), 8 * (size_t)k);
@@ -494,7 +503,7 @@ static void wide_pass(tid_ctx *ctx, WideSource src, const tid_pattern *pats, int
     a.wbound = wb.empty() ? nullptr : reinterpret_cast<const uint64_t *>(d + at_wb);
     a.n = src.n;
     a.pats = reinterpret_cast<const WidePat *>(d);
-    a.bucket = reinterpret_cast<const uint32_t *>(d + b_pats);
+    a.bucket = slice ? nullptr : reinterpret_cast<const uint32_t *>(d + b_pats);
     a.ids = reinterpret_cast<const uint16_t *>(d + b_pats + b_bucket);
     a.outs = reinterpret_cast<const WideOut *>(d + b_pats + b_bucket + b_ids);
     a.counts_out = reinterpret_cast<uint64_t **>(d + b_pats + b_bucket + b_ids + b_outs);

@@ -66,6 +66,16 @@ def test_kinds(ctx, keys, nl, nr):
         assert np.array_equal(got, want), kind
 
 
+@pytest.mark.parametrize("nl,nr", [(511, 255), (513, 257), (1 << 19, 1 << 18),
+                                   ((1 << 19) + 1, (1 << 18) + 1)])
+def test_rows_of_a_thread(ctx, nl, nr):
+    """The last sizes with few rows to a thread, and the first with more."""
+    L, R = tables(nl, nr, KEYS["dense"], nl + nr)
+    got = ctx.join(ctx.table(L, [0, 1]), 1, ctx.table(R, [1, 2]), 0, 1).to_numpy()
+    want = oracle.join(OTable(L, [0, 1]), 1, OTable(R, [1, 2]), 0, "sortmerge").rows
+    assert np.array_equal(got, want)
+
+
 def test_known_bounds_and_shared_variables(ctx):
     """Joins of scans (column bounds known), by index and by hash, and a
     natural join on two variables, in a batch."""
