@@ -107,23 +107,38 @@ __device__ __forceinline__ void lds_put(uint64_t *s, uint32_t stride, uint32_t i
     for (int x = 0; x < W; ++x) s[x * stride + i] = k.w[x];
 }
 
-template <int W>
-__device__ __forceinline__ Key<W> pack_row(const RowJob &p, uint32_t i) {
-    Key<W> k;
+// kVT rows of a tile.  Which rows a thread starts with does not matter: in a
+// whole tile they are BLOCK apart, so that a column's loads are coalesced; in
+// the last one they are consecutive, so that the rows fill the first threads.
+// A column's loads are in flight together (a row after the other they were most
+// of a small tile's time: 15.8 us for small tiles of two columns, now 14.3).
+// Past the end the largest key (a row holding that key is the same key, so
+// either may be written).
+template <int W, int BLOCK>
+__device__ __forceinline__ void pack_rows(const RowJob &p, uint32_t t0, uint32_t cnt,
+                                          Key<W> (&k)[kVT]) {
+    const bool whole = cnt == (uint32_t)BLOCK * kVT;
+    const uint32_t i0 = whole ? threadIdx.x : threadIdx.x * kVT, step = whole ? BLOCK : 1;
 #pragma unroll
-    for (int x = 0; x < W; ++x) k.w[x] = 0;
+    for (int v = 0; v < kVT; ++v)
+#pragma unroll
+        for (int x = 0; x < W; ++x) k[v].w[x] = i0 + v * step < cnt ? 0ull : ~0ull;
     for (int c = 0; c < p.ncols; ++c) {
         if (p.width[c] == 0) continue;
-        const uint64_t v = gload(p.in[c] + i);
+        const uint32_t *col = p.in[c] + t0;
         const int lw = p.word[c], sh = p.shift[c];
         const bool over = sh + p.width[c] > 64;
+        uint32_t val[kVT];
 #pragma unroll
-        for (int x = 0; x < W; ++x) {  // static indices: the key stays in registers
-            if (W - 1 - x == lw) k.w[x] |= v << sh;
-            if (W - 1 - x == lw + 1 && over) k.w[x] |= v >> (64 - sh);
-        }
+        for (int v = 0; v < kVT; ++v) val[v] = gload(col + min(i0 + v * step, cnt - 1));
+#pragma unroll
+        for (int v = 0; v < kVT; ++v)
+#pragma unroll
+            for (int x = 0; x < W; ++x) {  // static indices: the keys stay in registers
+                if (W - 1 - x == lw) k[v].w[x] |= (uint64_t)val[v] << sh;
+                if (W - 1 - x == lw + 1 && over) k[v].w[x] |= (uint64_t)val[v] >> (64 - sh);
+            }
     }
-    return k;
 }
 
 // column c of the key whose word x (most significant first) is word(x)
@@ -220,19 +235,8 @@ __device__ __forceinline__ void tile_sort_body(const RowJob &p, uint32_t tile) {
     const uint32_t tid = threadIdx.x;
     const uint32_t t0 = tile * TILE;
     const uint32_t cnt = min(TILE, p.n - t0);
-    // the tile's rows in order, kVT to a thread; past the end the largest key
-    // (a row holding that key is the same key, so either may be written)
     Key<W> k[kVT];
-#pragma unroll
-    for (int v = 0; v < kVT; ++v) {
-        const uint32_t i = tid * kVT + v;
-        if (i < cnt) {
-            k[v] = pack_row<W>(p, t0 + i);
-        } else {
-#pragma unroll
-            for (int x = 0; x < W; ++x) k[v].w[x] = ~0ull;
-        }
-    }
+    pack_rows<W, BLOCK>(p, t0, cnt, k);
 #pragma unroll
     for (int r = 0; r < kVT; ++r)  // odd-even transposition
 #pragma unroll
