@@ -678,34 +678,91 @@ __global__ void big_totals(const uint64_t *ltile, int J, const uint64_t *toff, u
         tot[j] = toff[ltile[j + 1]] - toff[ltile[j]];
 }
 
-// one output row per thread: its join, its probe tile (a search of the tiles'
-// offsets), its entry in it, the k-th partner of that entry's row
-__global__ void big_expand(const BigExpand *jobs, int J, const uint64_t *obase, uint64_t ntotal,
-                           const uint64_t *toff, const uint32_t *tcount, const BigEntry *entries,
-                           uint32_t tile) {
+// the last i of [lo, hi) with v(i) <= x (v does not fall; v(lo) <= x): the 64
+// lanes of a wave probe evenly spaced places, a ballot keeps the part that
+// holds it
+template <class V>
+__device__ __forceinline__ uint64_t wave_last(uint64_t lo, uint64_t hi, uint64_t x, const V &v) {
+    while (hi - lo > 1) {  // the same for every lane
+        const uint64_t step = (hi - lo + dev::kWave - 1) / dev::kWave;
+        const uint64_t m = lo + (uint64_t)dev::lane_id() * step;
+        const uint64_t c = (uint64_t)__popcll(dev::ballot(m < hi && v(m) <= x));
+        lo += (c - 1) * step;
+        hi = min(hi, lo + step);
+    }
+    return lo;
+}
+
+// One output row per thread.  A wave finds the join, the probe tile and the
+// entry of its first row with 64-way searches; its other rows in that tile are
+// of the next 63 entries at most, one of which a lane loads, and a row finds its
+// entry among the lanes.  Rows of later tiles search by themselves, as all do
+// where tiles put out few rows (DENSE false).  With every row searching, 24
+// dependent reads, the seven expansions of a batch of 256 queries took 595 us,
+// now 418.
+template <bool DENSE>
+__global__ __launch_bounds__(256) void big_expand(const BigExpand *jobs, int J,
+                                                  const uint64_t *obase, uint64_t ntotal,
+                                                  const uint64_t *toff, const uint32_t *tcount,
+                                                  const BigEntry *entries, uint32_t tile) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; g < ntotal; g += stride) {
-        const int j = job_of(obase, J, g);
+    const uint32_t lane = (uint32_t)dev::lane_id();
+    for (uint64_t g0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x - lane; g0 < ntotal;
+         g0 += stride) {
+        const uint64_t g = g0 + lane;
+        uint32_t j = 0, a = 0;
+        uint64_t rows = 0, l = 0, k = 0;  // rows: how many of the wave's are found here
+        if (DENSE) {
+            j = (uint32_t)wave_last(0, J, g0, [&](uint64_t i) { return obase[i]; });
+            const uint64_t x0 = toff[jobs[j].tile0] + (g0 - jobs[j].obase);
+            const uint64_t t = wave_last(jobs[j].tile0, jobs[j].tile1, x0,
+                                         [&](uint64_t i) { return toff[i]; });
+            const uint64_t in0 = x0 - toff[t];
+            rows = toff[t + 1] - x0;
+            const BigEntry *e = entries + t * tile;
+            const uint32_t n = tcount[t];
+            const uint32_t p0 =
+                (uint32_t)wave_last(0, n, in0, [&](uint64_t i) { return e[i].pre; });
+            BigEntry mine{0, 0, 0};
+            uint32_t first = dev::kWave;  // the entry's first output row, from the wave's
+            if (p0 + lane < n) {
+                mine = e[p0 + lane];
+                first = mine.pre <= in0 ? 0u : (uint32_t)min(mine.pre - in0, (uint64_t)dev::kWave);
+            }
+            uint32_t from = 0;  // the last lane whose entry starts at or before this row
+#pragma unroll
+            for (uint32_t step = dev::kWave / 2; step; step >>= 1) {
+                const uint32_t s = __shfl(first, (int)(from + step), dev::kWave);
+                if (s <= lane) from += step;
+            }
+            l = __shfl(mine.row, (int)from, dev::kWave);
+            a = __shfl(mine.at, (int)from, dev::kWave);
+            k = in0 + lane - __shfl(mine.pre, (int)from, dev::kWave);
+        }
+        if (g >= ntotal) continue;
+        if (lane >= rows) {
+            j = (uint32_t)job_of(obase, J, g);
+            const uint64_t x = toff[jobs[j].tile0] + (g - jobs[j].obase);
+            uint64_t lo = jobs[j].tile0, hi = jobs[j].tile1;  // last tile with toff <= x
+            while (hi - lo > 1) {
+                const uint64_t mid = (lo + hi) >> 1;
+                if (toff[mid] <= x) lo = mid;
+                else hi = mid;
+            }
+            const uint64_t in = x - toff[lo];
+            const BigEntry *f = entries + lo * tile;
+            uint32_t p = 0, q = tcount[lo];  // last entry with pre <= in
+            while (q - p > 1) {
+                const uint32_t mid = (p + q) >> 1;
+                if (f[mid].pre <= in) p = mid;
+                else q = mid;
+            }
+            l = f[p].row;
+            a = f[p].at;
+            k = in - f[p].pre;
+        }
         const BigExpand &b = jobs[j];
         const uint64_t o = g - b.obase;
-        const uint64_t x = toff[b.tile0] + o;
-        uint64_t lo = b.tile0, hi = b.tile1;  // last tile with toff <= x
-        while (hi - lo > 1) {
-            const uint64_t mid = (lo + hi) >> 1;
-            if (toff[mid] <= x) lo = mid;
-            else hi = mid;
-        }
-        const uint64_t in = x - toff[lo];
-        const BigEntry *e = entries + lo * tile;
-        uint32_t p = 0, q = tcount[lo];  // last entry with pre <= in
-        while (q - p > 1) {
-            const uint32_t mid = (p + q) >> 1;
-            if (e[mid].pre <= in) p = mid;
-            else q = mid;
-        }
-        const uint64_t l = e[p].row;
-        const uint32_t a = e[p].at;
-        uint64_t k = in - e[p].pre;
         const bool paired = a != kNoSlot32;
         uint32_t r = 0;
         if (paired && b.neq == 0) {
@@ -902,8 +959,11 @@ void flush_big_expand(tid_ctx *ctx, const BigArena &arena, std::vector<BigExpand
     char *d = bs.keep.back().get<char>();
     TID_HIP(hipMemcpyAsync(d, bs.host_keep.back().data(), bs.host_keep.back().size(),
                            hipMemcpyHostToDevice, ctx->stream));
+    uint64_t tiles = 0;
+    for (const BigExpand &b : jobs) tiles += b.tile1 - b.tile0;
     if (total)
-        hipLaunchKernelGGL(big_expand, dim3(grid_cap(total)), dim3(256), 0, ctx->stream,
+        hipLaunchKernelGGL(total >= 256 * tiles ? big_expand<true> : big_expand<false>,
+                           dim3(grid_cap(total)), dim3(256), 0, ctx->stream,
                            reinterpret_cast<const BigExpand *>(d), J,
                            reinterpret_cast<const uint64_t *>(d + bytes_jobs), total, arena.toff,
                            arena.tcount, arena.entries, arena.tile);
