@@ -13,7 +13,9 @@
 //              "GPU merge path").  A table of one tile is written out here;
 //   rank merge tables of up to 114,688 rows: a launch puts eight runs together
 //              (row_rank_merge);
-//   merge      larger ones: one launch per doubling of the run length: a workgroup
+//   radix      large tables of one-word keys: the radix passes of sort.hip on
+//              the packed keys, then unpacked (radix_better);
+//   merge      other larger ones: one launch per doubling of the run length: a workgroup
 //              produces kMergeTile rows, finds its two diagonals with a
 //              64-way search by a wave each, and merges out of LDS.  The last
 //              level writes the table's columns.
@@ -21,8 +23,8 @@
 // Bound: a level reads and writes 8 W bytes a row from cache or HBM; below
 // about a million rows it is bound by the latency of the diagonal searches
 // and of the launch.  kVT is odd, so that the blocked accesses of a wave's
-// lanes fall on different LDS banks.  Why merge sort and not the LSD radix
-// sort of sort.hip (three launches per 8 key bits, and the rows gathered at
+// lanes fall on different LDS banks.  Why merge sort and not an LSD radix
+// sort of row numbers (three launches per 8 key bits, and the rows gathered at
 // the end): see the sizes measured at rows_mergeable() below.
 #include "batch.hpp"
 #include "compact.hpp"
@@ -32,6 +34,7 @@
 namespace tid {
 
 void exclusive_scan_async(tid_ctx *ctx, const uint32_t *in, uint64_t n, uint64_t *out);
+bool sort_words(tid_ctx *ctx, uint64_t *k0, uint64_t *k1, uint64_t n, int bits);
 
 namespace {
 
@@ -657,6 +660,33 @@ __global__ __launch_bounds__(kMergeBlock) void row_merge_many(const RowJob *jobs
     merge_body<W>(p, tile - p.mtile0, level);
 }
 
+// rows of one-word keys to keys, and sorted keys to columns (radix sort)
+__global__ __launch_bounds__(kMergeBlock) void rows_to_words(RowJob p) {
+    const uint32_t t0 = blockIdx.x * kMergeTile, cnt = min(kMergeTile, p.n - t0);
+    Key<1> k[kVT];
+    pack_rows<1, kMergeBlock>(p, t0, cnt, k);
+    const bool whole = cnt == kMergeTile;
+#pragma unroll
+    for (int v = 0; v < kVT; ++v) {
+        const uint32_t i = whole ? v * kMergeBlock + threadIdx.x : threadIdx.x * kVT + v;
+        if (i < cnt) gstore(p.key[0] + t0 + i, k[v].w[0]);
+    }
+}
+
+__global__ __launch_bounds__(kMergeBlock) void words_to_columns(RowJob p, int from) {
+    const uint32_t t0 = blockIdx.x * kMergeTile, cnt = min(kMergeTile, p.n - t0);
+    const uint64_t *key = p.key[from] + t0;
+    uint64_t k[kVT];
+#pragma unroll
+    for (int v = 0; v < kVT; ++v) k[v] = gload(key + min(v * kMergeBlock + threadIdx.x, cnt - 1));
+    for (int c = 0; c < p.ncols; ++c)
+#pragma unroll
+        for (int v = 0; v < kVT; ++v) {
+            const uint32_t i = v * kMergeBlock + threadIdx.x;
+            if (i < cnt) gstore(p.out[c] + t0 + i, column_of<1>(p, c, [&](int) { return k[v]; }));
+        }
+}
+
 int bits_of(uint32_t v) { return v ? 32 - __builtin_clz(v) : 0; }
 
 // words of a row's packed key, by the columns' bounds
@@ -707,12 +737,35 @@ void allow_lds(tid_ctx *ctx) {
 constexpr uint32_t kFewTiles = 8;
 constexpr uint32_t kRankRows = kSmallTile * kVT * kWays * kWays;  // 114,688
 
+int key_bits(const RowJob &p) {
+    int bits = 0;
+    for (int c = 0; c < p.ncols; ++c) bits += p.width[c];
+    return std::max(1, bits);
+}
+
+// Whether a large table of one-word keys is sorted by the radix passes of
+// sort.hip on the packed keys instead of merge levels: a pass costs about as much
+// as 1.75 levels, whatever the number of rows.  A sort of two columns, merge /
+// radix, in us:
+//     bits (passes)   500,000 rows    1M          2M          4M          16M
+//     30 (3)          143 / 126   172 / 142   229 / 180   364 / 229  1360 /  693
+//     36 (4)          139 / 132   171 / 149   227 / 181   368 / 242  1363 /  697
+//     46 (5)          138 / 160   171 / 183   226 / 237   366 / 309  1359 /  943
+//     54 (6)          139 / 167   171 / 191   226 / 236   366 / 316  1365 /  943
+//     64 (7)          138 / 202   171 / 231   227 / 306   364 / 400  1364 / 1253
+bool radix_better(uint64_t n, int bits) {
+    const int passes = std::min((bits + 8) / 9, (bits + 9) / 10);
+    return n >= (passes <= 4 ? 1ull << 19 : passes <= 6 ? 3ull << 20 : 3ull << 22);
+}
+
 template <int W>
 void sort_one(tid_ctx *ctx, RowJob &p) {
     allow_lds<W>(ctx);
     constexpr size_t lds = (size_t)tile_rows(W) * 8 * W;
     // DISTINCT of rows that fit one large tile is done there
     const bool ranked = p.n <= kRankRows && !(p.distinct && p.n <= tile_rows(W));
+    const int bits = key_bits(p);
+    const bool radix = W == 1 && !ranked && p.levels > 0 && radix_better(p.n, bits);
     if (ranked) {
         p.levels = 0;
         for (uint64_t run = (uint64_t)kSmallTile * kVT; run < p.n; run *= kWays) ++p.levels;
@@ -732,7 +785,20 @@ void sort_one(tid_ctx *ctx, RowJob &p) {
         p.kept = kept.get<uint32_t>();
     }
     int from = p.levels & 1;  // the buffer of the sorted keys
-    if (ranked) {
+    if (radix) {
+        hipLaunchKernelGGL(rows_to_words, dim3(mtiles), dim3(kMergeBlock), 0, ctx->stream, p);
+        TID_HIP(hipGetLastError());
+        from = sort_words(ctx, p.key[0], p.key[1], p.n, bits);
+        if (p.distinct) {
+            hipLaunchKernelGGL(row_keep_firsts<W>, dim3(mtiles), dim3(kMergeBlock), 0,
+                               ctx->stream, p, from);
+            from ^= 1;
+        } else {
+            hipLaunchKernelGGL(words_to_columns, dim3(mtiles), dim3(kMergeBlock), 0, ctx->stream,
+                               p, from);
+        }
+        TID_HIP(hipGetLastError());
+    } else if (ranked) {
         constexpr uint32_t rows = (uint32_t)kSmallTile * kVT;
         hipLaunchKernelGGL((row_tile_sort<W, kSmallTile>), dim3((p.n + rows - 1) / rows),
                            dim3(kSmallTile), (size_t)rows * 8 * W, ctx->stream, p);

@@ -658,6 +658,17 @@ bool radix_sort_pairs(tid_ctx *ctx, uint64_t *k0, uint32_t *v0, uint64_t *k1, ui
     return ps.count & 1;
 }
 
+// Sort of n 64-bit words on bits [0, bits): in k0 if the return value is false,
+// in k1 if true.
+bool sort_words(tid_ctx *ctx, uint64_t *k0, uint64_t *k1, uint64_t n, int bits) {
+    TID_REQUIRE(n >= 1 && n < (1ull << 32) && bits >= 1, TID_E_UNSUPPORTED,
+                "sort: more than 2^32-1 rows");
+    const Passes ps(ctx, n, 0, bits);
+    for (int x = 0; x < ps.count; ++x)
+        ps.run(ctx, WordIn{x & 1 ? k1 : k0}, WordOut{x & 1 ? k0 : k1}, x);
+    return ps.count & 1;
+}
+
 // A column's values in ascending order and their rows (stable), on key bits
 // [0, bits): in (k0, v0) if the return value is false, in (k1, v1) if true.
 bool sort_keys32(tid_ctx *ctx, const uint32_t *col, uint64_t n, int bits, uint32_t *k0,

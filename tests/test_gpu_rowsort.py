@@ -100,3 +100,28 @@ def test_union_of_many(ctx, dedupe):
         ots.append(OTable(rows, vs))
     got, want = ctx.union(ts, dedupe), oracle.union(ots, dedupe)
     assert np.array_equal(got.to_numpy(), want.rows)
+
+
+@pytest.mark.parametrize("n,hi", [
+    ((1 << 19) - 1, [2**15 - 1, 2**15 - 1]),   # the last size that is merged
+    (1 << 19, [2**15 - 1, 2**15 - 1]),         # three radix passes
+    (1 << 19, [1]),                            # one bit
+    (600_011, [2**20 - 1, 0, 2**20 - 1]),      # four passes of ten bits
+    ((3 << 20) + 5, [2**23 - 1, 2**23 - 1]),   # five passes
+])
+@pytest.mark.parametrize("repeat", [False, True])
+def test_radix_of_packed_rows(ctx, n, hi, repeat):
+    rng = np.random.default_rng(n)
+    rows = np.stack([rng.integers(0, h + 1, n, dtype=np.int64) for h in hi], axis=1)
+    if repeat:
+        rows = rows[rng.integers(0, n // 3, n)]
+    rows[-1] = hi
+    rows = rows.astype(np.uint32)
+    key = np.zeros(n, dtype=np.uint64)
+    for c, h in enumerate(hi):
+        key = key << np.uint64(int(h).bit_length()) | rows[:, c].astype(np.uint64)
+    order = np.argsort(key, kind="stable")
+    t = ctx.table(rows, list(range(len(hi))))
+    assert np.array_equal(ctx.sort(t, False).to_numpy(), rows[order])
+    first = np.concatenate([[True], key[order][1:] != key[order][:-1]])
+    assert np.array_equal(ctx.sort(t, True).to_numpy(), rows[order][first])
