@@ -236,13 +236,8 @@ tid_status tid_load(tid_ctx *ctx, const uint32_t *triples, uint64_t n, int src_o
         g->n = n;
         const size_t bytes = (size_t)n * 12;
         g->data = tid::DevBuf(ctx, bytes + 64);
-        if (bytes)
-            TID_HIP(hipMemcpyAsync(g->data.get(), triples, bytes,
-                                   src_on_device ? hipMemcpyDeviceToDevice
-                                                 : hipMemcpyHostToDevice,
-                                   ctx->stream));
         TID_HIP(hipMemsetAsync(g->data.get<char>() + bytes, 0, 64, ctx->stream));
-        tid::build_stats(ctx, g.get());
+        tid::load_triples(ctx, g.get(), triples, src_on_device);
         ctx->sync();
     });
     if (st == TID_OK) *out = g.release();

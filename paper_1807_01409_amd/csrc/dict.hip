@@ -26,6 +26,7 @@
 
 namespace tid {
 
+bool on_this_device(tid_ctx *ctx, const void *p);
 void exclusive_scan_async(tid_ctx *ctx, const uint32_t *in, uint64_t n, uint64_t *out);
 void read_words(tid_ctx *ctx, const std::vector<const uint64_t *> &src, uint64_t *dst);
 
@@ -271,18 +272,19 @@ std::unique_ptr<tid_dict> encode(tid_ctx *ctx, const uint8_t *bytes, uint64_t nb
         TID_HIP(hipStreamSynchronize(ctx->stream));
         return dict;
     }
-    // Inputs on the device: a caller's device buffers are read where they are,
-    // unless rows would be written over them or the offsets are misaligned.
+    // Inputs on the device: buffers on the context's device are read where they
+    // are, unless rows would be written over them or the offsets are misaligned.
     DevBuf bytes_in, off_in;
     Terms in{bytes, offsets, nbytes, m, nullptr, nullptr};
     const auto kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-    if (nbytes && (!on_device || overlap(bytes, nbytes, rows, m * 4))) {
+    if (nbytes && (!on_device || overlap(bytes, nbytes, rows, m * 4) ||
+                   !on_this_device(ctx, bytes))) {
         bytes_in = DevBuf(ctx, nbytes);
         TID_HIP(hipMemcpyAsync(bytes_in.get(), bytes, nbytes, kind, ctx->stream));
         in.bytes = bytes_in.get<const uint8_t>();
     }
     if (!on_device || (uintptr_t)offsets % 8 != 0 ||
-        overlap(offsets, (m + 1) * 8, rows, m * 4)) {
+        overlap(offsets, (m + 1) * 8, rows, m * 4) || !on_this_device(ctx, offsets)) {
         off_in = DevBuf(ctx, (m + 1) * 8);
         TID_HIP(hipMemcpyAsync(off_in.get(), offsets, (m + 1) * 8, kind, ctx->stream));
         in.off = off_in.get<const uint64_t>();

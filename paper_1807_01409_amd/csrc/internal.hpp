@@ -189,12 +189,12 @@ inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a
 namespace tid {
 
 // How many triples hold each ID at one position, on the host: one byte an ID
-// (255: the count is in `big`), and per block of 64 IDs the triples and the
-// `big` entries of all IDs before it.  Nine bits an ID instead of the 64 of a
-// cumulative count, which is what loading a graph waits for: the copy to the
-// host and the first touch of its pages.
+// (255: the count is in `big`), and per block of 256 IDs the triples and the
+// `big` entries of all IDs before it.  Eight and a half bits an ID instead of the
+// 64 of a cumulative count, which is what loading a graph waits for: the copy to
+// the host and the first touch of its pages.
 struct IdCounts {
-    static constexpr uint32_t kBlock = 64;
+    static constexpr uint32_t kBlock = 256;
     static constexpr uint32_t kBig = 255;
     struct Mem {
         std::unique_ptr<uint8_t[]> bytes;   // of every position
@@ -213,8 +213,14 @@ struct IdCounts {
         const uint64_t b = first + id / kBlock;
         uint64_t s = mem->rows[b] - mem->rows[first];
         const uint8_t *c = mem->bytes.get() + b * kBlock;
+        uint32_t sum = 0, nbig = 0;
+        for (uint32_t i = 0; i < id % kBlock; ++i) {
+            sum += c[i];
+            nbig += c[i] == kBig;
+        }
+        s += sum;
         const uint32_t *big = mem->big.get() + mem->nbig[b];
-        for (uint64_t i = 0; i < id % kBlock; ++i) s += c[i] < kBig ? c[i] : *big++;
+        for (uint32_t i = 0; i < nbig; ++i) s += big[i] - kBig;
         return s;
     }
 };
@@ -410,7 +416,7 @@ void read_words(tid_ctx *ctx, const std::vector<const uint64_t *> &src, uint64_t
 // validate and return the schema of a pattern; throws on a malformed pattern
 int pattern_schema(const tid_pattern &p, int32_t *vars, int32_t *src);
 // per-position ID counts, from one pass over the graph, to the host
-void build_stats(tid_ctx *ctx, tid_graph *g);
+void load_triples(tid_ctx *ctx, tid_graph *g, const uint32_t *from, int on_device);
 void check_no_zero(tid_ctx *ctx, const tid_graph *g);
 
 }  // namespace tid

@@ -223,6 +223,78 @@ __global__ __launch_bounds__(kMinMaxBlock) void minmax_kernel(const uint32_t *__
     else if (threadIdx.x < 6) atomicMax(&mm[threadIdx.x], s_mm[threadIdx.x]);
 }
 
+// The same while the triples are copied: one read of them instead of two.  A
+// thread's 16-byte words are a multiple of three words apart, so that each of
+// their four IDs always has the same position.  50M triples: copy 226 us and
+// minmax 142, together 240.
+__global__ __launch_bounds__(kMinMaxBlock) void copy_minmax(const uint4 *__restrict__ src,
+                                                            uint4 *__restrict__ dst, uint64_t n,
+                                                            uint32_t *mm) {
+    __shared__ uint32_t s_mm[6];
+    constexpr int kU = 4;  // words a thread has in flight
+    if (threadIdx.x < 6) s_mm[threadIdx.x] = threadIdx.x < 3 ? 0xFFFFFFFFu : 0u;
+    __syncthreads();
+    uint32_t lo4[4] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi4[4] = {0, 0, 0, 0};
+    auto add = [&](const uint4 &q) {
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+            lo4[y] = min(lo4[y], w[y]);
+            hi4[y] = max(hi4[y], w[y]);
+        }
+    };
+    const uint64_t words = 3 * n, nv = words / 4;
+    const uint64_t stride = (uint64_t)gridDim.x * kMinMaxBlock;  // gridDim: a multiple of 3
+    const uint64_t i0 = (uint64_t)blockIdx.x * kMinMaxBlock + threadIdx.x;
+    uint64_t i = i0;
+    for (; i + (kU - 1) * stride < nv; i += kU * stride) {
+        uint4 q[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) q[u] = src[i + u * stride];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            dst[i + u * stride] = q[u];
+            add(q[u]);
+        }
+    }
+    for (; i < nv; i += stride) {
+        const uint4 q = src[i];
+        dst[i] = q;
+        add(q);
+    }
+    uint32_t lo[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi[3] = {0, 0, 0};
+    auto put = [&](uint32_t pos, uint32_t l, uint32_t h) {
+#pragma unroll
+        for (uint32_t x = 0; x < 3; ++x)
+            if (x == pos) {
+                lo[x] = min(lo[x], l);
+                hi[x] = max(hi[x], h);
+            }
+    };
+#pragma unroll
+    for (int y = 0; y < 4; ++y) put((uint32_t)((i0 + y) % 3), lo4[y], hi4[y]);  // 4 i + y mod 3
+    if (i0 < words - 4 * nv) {  // up to three IDs past the last whole word
+        const uint64_t w = 4 * nv + i0;
+        const uint32_t v = reinterpret_cast<const uint32_t *>(src)[w];
+        reinterpret_cast<uint32_t *>(dst)[w] = v;
+        put((uint32_t)(w % 3), v, v);
+    }
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+        for (int d = 32; d >= 1; d >>= 1) {
+            lo[x] = min(lo[x], (uint32_t)__shfl_xor((int)lo[x], d, 64));
+            hi[x] = max(hi[x], (uint32_t)__shfl_xor((int)hi[x], d, 64));
+        }
+        if (dev::lane_id() == 0) {
+            atomicMin(&s_mm[x], lo[x]);
+            atomicMax(&s_mm[3 + x], hi[x]);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) atomicMin(&mm[threadIdx.x], s_mm[threadIdx.x]);
+    else if (threadIdx.x < 6) atomicMax(&mm[threadIdx.x], s_mm[threadIdx.x]);
+}
+
 __global__ void init_minmax(uint32_t *mm) {
     if (threadIdx.x < 3) mm[threadIdx.x] = 0xFFFFFFFFu;
     else if (threadIdx.x < 6) mm[threadIdx.x] = 0u;
@@ -307,20 +379,28 @@ __global__ __launch_bounds__(kHistBlock) void hist3_kernel(const uint32_t *__res
 }
 
 // One byte a count (kBig: the count goes to the list of large ones), and per
-// block of 64 IDs (a wave) its triples and its large counts.
+// block of IDs (a wave each) its triples and its large counts.
+constexpr uint32_t kBlockWaves = IdCounts::kBlock / dev::kWave;  // steps of a wave
+
 __global__ void pack_counts(const uint32_t *__restrict__ bins, uint64_t nblocks, uint8_t *bytes,
                             uint32_t *rows, uint32_t *nbig) {
     const int lane = dev::lane_id();
     const uint64_t waves = (uint64_t)gridDim.x * blockDim.x / dev::kWave;
     for (uint64_t b = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / dev::kWave; b < nblocks;
          b += waves) {
-        const uint32_t c = bins[b * dev::kWave + lane];
-        bytes[b * dev::kWave + lane] = (uint8_t)min(c, IdCounts::kBig);
-        const uint64_t m = dev::ballot(c >= IdCounts::kBig);
-        const uint32_t sum = dev::wave_sum(c);
+        uint32_t sum = 0, big = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < kBlockWaves; ++u) {
+            const uint64_t i = b * IdCounts::kBlock + u * dev::kWave + lane;
+            const uint32_t c = bins[i];
+            bytes[i] = (uint8_t)min(c, IdCounts::kBig);
+            sum += c;
+            big += (uint32_t)__popcll(dev::ballot(c >= IdCounts::kBig));
+        }
+        sum = dev::wave_sum(sum);
         if (lane == 0) {
             rows[b] = sum;
-            nbig[b] = (uint32_t)__popcll(m);
+            nbig[b] = big;
         }
     }
 }
@@ -333,19 +413,23 @@ __global__ void list_big(const uint32_t *__restrict__ bins, uint64_t nblocks,
     for (uint64_t b = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / dev::kWave; b < nblocks;
          b += waves) {
         if (at[b + 1] == at[b]) continue;
-        const uint32_t c = bins[b * dev::kWave + lane];
-        const uint64_t m = dev::ballot(c >= IdCounts::kBig);
-        if (c >= IdCounts::kBig) big[at[b] + dev::rank_in_mask(m)] = c;
+        uint64_t to = at[b];
+#pragma unroll
+        for (uint32_t u = 0; u < kBlockWaves; ++u) {
+            const uint32_t c = bins[b * IdCounts::kBlock + u * dev::kWave + lane];
+            const uint64_t m = dev::ballot(c >= IdCounts::kBig);
+            if (c >= IdCounts::kBig) big[to + dev::rank_in_mask(m)] = c;
+            to += (uint64_t)__popcll(m);
+        }
     }
 }
 
 void exclusive_scan_async(tid_ctx *ctx, const uint32_t *in, uint64_t n, uint64_t *out);
 
-// Device bins (nblocks blocks of 64; counts below 2^32 in all per position) to
+// Device bins (nblocks blocks; counts below 2^32 in all per position) to
 // the host.
 static std::shared_ptr<IdCounts::Mem> counts_to_host(tid_ctx *ctx, const uint32_t *bins,
                                                      uint64_t nblocks) {
-    static_assert(IdCounts::kBlock == dev::kWave, "a block is a wave");
     DevBuf bytes(ctx, nblocks * IdCounts::kBlock), rows(ctx, nblocks * 4), nbig(ctx, nblocks * 4),
         offs(ctx, 2 * (nblocks + 1) * 8);
     uint64_t *r = offs.get<uint64_t>(), *b = r + nblocks + 1;
@@ -377,15 +461,43 @@ static std::shared_ptr<IdCounts::Mem> counts_to_host(tid_ctx *ctx, const uint32_
     return m;
 }
 
+// bytes of `ids` bins: whole blocks, so that every position starts on one
+static size_t bin_bytes(uint64_t ids) {
+    return (size_t)((ids + IdCounts::kBlock - 1) / IdCounts::kBlock) * IdCounts::kBlock *
+           sizeof(uint32_t);
+}
+
 constexpr uint32_t kMaxHistIds = 1u << 28;  // 1 GiB of uint32 counts per position
 
-void build_stats(tid_ctx *ctx, tid_graph *g) {
+// Whether p is memory of the context's own device, which its kernels may read
+// without a copy.
+bool on_this_device(tid_ctx *ctx, const void *p) {
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == ctx->device;
+}
+
+// The triples of `from` (on the device if on_device) to the graph's memory, and
+// its statistics.
+void load_triples(tid_ctx *ctx, tid_graph *g, const uint32_t *from, int on_device) {
     if (g->n == 0) return;
     DevBuf mm(ctx, 6 * sizeof(uint32_t));
     hipLaunchKernelGGL(init_minmax, dim3(1), dim3(64), 0, ctx->stream, mm.get<uint32_t>());
     const int blocks = (int)std::min<uint64_t>((g->n + kMinMaxBlock - 1) / kMinMaxBlock, 2048);
-    hipLaunchKernelGGL(minmax_kernel, dim3(blocks), dim3(kMinMaxBlock), 0, ctx->stream,
-                       g->data.get<const uint32_t>(), g->n, mm.get<uint32_t>());
+    if (on_device && (uintptr_t)from % sizeof(uint4) == 0 && on_this_device(ctx, from)) {
+        hipLaunchKernelGGL(copy_minmax, dim3((blocks + 2) / 3 * 3), dim3(kMinMaxBlock), 0,
+                           ctx->stream, reinterpret_cast<const uint4 *>(from),
+                           g->data.get<uint4>(), g->n, mm.get<uint32_t>());
+    } else {
+        TID_HIP(hipMemcpyAsync(g->data.get(), from, (size_t)g->n * 12,
+                               on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
+                               ctx->stream));
+        hipLaunchKernelGGL(minmax_kernel, dim3(blocks), dim3(kMinMaxBlock), 0, ctx->stream,
+                           g->data.get<const uint32_t>(), g->n, mm.get<uint32_t>());
+    }
     TID_HIP(hipGetLastError());
     uint32_t h[6];
     TID_HIP(hipMemcpyAsync(h, mm.get(), sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
@@ -403,7 +515,7 @@ void build_stats(tid_ctx *ctx, tid_graph *g) {
         if (h[3 + x] >= kMaxHistIds) continue;
         a.nbins[x] = h[3 + x] + 1;
         off[x] = total;
-        total += align_up((size_t)a.nbins[x] * sizeof(uint32_t));
+        total += bin_bytes(a.nbins[x]);
     }
     if (total == 0) return;
     DevBuf hist(ctx, total);
@@ -417,8 +529,6 @@ void build_stats(tid_ctx *ctx, tid_graph *g) {
                            g->data.get<const uint32_t>(), g->n, a);
         TID_HIP(hipGetLastError());
     }
-    // every position starts on a whole block (align_up: 64 bins)
-    static_assert(kAlign == IdCounts::kBlock * sizeof(uint32_t), "positions start on blocks");
     const auto mem = counts_to_host(ctx, hist.get<const uint32_t>(),
                                     total / sizeof(uint32_t) / IdCounts::kBlock);
     for (int x = 0; x < 3; ++x) {
@@ -489,7 +599,7 @@ void chunk_stats(tid_ctx *ctx, tid_graph *v) {
     if (v->n == 0 || v->max_id[1] >= kMaxHistIds) return;
     HistArgs a{};
     a.nbins[1] = v->max_id[1] + 1;
-    const size_t bytes = align_up((size_t)a.nbins[1] * sizeof(uint32_t));
+    const size_t bytes = bin_bytes(a.nbins[1]);
     DevBuf hist(ctx, bytes);
     TID_HIP(hipMemsetAsync(hist.get(), 0, bytes, ctx->stream));
     a.hist[1] = hist.get<uint32_t>();

@@ -1,5 +1,5 @@
 """The load-time ID counts (one byte an ID, a list of the counts of 255 and
-more, 64 IDs to a block) against numpy: every single ID, and ranges that start
+more, in blocks) against numpy: every single ID, and ranges that start
 and end inside blocks and past the largest ID."""
 import numpy as np
 import pytest
@@ -7,7 +7,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("ids", [1, 62, 63, 64, 65, 127, 128, 300])
+@pytest.mark.parametrize("ids", [1, 63, 64, 65, 128, 254, 255, 256, 257, 300, 511, 512, 600])
 @pytest.mark.parametrize("hubs", [False, True])
 def test_counts(ctx, ids, hubs):
     rng = np.random.default_rng(ids + hubs)
@@ -67,3 +67,32 @@ def test_counts_split(ctx, n, ids, hub):
             want = cum[hi] - cum[lo] if hi > lo else 0
             assert G.count(x, int(lo), int(hi)) == want, (x, lo, hi)
     G.free()
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 7, 1023, 1024, 262143, 800_001, 800_002, 800_003])
+@pytest.mark.parametrize("skip", [0, 1, 4])     # triples before: 12 bytes off, and 48
+def test_device_triples(ctx, n, skip):
+    """Triples copied from device memory: every row, the largest IDs, and ID 0
+    refused at either end."""
+    import torch
+    from paper_1807_01409_amd import TidError
+    rng = np.random.default_rng(n)
+    g = rng.integers(1, 5000, (n + skip, 3)).astype(np.uint32)
+    top = 70_000 + np.arange(3)
+    for x in range(3):
+        g[skip + (n - 1) * (x + 1) // 3, x] = top[x]
+    t = torch.from_numpy(g.view(np.int32)).cuda()[skip:]
+    torch.cuda.synchronize()
+    G = ctx.load(t)
+    from synth import pat
+    assert np.array_equal(ctx.scan(G, pat("?s ?p ?o")).to_numpy(), g[skip:])
+    for x in range(3):
+        assert G.count(x, int(top[x]), int(top[x]) + 1) == 1
+        assert G.count(x, 1, 1 << 20) == n
+    G.free()
+    for row, col in ((0, 0), (n - 1, 2), (n - 1, 1)):
+        bad = t.clone()
+        bad[row, col] = 0
+        torch.cuda.synchronize()
+        with pytest.raises(TidError):
+            ctx.load(bad)
