@@ -15,7 +15,7 @@
 //            workgroup a bucket, its bins stored, took 488 us for 234: the
 //            LDS atomics bound it, and equal shares balance them).
 // Bound: the split, which reads 12 bytes a triple and writes 2 a position.
-// 50M triples, 5M subject and object IDs: buckets 173 us, split 328, count 234;
+// 50M triples, 5M subject and object IDs: buckets 161 us, split 328, count 234;
 // with global atomics, an LDS table for the hubs before them, 3653 us.
 #include "compact.hpp"
 
@@ -38,7 +38,7 @@ constexpr int kBlock = 512;
 constexpr int kIPT = 8;
 constexpr uint32_t kTile = (uint32_t)kBlock * kIPT;
 constexpr int kNW = kBlock / dev::kWave;
-constexpr uint32_t kCopies = 4;                  // bucket counters of the waves
+constexpr uint32_t kCopies = 8;                  // counters of a bucket, side by side
 constexpr int kCountBlock = 1024;
 constexpr uint32_t kShares = 256;
 
@@ -59,7 +59,7 @@ struct IdArgs {
 
 __global__ __launch_bounds__(kBlock) void count_buckets(IdArgs a) {
     extern __shared__ uint32_t s_cnt[];
-    const uint32_t tid = threadIdx.x, copy = tid / dev::kWave % kCopies;
+    const uint32_t tid = threadIdx.x, copy = tid % kCopies;
     for (uint32_t i = tid; i < a.lds_words; i += kBlock) s_cnt[i] = 0;
     __syncthreads();
     const uint64_t r0 = (uint64_t)blockIdx.x * a.range, r1 = min(a.n, r0 + a.range);
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kBlock) void count_buckets(IdArgs a) {
         for (int x = 0; x < 3; ++x) {
             if (a.mode[x] == kDirect) atomicAdd(&s_cnt[a.lds[x] + v[x]], 1u);
             else if (a.mode[x] == kSplit)
-                atomicAdd(&s_cnt[a.lds[x] + copy * a.buckets[x] + (v[x] >> kLowBits)], 1u);
+                atomicAdd(&s_cnt[a.lds[x] + (v[x] >> kLowBits) * kCopies + copy], 1u);
         }
     };
     for (uint64_t t0 = r0; t0 < r1; t0 += kTile) {
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(kBlock) void count_buckets(IdArgs a) {
             for (uint32_t b = tid; b < B; b += kBlock) {
                 uint32_t sum = 0;
 #pragma unroll
-                for (uint32_t c = 0; c < kCopies; ++c) sum += s[c * B + b];
+                for (uint32_t c = 0; c < kCopies; ++c) sum += s[b * kCopies + c];
                 a.counts[x][(size_t)blockIdx.x * B + b] = sum;
             }
         }
