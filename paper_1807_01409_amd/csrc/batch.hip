@@ -431,6 +431,7 @@ namespace {
 constexpr int kBigBlock = 256;
 constexpr int kBigIPT = 4, kProbeIPT = 8;  // build and probe rows of a thread,
 constexpr int kFewIPT = 1, kFewProbeIPT = 2;  // and where that leaves the chip idle
+constexpr uint64_t kFewBuildRows = 1ull << 14;
 constexpr uint32_t kNoSlot32 = 0xFFFFFFFFu;
 
 // index j with base[j] <= x < base[j + 1] (base non-decreasing, base[0] = 0)
@@ -835,8 +836,12 @@ void flush_big_count(tid_ctx *ctx, std::vector<BigJoinReq> &reqs,
         if (r.c.nr < kSortBuildRows) build += r.c.nr;
         probe += r.c.nl;
     }
-    const uint64_t chip = 4ull * (uint64_t)device_cus(ctx) * kBigBlock;  // threads at a time
-    const bool few_build = build <= chip * kFewIPT, few_probe = probe <= chip * kFewProbeIPT;
+    // fewer rows a thread: for builds of up to kFewBuildRows (18 us with four
+    // rows a thread, 9 with one, for some thousand rows; for 60,000 24 and 35),
+    // for probes as long as four workgroups a CU take them all
+    const bool few_build = build <= kFewBuildRows;
+    const bool few_probe =
+        probe <= 4ull * (uint64_t)device_cus(ctx) * kBigBlock * kFewProbeIPT;
     const uint64_t btile = (uint64_t)kBigBlock * (few_build ? kFewIPT : kBigIPT);
     const uint64_t ptile = (uint64_t)kBigBlock * (few_probe ? kFewProbeIPT : kProbeIPT);
     arena->tile = (uint32_t)ptile;

@@ -66,8 +66,8 @@ def test_kinds(ctx, keys, nl, nr):
         assert np.array_equal(got, want), kind
 
 
-@pytest.mark.parametrize("nl,nr", [(511, 255), (513, 257), (1 << 19, 1 << 18),
-                                   ((1 << 19) + 1, (1 << 18) + 1)])
+@pytest.mark.parametrize("nl,nr", [(511, 255), (513, 257), (1 << 19, 1 << 14),
+                                   ((1 << 19) + 1, (1 << 14) + 1)])
 def test_rows_of_a_thread(ctx, nl, nr):
     """The last sizes with few rows to a thread, and the first with more."""
     L, R = tables(nl, nr, KEYS["dense"], nl + nr)
