@@ -408,7 +408,9 @@ static bool use_slices(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats
 }
 
 bool scan_pages_ok(tid_ctx *ctx, const tid_graph *g, int k, tid_table *const *outs);
-void run_scan_pages(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, int k,
+bool scan_pages_better(const tid_graph *g, const tid_pattern *pats, int k, const PatternSet *sets,
+                       const ScanFilter *filters);
+bool run_scan_pages(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, int k,
                     tid_table *const *outs, const PatternSet *sets, const ScanFilter *filters);
 
 // Whether one pass of the block-ranged kernel holds the rows the tables'
@@ -438,11 +440,10 @@ static void run_scan_any(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pa
     }
     const int shape = (int)ctx->opt.multi_shape;
     if (ctx->opt.multi_kernel == 0 && shape == 0 && ctx->opt.compact_kernel == 0 &&
-        ctx->opt.capacity_override == 0 && !staged_pass_ok(ctx, g, outs, k) &&
-        scan_pages_ok(ctx, g, k, outs)) {
-        run_scan_pages(ctx, g, pats, k, outs, sets, filters);
+        ctx->opt.capacity_override == 0 &&
+        (!staged_pass_ok(ctx, g, outs, k) || scan_pages_better(g, pats, k, sets, filters)) &&
+        scan_pages_ok(ctx, g, k, outs) && run_scan_pages(ctx, g, pats, k, outs, sets, filters))
         return;
-    }
     if (ctx->opt.multi_kernel == 0) {
         const int passes = (k + 3) / 4;
         for (int p0 = 0, p = 0; p < passes; ++p) {

@@ -21,9 +21,10 @@
 //    output column, so storing does not depend on the pattern.
 // The block-ranged kernel (passes of at most four patterns) stages rows in LDS
 // and reads the graph a second time where they do not fit; it stays for up to
-// four patterns whose rows do fit (run_scan_any in scan.hip).  Measured on one
+// four patterns whose rows do fit, unless they are a predicate each
+// (scan_pages_better).  Measured on one
 // MI355X: 12 patterns with 3.6M rows in all on 30M triples 884 us in three
-// block-ranged passes, 181 us here; 3 patterns with 45M rows on 200M triples
+// block-ranged passes, 145 us here; 3 patterns with 45M rows on 200M triples
 // 3353 us, 803 us here (2.4 GB read: 348 us at the plain read rate).
 #include "scan_common.hpp"
 
@@ -268,6 +269,80 @@ __global__ __launch_bounds__(kPgBlock) void predicates_to_pages(PageArgs a) {
     if (wave == 0 && lane < k) a.cnt[(size_t)lane * a.P + blockIdx.x] = l.run;
 }
 
+// The same by a table of the patterns' predicates in LDS: the work of a triple
+// does not grow with the patterns, and places are found in the same walk that
+// counts.  For more than kFewKeys patterns with predicates below kTableIds: on 30M
+// triples 131 us with compares and 142 with the table for 5 patterns, 166 and
+// 159 for 8, 272 and 212 for 16.
+constexpr int kFewKeys = 6;
+constexpr uint32_t kTableIds = 8192;
+__global__ __launch_bounds__(kPgBlock) void table_to_pages(PageArgs a) {
+    constexpr uint32_t kNone = 0xFFu;
+    __shared__ uint32_t s_c[2][kPgNW][TID_MAX_MULTI];  // matches per wave of a tile
+    __shared__ uint32_t s_page[TID_MAX_MULTI][kRing];  // a pattern's latest pages
+    __shared__ int32_t s_cols[TID_MAX_MULTI];
+    __shared__ uint32_t s_table[kTableIds / 4];        // a byte an ID: its pattern
+    __shared__ uint32_t s_run[kPgNW][TID_MAX_MULTI];   // a wave's matches so far in the tile
+    __shared__ uint4 s_list[kPgNW][TID_MAX_MULTI];     // its PageLists, by pattern
+    uint8_t *s_id = reinterpret_cast<uint8_t *>(s_table);
+    const int tid = threadIdx.x, lane = tid % dev::kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / dev::kWave);
+    const int k = a.k;
+    for (uint32_t i = tid; i < kTableIds / 4; i += kPgBlock) s_table[i] = 0xFFFFFFFFu;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < TID_MAX_MULTI; ++j)  // static indices into the kernel arguments
+        if (tid == j && j < k) {
+            s_id[a.pat[j].key[1]] = (uint8_t)j;  // all different
+            s_cols[j] = a.pat[j].ncols;
+        }
+    __syncthreads();
+    const bool stores = s_cols[min(lane, k - 1)] > 0;
+    const uint32_t storing = (uint32_t)dev::ballot(lane < k && stores);
+    PageLists l;
+    const uint64_t r0 = (uint64_t)blockIdx.x * a.range, r1 = min(a.n, r0 + a.range);
+    const uint64_t lt = (1ull << lane) - 1ull;
+    uint32_t *const ps = a.plane[0], *const po = a.plane[2];
+    Tri next[kPgIPT], t[kPgIPT];
+    if (r0 < r1) load_tile(a, r0, r1, wave, lane, next);
+    int par = 0;
+    for (uint64_t t0 = r0; t0 < r1; t0 += kPgTile, par ^= 1) {
+#pragma unroll
+        for (int it = 0; it < kPgIPT; ++it) t[it] = next[it];
+        if (t0 + kPgTile < r1) load_tile(a, t0 + kPgTile, r1, wave, lane, next);
+        if (lane < k) s_run[wave][lane] = 0;
+        uint32_t id[kPgIPT], rank[kPgIPT];
+#pragma unroll
+        for (int it = 0; it < kPgIPT; ++it)
+            id[it] = t[it].v[1] < kTableIds ? s_id[t[it].v[1]] : kNone;
+#pragma unroll
+        for (int it = 0; it < kPgIPT; ++it) {
+            const bool m = id[it] != kNone;
+            rank[it] = 0;
+            if (dev::ballot(m) == 0) continue;
+            const uint64_t peers = dev::match_digit<4>(id[it], m);
+            const uint32_t before = m ? s_run[wave][id[it]] : 0u;
+            rank[it] = before + (uint32_t)__popcll(peers & lt);
+            if (m && lane == __builtin_ctzll(peers))
+                s_run[wave][id[it]] = before + (uint32_t)__popcll(peers);
+        }
+        const uint32_t v_c = lane < k ? s_run[wave][lane] : 0u;
+        if (lane < k) s_c[par][wave][lane] = v_c;
+        __syncthreads();
+        place_tile(a, l, v_c, wave, lane, stores, s_c[par], s_page);
+        if (lane < k) s_list[wave][lane] = make_uint4(l.base, l.edge, l.off0, l.off1);
+#pragma unroll
+        for (int it = 0; it < kPgIPT; ++it) {
+            if (id[it] == kNone || !(storing >> id[it] & 1u)) continue;
+            const uint4 list = s_list[wave][id[it]];
+            const uint32_t x = list.x + rank[it], at = x + (x < list.y ? list.z : list.w);
+            put_row(ps, at, t[it].v[0]);
+            put_row(po, at, t[it].v[2]);
+        }
+    }
+    if (wave == 0 && lane < k) a.cnt[(size_t)lane * a.P + blockIdx.x] = l.run;
+}
+
 // Any patterns.  EXT: some pattern's test reads memory (a value set, a
 // filter), so the match masks of a tile are kept; DISJOINT: no triple matches
 // two of the patterns.
@@ -461,7 +536,39 @@ static bool apart(const tid_pattern &p, const tid_pattern &q) {
     return (p.s && q.s && p.s != q.s) || (p.p && q.p && p.p != q.p) || (p.o && q.o && p.o != q.o);
 }
 
-void run_scan_pages(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, int k,
+// a constant predicate, and nothing else to test
+static bool predicate_alone(const DevPattern &d) {
+    bool only = d.msk[1] != 0 && d.key[1] != 0 && d.msk[0] == 0 && d.msk[2] == 0 && d.eq == 0 &&
+                d.set_pos < 0 && d.fpos < 0;
+    for (int x = 0; x < 3; ++x) only &= d.rlo[x] == 0 && d.rmax[x] == 0xFFFFFFFFu;
+    return only;
+}
+
+// Whether the paged pass is the better one also where the staged one holds every
+// row: for the rows of several predicates, whose tests it does with one compare
+// or table read a triple.  Staged / paged, 0.1% of the triples or less out
+// (1%), in us:
+//                 2 patterns      3               4
+//   1M triples     31 /  34       38 /  38        43 /  42
+//   4M             45 /  45       56 /  48        64 /  52
+//   30M           114 /  91      166 /  94       204 /  99   (276 / 123)
+//   100M          285 / 218      445 / 221       563 / 226
+// Patterns with other tests as well are the staged pass's (two ranges of one
+// predicate on 30M triples: 132 / 171).
+bool scan_pages_better(const tid_graph *g, const tid_pattern *pats, int k, const PatternSet *sets,
+                       const ScanFilter *filters) {
+    for (int j = 0; j < k; ++j) {
+        if (!predicate_alone(compile_pattern(pats[j], sets ? &sets[j] : nullptr,
+                                             filters ? &filters[j] : nullptr)))
+            return false;
+        for (int i = 0; i < j; ++i)
+            if (!apart(pats[i], pats[j])) return false;
+    }
+    return k > 2 || g->n >= (1ull << 22);
+}
+
+// The pass; false, and nothing done, if there is no memory for the pages.
+bool run_scan_pages(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, int k,
                     tid_table *const *outs, const PatternSet *sets, const ScanFilter *filters) {
     PageArgs a{};
     PageGather b{};
@@ -471,11 +578,8 @@ void run_scan_pages(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, i
     for (int j = 0; j < k; ++j) {
         DevPattern &d = a.pat[j];
         d = compile_pattern(pats[j], sets ? &sets[j] : nullptr, filters ? &filters[j] : nullptr);
-        bool only = d.msk[0] == 0 && d.msk[2] == 0 && d.eq == 0 && d.set_pos < 0 && d.fpos < 0;
-        for (int x = 0; x < 3; ++x) only &= d.rlo[x] == 0 && d.rmax[x] == 0xFFFFFFFFu;
-        const bool constant = d.msk[1] != 0 && d.key[1] != 0;
-        a.kind[j] = constant ? kPredicateFirst : kGeneral;
-        preds &= constant && only;
+        a.kind[j] = d.msk[1] != 0 && d.key[1] != 0 ? kPredicateFirst : kGeneral;
+        preds &= predicate_alone(d);
         for (int i = 0; i < j; ++i) disjoint &= apart(pats[i], pats[j]);
         // a value set stands where the pattern holds one of its constants
         disjoint &= d.set_pos < 0;
@@ -489,7 +593,12 @@ void run_scan_pages(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, i
     const size_t o_cnt = 256, o_hdr = align_up(o_cnt + (size_t)k * P * 4);
     const size_t o_data = align_up(o_hdr + pages * 8);
     const size_t plane = (size_t)pages * kPageRows * 4;
-    DevBuf buf(ctx, o_data + plane * (size_t)(used[0] + used[1] + used[2]) + 4);
+    DevBuf buf;
+    try {
+        buf = DevBuf(ctx, o_data + plane * (size_t)(used[0] + used[1] + used[2]) + 4);
+    } catch (const Error &) {
+        return false;
+    }
     char *base = buf.get<char>(), *at = base + o_data;
     for (int x = 0; x < 3; ++x)
         if (used[x]) {
@@ -514,7 +623,10 @@ void run_scan_pages(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, i
                        dim3(256), 0, ctx->stream, a.npages, a.hdr, (uint32_t)pages);
     TID_HIP(hipGetLastError());
     const bool ext = any_ext(k, sets, filters);
-    auto kern = preds ? predicates_to_pages
+    bool table = preds && k > kFewKeys;
+    for (int j = 0; j < k; ++j) table &= a.pat[j].key[1] < kTableIds;
+    auto kern = table   ? table_to_pages
+                : preds ? predicates_to_pages
                 : ext ? (disjoint ? scan_to_pages<true, true> : scan_to_pages<true, false>)
                       : (disjoint ? scan_to_pages<false, true> : scan_to_pages<false, false>);
     hipLaunchKernelGGL(kern, dim3((uint32_t)P), dim3(kPgBlock), 0, ctx->stream, a);
@@ -523,6 +635,7 @@ void run_scan_pages(tid_ctx *ctx, const tid_graph *g, const tid_pattern *pats, i
         (unsigned)std::max<uint64_t>(k, std::min<uint64_t>(pages, 8ull * device_cus(ctx)));
     hipLaunchKernelGGL(pages_to_tables, dim3(grid), dim3(kGatherBlock), 0, ctx->stream, b);
     TID_HIP(hipGetLastError());
+    return true;
 }
 
 }  // namespace tid

@@ -71,3 +71,23 @@ def test_pages_sets_and_filters(ctx):
             assert np.array_equal(t.to_numpy(), oracle.query(g, p).rows)
     finally:
         ctx.set_option("semijoin_min", old)
+
+
+@pytest.mark.parametrize("n", [1, 4095, 4097, 300_007, 2_100_007])
+@pytest.mark.parametrize("k", [4, 5, 16])
+@pytest.mark.parametrize("top", [8191, 8192])      # the last ID of the LDS table, and the next
+def test_predicates_alone(ctx, n, k, top):
+    """Patterns that are a predicate each: rows of rare, common and absent
+    predicates, and one pattern that puts no column out."""
+    rng = np.random.default_rng(n + k)
+    ids = np.concatenate([np.arange(1, 40), [top, top - 1]])
+    w = np.arange(1, ids.size + 1) ** -1.0
+    g = np.stack([rng.integers(1, 5000, n), rng.choice(ids, n, p=w / w.sum()),
+                  rng.integers(1, 5000, n)], axis=1).astype(np.uint32)
+    G = ctx.load(g)
+    preds = [1, top, 3, 39, 777, 2] + [top - 1] + list(range(10, 19))
+    ps = [pat("? 3 ?") if p == 3 else pat(f"?s {p} ?o") for p in preds[:k]]
+    for p, t in zip(ps, ctx.scan_multi(G, ps)):
+        want = oracle.scan(g, p)
+        assert t.nrows == want.rows.shape[0], (n, k, p)
+        assert np.array_equal(t.to_numpy(), want.rows), (n, k, p)
