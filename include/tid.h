@@ -85,7 +85,7 @@ tid_status tid_ctx_synchronize(tid_ctx *ctx);
                           512-thread workgroup fits a compute unit)
      "multi_kernel"       multi-pattern scans: 0 one paged pass of up to 16
                           patterns, or passes of at most 4 patterns
-                          (unrolled) where their rows are few, 1 one pass of
+                          (unrolled) where that is faster, 1 one pass of
                           up to 16 patterns (LDS pattern loop) (autotuner)
      "multi_shape"        launch shape index 0..3 of that kernel (autotuner)
      "compact_kernel"     1: block-ranged compaction (one fixed range per

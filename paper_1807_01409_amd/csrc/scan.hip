@@ -381,14 +381,14 @@ static void launch_multi(tid_ctx *ctx, const tid_graph *g, MultiArgs &a, int k, 
     TID_HIP(hipGetLastError());
 }
 
-// multi_kernel option: 0 (default) the unrolled kernel for up to 4 patterns,
-// and more patterns as several passes of at most 4 (balanced); 1 the LDS
-// pattern-loop kernel (one pass for up to 16).  Per pattern, the loop kernel
-// stages a sixteenth of the LDS and falls back to re-reading the graph once
-// the outputs are dense; four-pattern passes keep the automatic choice
-// between block-ranged and chunked placement, and measure 2.5x faster for
-// eight patterns of ~1% selectivity.  multi_shape 0 is 512 threads x 8
-// triples for both.
+// multi_kernel option: 0 (default) the paged pass (run_scan_any below says
+// when), or the unrolled kernel for up to 4 patterns, and more patterns as
+// several passes of at most 4 (balanced); 1 the LDS pattern-loop kernel (one
+// pass for up to 16).  Per pattern, the loop kernel stages a sixteenth of the
+// LDS and falls back to re-reading the graph once the outputs are dense;
+// four-pattern passes keep the automatic choice between block-ranged and
+// chunked placement, and measure 2.5x faster for eight patterns of ~1%
+// selectivity.  multi_shape 0 is 512 threads x 8 triples for both.
 void scan_slice(tid_ctx *ctx, const tid_graph *g, const tid_pattern &p, tid_table *out,
                 const ScanFilter *filter);
 
