@@ -14,6 +14,7 @@
 //            bucket, in LDS bins, and adds the bins to the global ones (a
 //            workgroup a bucket, its bins stored, took 488 us for 234: the
 //            LDS atomics bound it, and equal shares balance them).
+// IDs of more than kMaxBuckets buckets take several passes over the triples.
 // Bound: the split, which reads 12 bytes a triple and writes 2 a position.
 // 50M triples, 5M subject and object IDs: buckets 161 us, split 328, count 234;
 // with global atomics, an LDS table for the hubs before them, 3653 us.
@@ -32,7 +33,9 @@ namespace {
 
 constexpr int kLowBits = 15;
 constexpr uint32_t kBucketIds = 1u << kLowBits;  // 128 KB of bins
-constexpr uint32_t kMaxBuckets = 512;
+constexpr uint32_t kMaxBuckets = 512;            // of a pass
+constexpr uint32_t kMaxPasses = 8;
+constexpr uint64_t kPassRows = 1ull << 22;
 constexpr uint32_t kDirectIds = 8192;            // counted without a split
 constexpr int kBlock = 512;
 constexpr int kIPT = 8;
@@ -49,7 +52,8 @@ struct IdArgs {
     uint64_t n, range;
     Mode mode[3];
     uint32_t ids[3];       // IDs are below this
-    uint32_t buckets[3];
+    uint32_t buckets[3];   // of the pass, from bucket `first` on
+    uint32_t first[3];
     uint32_t lds[3];       // first word of the position's counters in LDS
     uint32_t lds_words;
     uint32_t *hist[3];
@@ -67,8 +71,10 @@ __global__ __launch_bounds__(kBlock) void count_buckets(IdArgs a) {
 #pragma unroll
         for (int x = 0; x < 3; ++x) {
             if (a.mode[x] == kDirect) atomicAdd(&s_cnt[a.lds[x] + v[x]], 1u);
-            else if (a.mode[x] == kSplit)
-                atomicAdd(&s_cnt[a.lds[x] + (v[x] >> kLowBits) * kCopies + copy], 1u);
+            else if (a.mode[x] == kSplit) {
+                const uint32_t b = (v[x] >> kLowBits) - a.first[x];
+                if (b < a.buckets[x]) atomicAdd(&s_cnt[a.lds[x] + b * kCopies + copy], 1u);
+            }
         }
     };
     for (uint64_t t0 = r0; t0 < r1; t0 += kTile) {
@@ -114,7 +120,7 @@ __global__ __launch_bounds__(kBlock) void split_ids(IdArgs a) {
     __shared__ uint32_t s_run[3][kMaxBuckets];  // where the range's next ID of a bucket goes
     __shared__ uint32_t s_loc[kMaxBuckets];     // a bucket's first ID in the ordered tile
     __shared__ uint32_t s_off[kMaxBuckets];     // place of ordered ID i: s_off[bucket] + i
-    __shared__ uint32_t s_w[kNW];
+    __shared__ uint32_t s_w[kNW], s_all;
     const uint32_t tid = threadIdx.x, w = blockIdx.x;
     const int wave = tid / dev::kWave, lane = tid % dev::kWave;
     static_assert(kMaxBuckets <= kBlock, "a thread per bucket");
@@ -150,13 +156,17 @@ __global__ __launch_bounds__(kBlock) void split_ids(IdArgs a) {
 #pragma unroll
         for (int x = 0; x < 3; ++x) {
             if (a.mode[x] != kSplit) continue;
-            uint32_t rank[kIPT];
+            uint32_t rank[kIPT], bucket[kIPT];
 #pragma unroll
-            for (int u = 0; u < kIPT; ++u)
-                if (u * kBlock + tid < cnt) rank[u] = atomicAdd(&s_cnt[v[u][x] >> kLowBits], 1u);
+            for (int u = 0; u < kIPT; ++u) {
+                bucket[u] = (v[u][x] >> kLowBits) - a.first[x];
+                if (u * kBlock + tid >= cnt) bucket[u] = kMaxBuckets;
+                if (bucket[u] < a.buckets[x]) rank[u] = atomicAdd(&s_cnt[bucket[u]], 1u);
+            }
             __syncthreads();
             const uint32_t tot = tid < a.buckets[x] ? s_cnt[tid] : 0u;
             const uint32_t loc = prefix(tot);
+            if (tid == a.buckets[x] - 1) s_all = loc + tot;
             if (tid < a.buckets[x]) {
                 const uint32_t run = s_run[x][tid];
                 s_loc[tid] = loc;
@@ -167,14 +177,16 @@ __global__ __launch_bounds__(kBlock) void split_ids(IdArgs a) {
             __syncthreads();
 #pragma unroll
             for (int u = 0; u < kIPT; ++u)
-                if (u * kBlock + tid < cnt) s_id[s_loc[v[u][x] >> kLowBits] + rank[u]] = v[u][x];
+                if (bucket[u] < a.buckets[x]) s_id[s_loc[bucket[u]] + rank[u]] = v[u][x];
             __syncthreads();
+            const uint32_t all = s_all;  // the tile's IDs in the pass's buckets
 #pragma unroll
             for (int u = 0; u < kIPT; ++u) {
                 const uint32_t i = u * kBlock + tid;
-                if (i >= cnt) continue;
+                if (i >= all) continue;
                 const uint32_t id = s_id[i];
-                a.low[x][s_off[id >> kLowBits] + i] = (uint16_t)(id & (kBucketIds - 1));
+                a.low[x][s_off[(id >> kLowBits) - a.first[x]] + i] =
+                    (uint16_t)(id & (kBucketIds - 1));
             }
             __syncthreads();
         }
@@ -198,9 +210,9 @@ __global__ __launch_bounds__(kCountBlock) void count_split(IdArgs a) {
         if (tid == 0) s_first[B] = run;
     }
     __syncthreads();
-    const uint64_t share = (a.n + kShares - 1) / kShares;
+    const uint64_t n = s_first[B], share = (n + kShares - 1) / kShares;
     uint64_t at = blockIdx.x * share;
-    const uint64_t end = min(a.n, at + share);
+    const uint64_t end = min(n, at + share);
     uint32_t b = 0;  // the bucket that holds place `at`
     for (uint32_t hi = B; b + 1 < hi;) {
         const uint32_t mid = (b + hi) / 2;
@@ -211,7 +223,7 @@ __global__ __launch_bounds__(kCountBlock) void count_split(IdArgs a) {
     for (; at < end && b < B; ++b) {
         const uint64_t stop = min(end, (uint64_t)s_first[b + 1]);
         if (stop <= at) continue;
-        const uint32_t id0 = b << kLowBits, ids = min(kBucketIds, a.ids[x] - id0);
+        const uint32_t id0 = (a.first[x] + b) << kLowBits, ids = min(kBucketIds, a.ids[x] - id0);
         for (uint32_t i = tid; i < ids; i += kCountBlock) s_cnt[i] = 0;
         __syncthreads();
         for (uint64_t c = at / 8 + tid; 8 * c < stop; c += kCountBlock) {
@@ -237,8 +249,10 @@ __global__ __launch_bounds__(kCountBlock) void count_split(IdArgs a) {
 // nothing done, where the atomics of runtime.hip are the better way (a whole
 // load with them / with the split: 100,000 triples 171 / 198 us, 200,000 226 /
 // 228, 300,000 275 / 250, 4M 591 / 394; IDs up to 16M at 1M triples 2621 /
-// 2578), a position has more buckets than a tile can keep apart, or there is no
-// memory for the split.
+// 2578), IDs would take more than kMaxPasses passes of kMaxBuckets buckets or a
+// pass would have few triples (200M triples with 20M IDs 25.4 / 13.9 ms, with
+// 130M 81.9 / 75.0; 20M triples with 20M IDs 11.0 / 10.3, with 130M 63.1 / 63.7),
+// or there is no memory for the split.
 constexpr uint64_t kSplitRows = 1ull << 18;
 bool count_ids(tid_ctx *ctx, const uint32_t *g, uint64_t n, uint32_t *const *hist,
                const uint32_t *nbins) {
@@ -246,31 +260,25 @@ bool count_ids(tid_ctx *ctx, const uint32_t *g, uint64_t n, uint32_t *const *his
     IdArgs a{};
     a.g = g;
     a.n = n;
-    int splits = 0;
+    uint32_t total[3] = {0, 0, 0}, most = 0;  // buckets
     for (int x = 0; x < 3; ++x) {
         a.hist[x] = hist[x];
         a.ids[x] = nbins[x];
         if (!hist[x]) continue;
-        a.lds[x] = a.lds_words;
-        if (nbins[x] <= kDirectIds) {
-            a.mode[x] = kDirect;
-            a.lds_words += nbins[x];
-            continue;
-        }
-        a.mode[x] = kSplit;
-        a.buckets[x] = (nbins[x] + kBucketIds - 1) >> kLowBits;
-        if (a.buckets[x] > kMaxBuckets) return false;
-        a.lds_words += kCopies * a.buckets[x];
-        ++splits;
+        a.mode[x] = nbins[x] <= kDirectIds ? kDirect : kSplit;
+        if (a.mode[x] == kSplit) total[x] = (nbins[x] + kBucketIds - 1) >> kLowBits;
+        most = std::max(most, total[x]);
     }
+    const uint64_t passes = (most + kMaxBuckets - 1) / kMaxBuckets;
+    if (passes > kMaxPasses || (passes > 1 && n < passes * kPassRows)) return false;
     const uint64_t tiles = (n + kTile - 1) / kTile;
     uint64_t P = std::max<uint64_t>(1, std::min<uint64_t>(tiles, 3ull * device_cus(ctx)));
     a.range = (tiles + P - 1) / P * kTile;
     P = (n + a.range - 1) / a.range;
     DevBuf mem;
-    if (splits) {
+    if (most) {
         size_t bytes = 0;
-        for (int pass = 0; pass < 2; ++pass) {
+        for (int step = 0; step < 2; ++step) {
             char *at = mem.get<char>();
             bytes = 0;
             auto take = [&](size_t len) {
@@ -280,13 +288,14 @@ bool count_ids(tid_ctx *ctx, const uint32_t *g, uint64_t n, uint32_t *const *his
             };
             for (int x = 0; x < 3; ++x) {
                 if (a.mode[x] != kSplit) continue;
-                const size_t cells = (size_t)P * a.buckets[x] * 4;
+                const uint32_t B = std::min(total[x], kMaxBuckets);
+                const size_t cells = (size_t)P * B * 4;
                 a.counts[x] = reinterpret_cast<uint32_t *>(take(cells));
                 a.scan[x] = reinterpret_cast<uint32_t *>(take(cells));
-                a.totals[x] = reinterpret_cast<uint32_t *>(take((size_t)a.buckets[x] * 4));
+                a.totals[x] = reinterpret_cast<uint32_t *>(take((size_t)B * 4));
                 a.low[x] = reinterpret_cast<uint16_t *>(take((n + 8) * 2));
             }
-            if (pass) break;
+            if (step) break;
             try {
                 mem = DevBuf(ctx, bytes);
             } catch (const Error &) {
@@ -294,20 +303,33 @@ bool count_ids(tid_ctx *ctx, const uint32_t *g, uint64_t n, uint32_t *const *his
             }
         }
     }
-    const size_t lds = (size_t)a.lds_words * 4, bins = (size_t)kBucketIds * 4;
-    // above 64 KB a kernel must be allowed its dynamic LDS first
-    if (lds > (64u << 10)) (void)resident_blocks((const void *)count_buckets, kBlock, lds);
-    hipLaunchKernelGGL(count_buckets, dim3((uint32_t)P), dim3(kBlock), lds, ctx->stream, a);
-    TID_HIP(hipGetLastError());
-    if (!splits) return true;
-    for (int x = 0; x < 3; ++x)
-        if (a.mode[x] == kSplit)
-            scan_digits(ctx, a.counts[x], a.scan[x], a.totals[x], (uint32_t)P, a.buckets[x]);
-    hipLaunchKernelGGL(split_ids, dim3((uint32_t)P), dim3(kBlock), 0, ctx->stream, a);
-    TID_HIP(hipGetLastError());
-    (void)resident_blocks((const void *)count_split, kCountBlock, bins);
-    hipLaunchKernelGGL(count_split, dim3(kShares, 3), dim3(kCountBlock), bins, ctx->stream, a);
-    TID_HIP(hipGetLastError());
+    for (uint32_t first = 0; first == 0 || first < most; first += kMaxBuckets) {
+        a.lds_words = 0;
+        for (int x = 0; x < 3; ++x) {
+            if (first && a.mode[x] == kDirect) a.mode[x] = kNone;  // counted in the first pass
+            if (a.mode[x] == kSplit && first >= total[x]) a.mode[x] = kNone;
+            a.lds[x] = a.lds_words;
+            a.first[x] = first;
+            if (a.mode[x] == kDirect) a.lds_words += a.ids[x];
+            if (a.mode[x] != kSplit) continue;
+            a.buckets[x] = std::min(total[x] - first, kMaxBuckets);
+            a.lds_words += kCopies * a.buckets[x];
+        }
+        const size_t lds = (size_t)a.lds_words * 4, bins = (size_t)kBucketIds * 4;
+        // above 64 KB a kernel must be allowed its dynamic LDS first
+        if (lds > (64u << 10)) (void)resident_blocks((const void *)count_buckets, kBlock, lds);
+        hipLaunchKernelGGL(count_buckets, dim3((uint32_t)P), dim3(kBlock), lds, ctx->stream, a);
+        TID_HIP(hipGetLastError());
+        if (!most) return true;
+        for (int x = 0; x < 3; ++x)
+            if (a.mode[x] == kSplit)
+                scan_digits(ctx, a.counts[x], a.scan[x], a.totals[x], (uint32_t)P, a.buckets[x]);
+        hipLaunchKernelGGL(split_ids, dim3((uint32_t)P), dim3(kBlock), 0, ctx->stream, a);
+        TID_HIP(hipGetLastError());
+        (void)resident_blocks((const void *)count_split, kCountBlock, bins);
+        hipLaunchKernelGGL(count_split, dim3(kShares, 3), dim3(kCountBlock), bins, ctx->stream, a);
+        TID_HIP(hipGetLastError());
+    }
     return true;
 }
 

@@ -301,7 +301,7 @@ __global__ void init_minmax(uint32_t *mm) {
 }
 
 // Per-position ID histograms in one pass over the graph, where count_ids does
-// not take them (small graphs, IDs of 2^24 and more).  Each workgroup
+// not take them (small graphs, few triples to many IDs).  Each workgroup
 // counts in LDS first and adds its counts to the global bins at the end:
 //  - a position whose IDs fit kDirectBins bins (the predicates) is counted
 //    in LDS bins directly;

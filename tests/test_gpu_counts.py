@@ -42,6 +42,8 @@ def test_counts(ctx, ids, hubs):
     (300_001, (1_000_003, 90_000, 5)),                 # three kinds at once
     (4096 * 77 + 1, (70_000, 12, (1 << 24) - 1)),      # as many buckets as there may be
     (270_000, (1 << 24, 3, 50)),                       # one more
+    (2 * (1 << 22), (1 << 24, 3, 50)),                 # in two passes
+    (3 * (1 << 22) + 1, (40_000_000, 9000, 20_000_000)),    # three passes, one and two
     (3_000_000, (200_000, 50, 600_000)),
 ])
 @pytest.mark.parametrize("hub", [0.0, 0.7])
