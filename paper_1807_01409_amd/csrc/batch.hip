@@ -539,12 +539,12 @@ __device__ __forceinline__ bool big_agree(const uint32_t *const *el, const uint3
 
 // Index of a sorted build side: for every present key, or group of keys that
 // share key >> shift, where its run starts and ends in the sorted rows.
-__global__ void index_runs(const uint32_t *__restrict__ key, uint32_t n, int shift, uint2 *index) {
-    const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+__global__ void index_runs(const uint32_t *__restrict__ key, uint64_t n, int shift, uint2 *index) {
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         const uint32_t h = key[i] >> shift;
-        if (i == 0 || key[i - 1] >> shift != h) index[h].x = i;
-        if (i + 1 == n || key[i + 1] >> shift != h) index[h].y = i + 1;
+        if (i == 0 || key[i - 1] >> shift != h) index[h].x = (uint32_t)i;
+        if (i + 1 == n || key[i + 1] >> shift != h) index[h].y = (uint32_t)(i + 1);
     }
 }
 
@@ -797,6 +797,9 @@ unsigned grid_cap(uint64_t n, uint64_t cap = 16384) {
 // 392 us), against three or four radix passes and an index of plain stores
 // (3M rows: 130 us).  Below kSortBuildRows the passes' launches cost more.
 constexpr uint64_t kSortBuildRows = 1ull << 19;
+// Largest build side of one join: a table of two slots a row has then 2^31,
+// and every row number and slot fits 32 bits.
+constexpr uint64_t kMostBuildRows = 1ull << 30;
 
 static void sort_build_side(tid_ctx *ctx, BigCount &b, BigArena &arena) {
     // direct by key while that takes at most four index entries a row; else
@@ -814,7 +817,7 @@ static void sort_build_side(tid_ctx *ctx, BigCount &b, BigArena &arena) {
     TID_HIP(hipMemsetAsync(index.get(), 0xFF, n_index * sizeof(uint2), ctx->stream));
     DevBuf &key = moved ? k1 : k0, &row = moved ? v1 : v0;
     hipLaunchKernelGGL(index_runs, dim3(grid_cap(b.nr)), dim3(256), 0, ctx->stream,
-                       key.get<const uint32_t>(), (uint32_t)b.nr, b.shift, index.get<uint2>());
+                       key.get<const uint32_t>(), b.nr, b.shift, index.get<uint2>());
     TID_HIP(hipGetLastError());
     b.index = index.get<const uint2>();
     b.skey = key.get<const uint32_t>();
@@ -833,6 +836,8 @@ void flush_big_count(tid_ctx *ctx, std::vector<BigJoinReq> &reqs,
     auto arena = std::make_shared<BigArena>();
     uint64_t S = 0, build = 0, probe = 0;
     for (const BigJoinReq &r : reqs) {
+        TID_REQUIRE(r.c.nr <= kMostBuildRows, TID_E_UNSUPPORTED,
+                    "join: the build side has more than 2^30 rows");
         if (r.c.nr < kSortBuildRows) build += r.c.nr;
         probe += r.c.nl;
     }

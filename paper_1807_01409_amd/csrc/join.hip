@@ -478,6 +478,11 @@ static std::unique_ptr<tid_table> unmatched_right(tid_ctx *ctx, const tid_table 
                                                   int rc, const std::vector<int32_t> &vars) {
     TID_REQUIRE(nl < (1ull << 32) && nr < (1ull << 32), TID_E_UNSUPPORTED,
                 "join: inputs of 2^32 rows or more");
+    if (nr == 0) {
+        auto none = make_table(ctx, (int)vars.size(), vars.data(), 0);
+        set_count(none.get(), 0);
+        return none;
+    }
     PendingJoin pj;
     std::vector<BigJoinReq> reqs(1);
     BigCount &q = reqs[0].c;
