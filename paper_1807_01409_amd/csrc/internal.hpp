@@ -13,6 +13,7 @@
 #include <string>
 #include <vector>
 
+#include "idcounts.hpp"
 #include "../../include/tid.h"
 
 namespace tid {
@@ -183,47 +184,6 @@ constexpr size_t kAlign = 256;
 // Chunked-compaction launch stamps run 1..kEpochMax; then the slots are zeroed.
 constexpr uint32_t kEpochMax = (1u << 23) - 1;
 inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a; }
-
-}  // namespace tid
-
-namespace tid {
-
-// How many triples hold each ID at one position, on the host: one byte an ID
-// (255: the count is in `big`), and per block of 256 IDs the triples and the
-// `big` entries of all IDs before it.  Eight and a half bits an ID instead of the
-// 64 of a cumulative count, which is what loading a graph waits for: the copy to
-// the host and the first touch of its pages.
-struct IdCounts {
-    static constexpr uint32_t kBlock = 256;
-    static constexpr uint32_t kBig = 255;
-    struct Mem {
-        std::unique_ptr<uint8_t[]> bytes;   // of every position
-        std::unique_ptr<uint64_t[]> rows;   // per block: triples before it
-        std::unique_ptr<uint64_t[]> nbig;   // per block: `big` entries before it
-        std::unique_ptr<uint32_t[]> big;
-    };
-    std::shared_ptr<Mem> mem;               // shared by a graph's positions
-    uint64_t first = 0;                     // the position's first block in `mem`
-    uint64_t ids = 0;                       // IDs 0 .. ids - 1 (0: not counted)
-    uint64_t total = 0;                     // triples
-    bool empty() const { return ids == 0; }
-    // triples whose position holds an ID below `id`
-    uint64_t below(uint64_t id) const {
-        if (id >= ids) return total;
-        const uint64_t b = first + id / kBlock;
-        uint64_t s = mem->rows[b] - mem->rows[first];
-        const uint8_t *c = mem->bytes.get() + b * kBlock;
-        uint32_t sum = 0, nbig = 0;
-        for (uint32_t i = 0; i < id % kBlock; ++i) {
-            sum += c[i];
-            nbig += c[i] == kBig;
-        }
-        s += sum;
-        const uint32_t *big = mem->big.get() + mem->nbig[b];
-        for (uint32_t i = 0; i < nbig; ++i) s += big[i] - kBig;
-        return s;
-    }
-};
 
 }  // namespace tid
 

@@ -426,10 +426,17 @@ __global__ void list_big(const uint32_t *__restrict__ bins, uint64_t nblocks,
 
 void exclusive_scan_async(tid_ctx *ctx, const uint32_t *in, uint64_t n, uint64_t *out);
 
-// Device bins (nblocks blocks; counts below 2^32 in all per position) to
-// the host.
+// Device bins (nblocks blocks) of n triples to the host.  A block's sum is 32
+// bits in pack_counts; from 2^32 triples on, the host sums the bins itself.
 static std::shared_ptr<IdCounts::Mem> counts_to_host(tid_ctx *ctx, const uint32_t *bins,
-                                                     uint64_t nblocks) {
+                                                     uint64_t nblocks, uint64_t n) {
+    if (n >= (1ull << 32)) {
+        std::vector<uint32_t> host(nblocks * IdCounts::kBlock);
+        TID_HIP(hipMemcpyAsync(host.data(), bins, host.size() * sizeof(uint32_t),
+                               hipMemcpyDeviceToHost, ctx->stream));
+        ctx->sync();
+        return counts_of_bins(host.data(), nblocks);
+    }
     DevBuf bytes(ctx, nblocks * IdCounts::kBlock), rows(ctx, nblocks * 4), nbig(ctx, nblocks * 4),
         offs(ctx, 2 * (nblocks + 1) * 8);
     uint64_t *r = offs.get<uint64_t>(), *b = r + nblocks + 1;
@@ -439,9 +446,9 @@ static std::shared_ptr<IdCounts::Mem> counts_to_host(tid_ctx *ctx, const uint32_
     TID_HIP(hipGetLastError());
     exclusive_scan_async(ctx, rows.get<const uint32_t>(), nblocks, r);
     exclusive_scan_async(ctx, nbig.get<const uint32_t>(), nblocks, b);
-    uint64_t n = 0;
-    read_words(ctx, {b + nblocks}, &n);
-    DevBuf big(ctx, std::max<uint64_t>(n, 1) * 4);
+    uint64_t nlarge = 0;
+    read_words(ctx, {b + nblocks}, &nlarge);
+    DevBuf big(ctx, std::max<uint64_t>(nlarge, 1) * 4);
     hipLaunchKernelGGL(list_big, dim3(grid), dim3(256), 0, ctx->stream, bins, nblocks, b,
                        big.get<uint32_t>());
     TID_HIP(hipGetLastError());
@@ -449,14 +456,14 @@ static std::shared_ptr<IdCounts::Mem> counts_to_host(tid_ctx *ctx, const uint32_
     m->bytes.reset(new uint8_t[nblocks * IdCounts::kBlock]);
     m->rows.reset(new uint64_t[nblocks + 1]);
     m->nbig.reset(new uint64_t[nblocks + 1]);
-    m->big.reset(new uint32_t[std::max<uint64_t>(n, 1)]);
+    m->big.reset(new uint32_t[std::max<uint64_t>(nlarge, 1)]);
     auto get = [&](void *dst, const void *src, size_t len) {
         if (len) TID_HIP(hipMemcpyAsync(dst, src, len, hipMemcpyDeviceToHost, ctx->stream));
     };
     get(m->bytes.get(), bytes.get(), nblocks * IdCounts::kBlock);
     get(m->rows.get(), r, (nblocks + 1) * 8);
     get(m->nbig.get(), b, (nblocks + 1) * 8);
-    get(m->big.get(), big.get(), n * 4);
+    get(m->big.get(), big.get(), nlarge * 4);
     ctx->sync();
     return m;
 }
@@ -530,7 +537,7 @@ void load_triples(tid_ctx *ctx, tid_graph *g, const uint32_t *from, int on_devic
         TID_HIP(hipGetLastError());
     }
     const auto mem = counts_to_host(ctx, hist.get<const uint32_t>(),
-                                    total / sizeof(uint32_t) / IdCounts::kBlock);
+                                    total / sizeof(uint32_t) / IdCounts::kBlock, g->n);
     for (int x = 0; x < 3; ++x) {
         if (!a.nbins[x]) continue;
         g->counts[x].mem = mem;
@@ -608,9 +615,13 @@ void chunk_stats(tid_ctx *ctx, tid_graph *v) {
     hipLaunchKernelGGL(hist3_kernel, dim3(hb), dim3(kHistBlock), 0, ctx->stream, v->triples(),
                        v->n, a);
     TID_HIP(hipGetLastError());
+    const uint64_t blocks = bytes / sizeof(uint32_t) / IdCounts::kBlock;
+    auto mem = counts_to_host(ctx, hist.get<const uint32_t>(), blocks, v->n);
+    // a predicate of 2^32 triples or more wraps in its bin: no counts then, and
+    // every bound is the view's triples
+    if (mem->rows[blocks] != v->n) return;
     IdCounts &c = v->counts[1];
-    c.mem = counts_to_host(ctx, hist.get<const uint32_t>(),
-                           bytes / sizeof(uint32_t) / IdCounts::kBlock);
+    c.mem = std::move(mem);
     c.ids = a.nbins[1];
     c.total = v->n;
 }
