@@ -384,7 +384,8 @@ void tid_serve_close(tid_server *s);
    the terms s, p, o of triple 0, then triple 1, and so on.  rows_out (device,
    3n uint32) receives the rows (row-major, the tid_load layout); *dict the
    dictionary (device resident).  TID_E_UNSUPPORTED if two different terms
-   share a 64-bit hash (checked, never merged).  Synchronises. */
+   share a 64-bit hash (checked, never merged), or a term has 2^32 bytes or
+   more.  Synchronises. */
 tid_status tid_encode(tid_ctx *ctx, const uint8_t *bytes, uint64_t nbytes,
                       const uint64_t *offsets, uint64_t n, int on_device, uint32_t *rows_out,
                       tid_dict **dict);

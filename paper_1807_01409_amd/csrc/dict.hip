@@ -81,7 +81,8 @@ struct Terms {
     const uint64_t *off;
     uint64_t nbytes, m;
     uint32_t *falls, *past;  // offsets that fall, or reach past the bytes
-    // length of term t; 0 if its offsets are bad
+    uint32_t *wide;          // a term of 2^32 bytes or more: lengths are summed as 32-bit words
+    // length of term t; 0 if it is refused
     __device__ __forceinline__ uint64_t length(uint64_t t, uint64_t &at) const {
         at = off[t];
         const uint64_t end = off[t + 1];
@@ -91,6 +92,10 @@ struct Terms {
         }
         if (end > nbytes) {
             dev::raise(past);
+            return 0;
+        }
+        if (end - at >> 32) {
+            dev::raise(wide);
             return 0;
         }
         return end - at;
@@ -236,12 +241,12 @@ __global__ void decode_copy(const uint32_t *ids, uint64_t n, const uint64_t *dof
     }
 }
 
-// The context's three pinned flags of a dictionary call.  Their kernels have
+// The context's four pinned flags of a dictionary call.  Their kernels have
 // run when the call ends, however it ends, so the next call may clear them.
 struct Flags {
     tid_ctx *ctx;
     explicit Flags(tid_ctx *c) : ctx(c) {
-        for (int x = 0; x < 3; ++x) at(x)[0] = 0;
+        for (int x = 0; x < 4; ++x) at(x)[0] = 0;
     }
     Flags(const Flags &) = delete;
     Flags &operator=(const Flags &) = delete;
@@ -275,7 +280,7 @@ std::unique_ptr<tid_dict> encode(tid_ctx *ctx, const uint8_t *bytes, uint64_t nb
     // Inputs on the device: buffers on the context's device are read where they
     // are, unless rows would be written over them or the offsets are misaligned.
     DevBuf bytes_in, off_in;
-    Terms in{bytes, offsets, nbytes, m, nullptr, nullptr};
+    Terms in{bytes, offsets, nbytes, m, nullptr, nullptr, nullptr};
     const auto kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     if (nbytes && (!on_device || overlap(bytes, nbytes, rows, m * 4) ||
                    !on_this_device(ctx, bytes))) {
@@ -292,6 +297,7 @@ std::unique_ptr<tid_dict> encode(tid_ctx *ctx, const uint8_t *bytes, uint64_t nb
     const Flags flags(ctx);
     in.falls = flags.at(0);
     in.past = flags.at(1);
+    in.wide = flags.at(3);
     // 1-2: the first appearance of every term.  The table is 2/3 full if no
     // term repeats, and is given back before the prefix sums.
     DevBuf lead(ctx, m * 4), first(ctx, m * 4), len(ctx, m * 4);
@@ -317,6 +323,7 @@ std::unique_ptr<tid_dict> encode(tid_ctx *ctx, const uint8_t *bytes, uint64_t nb
     read_words(ctx, {rank.get<const uint64_t>() + m, place.get<const uint64_t>() + m}, sums);
     TID_REQUIRE(!flags.raised(0), TID_E_INVALID_ARG, "encode: offsets must not fall");
     TID_REQUIRE(!flags.raised(1), TID_E_INVALID_ARG, "encode: offsets past the bytes");
+    TID_REQUIRE(!flags.raised(3), TID_E_UNSUPPORTED, "encode: a term of 2^32 bytes or more");
     TID_REQUIRE(!flags.raised(2), TID_E_UNSUPPORTED,
                 "encode: two different terms share a 64-bit hash; not encoded");
     const uint64_t d = sums[0], total = sums[1];
