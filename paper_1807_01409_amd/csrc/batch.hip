@@ -906,7 +906,9 @@ void flush_big_count(tid_ctx *ctx, std::vector<BigJoinReq> &reqs,
     std::memcpy(host.data() + o_rb, rbase.data(), (J + 1) * 8);
     std::memcpy(host.data() + o_lt, ltile.data(), (J + 1) * 8);
     std::memset(host.data() + o_work, 0, 8);
-    TID_HIP(hipMemcpyAsync(base, host.data(), o_slots, hipMemcpyHostToDevice, ctx->stream));
+    ctx->uploads.push_back(std::move(host));
+    TID_HIP(hipMemcpyAsync(base, ctx->uploads.back().data(), o_slots, hipMemcpyHostToDevice,
+                           ctx->stream));
     const BigCount *dj = reinterpret_cast<const BigCount *>(base + o_jobs);
     const uint64_t *dtb = reinterpret_cast<const uint64_t *>(base + o_tb);
     const uint64_t *drb = reinterpret_cast<const uint64_t *>(base + o_rb);
@@ -964,11 +966,11 @@ void flush_big_expand(tid_ctx *ctx, const BigArena &arena, std::vector<BigExpand
     std::vector<char> host(bytes_jobs + (J + 1) * 8);
     std::memcpy(host.data(), jobs.data(), J * sizeof(BigExpand));
     std::memcpy(host.data() + bytes_jobs, obase.data(), (J + 1) * 8);
-    bs.host_keep.push_back(std::move(host));
-    bs.keep.emplace_back(ctx, bs.host_keep.back().size());
+    ctx->uploads.push_back(std::move(host));
+    const std::vector<char> &table = ctx->uploads.back();
+    bs.keep.emplace_back(ctx, table.size());
     char *d = bs.keep.back().get<char>();
-    TID_HIP(hipMemcpyAsync(d, bs.host_keep.back().data(), bs.host_keep.back().size(),
-                           hipMemcpyHostToDevice, ctx->stream));
+    TID_HIP(hipMemcpyAsync(d, table.data(), table.size(), hipMemcpyHostToDevice, ctx->stream));
     uint64_t tiles = 0;
     for (const BigExpand &b : jobs) tiles += b.tile1 - b.tile0;
     if (total)

@@ -120,6 +120,9 @@ struct tid_ctx {
 
     void *alloc(size_t bytes);
     void free(void *p, size_t bytes);
+    // Host tables that queued copies start from.  The runtime may read them at any
+    // time until the stream has passed the copy, so they are kept until sync().
+    std::vector<std::vector<char>> uploads;
     // stamp for the next chunked launch; *state gets the slot area of `bytes`
     uint32_t next_epoch(size_t bytes, uint64_t **state);
     void sync();

@@ -591,7 +591,10 @@ uint32_t tid_ctx::next_epoch(size_t bytes, uint64_t **state) {
     return epoch;
 }
 
-void tid_ctx::sync() { TID_HIP(hipStreamSynchronize(stream)); }
+void tid_ctx::sync() {
+    TID_HIP(hipStreamSynchronize(stream));
+    uploads.clear();
+}
 
 void tid_ctx::check_flags() const {
     TID_REQUIRE(*static_cast<const volatile uint32_t *>(d_flags) == 0, TID_E_INTERNAL,
