@@ -898,7 +898,9 @@ void merge_sort_rows(tid_ctx *ctx, const tid_table *in, uint64_t n, tid_table *o
 void merge_sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &all,
                              std::vector<DevBuf> &keep,
                              std::vector<std::vector<char>> &host_keep) {
-    // chunks of jobs in order, each with at most kChunkBytes of keys (a larger job alone)
+    // chunks of jobs in order, each with at most kChunkBytes of keys (a larger job
+    // alone); a chunk's key buffers go back, in stream order, before the next
+    // chunk's are taken
     constexpr uint64_t kChunkBytes = 4ull << 30;
     for (size_t j0 = 0; j0 < all.size();) {
         std::vector<RowJob> by_words[kMaxWords + 1];
@@ -953,7 +955,6 @@ void merge_sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &all,
             else if (w == 3) sort_many<3>(ctx, v, dev + first[w]);
             else sort_many<4>(ctx, v, dev + first[w]);
         }
-        keep.push_back(std::move(arena));
         j0 = j1;
     }
 }

@@ -871,9 +871,9 @@ std::unique_ptr<tid_table> sort_rows(tid_ctx *ctx, const tid_table *t, uint64_t 
 // Row sorts of many tables of one round.  Every table needs its column bounds
 // on the host and fewer than 2^32 rows; each output table is allocated by the
 // caller with n rows.  The tables the merge sort takes share its launches;
-// the others are sorted one by one.  Job tables, key arrays and permutations
-// go into `keep` / `host_keep`, which the caller holds until the stream has
-// passed these launches.
+// the others are sorted one by one.  Job tables go into `keep` / `host_keep`,
+// which the caller holds until the stream has passed these launches; key arrays
+// and permutations go back in stream order.
 void sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &jobs,
                        std::vector<DevBuf> &keep, std::vector<std::vector<char>> &host_keep) {
     std::vector<RowSortJob> merged;
@@ -885,8 +885,8 @@ void sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &jobs,
             merged.push_back(job);
             continue;
         }
-        keep.push_back(sort_permutation(ctx, job.in, job.n));
-        gather_table(ctx, job.in, keep.back().get<const uint32_t>(), job.n, job.out);
+        const DevBuf perm = sort_permutation(ctx, job.in, job.n);
+        gather_table(ctx, job.in, perm.get<const uint32_t>(), job.n, job.out);
     }
     if (merged.size() == 1)
         merge_sort_rows(ctx, merged[0].in, merged[0].n, merged[0].out, 0);
