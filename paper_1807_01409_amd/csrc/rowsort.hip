@@ -758,8 +758,10 @@ bool radix_better(uint64_t n, int bits) {
     return n >= (passes <= 4 ? 1ull << 19 : passes <= 6 ? 3ull << 20 : 3ull << 22);
 }
 
+// One table; false, and nothing done, if there is no memory for two or more
+// words a row: the radix sort of row numbers takes 24 B a row for any width.
 template <int W>
-void sort_one(tid_ctx *ctx, RowJob &p) {
+bool sort_one(tid_ctx *ctx, RowJob &p) {
     allow_lds<W>(ctx);
     constexpr size_t lds = (size_t)tile_rows(W) * 8 * W;
     // DISTINCT of rows that fit one large tile is done there
@@ -770,20 +772,23 @@ void sort_one(tid_ctx *ctx, RowJob &p) {
         p.levels = 0;
         for (uint64_t run = (uint64_t)kSmallTile * kVT; run < p.n; run *= kWays) ++p.levels;
     }
-    DevBuf keys;
+    const uint32_t mtiles = (p.n + kMergeTile - 1) / kMergeTile;
+    DevBuf keys, kept, first;
+    try {
+        if (p.levels) keys = DevBuf(ctx, 2 * (size_t)p.n * 8 * W);
+        if (p.distinct && p.levels && !(ranked && mtiles <= kFewTiles)) {
+            kept = DevBuf(ctx, (size_t)mtiles * 4);
+            first = DevBuf(ctx, ((size_t)mtiles + 1) * 8);
+        }
+    } catch (const Error &) {
+        if (W == 1) throw;
+        return false;
+    }
     if (p.levels) {
-        const size_t half = (size_t)p.n * 8 * W;
-        keys = DevBuf(ctx, 2 * half);
         p.key[0] = keys.get<uint64_t>();
         p.key[1] = p.key[0] + (size_t)p.n * W;
     }
-    const uint32_t mtiles = (p.n + kMergeTile - 1) / kMergeTile;
-    DevBuf kept, first;
-    if (p.distinct && p.levels && !(ranked && mtiles <= kFewTiles)) {
-        kept = DevBuf(ctx, (size_t)mtiles * 4);
-        first = DevBuf(ctx, ((size_t)mtiles + 1) * 8);
-        p.kept = kept.get<uint32_t>();
-    }
+    p.kept = kept.get<uint32_t>();
     int from = p.levels & 1;  // the buffer of the sorted keys
     if (radix) {
         hipLaunchKernelGGL(rows_to_words, dim3(mtiles), dim3(kMergeBlock), 0, ctx->stream, p);
@@ -828,11 +833,12 @@ void sort_one(tid_ctx *ctx, RowJob &p) {
             TID_HIP(hipGetLastError());
         }
     }
-    if (!p.kept) return;
+    if (!p.kept) return true;
     exclusive_scan_async(ctx, p.kept, mtiles, first.get<uint64_t>());
     hipLaunchKernelGGL(kept_to_columns<W>, dim3(mtiles), dim3(kMergeBlock), 0, ctx->stream, p,
                        from, first.get<const uint64_t>());
     TID_HIP(hipGetLastError());
+    return true;
 }
 
 template <int W>
@@ -882,22 +888,23 @@ bool rows_mergeable(const tid_table *t, uint64_t n) {
 
 // The n >= 1 rows of `in` in lexicographic order into `out` (n rows
 // allocated); distinct = 1: without repeats, the count left to the kernels.
-void merge_sort_rows(tid_ctx *ctx, const tid_table *in, uint64_t n, tid_table *out,
+// False, and nothing done, if there is no memory for the keys.
+bool merge_sort_rows(tid_ctx *ctx, const tid_table *in, uint64_t n, tid_table *out,
                      int distinct) {
     const int w = key_words(in);
     RowJob p = row_job(in, out, n, w, distinct);
     if (distinct) p.count = out->d_count;
-    if (w == 1) sort_one<1>(ctx, p);
-    else if (w == 2) sort_one<2>(ctx, p);
-    else if (w == 3) sort_one<3>(ctx, p);
-    else sort_one<4>(ctx, p);
+    return w == 1 ? sort_one<1>(ctx, p) : w == 2 ? sort_one<2>(ctx, p)
+         : w == 3 ? sort_one<3>(ctx, p) : sort_one<4>(ctx, p);
 }
 
 // The same for many tables in shared launches (no DISTINCT, counts set by the
-// caller); every table must be rows_mergeable.
-void merge_sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &all,
-                             std::vector<DevBuf> &keep,
-                             std::vector<std::vector<char>> &host_keep) {
+// caller); every table must be rows_mergeable.  Returns the jobs that there was
+// no memory for, with nothing done for them.
+std::vector<RowSortJob> merge_sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &all,
+                                                std::vector<DevBuf> &keep,
+                                                std::vector<std::vector<char>> &host_keep) {
+    std::vector<RowSortJob> left;
     // chunks of jobs in order, each with at most kChunkBytes of keys (a larger job
     // alone); a chunk's key buffers go back, in stream order, before the next
     // chunk's are taken
@@ -915,7 +922,14 @@ void merge_sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &all,
             bytes += need;
             by_words[w].push_back(p);
         }
-        DevBuf arena(ctx, std::max<uint64_t>(bytes, 8));
+        DevBuf arena;
+        try {
+            arena = DevBuf(ctx, std::max<uint64_t>(bytes, 8));
+        } catch (const Error &) {
+            left.insert(left.end(), all.begin() + j0, all.begin() + j1);
+            j0 = j1;
+            continue;
+        }
         uint64_t *at = arena.get<uint64_t>();
         std::vector<RowJob> table;
         size_t first[kMaxWords + 2] = {};
@@ -957,6 +971,7 @@ void merge_sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &all,
         }
         j0 = j1;
     }
+    return left;
 }
 
 }  // namespace tid

@@ -33,10 +33,10 @@
 namespace tid {
 
 bool rows_mergeable(const tid_table *t, uint64_t n);
-void merge_sort_rows(tid_ctx *ctx, const tid_table *in, uint64_t n, tid_table *out, int distinct);
-void merge_sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &all,
-                             std::vector<DevBuf> &keep,
-                             std::vector<std::vector<char>> &host_keep);
+bool merge_sort_rows(tid_ctx *ctx, const tid_table *in, uint64_t n, tid_table *out, int distinct);
+std::vector<RowSortJob> merge_sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &all,
+                                                std::vector<DevBuf> &keep,
+                                                std::vector<std::vector<char>> &host_keep);
 
 constexpr int kRadixBits = 8;                 // digit of the small sort
 constexpr uint32_t kRadix = 1u << kRadixBits;
@@ -854,8 +854,7 @@ std::unique_ptr<tid_table> sort_rows(tid_ctx *ctx, const tid_table *t, uint64_t 
         set_count(sorted.get(), n);
         return sorted;
     }
-    if (rows_mergeable(t, n)) {
-        merge_sort_rows(ctx, t, n, sorted.get(), distinct);
+    if (rows_mergeable(t, n) && merge_sort_rows(ctx, t, n, sorted.get(), distinct)) {
         if (distinct) return sorted;  // its count is still to come
         sorted->nrows = n;
         sorted->count_known = true;
@@ -876,22 +875,24 @@ std::unique_ptr<tid_table> sort_rows(tid_ctx *ctx, const tid_table *t, uint64_t 
 // and permutations go back in stream order.
 void sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &jobs,
                        std::vector<DevBuf> &keep, std::vector<std::vector<char>> &host_keep) {
-    std::vector<RowSortJob> merged;
+    std::vector<RowSortJob> merged, alone;
     for (const RowSortJob &job : jobs) {
         TID_REQUIRE(job.in->maxv_known && job.n >= 1 && job.n < (1ull << 32) &&
                         job.in->ncols > 0,
                     TID_E_INTERNAL, "batched sort: bad job");
-        if (rows_mergeable(job.in, job.n)) {
-            merged.push_back(job);
-            continue;
-        }
+        (rows_mergeable(job.in, job.n) ? merged : alone).push_back(job);
+    }
+    if (merged.size() == 1) {
+        if (!merge_sort_rows(ctx, merged[0].in, merged[0].n, merged[0].out, 0))
+            alone.push_back(merged[0]);
+    } else if (!merged.empty()) {
+        for (const RowSortJob &job : merge_sort_rows_batched(ctx, merged, keep, host_keep))
+            alone.push_back(job);
+    }
+    for (const RowSortJob &job : alone) {
         const DevBuf perm = sort_permutation(ctx, job.in, job.n);
         gather_table(ctx, job.in, perm.get<const uint32_t>(), job.n, job.out);
     }
-    if (merged.size() == 1)
-        merge_sort_rows(ctx, merged[0].in, merged[0].n, merged[0].out, 0);
-    else if (!merged.empty())
-        merge_sort_rows_batched(ctx, merged, keep, host_keep);
 }
 
 std::unique_ptr<tid_table> sort_table(tid_ctx *ctx, const tid_table *t, int distinct) {
