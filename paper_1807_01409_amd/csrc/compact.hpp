@@ -287,8 +287,6 @@ __global__ __launch_bounds__(BLOCK) void compact_kernel(Src src, CompactArgs<MAX
             if (dst < o.cap) {
                 TID_FOR_COLS(MAXC, c, o.ncols)
                     dev::put(&o.col[c][dst], stage[o.stage_off + (uint32_t)c * o.stage_cap + r]);
-            } else {
-                dev::raise(&flags[1]);
             }
         }
     }
@@ -318,8 +316,6 @@ __global__ __launch_bounds__(BLOCK) void compact_kernel(Src src, CompactArgs<MAX
                     if (dst < o.cap) {
                         TID_FOR_COLS(MAXC, c, o.ncols)
                             dev::put(&o.col[c][dst], src.value(j, c, item[it], i));
-                    } else {
-                        dev::raise(&flags[1]);
                     }
                 }
             }
@@ -490,8 +486,6 @@ __global__ __launch_bounds__(BLOCK) void chunk_compact_kernel(Src src, CompactAr
                 if (dst < o.cap) {
                     TID_FOR_COLS(MAXC, c, o.ncols)
                         dev::put(&o.col[c][dst], pb[o.stage_off + (uint32_t)c * o.stage_cap + r]);
-                } else {
-                    dev::raise(&flags[1]);
                 }
             }
         }
@@ -522,8 +516,6 @@ __global__ __launch_bounds__(BLOCK) void chunk_compact_kernel(Src src, CompactAr
                         if (dst < o.cap) {
                             TID_FOR_COLS(MAXC, c, o.ncols)
                                 dev::put(&o.col[c][dst], src.value(j, c, item[it], i));
-                        } else {
-                            dev::raise(&flags[1]);
                         }
                     }
                 }
@@ -721,7 +713,7 @@ void launch_chunked(tid_ctx *ctx, const Src &src, CompactArgs<MAXK, MAXC> &a, in
 // `stage_words` words of LDS, fixes the ranges (a.P, a.range, a.k) and
 // returns the state words the launch needs (the ticket and done counters in
 // one word, then k * P count words); block_ranged_launch starts the kernel
-// with that state and a.epoch, and `flags` (2 words: spin limit, overflow).
+// with that state and a.epoch, and `flags` (a word: spin limit).
 template <class Src, int BLOCK, int IPT, int MAXK, int MAXC, bool PREFETCH = false>
 size_t block_ranged_layout(tid_ctx *ctx, const Src &src, CompactArgs<MAXK, MAXC> &a, int k,
                            uint32_t stage_words) {

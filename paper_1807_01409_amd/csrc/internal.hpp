@@ -110,7 +110,7 @@ struct tid_ctx {
     void *ep_state = nullptr;
     size_t ep_bytes = 0;
     uint32_t epoch = 0;
-    // pinned host words that kernels write: 0-1 error and overflow flags, 2 the
+    // pinned host words that kernels write: 0 the error flag, 2 the
     // read probe's sink, 4-7 of a dictionary call
     uint32_t *d_flags = nullptr;
     tid::HostWords words;

@@ -198,8 +198,6 @@ __global__ __launch_bounds__(BLOCK) void scan_multi_kernel(const uint32_t *__res
             if (dst < o.cap) {
                 TID_FOR_COLS(3, c, o.ncols)
                     o.col[c][dst] = stage[o.stage_off + (uint32_t)c * o.stage_cap + r];
-            } else {
-                dev::raise(&flags[1]);
             }
         }
     }
@@ -222,8 +220,6 @@ __global__ __launch_bounds__(BLOCK) void scan_multi_kernel(const uint32_t *__res
                     const uint64_t dst = base + s_off[j][it * NW + wave] + dev::rank_in_mask(b);
                     if (dst < o.cap) {
                         TID_FOR_COLS(3, c, o.ncols) o.col[c][dst] = pick(t[it], q.src[c]);
-                    } else {
-                        dev::raise(&flags[1]);
                     }
                 }
             }

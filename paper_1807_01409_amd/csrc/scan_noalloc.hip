@@ -13,7 +13,7 @@ namespace tid {
 // ---------------------------------------------------------------------------
 // Allocation-free scan.  The
 // block-ranged kernel's cross-workgroup state (ticket and done counters, one
-// epoch-stamped count word per range) and its two flag words live in a
+// epoch-stamped count word per range) and its flag word live in a
 // file-scope device array.  Its address is looked up once per device at
 // context creation and kept; host code never passes the array's own name.
 // Every call on a device shares the array: calls that overlap on one device
@@ -21,7 +21,7 @@ namespace tid {
 // ---------------------------------------------------------------------------
 
 // words: [0] ticket and done counters; [1, 1 + 4096] one count word per range
-// (at most 512 x 8 = 4096 ranges per launch); [kNoAllocFlagWord] two flags
+// (at most 512 x 8 = 4096 ranges per launch); [kNoAllocFlagWord] the error flag
 constexpr size_t kNoAllocRanges = 512 * kPrefixPer;
 constexpr size_t kNoAllocFlagWord = 1 + kNoAllocRanges;
 constexpr size_t kNoAllocWords = kNoAllocFlagWord + 1;

@@ -143,8 +143,7 @@ __device__ __forceinline__ uint32_t wide_seg_of(const WideArgs &a, uint64_t v) {
 template <bool WRITE, bool SLICE>
 __device__ __forceinline__ void wide_walk(const WideArgs &a, const WidePat *s_pat,
                                           const uint32_t *s_bucket, const uint16_t *s_ids,
-                                          uint32_t *s_run, uint64_t r0, uint64_t r1,
-                                          uint32_t *flags) {
+                                          uint32_t *s_run, uint64_t r0, uint64_t r1) {
     const int lane = dev::lane_id();
     const uint64_t lt = (1ull << lane) - 1ull;
     // segment pass: the segment holding the current step (steps only move forward)
@@ -211,8 +210,6 @@ __device__ __forceinline__ void wide_walk(const WideArgs &a, const WidePat *s_pa
                             const uint32_t src = (q.flags >> (8 + 2 * cc)) & 3u;
                             o.col[cc][pos] = t[it].v[src];
                         }
-                    } else {
-                        dev::raise(&flags[1]);
                     }
                 }
                 if (lane == __builtin_ctzll(peers)) s_run[pid] = before + (uint32_t)__popcll(peers);
@@ -240,7 +237,7 @@ __device__ __forceinline__ WideLds wide_lds(uint32_t *lds, int k, bool slice) {
 }
 
 template <bool SLICE>
-__global__ __launch_bounds__(kWideBlock) void wide_count(WideArgs a, uint32_t *flags) {
+__global__ __launch_bounds__(kWideBlock) void wide_count(WideArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     const WideLds l = wide_lds(lds, a.k, SLICE);
     WidePat *s_pat = l.pat;
@@ -256,7 +253,7 @@ __global__ __launch_bounds__(kWideBlock) void wide_count(WideArgs a, uint32_t *f
     if (gw < a.W) {
         const uint64_t r0 = a.wbound ? a.wbound[gw] : (uint64_t)gw * a.sub;
         const uint64_t r1 = a.wbound ? a.wbound[gw + 1] : min(a.n, r0 + a.sub);
-        wide_walk<false, SLICE>(a, s_pat, s_bucket, s_ids, run, r0, r1, flags);
+        wide_walk<false, SLICE>(a, s_pat, s_bucket, s_ids, run, r0, r1);
         for (int j = lane; j < a.k; j += dev::kWave) a.cnt[(size_t)gw * a.k + j] = run[j];
     }
 }
@@ -293,7 +290,7 @@ __global__ __launch_bounds__(kColBlock) void wide_offsets(WideArgs a) {
 }
 
 template <bool SLICE>
-__global__ __launch_bounds__(kWideBlock) void wide_write(WideArgs a, uint32_t *flags) {
+__global__ __launch_bounds__(kWideBlock) void wide_write(WideArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     const WideLds l = wide_lds(lds, a.k, SLICE);
     WidePat *s_pat = l.pat;
@@ -310,7 +307,7 @@ __global__ __launch_bounds__(kWideBlock) void wide_write(WideArgs a, uint32_t *f
     if (gw < a.W) {
         const uint64_t r0 = a.wbound ? a.wbound[gw] : (uint64_t)gw * a.sub;
         const uint64_t r1 = a.wbound ? a.wbound[gw + 1] : min(a.n, r0 + a.sub);
-        wide_walk<true, SLICE>(a, s_pat, s_bucket, s_ids, run, r0, r1, flags);
+        wide_walk<true, SLICE>(a, s_pat, s_bucket, s_ids, run, r0, r1);
     }
 }
 
@@ -513,7 +510,7 @@ static void wide_pass(tid_ctx *ctx, WideSource src, const tid_pattern *pats, int
     a.W = (uint32_t)W;
     a.cnt = cnt.get<uint32_t>();
     const unsigned blocks = (unsigned)((W + kWideNW - 1) / kWideNW);
-    void *args[] = {&a, &ctx->d_flags};
+    void *args[] = {&a};
     TID_HIP(hipLaunchKernel(count_fn, dim3(blocks), dim3(kWideBlock), args, lds, ctx->stream));
     TID_HIP(hipGetLastError());
     hipLaunchKernelGGL(wide_offsets, dim3((unsigned)((k + dev::kWave - 1) / dev::kWave)),
