@@ -234,9 +234,6 @@ tid_status tid_load(tid_ctx *ctx, const uint32_t *triples, uint64_t n, int src_o
         g = std::make_unique<tid_graph>();
         g->ctx = ctx;
         g->n = n;
-        const size_t bytes = (size_t)n * 12;
-        g->data = tid::DevBuf(ctx, bytes + 64);
-        TID_HIP(hipMemsetAsync(g->data.get<char>() + bytes, 0, 64, ctx->stream));
         tid::load_triples(ctx, g.get(), triples, src_on_device);
         ctx->sync();
     });

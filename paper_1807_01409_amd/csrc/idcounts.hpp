@@ -58,11 +58,16 @@ inline std::shared_ptr<IdCounts::Mem> counts_of_bins(const uint32_t *bins, uint6
     for (uint64_t b = 0; b < blocks; ++b) {
         m->rows[b] = rows;
         m->nbig[b] = big.size();
-        for (uint64_t i = b * IdCounts::kBlock; i < (b + 1) * IdCounts::kBlock; ++i) {
-            m->bytes[i] = (uint8_t)std::min(bins[i], IdCounts::kBig);
-            if (bins[i] >= IdCounts::kBig) big.push_back(bins[i]);
-            rows += bins[i];
+        const uint32_t *in = bins + b * IdCounts::kBlock;
+        uint8_t *out = m->bytes.get() + b * IdCounts::kBlock;
+        uint32_t large = 0;
+        for (uint32_t i = 0; i < IdCounts::kBlock; ++i) {  // no branches: vector code
+            out[i] = (uint8_t)std::min(in[i], IdCounts::kBig);
+            large += in[i] >= IdCounts::kBig;
+            rows += in[i];
         }
+        for (uint32_t i = 0; large && i < IdCounts::kBlock; ++i)
+            if (in[i] >= IdCounts::kBig) big.push_back(in[i]);
     }
     m->rows[blocks] = rows;
     m->nbig[blocks] = big.size();

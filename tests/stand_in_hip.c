@@ -18,7 +18,7 @@ uint64_t host_word = 0;        /* every 64-bit word of new pinned memory */
 uint32_t read_word = 1;        /* every 32-bit word of a copy to the host */
 uint64_t live_bytes = 0, peak_bytes = 0, most_bytes = ~0ull; /* device memory */
 uint64_t copies = 0, changed = 0;   /* copies from the host; those whose source changed */
-char launched[1 << 20];        /* names of the launched kernels, a line each */
+char launched[1 << 20];        /* names of the launched kernels and the copies, a line each */
 
 static uint64_t next_addr = DEVICE_BASE;
 static struct { uint64_t at, bytes; } blocks[MOST];
@@ -27,6 +27,11 @@ static struct { const void *src; void *was; size_t n; } pending[MOST];
 static int npending;
 static struct { const void *fn; char name[160]; } kernels[4096];
 static int nkernels;
+
+static void note(const char *what) {
+    static size_t at;
+    if (at + 200 < sizeof launched) at += (size_t)sprintf(launched + at, "%s\n", what);
+}
 
 int hipMalloc(void **p, size_t n) {
     if (live_bytes + n > most_bytes || nblocks == MOST) return 2; /* out of memory */
@@ -58,6 +63,7 @@ int hipHostMalloc(void **p, size_t n, unsigned flags) {
 int hipHostFree(void *p) { free(p); return 0; }
 int hipMemcpyAsync(void *dst, const void *src, size_t n, int kind, void *stream) {
     (void)stream;
+    note(kind == 1 ? "copy up" : kind == 2 ? "copy down" : "copy across");
     if (kind == 1) {
         ++copies;
         if (npending < MOST && n) {
@@ -129,9 +135,7 @@ int __hipPopCallConfiguration(dim3_t *g, dim3_t *b, size_t *lds, void **s) {
 }
 int hipLaunchKernel(const void *fn, dim3_t g, dim3_t b, void **args, size_t lds, void *s) {
     (void)g; (void)b; (void)args; (void)lds; (void)s;
-    static size_t at;
     for (int i = 0; i < nkernels; ++i)
-        if (kernels[i].fn == fn && at + 200 < sizeof launched)
-            at += (size_t)sprintf(launched + at, "%s\n", kernels[i].name);
+        if (kernels[i].fn == fn) note(kernels[i].name);
     return 0;
 }
