@@ -62,6 +62,7 @@ struct RowJob {
     uint32_t n;
     uint32_t tile0, mtile0;        // the job's first tile in the two kinds of launch
     int32_t levels;                // merge launches the job takes part in
+    uint64_t tag;                  // radix sort of several tables: their order, above the key
     int16_t ncols;
     int16_t distinct;              // one tile: keep the first of equal rows; several: the
                                    // last row_merge keeps them, tile by tile; the last
@@ -661,20 +662,20 @@ __global__ __launch_bounds__(kMergeBlock) void row_merge_many(const RowJob *jobs
 }
 
 // rows of one-word keys to keys, and sorted keys to columns (radix sort)
-__global__ __launch_bounds__(kMergeBlock) void rows_to_words(RowJob p) {
-    const uint32_t t0 = blockIdx.x * kMergeTile, cnt = min(kMergeTile, p.n - t0);
+__device__ __forceinline__ void words_body(const RowJob &p, uint32_t tile) {
+    const uint32_t t0 = tile * kMergeTile, cnt = min(kMergeTile, p.n - t0);
     Key<1> k[kVT];
     pack_rows<1, kMergeBlock>(p, t0, cnt, k);
     const bool whole = cnt == kMergeTile;
 #pragma unroll
     for (int v = 0; v < kVT; ++v) {
         const uint32_t i = whole ? v * kMergeBlock + threadIdx.x : threadIdx.x * kVT + v;
-        if (i < cnt) gstore(p.key[0] + t0 + i, k[v].w[0]);
+        if (i < cnt) gstore(p.key[0] + t0 + i, k[v].w[0] | p.tag);
     }
 }
 
-__global__ __launch_bounds__(kMergeBlock) void words_to_columns(RowJob p, int from) {
-    const uint32_t t0 = blockIdx.x * kMergeTile, cnt = min(kMergeTile, p.n - t0);
+__device__ __forceinline__ void columns_body(const RowJob &p, uint32_t tile, int from) {
+    const uint32_t t0 = tile * kMergeTile, cnt = min(kMergeTile, p.n - t0);
     const uint64_t *key = p.key[from] + t0;
     uint64_t k[kVT];
 #pragma unroll
@@ -685,6 +686,25 @@ __global__ __launch_bounds__(kMergeBlock) void words_to_columns(RowJob p, int fr
             const uint32_t i = v * kMergeBlock + threadIdx.x;
             if (i < cnt) gstore(p.out[c] + t0 + i, column_of<1>(p, c, [&](int) { return k[v]; }));
         }
+}
+
+__global__ __launch_bounds__(kMergeBlock) void rows_to_words(RowJob p) {
+    words_body(p, blockIdx.x);
+}
+
+__global__ __launch_bounds__(kMergeBlock) void words_to_columns(RowJob p, int from) {
+    columns_body(p, blockIdx.x, from);
+}
+
+__global__ __launch_bounds__(kMergeBlock) void rows_to_words_many(const RowJob *jobs, int J) {
+    const RowJob &p = jobs[row_job_of<true>(jobs, J, blockIdx.x)];
+    words_body(p, blockIdx.x - p.mtile0);
+}
+
+__global__ __launch_bounds__(kMergeBlock) void words_to_columns_many(const RowJob *jobs, int J,
+                                                                     int from) {
+    const RowJob &p = jobs[row_job_of<true>(jobs, J, blockIdx.x)];
+    columns_body(p, blockIdx.x - p.mtile0, from);
 }
 
 int bits_of(uint32_t v) { return v ? 32 - __builtin_clz(v) : 0; }
@@ -743,19 +763,34 @@ int key_bits(const RowJob &p) {
     return std::max(1, bits);
 }
 
-// Whether a large table of one-word keys is sorted by the radix passes of
-// sort.hip on the packed keys instead of merge levels: a pass costs about as much
-// as 1.75 levels, whatever the number of rows.  A sort of two columns, merge /
-// radix, in us:
+// Passes of sort_words over keys of so many bits.
+int radix_passes(int bits) { return std::max(1, std::min((bits + 8) / 9, (bits + 9) / 10)); }
+
+// Whether a table of one-word keys is sorted by the radix passes of sort.hip on
+// the packed keys instead of merge levels.  For large tables a pass costs about as
+// much as 1.75 levels, for small ones two and a half.  A sort of two columns (one
+// for 2 and 10 bits), merge (up to 114,688 rows: rank merge) / radix, in us:
+//     bits (passes)   4,000 rows  16,000     100,000    200,000    400,000
+//      2 (1)          60 / 55    77 / 58    93 / 61    99 / 64   113 / 65
+//      8 (1)          60 / 58
+//     10 (1)                     74 / 63    81 / 67   102 / 69   116 / 72
+//     16 (2)                                86 / 90   109 / 94   126 / 97
+//     20 (2)                                86 / 98   109 / 106  126 / 111
+//     26 (3)                                          110 / 121  126 / 121
 //     bits (passes)   500,000 rows    1M          2M          4M          16M
 //     30 (3)          143 / 126   172 / 142   229 / 180   364 / 229  1360 /  693
 //     36 (4)          139 / 132   171 / 149   227 / 181   368 / 242  1363 /  697
 //     46 (5)          138 / 160   171 / 183   226 / 237   366 / 309  1359 /  943
 //     54 (6)          139 / 167   171 / 191   226 / 236   366 / 316  1365 /  943
 //     64 (7)          138 / 202   171 / 231   227 / 306   364 / 400  1364 / 1253
+// Rows of one small tile (1,792) take one launch, which is as good (54 / 55).
 bool radix_better(uint64_t n, int bits) {
-    const int passes = std::min((bits + 8) / 9, (bits + 9) / 10);
-    return n >= (passes <= 4 ? 1ull << 19 : passes <= 6 ? 3ull << 20 : 3ull << 22);
+    const int passes = radix_passes(bits);
+    return n > (passes == 1   ? kSmallTile * kVT
+                : passes == 2 ? kRankRows
+                : passes <= 4 ? (1u << 19) - 1
+                : passes <= 6 ? (3u << 20) - 1
+                              : (3u << 22) - 1);
 }
 
 // One table; false, and nothing done, if there is no memory for two or more
@@ -764,10 +799,12 @@ template <int W>
 bool sort_one(tid_ctx *ctx, RowJob &p) {
     allow_lds<W>(ctx);
     constexpr size_t lds = (size_t)tile_rows(W) * 8 * W;
-    // DISTINCT of rows that fit one large tile is done there
-    const bool ranked = p.n <= kRankRows && !(p.distinct && p.n <= tile_rows(W));
     const int bits = key_bits(p);
-    const bool radix = W == 1 && !ranked && p.levels > 0 && radix_better(p.n, bits);
+    // DISTINCT of rows that fit one large tile is done there
+    const bool one_tile = p.distinct && p.n <= tile_rows(W);
+    const bool radix = W == 1 && !one_tile && radix_better(p.n, bits);
+    const bool ranked = !radix && !one_tile && p.n <= kRankRows;
+    if (radix) p.levels = std::max(p.levels, 1);  // it takes the key buffers
     if (ranked) {
         p.levels = 0;
         for (uint64_t run = (uint64_t)kSmallTile * kVT; run < p.n; run *= kWays) ++p.levels;
