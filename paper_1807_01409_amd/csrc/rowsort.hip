@@ -901,6 +901,67 @@ void sort_many(tid_ctx *ctx, std::vector<RowJob *> jobs, const RowJob *dev) {
     }
 }
 
+// Which of a round's one-word tables are sorted together by radix passes, their
+// order above the keys: those of at most the bits that this returns, besides the
+// order's (0: none).  A pass over R rows takes about 24 us + 13.6 ps a row, a merge
+// level 9.5 us + 7.6 ps for every row of its tables, whose levels grow with the
+// rows; so tables of few bits and many rows take the passes.  More than three
+// passes are left to the levels.  A batch of whole-predicate plans, levels /
+// passes, in us:
+//     8 tables of 100,000 rows, 5 bits     114 /  72
+//     8 of 1M, 5 bits                      491 / 146
+//     8 of 1M, 10 bits                     500 / 202
+//     64 of 400,000, 10 bits              1236 / 708
+//     4 of 5M, 5 bits                     1262 / 250
+int radix_bits_of_round(const std::vector<RowJob> &jobs, int order_bits) {
+    double best = 0;
+    int bits = 0;
+    for (int passes = 0; passes <= 3; ++passes) {
+        const int most = passes ? 10 * passes - order_bits : 0;
+        double rows = 0, us = 0;
+        std::vector<double> merged;  // rows of every level
+        for (const RowJob &p : jobs) {
+            if (p.levels && key_bits(p) <= most) {
+                rows += p.n;
+                continue;
+            }
+            merged.resize(std::max(merged.size(), (size_t)p.levels));
+            for (int l = 0; l < p.levels; ++l) merged[l] += p.n;
+        }
+        if (passes && rows == 0) continue;
+        us += passes * (24 + 13.6e-6 * rows);
+        for (const double m : merged) us += 9.5 + 7.6e-6 * m;
+        if (passes == 0 || us < best) {
+            best = us;
+            bits = most;
+        }
+    }
+    return bits;
+}
+
+// bits that hold 0 .. n - 1
+int index_bits(size_t n) {
+    int bits = 0;
+    while (n > 1 && (n - 1) >> bits) ++bits;
+    return bits;
+}
+
+// Several tables of one-word keys by radix passes of all their rows at once: a
+// row's key has the number of its table above it, so that every table's rows
+// end at its own place.  The jobs' key buffers are parts of two arrays, in order.
+void sort_round(tid_ctx *ctx, const std::vector<RowJob *> &jobs, const RowJob *dev, int bits) {
+    const int J = (int)jobs.size();
+    const RowJob &last = *jobs.back();
+    const uint32_t tiles = last.mtile0 + (last.n + kMergeTile - 1) / kMergeTile;
+    const uint64_t rows = (uint64_t)(last.key[0] - jobs[0]->key[0]) + last.n;
+    hipLaunchKernelGGL(rows_to_words_many, dim3(tiles), dim3(kMergeBlock), 0, ctx->stream, dev, J);
+    TID_HIP(hipGetLastError());
+    const int from = sort_words(ctx, jobs[0]->key[0], jobs[0]->key[1], rows, bits);
+    hipLaunchKernelGGL(words_to_columns_many, dim3(tiles), dim3(kMergeBlock), 0, ctx->stream, dev,
+                       J, from);
+    TID_HIP(hipGetLastError());
+}
+
 }  // namespace
 
 // Whether the merge sort takes a table's rows: column bounds on the host, at
@@ -959,6 +1020,19 @@ std::vector<RowSortJob> merge_sort_rows_batched(tid_ctx *ctx, const std::vector<
             bytes += need;
             by_words[w].push_back(p);
         }
+        // by_words[0]: the one-word tables that are sorted together by radix passes
+        const int few = radix_bits_of_round(by_words[1], index_bits(by_words[1].size()));
+        int bits = 0;
+        if (few) {
+            std::vector<RowJob> rest;
+            for (const RowJob &p : by_words[1])
+                (p.levels && key_bits(p) <= few ? by_words[0] : rest).push_back(p);
+            by_words[1].swap(rest);
+            for (const RowJob &p : by_words[0]) bits = std::max(bits, key_bits(p));
+            for (size_t x = 0; x < by_words[0].size(); ++x)
+                by_words[0][x].tag = (uint64_t)x << bits;
+            bits += index_bits(by_words[0].size());
+        }
         DevBuf arena;
         try {
             arena = DevBuf(ctx, std::max<uint64_t>(bytes, 8));
@@ -970,22 +1044,28 @@ std::vector<RowSortJob> merge_sort_rows_batched(tid_ctx *ctx, const std::vector<
         uint64_t *at = arena.get<uint64_t>();
         std::vector<RowJob> table;
         size_t first[kMaxWords + 2] = {};
-        for (int w = 1; w <= kMaxWords; ++w) {
+        for (int w = 0; w <= kMaxWords; ++w) {
             std::vector<RowJob> &v = by_words[w];
-            std::stable_sort(v.begin(), v.end(),
-                             [](const RowJob &x, const RowJob &y) { return x.n > y.n; });
+            const uint64_t words = std::max(w, 1);
+            uint64_t together = 0;  // rows sorted together: all of one buffer, then the other
+            if (w == 0)
+                for (const RowJob &p : v) together += p.n;
+            else
+                std::stable_sort(v.begin(), v.end(),
+                                 [](const RowJob &x, const RowJob &y) { return x.n > y.n; });
             uint32_t tiles = 0, mtiles = 0;
             for (RowJob &p : v) {
                 if (p.levels) {
                     p.key[0] = at;
-                    p.key[1] = at + (size_t)p.n * w;
-                    at += 2 * (size_t)p.n * w;
+                    p.key[1] = at + (together ? together : p.n * words);
+                    at += (together ? 1 : 2) * p.n * words;
                 }
                 p.tile0 = tiles;
                 p.mtile0 = mtiles;
-                tiles += (p.n + tile_rows(w) - 1) / tile_rows(w);
+                tiles += (p.n + tile_rows(words) - 1) / tile_rows(words);
                 mtiles += (p.n + kMergeTile - 1) / kMergeTile;
             }
+            at += together;
             first[w] = table.size();
             table.insert(table.end(), v.begin(), v.end());
         }
@@ -997,11 +1077,12 @@ std::vector<RowSortJob> merge_sort_rows_batched(tid_ctx *ctx, const std::vector<
         const RowJob *dev = keep.back().get<const RowJob>();
         TID_HIP(hipMemcpyAsync(keep.back().get(), host_keep.back().data(), tb,
                                hipMemcpyHostToDevice, ctx->stream));
-        for (int w = 1; w <= kMaxWords; ++w) {
+        for (int w = 0; w <= kMaxWords; ++w) {
             std::vector<RowJob *> v;
             for (size_t x = first[w]; x < first[w + 1]; ++x) v.push_back(&table[x]);
             if (v.empty()) continue;
-            if (w == 1) sort_many<1>(ctx, v, dev + first[w]);
+            if (w == 0) sort_round(ctx, v, dev, bits);
+            else if (w == 1) sort_many<1>(ctx, v, dev + first[w]);
             else if (w == 2) sort_many<2>(ctx, v, dev + first[w]);
             else if (w == 3) sort_many<3>(ctx, v, dev + first[w]);
             else sort_many<4>(ctx, v, dev + first[w]);

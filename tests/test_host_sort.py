@@ -40,3 +40,32 @@ out = dict(st=st, error=error(ctx), queued=kernels()[done:])
     if distinct and rows <= 7168:       # one large tile
         kinds = {"row_tile_sort"}
     assert sorts(out["queued"]) == kinds
+
+
+@pytest.mark.parametrize("plans,columns,passes", [(2, 2, 0), (2, 1, 2), (64, 1, 2)])
+def test_route_of_a_round(tmp_path, plans, columns, passes):
+    """A round's tables of 300,000 rows with columns of 10 bits: radix passes over
+    all their rows, or six merge levels."""
+    out = stand_in.run(tmp_path, f"""
+from types import SimpleNamespace as NS
+from paper_1807_01409_amd import tid
+ctx = context()
+n = 1 << 20
+word("read_word", ctypes.c_uint32).value = 1000      # the largest ID, and every ID's triples
+g = ctypes.c_void_p()
+assert lib.tid_load(ctx, device(12 * n), n, 1, ctypes.byref(g)) == 0
+word("host_word").value = 300_000                    # every scan's rows
+p = NS(s=0, p=1, o=0, vs=0, vp=-1, vo=1, range_pos=-1, lo=0, hi=0)
+ops = [1, 0, 5, {columns}, 1, 0][:4 + {columns}]     # SCAN, PROJECT
+block = tid._Plans([NS(patterns=[p], ops=ops)] * {plans})
+outs = (ctypes.c_void_p * {plans})()
+done = len(kernels())
+st = lib.tid_query_batch(ctx, g, ctypes.cast(block.pointers(),
+                         ctypes.POINTER(ctypes.POINTER(L.tid_plan))), {plans}, outs)
+out = dict(st=st, error=error(ctx), queued=kernels()[done:])
+""")
+    assert out["st"] == 0, out["error"]
+    q = out["queued"]
+    assert any("row_merge_many" in k for k in q) == (not passes), q
+    assert any("rows_to_words_many" in k for k in q) == bool(passes), q
+    assert sum("radix_scatter" in k for k in q) == passes, q
