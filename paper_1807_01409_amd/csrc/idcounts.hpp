@@ -60,14 +60,20 @@ inline std::shared_ptr<IdCounts::Mem> counts_of_bins(const uint32_t *bins, uint6
         m->nbig[b] = big.size();
         const uint32_t *in = bins + b * IdCounts::kBlock;
         uint8_t *out = m->bytes.get() + b * IdCounts::kBlock;
-        uint32_t large = 0;
-        for (uint32_t i = 0; i < IdCounts::kBlock; ++i) {  // no branches: vector code
+        uint32_t any = 0;
+        for (uint32_t i = 0; i < IdCounts::kBlock; ++i) any |= in[i];
+        if (any < IdCounts::kBig) {  // most blocks: vector code, sums of 32 bits
+            uint32_t sum = 0;
+            for (uint32_t i = 0; i < IdCounts::kBlock; ++i) sum += in[i];
+            for (uint32_t i = 0; i < IdCounts::kBlock; ++i) out[i] = (uint8_t)in[i];
+            rows += sum;
+            continue;
+        }
+        for (uint32_t i = 0; i < IdCounts::kBlock; ++i) {
             out[i] = (uint8_t)std::min(in[i], IdCounts::kBig);
-            large += in[i] >= IdCounts::kBig;
+            if (in[i] >= IdCounts::kBig) big.push_back(in[i]);
             rows += in[i];
         }
-        for (uint32_t i = 0; large && i < IdCounts::kBlock; ++i)
-            if (in[i] >= IdCounts::kBig) big.push_back(in[i]);
     }
     m->rows[blocks] = rows;
     m->nbig[blocks] = big.size();

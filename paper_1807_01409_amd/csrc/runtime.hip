@@ -427,10 +427,10 @@ __global__ void list_big(const uint32_t *__restrict__ bins, uint64_t nblocks,
 void exclusive_scan_async(tid_ctx *ctx, const uint32_t *in, uint64_t n, uint64_t *out);
 
 // Up to so many blocks of bins go to the host as they are: one copy, where the
-// packed ones take five launches, two waits and four copies.  A load of 3000
-// triples with 2,000 / 20,000 / 80,000 / 120,000 / 160,000 IDs in all, packed: 103
-// / 115 / 119 / 121 / 123 us, summed on the host: 57 / 72 / 102 / 122 / 148 us.
-constexpr uint64_t kHostBlocks = 448;
+// packed ones take five launches, two waits and four copies.  A load of 1000
+// triples with 2,000 / 120,000 / 160,000 / 200,000 / 240,000 IDs in all, packed: 103
+// / 120 / 122 / 124 / 126 us, summed on the host: 58 / 98 / 111 / 122 / 134 us.
+constexpr uint64_t kHostBlocks = 800;
 
 // Device bins (nblocks blocks) of n triples to the host: packed on the device,
 // unless they are few, a block's sum could pass 32 bits or there is no memory.

@@ -63,7 +63,7 @@ def test_large_views_are_summed_on_the_host(tmp_path, chunks, on_device):
     out = stand_in.run(tmp_path, f"""
 ctx = context()
 n = (1 << 32) + 4096
-word("read_word", ctypes.c_uint32).value = 200000  # smallest and largest ID, and every count
+word("read_word", ctypes.c_uint32).value = 300000  # smallest and largest ID, and every count
 g, s = ctypes.c_void_p(), ctypes.c_void_p()
 assert lib.tid_load(ctx, device(12 * n), n, 1, ctypes.byref(g)) == 0
 st = lib.tid_serve_open(ctx, g, {chunks}, 1, ctypes.byref(s))
