@@ -49,7 +49,8 @@ void sort_rows_batched(tid_ctx *ctx, const std::vector<RowSortJob> &jobs,
                        std::vector<DevBuf> &keep, std::vector<std::vector<char>> &host_keep);
 
 // Jobs of one round of a batch, launched together; the device job tables
-// and the host copies they came from are kept until the round's wait.
+// and the host copies they came from (some in tid_ctx::uploads) are kept until
+// the round's wait.
 struct BatchState {
     std::vector<JoinJob> count_jobs, expand_jobs;
     std::vector<RowSortJob> row_sorts;

@@ -235,11 +235,10 @@ constexpr uint64_t kHashAutoMaxRows = 1ull << 23;
 struct ExpandArgs {
     const uint64_t *off;    // nq + 1 output offsets per probe position
     const uint32_t *start;  // per probe position: first matching build position
-    const uint32_t *qrow;   // probe position -> probe table row (null: identity)
-    const uint32_t *brow;   // build position -> build table row
+    const uint32_t *qrow;   // probe position -> L row
+    const uint32_t *brow;   // build position -> R row
     const uint32_t *matches;  // left outer join: true match count per probe position
     uint64_t nq, total;
-    int probe_is_left;
     const uint32_t *lcol[TID_MAX_COLS];
     const uint32_t *rcol[TID_MAX_COLS];
     uint32_t *out[TID_MAX_COLS];
@@ -256,16 +255,14 @@ __global__ void join_expand(ExpandArgs a) {
             if (a.off[mid] <= o) lo = mid;
             else hi = mid;
         }
-        const uint32_t pr = a.qrow ? a.qrow[lo] : (uint32_t)lo;
+        const uint32_t lr = a.qrow[lo];
         if (a.matches && a.matches[lo] == 0) {  // a left row with no partner
-            for (int c = 0; c < a.nl; ++c) a.out[c][o] = a.lcol[c][pr];
+            for (int c = 0; c < a.nl; ++c) a.out[c][o] = a.lcol[c][lr];
             for (int c = 0; c < a.nr; ++c) a.out[a.nl + c][o] = 0u;
             continue;
         }
         const uint64_t j = a.start[lo] + (o - a.off[lo]);
-        const uint32_t br = a.brow[j];
-        const uint32_t lr = a.probe_is_left ? pr : br;
-        const uint32_t rr = a.probe_is_left ? br : pr;
+        const uint32_t rr = a.brow[j];
         for (int c = 0; c < a.nl; ++c) a.out[c][o] = a.lcol[c][lr];
         for (int c = 0; c < a.nr; ++c) a.out[a.nl + c][o] = a.rcol[c][rr];
     }
@@ -359,7 +356,6 @@ std::unique_ptr<PendingJoin> join_begin(tid_ctx *ctx, const tid_table *L, uint64
         TID_HIP(hipGetLastError());
         pj->qrow = lv;
         pj->brow = rv;
-        pj->probe_is_left = 1;
     } else {
         // build on the smaller side; a left join probes with L
         const bool build_right = kind == kJoinLeft || nr <= nl;
@@ -441,7 +437,6 @@ std::unique_ptr<tid_table> join_finish(tid_ctx *ctx, PendingJoin &pj) {
         ea.qrow = pj.qrow;
         ea.brow = pj.brow;
         ea.matches = pj.outer ? pj.matches.get<const uint32_t>() : nullptr;
-        ea.probe_is_left = pj.probe_is_left;
         ea.nq = pj.nq;
         ea.total = total;
         ea.nl = (int)pj.jp.lkeep.size();

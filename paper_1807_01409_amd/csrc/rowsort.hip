@@ -7,14 +7,15 @@
 // neither stability nor a permutation, and the sorted rows are unpacked from
 // the keys: no gather.
 //   tile sort  a workgroup packs its tile of rows, each thread sorts kVT keys
-//              in registers, then runs are merged pairwise in LDS, every
+//              in registers (odd-even transposition, Habermann), then runs are merged pairwise in LDS, every
 //              thread finding the kVT keys it produces by a binary search
 //              along its diagonal (the merge path of Green, McColl and Bader,
 //              "GPU merge path").  A table of one tile is written out here;
 //   rank merge tables of up to 114,688 rows: a launch puts eight runs together
 //              (row_rank_merge);
-//   radix      large tables of one-word keys: the radix passes of sort.hip on
-//              the packed keys, then unpacked (radix_better);
+//   radix      one-word keys, many rows for their bits: the radix passes of
+//              sort.hip on the packed keys, then unpacked (radix_better); such
+//              tables of a batch round all together (radix_bits_of_round);
 //   merge      other larger ones: one launch per doubling of the run length: a workgroup
 //              produces kMergeTile rows, finds its two diagonals with a
 //              64-way search by a wave each, and merges out of LDS.  The last
@@ -316,9 +317,9 @@ __global__ __launch_bounds__(BLOCK) void row_tile_sort(RowJob p) {
 }
 
 template <int W>
-__global__ __launch_bounds__(tile_block(W)) void row_tile_sort_many(const RowJob *jobs, int J,
-                                                                    uint32_t tile_base) {
-    const uint32_t tile = tile_base + blockIdx.x;
+__global__ __launch_bounds__(tile_block(W)) void row_tile_sort_many(const RowJob *jobs,
+                                                                    int J) {
+    const uint32_t tile = blockIdx.x;
     const RowJob &p = jobs[row_job_of<false>(jobs, J, tile)];
     tile_sort_body<W, tile_block(W)>(p, tile - p.tile0);
 }
@@ -655,8 +656,8 @@ __global__ __launch_bounds__(kMergeBlock) void row_merge(RowJob p, int level) {
 
 template <int W>
 __global__ __launch_bounds__(kMergeBlock) void row_merge_many(const RowJob *jobs, int J,
-                                                              int level, uint32_t tile_base) {
-    const uint32_t tile = tile_base + blockIdx.x;
+                                                              int level) {
+    const uint32_t tile = blockIdx.x;
     const RowJob &p = jobs[row_job_of<true>(jobs, J, tile)];
     merge_body<W>(p, tile - p.mtile0, level);
 }
@@ -735,10 +736,9 @@ RowJob row_job(const tid_table *in, const tid_table *out, uint64_t n, int words,
 }
 
 template <int W>
-void allow_lds(tid_ctx *ctx) {
+void allow_lds() {
     // above 64 KB a kernel must be allowed its dynamic LDS first
     constexpr size_t lds = (size_t)tile_rows(W) * 8 * W;
-    (void)ctx;
     (void)resident_blocks((const void *)row_rank_merge<W>, kRankBlock, (size_t)kRankPart * 8 * W);
     (void)resident_blocks((const void *)row_tile_sort<W, tile_block(W)>, tile_block(W), lds);
     (void)resident_blocks((const void *)row_tile_sort_many<W>, tile_block(W), lds);
@@ -752,6 +752,8 @@ void allow_lds(tid_ctx *ctx) {
 //   100,000 rows   77 / 104 us against 101 / 151 us
 //   250,000 rows  114 / 175 us against 120 / 183 us
 //   500,000 rows  157 / 246 us against 143 / 216 us
+// (the last two with a third level; where between them the two are equal was not
+// measured, so the line stands where two levels end).
 // DISTINCT after it in one launch (row_keep_firsts) for so many merge tiles,
 // else in three: 14,000 rows of one word 69 us against 83, 28,000 rows 102 against 95.
 constexpr uint32_t kFewTiles = 8;
@@ -797,7 +799,7 @@ bool radix_better(uint64_t n, int bits) {
 // words a row: the radix sort of row numbers takes 24 B a row for any width.
 template <int W>
 bool sort_one(tid_ctx *ctx, RowJob &p) {
-    allow_lds<W>(ctx);
+    allow_lds<W>();
     constexpr size_t lds = (size_t)tile_rows(W) * 8 * W;
     const int bits = key_bits(p);
     // DISTINCT of rows that fit one large tile is done there
@@ -880,13 +882,13 @@ bool sort_one(tid_ctx *ctx, RowJob &p) {
 
 template <int W>
 void sort_many(tid_ctx *ctx, std::vector<RowJob *> jobs, const RowJob *dev) {
-    allow_lds<W>(ctx);
+    allow_lds<W>();
     constexpr size_t lds = (size_t)tile_rows(W) * 8 * W;
     const int J = (int)jobs.size();
     const RowJob &last = *jobs.back();
     const uint32_t tiles = last.tile0 + (last.n + tile_rows(W) - 1) / tile_rows(W);
     hipLaunchKernelGGL(row_tile_sort_many<W>, dim3(tiles), dim3(tile_block(W)), lds, ctx->stream,
-                       dev, J, 0u);
+                       dev, J);
     TID_HIP(hipGetLastError());
     // jobs stand in order of falling size: a level's jobs are the first ones
     int active = J;
@@ -896,7 +898,7 @@ void sort_many(tid_ctx *ctx, std::vector<RowJob *> jobs, const RowJob *dev) {
         const RowJob &p = *jobs[active - 1];
         const uint32_t mt = p.mtile0 + (p.n + kMergeTile - 1) / kMergeTile;
         hipLaunchKernelGGL(row_merge_many<W>, dim3(mt), dim3(kMergeBlock), 0, ctx->stream, dev,
-                           active, l, 0u);
+                           active, l);
         TID_HIP(hipGetLastError());
     }
 }

@@ -11,7 +11,8 @@
 // table.
 //
 // Bound: the graph's 12 bytes a triple once, the vector instructions of the
-// tests, and 16-24 bytes a matching row for the page and its copy.  So:
+// tests, and 12 bytes a column of a matching row: written to its page, read
+// from it, written to the table.  So:
 //  - a pattern with a constant predicate costs one compare a triple to count
 //    and one to place; its other tests run only in waves that hold the
 //    predicate;
