@@ -83,22 +83,12 @@ struct Terms {
     uint32_t *falls, *past;  // offsets that fall, or reach past the bytes
     uint32_t *wide;          // a term of 2^32 bytes or more: lengths are summed as 32-bit words
     // length of term t; 0 if it is refused
-    __device__ __forceinline__ uint64_t length(uint64_t t, uint64_t &at) const {
+    __device__ __forceinline__ uint32_t length(uint64_t t, uint64_t &at) const {
         at = off[t];
-        const uint64_t end = off[t + 1];
-        if (end < at) {
-            dev::raise(falls);
-            return 0;
-        }
-        if (end > nbytes) {
-            dev::raise(past);
-            return 0;
-        }
-        if (end - at >> 32) {
-            dev::raise(wide);
-            return 0;
-        }
-        return end - at;
+        const uint64_t end = off[t + 1], len = end - at;
+        if ((end >= at) & (end <= nbytes) & (len >> 32 == 0)) return (uint32_t)len;
+        dev::raise(end < at ? falls : end > nbytes ? past : wide);
+        return 0;
     }
 };
 
