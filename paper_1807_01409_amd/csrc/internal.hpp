@@ -114,7 +114,7 @@ struct tid_ctx {
     // read probe's sink, 4-7 of a dictionary call
     uint32_t *d_flags = nullptr;
     tid::HostWords words;
-    // pinned host memory that read_words' kernel writes
+    // pinned host memory that read_words' kernel writes and ID counts are copied to
     uint64_t *rw_host = nullptr;
     size_t rw_cap = 0;
 

@@ -119,17 +119,21 @@ __global__ __launch_bounds__(kReadWords) void gather_words(WordList src, uint64_
     if ((int)threadIdx.x < n) dst[threadIdx.x] = *src.p[threadIdx.x];
 }
 
+// at least n words at ctx->rw_host
+static void grow_host_words(tid_ctx *ctx, size_t n) {
+    if (ctx->rw_cap >= n) return;
+    if (ctx->rw_host) (void)hipHostFree(ctx->rw_host);
+    ctx->rw_host = nullptr;
+    const size_t cap = std::max<size_t>({n, 2 * ctx->rw_cap, 1024});
+    ctx->rw_cap = 0;
+    TID_HIP(hipHostMalloc((void **)&ctx->rw_host, cap * 8, hipHostMallocCoherent));
+    ctx->rw_cap = cap;
+}
+
 void read_words(tid_ctx *ctx, const std::vector<const uint64_t *> &src, uint64_t *dst) {
     const size_t n = src.size();
     if (n == 0) return;
-    if (ctx->rw_cap < n) {
-        if (ctx->rw_host) (void)hipHostFree(ctx->rw_host);
-        ctx->rw_host = nullptr;
-        const size_t cap = std::max<size_t>({n, 2 * ctx->rw_cap, 1024});
-        ctx->rw_cap = 0;
-        TID_HIP(hipHostMalloc((void **)&ctx->rw_host, cap * 8, hipHostMallocCoherent));
-        ctx->rw_cap = cap;
-    }
+    grow_host_words(ctx, n);
     for (size_t i = 0; i < n; i += kReadWords) {
         WordList w{};
         const int m = (int)std::min<size_t>(kReadWords, n - i);
@@ -426,11 +430,13 @@ __global__ void list_big(const uint32_t *__restrict__ bins, uint64_t nblocks,
 
 void exclusive_scan_async(tid_ctx *ctx, const uint32_t *in, uint64_t n, uint64_t *out);
 
-// Up to so many blocks of bins go to the host as they are: one copy, where the
-// packed ones take five launches, two waits and four copies.  A load of 1000
-// triples with 2,000 / 120,000 / 160,000 / 200,000 / 240,000 IDs in all, packed: 103
-// / 120 / 122 / 124 / 126 us, summed on the host: 58 / 98 / 111 / 122 / 134 us.
-constexpr uint64_t kHostBlocks = 800;
+// Up to so many blocks of bins (1 MB) go to the host as they are: one copy, through
+// the context's pinned words, where the packed ones take five launches, two waits
+// and four copies.  A load of 1000 triples with 2,000 / 120,000 / 200,000 / 240,000
+// IDs in all, packed: 103 / 120 / 124 / 128 us, summed on the host: 58 / 88 / 106 /
+// 117 us.  (To pageable memory: 58 / 98 / 122 / 134, and 8 us more in the first
+// scan after it.)
+constexpr uint64_t kHostBlocks = 1024;
 
 // Device bins (nblocks blocks) of n triples to the host: packed on the device,
 // unless they are few, a block's sum could pass 32 bits or there is no memory.
@@ -450,11 +456,18 @@ static std::shared_ptr<IdCounts::Mem> counts_to_host(tid_ctx *ctx, const uint32_
     }
     if (!packed) {
         const uint64_t nbins = nblocks * IdCounts::kBlock;
-        const std::unique_ptr<uint32_t[]> host(new uint32_t[nbins]);
-        TID_HIP(hipMemcpyAsync(host.get(), bins, nbins * sizeof(uint32_t), hipMemcpyDeviceToHost,
+        std::unique_ptr<uint32_t[]> pageable;
+        uint32_t *host;
+        if (nblocks <= kHostBlocks) {
+            grow_host_words(ctx, kHostBlocks * IdCounts::kBlock / 2);
+            host = reinterpret_cast<uint32_t *>(ctx->rw_host);
+        } else {
+            pageable.reset(host = new uint32_t[nbins]);
+        }
+        TID_HIP(hipMemcpyAsync(host, bins, nbins * sizeof(uint32_t), hipMemcpyDeviceToHost,
                                ctx->stream));
         ctx->sync();
-        return counts_of_bins(host.get(), nblocks);
+        return counts_of_bins(host, nblocks);
     }
     uint64_t *r = offs.get<uint64_t>(), *b = r + nblocks + 1;
     const unsigned grid = (unsigned)std::min<uint64_t>((nblocks + 3) / 4, 8192);

@@ -1,4 +1,4 @@
-"""Load-time ID counts on both sides of the line (800 blocks of 256 IDs in all)
+"""Load-time ID counts on both sides of the line (1024 blocks of 256 IDs in all)
 up to which the bins are summed on the host: every ID, against numpy."""
 import numpy as np
 import pytest
@@ -6,8 +6,8 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("ids", [(256 * 798 - 1, 255, 1), (256 * 798, 255, 1), (255, 256 * 799, 3),
-                                 (90_000, 50, 130_000), (40_000, 40_000, 40_000)])
+@pytest.mark.parametrize("ids", [(256 * 1022 - 1, 255, 1), (256 * 1022, 255, 1), (255, 256 * 1023, 3),
+                                 (120_000, 50, 160_000), (40_000, 40_000, 40_000)])
 @pytest.mark.parametrize("where", ["host", "device"])
 def test_counts(ctx, ids, where):
     import torch

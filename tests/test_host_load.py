@@ -17,10 +17,10 @@ out = dict(st=st, error=error(ctx), queued=kernels()[done:])
 
 
 @pytest.mark.parametrize("device", [0, 1])
-@pytest.mark.parametrize("ids,packed", [(3, False), (5000, False), (68_000, False),
-                                        (68_500, True), (200_000, True)])
+@pytest.mark.parametrize("ids,packed", [(3, False), (5000, False), (87_000, False),
+                                        (87_500, True), (200_000, True)])
 def test_small_tables_of_counts_are_not_packed(tmp_path, device, ids, packed):
-    """Up to 800 blocks of 256 IDs (three positions) the bins go to the host as
+    """Up to 1024 blocks of 256 IDs (three positions) the bins go to the host as
     they are: one copy, after the extreme IDs'."""
     source = "device(12 * n)" if device else "host"
     out = stand_in.run(tmp_path, LOAD.format(n=1000, ids=ids, device=device, source=source))

@@ -42,19 +42,19 @@ out = dict(st=st, error=error(ctx), queued=kernels()[done:])
     assert sorts(out["queued"]) == kinds
 
 
-@pytest.mark.parametrize("plans,columns,passes", [(2, 2, 0), (2, 1, 2), (64, 1, 2)])
+@pytest.mark.parametrize("plans,columns,passes", [(2, 2, 0), (2, 1, 2), (64, 1, 3)])
 def test_route_of_a_round(tmp_path, plans, columns, passes):
-    """A round's tables of 300,000 rows with columns of 10 bits: radix passes over
+    """A round's tables of 300,000 rows with columns of 17 bits: radix passes over
     all their rows, or six merge levels."""
     out = stand_in.run(tmp_path, f"""
 from types import SimpleNamespace as NS
 from paper_1807_01409_amd import tid
 ctx = context()
 n = 1 << 20
-word("read_word", ctypes.c_uint32).value = 1000      # the largest ID, and every ID's triples
+word("read_word", ctypes.c_uint32).value = 100_000   # the largest ID
+word("host_word").value = 300_000                    # every scan's rows
 g = ctypes.c_void_p()
 assert lib.tid_load(ctx, device(12 * n), n, 1, ctypes.byref(g)) == 0
-word("host_word").value = 300_000                    # every scan's rows
 p = NS(s=0, p=1, o=0, vs=0, vp=-1, vo=1, range_pos=-1, lo=0, hi=0)
 ops = [1, 0, 5, {columns}, 1, 0][:4 + {columns}]     # SCAN, PROJECT
 block = tid._Plans([NS(patterns=[p], ops=ops)] * {plans})
