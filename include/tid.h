@@ -265,7 +265,9 @@ tid_status tid_filter(tid_ctx *ctx, const tid_table *t, int32_t col, uint32_t lo
    the inner equi-join of l and r on l[lcol] = r[rcol].  Output columns are
    l's columns followed by r's columns without rcol; rows are returned in
    lexicographic order over all output columns.  algo: 0 automatic, 1 hash
-   join, 2 sort-merge join (same result).  Synchronises (output size). */
+   join, 2 sort-merge join (same result).  A hash join builds on the smaller
+   side (an outer one on the other side), of at most 2^30 rows: above,
+   TID_E_UNSUPPORTED.  Synchronises (output size). */
 tid_status tid_join(tid_ctx *ctx, const tid_table *l, int32_t lcol, const tid_table *r,
                     int32_t rcol, int32_t algo, tid_table **out);
 /* Sec. 4.2 (the join library's Left, Right and Outer kinds besides Inner):
