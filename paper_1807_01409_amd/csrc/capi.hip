@@ -95,8 +95,7 @@ tid_status tid_ctx_create(int device, void *stream, tid_alloc_fn alloc, tid_free
         ctx->alloc_fn = alloc;
         ctx->free_fn = free_fn;
         ctx->user = user;
-        TID_HIP(hipHostMalloc((void **)&ctx->d_flags, 8 * sizeof(uint32_t),
-                              hipHostMallocCoherent));
+        ctx->d_flags = reinterpret_cast<uint32_t *>(ctx->words.keep(4));
         std::memset(ctx->d_flags, 0, 8 * sizeof(uint32_t));
         // once per device: the allocation-free scan's state array
         tid::noalloc_init(ctx);
@@ -115,7 +114,6 @@ void tid_ctx_destroy(tid_ctx *ctx) {
     if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
     if (ctx->ep_state) ctx->free(ctx->ep_state, ctx->ep_bytes);
     if (ctx->rw_host) (void)hipHostFree(ctx->rw_host);
-    if (ctx->d_flags) (void)hipHostFree(ctx->d_flags);
     if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;

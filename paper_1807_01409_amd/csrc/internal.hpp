@@ -61,9 +61,12 @@ class HostWords {
   public:
     ~HostWords();
     uint64_t *take();
+    // the first `n` words, for good (before any is taken)
+    uint64_t *keep(size_t n);
     void give(uint64_t *w) { free_.push_back(w); }
 
   private:
+    void grow();
     static constexpr size_t kSlab = 4096;  // words per allocation
     std::vector<uint64_t *> slabs_, free_;
 };

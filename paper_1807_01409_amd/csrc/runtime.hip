@@ -73,13 +73,21 @@ HostWords::~HostWords() {
     for (uint64_t *s : slabs_) (void)hipHostFree(s);
 }
 
+void HostWords::grow() {
+    uint64_t *s = nullptr;
+    TID_HIP(hipHostMalloc((void **)&s, kSlab * 8, hipHostMallocCoherent));
+    slabs_.push_back(s);
+    for (size_t i = kSlab; i-- > 0;) free_.push_back(s + i);
+}
+
+uint64_t *HostWords::keep(size_t n) {
+    grow();
+    free_.resize(free_.size() - n);  // the slab's first words are its last to be listed
+    return slabs_.back();
+}
+
 uint64_t *HostWords::take() {
-    if (free_.empty()) {
-        uint64_t *s = nullptr;
-        TID_HIP(hipHostMalloc((void **)&s, kSlab * 8, hipHostMallocCoherent));
-        slabs_.push_back(s);
-        for (size_t i = kSlab; i-- > 0;) free_.push_back(s + i);
-    }
+    if (free_.empty()) grow();
     uint64_t *w = free_.back();
     free_.pop_back();
     return w;

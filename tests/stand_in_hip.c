@@ -17,6 +17,7 @@
 uint64_t host_word = 0;        /* every 64-bit word of new pinned memory */
 uint32_t read_word = 1;        /* every 32-bit word of a copy to the host */
 uint64_t live_bytes = 0, peak_bytes = 0, most_bytes = ~0ull; /* device memory */
+uint64_t pinned = 0;           /* allocations of pinned host memory */
 uint64_t copies = 0, changed = 0;   /* copies from the host; those whose source changed */
 char launched[1 << 20];        /* names of the launched kernels and the copies, a line each */
 
@@ -56,6 +57,7 @@ int hipHostMalloc(void **p, size_t n, unsigned flags) {
     (void)flags;
     uint64_t *w = malloc((n + 7) / 8 * 8);
     if (!w) return 2;
+    ++pinned;
     for (size_t i = 0; i < (n + 7) / 8; ++i) w[i] = host_word;
     *p = w;
     return 0;
