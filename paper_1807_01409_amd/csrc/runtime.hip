@@ -446,37 +446,12 @@ void exclusive_scan_async(tid_ctx *ctx, const uint32_t *in, uint64_t n, uint64_t
 // scan after it.)
 constexpr uint64_t kHostBlocks = 1024;
 
-// Device bins (nblocks blocks) of n triples to the host: packed on the device,
-// unless they are few, a block's sum could pass 32 bits or there is no memory.
-static std::shared_ptr<IdCounts::Mem> counts_to_host(tid_ctx *ctx, const uint32_t *bins,
-                                                     uint64_t nblocks, uint64_t n) {
-    bool packed = n < (1ull << 32) && nblocks > kHostBlocks;
-    DevBuf bytes, rows, nbig, offs;
-    if (packed) {
-        try {
-            bytes = DevBuf(ctx, nblocks * IdCounts::kBlock);
-            rows = DevBuf(ctx, nblocks * 4);
-            nbig = DevBuf(ctx, nblocks * 4);
-            offs = DevBuf(ctx, 2 * (nblocks + 1) * 8);
-        } catch (const Error &) {
-            packed = false;
-        }
-    }
-    if (!packed) {
-        const uint64_t nbins = nblocks * IdCounts::kBlock;
-        std::unique_ptr<uint32_t[]> pageable;
-        uint32_t *host;
-        if (nblocks <= kHostBlocks) {
-            grow_host_words(ctx, kHostBlocks * IdCounts::kBlock / 2);
-            host = reinterpret_cast<uint32_t *>(ctx->rw_host);
-        } else {
-            pageable.reset(host = new uint32_t[nbins]);
-        }
-        TID_HIP(hipMemcpyAsync(host, bins, nbins * sizeof(uint32_t), hipMemcpyDeviceToHost,
-                               ctx->stream));
-        ctx->sync();
-        return counts_of_bins(host, nblocks);
-    }
+// Device bins (nblocks blocks) to the host, packed on the device (counts below 2^32
+// in all per block).
+static std::shared_ptr<IdCounts::Mem> packed_counts(tid_ctx *ctx, const uint32_t *bins,
+                                                    uint64_t nblocks) {
+    DevBuf bytes(ctx, nblocks * IdCounts::kBlock), rows(ctx, nblocks * 4), nbig(ctx, nblocks * 4),
+        offs(ctx, 2 * (nblocks + 1) * 8);
     uint64_t *r = offs.get<uint64_t>(), *b = r + nblocks + 1;
     const unsigned grid = (unsigned)std::min<uint64_t>((nblocks + 3) / 4, 8192);
     hipLaunchKernelGGL(pack_counts, dim3(grid), dim3(256), 0, ctx->stream, bins, nblocks,
@@ -504,6 +479,38 @@ static std::shared_ptr<IdCounts::Mem> counts_to_host(tid_ctx *ctx, const uint32_
     get(m->big.get(), big.get(), nlarge * 4);
     ctx->sync();
     return m;
+}
+
+// The same from the bins as they are, summed on the host.
+static std::shared_ptr<IdCounts::Mem> summed_counts(tid_ctx *ctx, const uint32_t *bins,
+                                                    uint64_t nblocks) {
+    const uint64_t nbins = nblocks * IdCounts::kBlock;
+    std::unique_ptr<uint32_t[]> pageable;
+    uint32_t *host;
+    if (nblocks <= kHostBlocks) {
+        grow_host_words(ctx, kHostBlocks * IdCounts::kBlock / 2);
+        host = reinterpret_cast<uint32_t *>(ctx->rw_host);
+    } else {
+        pageable.reset(host = new uint32_t[nbins]);
+    }
+    TID_HIP(hipMemcpyAsync(host, bins, nbins * sizeof(uint32_t), hipMemcpyDeviceToHost,
+                           ctx->stream));
+    ctx->sync();
+    return counts_of_bins(host, nblocks);
+}
+
+// The bins of n triples: packed, unless they are few, a block's sum could pass 32
+// bits or there is no memory for it.
+static std::shared_ptr<IdCounts::Mem> counts_to_host(tid_ctx *ctx, const uint32_t *bins,
+                                                     uint64_t nblocks, uint64_t n) {
+    if (n < (1ull << 32) && nblocks > kHostBlocks) {
+        try {
+            return packed_counts(ctx, bins, nblocks);
+        } catch (const Error &e) {
+            if (e.code != TID_E_OOM) throw;
+        }
+    }
+    return summed_counts(ctx, bins, nblocks);
 }
 
 // bytes of `ids` bins: whole blocks, so that every position starts on one
