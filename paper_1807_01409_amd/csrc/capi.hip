@@ -95,7 +95,9 @@ tid_status tid_ctx_create(int device, void *stream, tid_alloc_fn alloc, tid_free
         ctx->alloc_fn = alloc;
         ctx->free_fn = free_fn;
         ctx->user = user;
-        ctx->d_flags = reinterpret_cast<uint32_t *>(ctx->words.keep(4));
+        // away from the count words: a flag that the host has read in a count's cache
+        // line costs that scan half a microsecond
+        ctx->d_flags = reinterpret_cast<uint32_t *>(ctx->words.keep(64));
         std::memset(ctx->d_flags, 0, 8 * sizeof(uint32_t));
         // once per device: the allocation-free scan's state array
         tid::noalloc_init(ctx);
